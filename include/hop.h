@@ -262,8 +262,12 @@ int hop_schedule_bind(hop_ctx* ctx, hop_schedule* s, void* workspace, size_t byt
  * margins ride in the Reduce launch and the gradient is applied to the results right after it (scattered,
  * or in place); with larger dense minibatches the gradient kernel itself reduces and applies its record,
  * and the Reduce launch only holds the records without a gradient; synthetic gradients of up to
- * hop_opts.grad_ahead consecutive waves are generated in front of the first of them.  The results are the
- * same in every arrangement up to the rounding of the sums.  The first call for a schedule (and the first after the gradient
+ * hop_opts.grad_ahead consecutive waves are generated in front of the first of them.  A call that covers the
+ * whole schedule (wave_begin 0, wave_end -1 or n_waves) and is not being profiled runs as ONE launch when
+ * gradients are absent, synthetic or external and the schedule suits it (not too many workers, nor many
+ * records per wave on a narrow model): every column then goes through all records by itself, no gradient is
+ * written to memory, and the results are those of the waves bit for bit.  The results are the same in every
+ * arrangement up to the rounding of the sums.  The first call for a schedule (and the first after the gradient
  * source or a data set changed) copies the descriptors into the schedule's workspace with synchronous
  * host-to-device copies; after that the call only launches.  Records of one wave touch no
  * ring slot in a conflicting way, so the result equals running the records one by one in schedule
@@ -276,7 +280,8 @@ int hop_step(hop_ctx* ctx, const hop_schedule* s, int32_t wave_begin, int32_t wa
  * n_waves) and is not being profiled records its launches once into a HIP graph and replays that
  * graph from then on: one launch call per pass instead of up to four per wave, which is what
  * matters for schedules of many small waves (Exp(1) delays de-synchronise the workers).  Partial
- * ranges and profiled passes always run kernel by kernel.  Off by default. */
+ * ranges and profiled passes always run kernel by kernel.  Off by default; without effect where a whole
+ * pass is a single launch anyway (see hop_step). */
 int hop_use_graph(hop_ctx* ctx, int enable);
 
 /* Newest parameter vector of a worker (device, d floats) and its iteration number. */

@@ -71,6 +71,7 @@ void free_device_side(hop_schedule* s) {
     s->grad_dev = nullptr;
     s->rows_dev = nullptr;
     s->coef_dev = nullptr;
+    s->sweep = HopSweepArgs{};
     s->built_mode = -1;
     if (s->graph_exec) (void)hipGraphExecDestroy((hipGraphExec_t)s->graph_exec);
     s->graph_exec = nullptr;
@@ -153,10 +154,231 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
     return distinct;
 }
 
+// Hands every value of the pass (the content a ring slot has between two writes) a local slot from its production, or
+// its load at the start, to its last reader, reusing slots greedily.  A result may take over the slot of a source that
+// this record reads for the last time: a lane reads all its sources before it writes.
+bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int n_workers, HopSweepPlan* plan) {
+    const int R = (int)given.size();
+    std::vector<int> last_writer((size_t)n_ring_slots, -1), reader_after((size_t)n_ring_slots, 0);
+    std::vector<int> kind((size_t)R);                // what the record's run is written down as
+    for (int r = 0; r < R; ++r) last_writer[given[r].out_slot] = r;
+    for (int r = R - 1; r >= 0; --r) {
+        const HopSweepOp& op = given[r];
+        const bool only_kept = reader_after[op.out_slot] && last_writer[op.out_slot] != r;
+        kind[r] = op.terms.size() > (size_t)kSweepInline ? kSweepOther
+                  : (int)(op.terms.size() + (op.grad ? kSweepGrad << 4 : 0) + (only_kept ? 0 : kSweepStore << 4));
+        reader_after[op.out_slot] = 0;
+        for (const auto& t : op.terms) reader_after[t.first] = 1;
+    }
+    // by kind inside a wave, beginning with the kind that the wave before ended on: long runs
+    std::vector<int> order((size_t)R);
+    for (int b = 0; b < R;) {
+        int e = b;
+        for (; e < R && given[e].wave == given[b].wave; ++e) order[e] = e;
+        const int open = b ? kind[order[b - 1]] : 0;
+        std::stable_sort(order.begin() + b, order.begin() + e, [&](int x, int y) {
+            return std::make_pair(kind[x] != open, kind[x]) < std::make_pair(kind[y] != open, kind[y]);
+        });
+        b = e;
+    }
+    auto op_at = [&](int r) -> const HopSweepOp& { return given[order[r]]; };
+    std::vector<int> holds((size_t)n_ring_slots, -1);
+    std::vector<int> last_use;                       // by value
+    std::vector<std::pair<int, int>> initial;        // (ring slot, value) read before it is written
+    std::vector<std::vector<int>> reads((size_t)R);
+    std::vector<int> result((size_t)R);
+    for (int r = 0; r < R; ++r) {
+        const HopSweepOp& op = op_at(r);
+        for (const auto& t : op.terms) {
+            int& v = holds[t.first];
+            if (v < 0) {
+                v = (int)last_use.size();
+                last_use.push_back(-1);
+                initial.emplace_back(t.first, v);
+            }
+            last_use[v] = r;
+            reads[r].push_back(v);
+        }
+        holds[op.out_slot] = result[r] = (int)last_use.size();
+        last_use.push_back(-1);
+    }
+    int n_local = 0;
+    std::vector<int> spare, local(last_use.size(), -1);
+    auto take = [&] {
+        if (spare.empty()) return n_local++;
+        const int l = spare.back();
+        spare.pop_back();
+        return l;
+    };
+    for (const auto& i : initial) local[i.second] = take();
+    std::vector<int> vel((size_t)n_workers, -1);
+    int n_vel = 0;
+    for (const HopSweepOp& op : given)
+        if (op.vel && vel[op.worker] < 0) {
+            vel[op.worker] = take();
+            ++n_vel;
+        }
+    if (n_local > kSweepMaxLocal) return false;
+    auto bits = [](float f) {
+        uint32_t u;
+        std::memcpy(&u, &f, sizeof(u));
+        return u;
+    };
+    constexpr uint32_t kLane = 64 * sizeof(float);   // bytes of a local slot at one column per lane
+    std::vector<uint32_t>& prog = plan->program;
+    prog.clear();
+    for (int r = 0; r < R; ++r) {
+        const int k = kind[order[r]];
+        if (r == 0 || k != kind[order[r - 1]]) prog.push_back((uint32_t)k);
+        prog.back() += 256u;
+    }
+    plan->n_runs = (int)prog.size();
+    prog.resize((prog.size() + 4) / 4 * 4, 0u);      // at least one word of padding: the next run is read ahead
+    plan->first_record = (int)prog.size();
+    for (int r = 0; r < R; ++r) {
+        const HopSweepOp& op = op_at(r);
+        const size_t A = op.terms.size(), at = prog.size();
+        prog.resize(at + hop_sweep_words((int)A), 0u);
+        uint32_t* p = prog.data() + at;
+        p[7] = (uint32_t)A;
+        for (size_t t = 0; t < A; ++t) {
+            p[kSweepHead + 2 * t] = (uint32_t)local[reads[r][t]] * kLane;
+            p[kSweepHead + 2 * t + 1] = bits(op.terms[t].second);
+        }
+        for (int v : reads[r])
+            if (last_use[v] == r && local[v] >= 0) {
+                spare.push_back(local[v]);
+                local[v] = -1;                       // once, also for a vector that the record lists twice
+            }
+        const int v = result[r];
+        if (last_use[v] >= 0) {
+            local[v] = take();
+            if (n_local > kSweepMaxLocal) return false;
+            p[0] |= kSweepKeep;
+            p[1] = (uint32_t)local[v] * kLane;
+        }
+        if (last_writer[op.out_slot] == order[r]) {
+            p[0] |= kSweepStore;
+            p[2] = (uint32_t)op.out_slot;
+        }
+        if (op.grad) {
+            p[0] |= kSweepGrad;
+            for (int k = 0; k < 3; ++k) p[4 + k] = op.key[k];
+        }
+        if (op.vel) p[3] = (uint32_t)vel[op.worker] * kLane;
+    }
+    prog.resize(prog.size() + hop_sweep_words(kSweepInline), 0u);
+    int following = -1;                              // from the last record with an external gradient to the first
+    size_t at_word = plan->n_runs ? prog.size() - hop_sweep_words(kSweepInline) : 0;
+    for (int r = R - 1; r >= 0; --r) {
+        const HopSweepOp& op = op_at(r);
+        at_word -= hop_sweep_words((int)op.terms.size());
+        if (!op.external) continue;
+        prog[at_word + 5] = (uint32_t)(following < 0 ? op.worker : following);
+        following = op.worker;
+    }
+    plan->first_external = std::max(following, 0);
+    plan->first_load = (int)prog.size();
+    // the initial values were given the first local slots, in this order
+    for (size_t i = 0; i < initial.size(); ++i) {
+        prog.push_back((uint32_t)initial[i].first);
+        prog.push_back((uint32_t)i * kLane);
+    }
+    for (int w = 0; w < n_workers; ++w)
+        if (vel[w] >= 0) {
+            prog.push_back((uint32_t)w);
+            prog.push_back((uint32_t)vel[w] * kLane);
+        }
+    plan->n_local = std::max(n_local, 1);
+    plan->n_loads = (int)initial.size();
+    plan->n_vel = n_vel;
+    return true;
+}
+
 namespace {
 
 float* slot_ptr(const hop_ctx* c, int worker, int slot) {
     return c->ring + ((int64_t)worker * c->slots + slot) * c->stride;
+}
+
+// The whole pass as one program, where no gradient needs a sum over the columns.  Sums are taken in the order in which
+// the wave-by-wave kernels take them (that of the union of a pair), so both ways give the same bits.  The program goes
+// into the part of the workspace that this kind of context leaves unused: the record-by-record Reduce descriptors, or
+// with velocities the paired ones.
+int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, const std::vector<HopPairJob>& pairs,
+                char* room, size_t room_bytes) {
+    const int mode = c->grad_mode;
+    if (!hopk_sweep || (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL)) return HOP_OK;
+    auto slot_of = [c](const float* p) { return (int)((p - c->ring) / c->stride); };
+    const int R = (int)mix.size();
+    std::vector<HopSweepOp> ops((size_t)R);
+    std::vector<int> at((size_t)c->N * c->slots, -1);            // position of the record that writes a slot, this wave
+    for (int w = 0; w < s->n_waves; ++w) {
+        for (int p = s->wave_begin[w]; p < s->wave_begin[w + 1]; ++p) {
+            const int e = s->wave_order[p];
+            HopSweepOp& op = ops[p];
+            op.wave = w;
+            op.out_slot = slot_of(mix[p].out);
+            op.worker = s->worker[e];
+            op.grad = mix[p].g != nullptr;
+            op.vel = mix[p].vel != nullptr;
+            if (op.grad && mode == HOP_GRAD_SYNTH) {
+                hoprng::synth_keys(c->opts.seed, op.worker, s->iter[e], &op.key[0], &op.key[1], &op.key[2]);
+                for (int k = 0; k < 2; ++k) op.key[k] ^= op.key[k] >> 16;
+            } else if (op.grad) {
+                op.key[0] = (uint32_t)op.worker;
+                op.external = true;
+            }
+            if (c->vel)
+                for (int a = 0; a < mix[p].A; ++a) op.terms.emplace_back(slot_of(mix[p].src[a]), mix[p].w[a]);
+            else
+                at[op.out_slot] = p;
+        }
+        if (c->vel) continue;
+        for (int q = s->pair_begin[w]; q < s->pair_begin[w + 1]; ++q) {
+            const HopPairJob& pj = pairs[q];
+            for (int r = 0; r < pj.G; ++r) {
+                HopSweepOp& op = ops[at[slot_of(pj.out[r])]];
+                for (int u = 0; u < pj.U; ++u)
+                    if ((pj.mask[r] >> u) & 1u) op.terms.emplace_back(slot_of(pj.src[u]), pj.w[r][u]);
+            }
+        }
+    }
+    HopSweepPlan plan;
+    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan)) return HOP_OK;
+    // The more local slots, the fewer wavefronts per CU there are to hide each other's latency: 2 M columns and 64, 81
+    // and 100 workers in lock-step (80, 99 and 120 slots) take, wave by wave against sweep, 1.5, 1.1 and 0.94 times as
+    // long without a gradient, 1.05, 0.74 and 0.64 with external ones (loads on the way), 2.5, 2 and 1.6 with synthetic
+    // ones (arithmetic on the way).
+    const int most_local = mode == HOP_GRAD_SYNTH ? kSweepMaxLocal : mode == HOP_GRAD_ZERO ? 112 : 84;
+    // Narrow models leave most of the GPU idle in a sweep, whose records then follow each other at 0.14 us; a wave of
+    // its own takes 3.5 to 5 us (two launches with synthetic gradients: 6 to 9), whatever its records.  1024 columns in
+    // lock-step, wave by wave against sweep: 16 records per wave 2 to 3 times, 32 records 0.84 (synthetic 1.3), 64
+    // records 0.5 (0.86).  From 65536 columns on the sweep is ahead in every case above.
+    const int most_per_wave = mode == HOP_GRAD_SYNTH ? 40 : 24;
+    if (plan.n_local > most_local || (c->d < 65536 && R > most_per_wave * s->n_waves)) return HOP_OK;
+    const size_t bytes = plan.program.size() * sizeof(uint32_t);
+    if (bytes > room_bytes) return HOP_OK;
+    HOP_HIP(c, hipMemcpy(room, plan.program.data(), bytes, hipMemcpyHostToDevice));
+    HopSweepArgs& a = s->sweep;
+    a.program = (const uint32_t*)room;
+    a.n_runs = plan.n_runs;
+    a.first_record = plan.first_record;
+    a.first_load = plan.first_load;
+    a.first_external = plan.first_external;
+    a.n_local = plan.n_local;
+    a.n_loads = plan.n_loads;
+    a.n_vel = plan.n_vel;
+    a.mode = mode;
+    a.ring = c->ring;
+    a.vel = c->vel;
+    a.external = c->external;
+    a.stride = c->stride;
+    a.d = c->d;
+    a.eta = c->opts.lr;
+    a.mu = c->opts.momentum;
+    a.scale = hoprng::synth_scale(c->synth_variance);
+    return HOP_OK;
 }
 
 // Translate the schedule into device descriptors for the context's current gradient source.
@@ -298,12 +520,11 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
         }
         s->grad_begin[w + 1] = (int32_t)grad.size();
     }
-    if (R > 0) HOP_HIP(c, hipMemcpy(s->mix_dev, mix.data(), (size_t)R * sizeof(HopMixJob), hipMemcpyHostToDevice));
     // without velocities the Reduce runs on records packed in pairs
     s->pair_begin.assign(s->n_waves + 1, 0);
     s->wave_sources.assign(s->n_waves, 0);
+    std::vector<HopPairJob> pairs;
     if (!c->vel && R > 0) {
-        std::vector<HopPairJob> pairs;
         pairs.reserve((size_t)R);
         for (int w = 0; w < s->n_waves; ++w) {
             s->wave_sources[w] = hop_pack_pairs(mix.data() + s->wave_begin[w], s->wave_mix_jobs[w], pairs);
@@ -311,6 +532,14 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
         }
         s->pair_dev = (HopPairJob*)carve((size_t)R * sizeof(HopPairJob));
         HOP_HIP(c, hipMemcpy(s->pair_dev, pairs.data(), pairs.size() * sizeof(HopPairJob), hipMemcpyHostToDevice));
+    }
+    if (R > 0) {
+        // the record-by-record descriptors are read with a velocity, and by gradient kernels that do a record's Reduce
+        if (c->vel || dense_fused)
+            HOP_HIP(c, hipMemcpy(s->mix_dev, mix.data(), (size_t)R * sizeof(HopMixJob), hipMemcpyHostToDevice));
+        const size_t room = (size_t)R * (c->vel ? sizeof(HopPairJob) : sizeof(HopMixJob));
+        const int rc = build_sweep(c, s, mix, pairs, c->vel ? carve(room) : (char*)s->mix_dev, room);
+        if (rc != HOP_OK) return rc;
     }
     if (!grad.empty()) {
         s->grad_dev = (HopGradJob*)carve((size_t)R * sizeof(HopGradJob));
@@ -854,7 +1083,9 @@ int hop_step(hop_ctx* c, const hop_schedule* sched, int32_t wave_begin, int32_t 
     }
     c->running = s;
     int rc;
-    if (c->use_graph && !c->profiling && wave_begin == 0 && wave_end == s->n_waves && s->n_waves > 0) {
+    if (s->sweep.program && !c->profiling && wave_begin == 0 && wave_end == s->n_waves) {
+        HOP_LAUNCH(c, hopk_sweep(s->sweep, c->stream));          // the whole pass is one launch: nothing for a graph to save
+    } else if (c->use_graph && !c->profiling && wave_begin == 0 && wave_end == s->n_waves && s->n_waves > 0) {
         if (!s->graph_exec || s->graph_epoch != c->epoch || s->graph_mode != c->grad_mode)
             if ((rc = capture_graph(c, s)) != HOP_OK) return rc;
         HOP_HIP(c, hipGraphLaunch((hipGraphExec_t)s->graph_exec, (hipStream_t)c->stream));

@@ -61,6 +61,55 @@ struct alignas(16) HopGradJob {
     float scale;               // synth: fp32 factor
 };
 
+// ---- a whole pass as a program for sweep_kernel ------------------------------------
+// The records of a pass in an order that respects their dependences, for gradients that need no sum over the columns
+// (none, synthetic, external): every column can then run the whole pass by itself.  Words of 32 bits:
+//   runs     count << 8 | kind for every run of records of one kind: the number of sources, + kSweepGrad << 4 with a
+//            gradient, + kSweepStore << 4 where a result is not just kept in a local slot (the flags of each record say);
+//            kSweepOther: more sources than are unrolled
+//   records  0 flags, 1 local slot of the result, 2 ring slot it is stored to, 3 local slot of the velocity, 4..6 key[]
+//            (synthetic: hash keys, the first two folded; external: the worker, and the worker of
+//            the next record with a gradient, whose load is issued ahead), 7 number of sources, then (local slot,
+//            weight) of every source, padded to whole fours; one empty record behind the last
+//   loads    (ring slot, local slot) of the values read from the rings, then (worker, local slot) of the velocities
+// A local slot is written as its byte offset.
+constexpr int kSweepHead = 8;
+constexpr int kSweepInline = 12;        // most sources that the kernel unrolls
+constexpr int kSweepOther = 255;
+constexpr int kSweepMaxLocal = 160;     // most local slots: 40 KB of LDS per wavefront, 4 wavefronts per CU
+enum : uint32_t { kSweepGrad = 1u, kSweepStore = 2u, kSweepKeep = 4u };
+constexpr int hop_sweep_words(int A) { return kSweepHead + (2 * A + 3) / 4 * 4; }
+
+struct HopSweepOp {                     // one record, in ring-slot terms (host only)
+    int wave = 0, out_slot = 0, worker = 0;
+    bool grad = false, vel = false, external = false;
+    uint32_t key[3] = {0, 0, 0};
+    std::vector<std::pair<int, float>> terms;   // (ring slot, weight), in the order the sum is taken
+};
+
+struct HopSweepPlan {
+    int n_runs = 0, n_local = 0, n_loads = 0, n_vel = 0;
+    int first_record = 0, first_load = 0;       // words
+    int first_external = 0;
+    std::vector<uint32_t> program;
+};
+
+// Ops come wave by wave; records of one wave are independent of each other and may change places.
+// False if the pass needs more than kSweepMaxLocal values at a time.  Host only.
+bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_workers, HopSweepPlan* plan);
+
+struct HopSweepArgs {
+    const uint32_t* program;            // device copy of HopSweepPlan::program
+    int32_t n_runs, n_local, n_loads, n_vel, first_record, first_load;
+    int32_t mode;                       // HOP_GRAD_ZERO, HOP_GRAD_SYNTH or HOP_GRAD_EXTERNAL
+    float* ring;
+    float* vel;                         // null: no velocities
+    const float* external;              // n_workers x d
+    int32_t first_external;             // worker of the first record with a gradient
+    int64_t stride, d;
+    float eta, mu, scale;
+};
+
 // Packs the Reduce jobs of one wave for pair_mix_kernel (appends to `out`; see its definition for the rule); returns the
 // number of distinct vectors the jobs read.  Host only.
 int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out);
@@ -86,6 +135,8 @@ int hopk_csr_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d
 int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int64_t first, int64_t nnz, int64_t d,
                    int* flag_dev, void* stream);
 int hopk_copy(void* dst, const void* src, size_t bytes, void* stream);
+// weak, so that the host files still link for checks that stub the launchers above and never reach a device
+__attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
 // ---- host-side random numbers (hop_sim.cpp) ---------------------------------------
@@ -116,6 +167,7 @@ struct hop_schedule {
     HopMixJob* mix_dev = nullptr;       // n_records, in wave order
     HopPairJob* pair_dev = nullptr;     // the same records packed in pairs, wave by wave (null with a velocity)
     HopGradJob* grad_dev = nullptr;     // STEP records only, in wave order
+    HopSweepArgs sweep{};               // the whole pass as one launch (program null: not available for this schedule)
     int32_t* rows_dev = nullptr;        // n_records x batch
     float* coef_dev = nullptr;          // n_records x batch
     bool dense_in_place = false;        // dense SVM: margins beside the Reduce, gradient applied in place

@@ -501,8 +501,10 @@ inline int64_t pair_grid(int n_jobs, int64_t n_chunks, int run) {
 // ------------------------------------------------------------------- synthetic gradient ----
 // g[c] = (sum of the 12 bytes of a = h32(c ^ k0), b = h32(c ^ k1), (a + rotl(b, 16)) ^ k2  - 1530) * scale:
 // integer work and one correctly rounded multiply, so any implementation agrees bit for bit.
-__device__ __forceinline__ uint32_t h32(uint32_t x) {
-    x ^= x >> 16;
+// x ^ (x >> 16), the first step of the 32-bit hash below, is linear over xor: of a column and a key it is taken once each,
+// and a hash starts from the xor of the two
+__device__ __forceinline__ uint32_t fold16(uint32_t x) { return x ^ (x >> 16); }
+__device__ __forceinline__ uint32_t h32_folded(uint32_t x) {
     x *= 0x7FEB352Du;
     x ^= x >> 15;
     x *= 0x846CA68Bu;
@@ -512,16 +514,17 @@ __device__ __forceinline__ uint32_t h32(uint32_t x) {
 __device__ __forceinline__ uint32_t byte_sum(uint32_t x, uint32_t acc) {
     return __builtin_amdgcn_sad_u8(x, 0u, acc);       // acc + sum of the four bytes of x
 }
-__device__ __forceinline__ float synth_one(uint32_t c, uint32_t k0, uint32_t k1, uint32_t k2, float scale) {
+// cf, f0, f1: fold16 of the column, k0 and k1
+__device__ __forceinline__ float synth_one(uint32_t cf, uint32_t f0, uint32_t f1, uint32_t k2, float scale) {
     // two hashed words and a third made of both: a + rotl(b, 16) is uniform and independent of a and of
     // b taken one at a time, so the twelve bytes are pairwise independent and the variance is exact,
     // at two thirds of the integer multiplies (32-bit multiplies are the slow instruction here)
-    const uint32_t a = h32(c ^ k0), b = h32(c ^ k1);
+    const uint32_t a = h32_folded(cf ^ f0), b = h32_folded(cf ^ f1);
     const uint32_t t = (a + ((b << 16) | (b >> 16))) ^ k2;
-    uint32_t s = byte_sum(a, 0u);
+    uint32_t s = byte_sum(a, (uint32_t)-1530);
     s = byte_sum(b, s);
     s = byte_sum(t, s);
-    return (float)((int)s - 1530) * scale;
+    return (float)(int)s * scale;
 }
 
 constexpr int kSynthVec = 2;
@@ -536,7 +539,7 @@ __global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __res
     if (!map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) return;
     if (reverse) chunk = n_chunks - 1 - chunk;
     const HopGradJob* job = jobs + j;
-    const uint32_t k0 = job->k0, k1 = job->k1, k2 = job->k2;
+    const uint32_t f0 = fold16(job->k0), f1 = fold16(job->k1), k2 = job->k2;
     const float scale = job->scale;
     float* g = job->g;
     const int64_t n4 = d >> 2;
@@ -546,17 +549,246 @@ __global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __res
         if (i < n4) {
             uint32_t c = (uint32_t)(i << 2);
             float4 v;
-            v.x = synth_one(c, k0, k1, k2, scale);
-            v.y = synth_one(c + 1, k0, k1, k2, scale);
-            v.z = synth_one(c + 2, k0, k1, k2, scale);
-            v.w = synth_one(c + 3, k0, k1, k2, scale);
+            v.x = synth_one(fold16(c), f0, f1, k2, scale);
+            v.y = synth_one(fold16(c + 1), f0, f1, k2, scale);
+            v.z = synth_one(fold16(c + 2), f0, f1, k2, scale);
+            v.w = synth_one(fold16(c + 3), f0, f1, k2, scale);
             st4(g, i, v);
         }
     }
     if (chunk == n_chunks - 1) {
         int64_t c = (n4 << 2) + threadIdx.x;
-        if (threadIdx.x < 4 && c < d) g[c] = synth_one((uint32_t)c, k0, k1, k2, scale);
+        if (threadIdx.x < 4 && c < d) g[c] = synth_one(fold16((uint32_t)c), f0, f1, k2, scale);
     }
+}
+
+// ------------------------------------------------------------- a whole pass, column by column ----
+// Reduce, Apply and the synthetic (external, absent) gradient act on every column by itself, so a wavefront can run ALL
+// records of a pass on its own 64 columns: no launch, no barrier and no trip to HBM between two waves of the schedule.
+// The values that later records still read live in LDS (the host hands out the local slots by live range: about 1.6
+// vectors per worker, whatever the ring depth), gradients in registers; a ring slot is read once if its old content is
+// used and written once if its content survives the pass.  Lanes never exchange data: one wavefront is a workgroup.
+// Bound by instruction issue: 20 integer instructions (4 of them half-rate multiplies) for a synthetic gradient and two
+// vector instructions per source, at 87 % of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x 25 M
+// columns x 3136 records (52 local slots): 246.7 ms wave by wave -> 87.3 to 91.8 ms; 16 workers x 2 M columns x 640 records with
+// momentum: 7.87 -> 1.78 ms.  On the way there: words unpacked from bytes 180 ms (scalar unit), flags tested per record
+// 110 ms, next words loaded where the compiler moves them 99 ms; 2 and 4 columns per lane (fewer wavefronts per CU: the
+// local slots fill LDS either way) 115 and 190 ms; several wavefronts per workgroup 109 to 130 ms.
+typedef const __attribute__((address_space(4))) uint32_t* sweep_words;     // scalar loads
+
+// N program words (a multiple of 4, at most 32) by as few scalar loads as there can be
+template <int N>
+struct SweepWords {
+    static constexpr int N0 = N >= 16 ? 16 : N >= 8 ? 8 : 4, N1 = N - N0 >= 16 ? 16 : N - N0 >= 8 ? 8 : 4;
+    static constexpr bool TWO = N > N0, THREE = N > N0 + N1;
+    template <int LEN> struct Part { typedef uint32_t type __attribute__((ext_vector_type(LEN), aligned(16))); };
+    typename Part<N0>::type a;
+    typename Part<N1>::type b;
+    typename Part<4>::type c;
+    static_assert(N % 4 == 0 && N <= N0 + N1 + 4, "records come in whole fours, up to 12 sources");
+    template <class T>
+    static __device__ __forceinline__ T part(sweep_words p) { return *(const __attribute__((address_space(4))) T*)p; }
+    __device__ __forceinline__ void load(sweep_words p) {
+        a = part<typename Part<N0>::type>(p);
+        if constexpr (TWO) b = part<typename Part<N1>::type>(p + N0);
+        if constexpr (THREE) c = part<typename Part<4>::type>(p + N0 + N1);
+    }
+    __device__ __forceinline__ uint32_t operator[](int k) const {          // k constant
+        return k < N0 ? a[k < N0 ? k : 0] : k < N0 + N1 ? b[k < N0 + N1 ? k - N0 : 0] : c[(k - N0 - N1) & 3];
+    }
+    // a use of all words: the loads stay in front of it
+    __device__ __forceinline__ void hold() const {
+        asm volatile("" ::"s"(a));
+        if constexpr (TWO) asm volatile("" ::"s"(b));
+        if constexpr (THREE) asm volatile("" ::"s"(c));
+    }
+};
+
+// what a wavefront works on: column c of every vector, its lane's part of LDS
+struct SweepLane {
+    char* lds;
+    int64_t c;
+    bool exists;             // c < d
+    uint32_t folded;         // fold16(c)
+    float ahead;             // external gradients: that of the next record with one
+};
+__device__ __forceinline__ float& sweep_local(const SweepLane& l, uint32_t offset) { return *(float*)(l.lds + offset); }
+
+// FULL: all 64 columns exist
+template <bool FULL>
+__device__ __forceinline__ float sweep_load(const float* p, const SweepLane& l) {
+    if (FULL) return __builtin_nontemporal_load((const HOP_GLOBAL float*)p + l.c);
+    return l.exists ? p[l.c] : 0.f;
+}
+template <bool FULL>
+__device__ __forceinline__ void sweep_store(float* p, const SweepLane& l, float v) {
+    if (FULL) __builtin_nontemporal_store(v, (HOP_GLOBAL float*)p + l.c);
+    else if (l.exists) p[l.c] = v;
+}
+
+// a worker's external gradient; its next record reads it again: ordinary loads
+template <bool FULL>
+__device__ __forceinline__ float sweep_external(const HopSweepArgs& a, uint32_t worker, const SweepLane& l) {
+    const float* p = a.external + (int64_t)worker * a.d;
+    return FULL ? ((const HOP_GLOBAL float*)p)[l.c] : sweep_load<false>(p, l);
+}
+
+template <int MODE, bool FULL, class Words>
+__device__ __forceinline__ float sweep_grad(const HopSweepArgs& a, const Words& h, SweepLane& l) {
+    if (MODE == HOP_GRAD_SYNTH) return synth_one(l.folded, h[4], h[5], h[6], a.scale);
+    if (MODE == HOP_GRAD_EXTERNAL) {
+        const float g = l.ahead;
+        l.ahead = sweep_external<FULL>(a, h[5], l);
+        return g;
+    }
+    return 0.f;
+}
+
+// acc - eta g, through the velocity with MOM
+template <bool MOM, class Words>
+__device__ __forceinline__ float sweep_apply(const HopSweepArgs& a, const Words& h, const SweepLane& l, float g, float acc) {
+    if (MOM) {
+        float& v = sweep_local(l, h[3]);
+        g = fmaf(a.mu, v, g);
+        v = g;
+    }
+    return fmaf(-a.eta, g, acc);
+}
+
+// the first term of a sum, as mix_tile (MOM) and pair_tile begin theirs: all ways of running a record give the same bits
+template <bool MOM>
+__device__ __forceinline__ float sweep_first(uint32_t w, float x) {
+    return MOM ? __uint_as_float(w) * x : fmaf(__uint_as_float(w), x, 0.f);
+}
+
+// the result of a record to where it is read from or stays
+template <bool FULL, class Words>
+__device__ __forceinline__ void sweep_put(const HopSweepArgs& a, const Words& h, const SweepLane& l, float acc) {
+    if (h[0] & kSweepKeep) sweep_local(l, h[1]) = acc;
+    if (h[0] & kSweepStore) sweep_store<FULL>(a.ring + (int64_t)h[2] * a.stride, l, acc);
+}
+
+// One record with A sources, while the words of the next are loaded; KEPT: the result goes to a local slot and nowhere
+// else.  All loads come first, then the gradient's arithmetic over their latency (scalar loads answer out of order, so
+// the first wait for a source is a wait for the next words too), then the sum.
+template <int A, bool GRAD, bool KEPT, int MODE, bool MOM>
+__device__ __forceinline__ void sweep_record(const HopSweepArgs& a, const SweepWords<hop_sweep_words(A)>& h,
+                                             SweepWords<hop_sweep_words(A)>& next, sweep_words ahead, SweepLane& l) {
+    float x[A], g = 0.f;
+    next.load(ahead);
+#pragma unroll
+    for (int t = 0; t < A; ++t) x[t] = sweep_local(l, h[kSweepHead + 2 * t]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (GRAD) g = sweep_grad<MODE, true>(a, h, l);
+    if (GRAD && MODE == HOP_GRAD_SYNTH) asm volatile("" : "+v"(g));        // computed here, not where it is used
+    __builtin_amdgcn_sched_barrier(0);
+    float acc = sweep_first<MOM>(h[kSweepHead + 1], x[0]);
+#pragma unroll
+    for (int t = 1; t < A; ++t) acc = fmaf(__uint_as_float(h[kSweepHead + 2 * t + 1]), x[t], acc);
+    if (GRAD) acc = sweep_apply<MOM>(a, h, l, g, acc);
+    next.hold();                                           // else the compiler loads them where they are first needed
+    if (KEPT) sweep_local(l, h[1]) = acc;
+    else sweep_put<true>(a, h, l, acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// a run of such records, two a turn so that their words need not be moved; returns the words behind it
+template <int A, bool GRAD, bool KEPT, int MODE, bool MOM>
+__device__ __forceinline__ sweep_words sweep_run(const HopSweepArgs& a, sweep_words rec, uint32_t count, SweepLane& l) {
+    constexpr int N = hop_sweep_words(A);
+    SweepWords<N> even, odd;
+    even.load(rec);
+    for (;;) {
+        rec += N;
+        sweep_record<A, GRAD, KEPT, MODE, MOM>(a, even, odd, rec, l);
+        if (--count == 0) break;
+        rec += N;
+        sweep_record<A, GRAD, KEPT, MODE, MOM>(a, odd, even, rec, l);
+        if (--count == 0) break;
+    }
+    return rec;                                            // the words loaded behind the last record were not used
+}
+
+// a run of any records
+template <int MODE, bool MOM, bool FULL>
+__device__ sweep_words sweep_run_any(const HopSweepArgs& a, sweep_words rec, uint32_t count, SweepLane& l) {
+    do {
+        SweepWords<kSweepHead> h;
+        h.load(rec);
+        const sweep_words term = rec + kSweepHead;
+        float acc = sweep_first<MOM>(term[1], sweep_local(l, term[0]));
+        for (uint32_t t = 1; t < h[7]; ++t) acc = fmaf(__uint_as_float(term[2 * t + 1]), sweep_local(l, term[2 * t]), acc);
+        if (MODE != HOP_GRAD_ZERO && (h[0] & kSweepGrad))
+            acc = sweep_apply<MOM>(a, h, l, sweep_grad<MODE, FULL>(a, h, l), acc);
+        sweep_put<FULL>(a, h, l, acc);
+        rec += hop_sweep_words((int)h[7]);
+    } while (--count);
+    return rec;
+}
+
+// `n` vectors (rows of `base`) into their local slots, eight loads in flight
+template <bool FULL>
+__device__ __forceinline__ void sweep_fill(const uint32_t* __restrict__ list, int n, const float* base, int64_t stride,
+                                           const SweepLane& l) {
+    for (int k = 0; k < n; k += 8) {
+        float t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (k + q < n) t[q] = sweep_load<FULL>(base + (int64_t)list[2 * (k + q)] * stride, l);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (k + q < n) sweep_local(l, list[2 * (k + q) + 1]) = t[q];
+    }
+}
+
+template <int MODE, bool MOM, bool FULL>
+__device__ __forceinline__ void sweep_columns(const HopSweepArgs& a, SweepLane& l) {
+    const uint32_t* lists = a.program + a.first_load;
+    sweep_fill<FULL>(lists, a.n_loads, a.ring, a.stride, l);
+    lists += 2 * a.n_loads;
+    if (MOM) sweep_fill<FULL>(lists, a.n_vel, a.vel, a.stride, l);
+    if (MODE == HOP_GRAD_EXTERNAL) l.ahead = sweep_external<FULL>(a, (uint32_t)a.first_external, l);
+    const sweep_words runs = (sweep_words)a.program;
+    sweep_words rec = runs + a.first_record;
+    uint32_t ahead = runs[0];
+    for (int k = 0; k < a.n_runs; ++k) {
+        const uint32_t run = ahead, count = run >> 8;
+        ahead = runs[k + 1];
+        static_assert(kSweepInline == 12, "the switches below unroll 1..12 sources");
+#define HOP_SWEEP_CASE(AA)                                                                     \
+    case AA: rec = sweep_run<AA, false, true, MODE, MOM>(a, rec, count, l); continue;          \
+    case AA + 32: rec = sweep_run<AA, false, false, MODE, MOM>(a, rec, count, l); continue;
+#define HOP_SWEEP_GRAD(AA)                                                                     \
+    case AA + 16: rec = sweep_run<AA, true, true, MODE, MOM>(a, rec, count, l); continue;      \
+    case AA + 48: rec = sweep_run<AA, true, false, MODE, MOM>(a, rec, count, l); continue;
+        if (FULL) {                                        // the wavefront at the end of the vectors takes the plain way
+            switch (run & 0xFFu) {
+                HOP_SWEEP_CASE(1) HOP_SWEEP_CASE(2) HOP_SWEEP_CASE(3) HOP_SWEEP_CASE(4) HOP_SWEEP_CASE(5) HOP_SWEEP_CASE(6)
+                HOP_SWEEP_CASE(7) HOP_SWEEP_CASE(8) HOP_SWEEP_CASE(9) HOP_SWEEP_CASE(10) HOP_SWEEP_CASE(11) HOP_SWEEP_CASE(12)
+                default: break;
+            }
+            if (MODE != HOP_GRAD_ZERO) switch (run & 0xFFu) {
+                HOP_SWEEP_GRAD(1) HOP_SWEEP_GRAD(2) HOP_SWEEP_GRAD(3) HOP_SWEEP_GRAD(4) HOP_SWEEP_GRAD(5) HOP_SWEEP_GRAD(6)
+                HOP_SWEEP_GRAD(7) HOP_SWEEP_GRAD(8) HOP_SWEEP_GRAD(9) HOP_SWEEP_GRAD(10) HOP_SWEEP_GRAD(11) HOP_SWEEP_GRAD(12)
+                default: break;
+            }
+        }
+        rec = sweep_run_any<MODE, MOM, FULL>(a, rec, count, l);
+#undef HOP_SWEEP_CASE
+#undef HOP_SWEEP_GRAD
+    }
+    if (MOM)
+        for (int n = 0; n < a.n_vel; ++n)
+            sweep_store<FULL>(a.vel + (int64_t)lists[2 * n] * a.stride, l, sweep_local(l, lists[2 * n + 1]));
+}
+
+template <int MODE, bool MOM>
+__global__ __launch_bounds__(64) void sweep_kernel(const HopSweepArgs a) {
+    extern __shared__ float sweep_lds[];
+    const int64_t first = (int64_t)blockIdx.x * 64, c = first + threadIdx.x;
+    SweepLane l{(char*)(sweep_lds + threadIdx.x), c, c < a.d, fold16((uint32_t)c), 0.f};
+    if (first + 64 <= a.d) sweep_columns<MODE, MOM, true>(a, l);
+    else sweep_columns<MODE, MOM, false>(a, l);
 }
 
 // ------------------------------------------------------------------ wavefront reductions ----
@@ -1030,6 +1262,23 @@ int hopk_synth(const HopGradJob* jobs_dev, int n_jobs, int reverse, int64_t d, v
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(synth_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev,
                        n_jobs, d, n_chunks, reverse);
+    return launch_status();
+}
+
+template <int MODE>
+static void launch_sweep(const HopSweepArgs& a, unsigned grid, void* stream) {
+    const size_t lds = (size_t)a.n_local * 64 * sizeof(float);
+    if (a.vel) hipLaunchKernelGGL((sweep_kernel<MODE, true>), dim3(grid), dim3(64), lds, (hipStream_t)stream, a);
+    else hipLaunchKernelGGL((sweep_kernel<MODE, false>), dim3(grid), dim3(64), lds, (hipStream_t)stream, a);
+}
+
+int hopk_sweep(const HopSweepArgs& a, void* stream) {
+    if (a.n_runs <= 0) return 0;
+    const int64_t grid = (a.d + 63) / 64;
+    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    if (a.mode == HOP_GRAD_SYNTH) launch_sweep<HOP_GRAD_SYNTH>(a, (unsigned)grid, stream);
+    else if (a.mode == HOP_GRAD_EXTERNAL) launch_sweep<HOP_GRAD_EXTERNAL>(a, (unsigned)grid, stream);
+    else launch_sweep<HOP_GRAD_ZERO>(a, (unsigned)grid, stream);
     return launch_status();
 }
 

@@ -35,6 +35,34 @@ __device__ __forceinline__ void st4(float* p, int64_t i4, float4 v) {
     vf4 t = {v.x, v.y, v.z, v.w};
     ((gvec_out)p)[i4] = t;
 }
+// Four columns from column c on of a vector that need not be 16-byte aligned (the rows of a dense data set when d is no
+// multiple of 4): global memory takes 128-bit accesses at any multiple of 4 bytes.  `n`: columns that exist, at least 1.
+typedef float vf4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 ldu4(const float* p, int64_t c) {
+    const vf4u v = *(const HOP_GLOBAL vf4u*)(p + c);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ldu4_stream(const float* p, int64_t c) {
+    const vf4u v = __builtin_nontemporal_load((const HOP_GLOBAL vf4u*)(p + c));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ldu4(const float* p, int64_t c, int n) {
+    if (n >= 4) return ldu4(p, c);
+    return make_float4(p[c], n > 1 ? p[c + 1] : 0.f, n > 2 ? p[c + 2] : 0.f, 0.f);
+}
+__device__ __forceinline__ void stu4(float* p, int64_t c, int n, float4 v) {
+    if (n >= 4) {
+        const vf4u t = {v.x, v.y, v.z, v.w};
+        *(HOP_GLOBAL vf4u*)(p + c) = t;
+        return;
+    }
+    p[c] = v.x;
+    if (n > 1) p[c + 1] = v.y;
+    if (n > 2) p[c + 2] = v.z;
+}
+__device__ __forceinline__ float4 fma4(float a, float4 x, float4 y) {
+    return make_float4(fmaf(a, x.x, y.x), fmaf(a, x.y, y.y), fmaf(a, x.z, y.z), fmaf(a, x.w, y.w));
+}
 // streaming (non-temporal) 128-bit accesses for data touched once
 __device__ __forceinline__ float4 ld4_stream(const float* p, int64_t i4) {
     vf4 v = __builtin_nontemporal_load((gvec_in)p + i4);
@@ -798,19 +826,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;                                          // lane 0 holds the sum
 }
 
-__device__ __forceinline__ float block_sum(float v, float* red) {
-    v = wave_sum(v);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) red[wv] = v;
-    __syncthreads();
-    float t = 0.f;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < kThreads / 64; ++k) t += red[k];
-    }
-    return t;                                          // thread 0 holds the sum
-}
-
 // c_m of g = lambda w - sum_m c_m x_m: hinge y/B where y <x, w> < 1, log loss y / (B (1 + e^{y <x, w>}))
 __device__ __forceinline__ float loss_coef(float y, float dot, float invB, int loss) {
     const float m = y * dot;
@@ -824,99 +839,77 @@ constexpr int kSegVec = 16;
 constexpr int kSeg4 = kThreads * kSegVec;             // float4 per segment
 constexpr int64_t kSegCols = (int64_t)kSeg4 * 4;
 
-__device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
-                                                   int64_t b, float* red) {
-    const int seg = (int)(b % nseg);
-    const int m = (int)((b / nseg) % B);
-    const HopGradJob* job = jobs + b / ((int64_t)nseg * B);
-    const float* x = job->X + (int64_t)job->rows[m] * d;
+// ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t.
+// Each row is summed in the same order whatever ROWS is.
+template <int ROWS>
+__device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, int seg,
+                                                  int m0, float (*red)[kThreads / 64]) {
     const float* w = job->w;
-    float acc = 0.f;
+    const float* x[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) x[r] = job->X + (int64_t)job->rows[min(m0 + r, B - 1)] * d;
     const int64_t lo = (int64_t)seg * kSegCols;
     const int64_t hi = min(d, lo + kSegCols);
-    if ((d & 3) == 0) {
-        const int64_t lo4 = lo >> 2, hi4 = hi >> 2;
-        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-#pragma unroll 4
-        for (int64_t i = lo4 + threadIdx.x; i < hi4; i += kThreads) {
-            float4 xv = ld4_stream(x, i);
-            float4 wv = ld4(w, i);
-            a0 = fmaf(xv.x, wv.x, a0);
-            a1 = fmaf(xv.y, wv.y, a1);
-            a2 = fmaf(xv.z, wv.z, a2);
-            a3 = fmaf(xv.w, wv.w, a3);
+    float a[ROWS][4];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) a[r][0] = a[r][1] = a[r][2] = a[r][3] = 0.f;
+    const int64_t hi4 = hi >> 2;
+    constexpr int kAhead = ROWS == 1 ? 8 : 4;
+#pragma unroll kAhead
+    for (int64_t i = (lo >> 2) + threadIdx.x; i < hi4; i += kThreads) {
+        const float4 wv = ldu4(w, i << 2);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const float4 xv = ldu4_stream(x[r], i << 2);
+            a[r][0] = fmaf(xv.x, wv.x, a[r][0]);
+            a[r][1] = fmaf(xv.y, wv.y, a[r][1]);
+            a[r][2] = fmaf(xv.z, wv.z, a[r][2]);
+            a[r][3] = fmaf(xv.w, wv.w, a[r][3]);
         }
-        acc = (a0 + a1) + (a2 + a3);
-    } else {
-        for (int64_t c = lo + threadIdx.x; c < hi; c += kThreads) acc = fmaf(x[c], w[c], acc);
     }
-    float tot = block_sum(acc, red);
-    if (threadIdx.x == 0) job->partial[(int64_t)m * nseg + seg] = tot;
-}
-
-// The margin pass as a launch of its own: four minibatch rows per workgroup share every load of w (the L2 sees
-// 5 requests per 4 row pieces instead of 8), each row summed exactly as dense_margin_block sums it, so the partial
-// dot products are the same bit for bit.  Rows by non-temporal loads: a wave's rows are new to every cache, and a
-// cold stream runs faster without allocating in the memory-side cache (6.9 against 5.5 TB/s stand-alone).  Leaving
-// them there for the gradient pass with ordinary loads was measured on 16 workers x 65536 columns, B = 128:
-// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained.
-constexpr int kMarginRows = 4;
-
-__global__ __launch_bounds__(kThreads) void dense_margin4_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
-                                                                 int nseg, int row_groups) {
-    __shared__ float red[kMarginRows][kThreads / 64];
-    const int64_t b = blockIdx.x;
-    const int seg = (int)(b % nseg);
-    const int m0 = (int)((b / nseg) % row_groups) * kMarginRows;
-    const HopGradJob* job = jobs + b / ((int64_t)nseg * row_groups);
-    const float* w = job->w;
-    const float* x[kMarginRows];
+    if (const int64_t c = (hi4 << 2) + threadIdx.x; c < hi) {      // the d mod 4 last columns
 #pragma unroll
-    for (int r = 0; r < kMarginRows; ++r) x[r] = job->X + (int64_t)job->rows[min(m0 + r, B - 1)] * d;
-    const int64_t lo = (int64_t)seg * kSegCols;
-    const int64_t hi = min(d, lo + kSegCols);
-    float acc[kMarginRows];
-    if ((d & 3) == 0) {
-        const int64_t lo4 = lo >> 2, hi4 = hi >> 2;
-        float a[kMarginRows][4];
-#pragma unroll
-        for (int r = 0; r < kMarginRows; ++r) a[r][0] = a[r][1] = a[r][2] = a[r][3] = 0.f;
-#pragma unroll 4
-        for (int64_t i = lo4 + threadIdx.x; i < hi4; i += kThreads) {
-            const float4 wv = ld4(w, i);
-#pragma unroll
-            for (int r = 0; r < kMarginRows; ++r) {
-                const float4 xv = ld4_stream(x[r], i);
-                a[r][0] = fmaf(xv.x, wv.x, a[r][0]);
-                a[r][1] = fmaf(xv.y, wv.y, a[r][1]);
-                a[r][2] = fmaf(xv.z, wv.z, a[r][2]);
-                a[r][3] = fmaf(xv.w, wv.w, a[r][3]);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < kMarginRows; ++r) acc[r] = (a[r][0] + a[r][1]) + (a[r][2] + a[r][3]);
-    } else {
-#pragma unroll
-        for (int r = 0; r < kMarginRows; ++r) acc[r] = 0.f;
-        for (int64_t c = lo + threadIdx.x; c < hi; c += kThreads) {
-            const float wc = w[c];
-#pragma unroll
-            for (int r = 0; r < kMarginRows; ++r) acc[r] = fmaf(x[r][c], wc, acc[r]);
-        }
+        for (int r = 0; r < ROWS; ++r) a[r][0] = fmaf(x[r][c], w[c], a[r][0]);
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int r = 0; r < kMarginRows; ++r) {
-        const float v = wave_sum(acc[r]);
+    for (int r = 0; r < ROWS; ++r) {
+        const float v = wave_sum((a[r][0] + a[r][1]) + (a[r][2] + a[r][3]));
         if (lane == 0) red[r][wv] = v;
     }
     __syncthreads();
-    if (threadIdx.x < kMarginRows && m0 + threadIdx.x < B) {
+    if (threadIdx.x < ROWS && m0 + threadIdx.x < B) {
         float t = 0.f;
 #pragma unroll
         for (int k = 0; k < kThreads / 64; ++k) t += red[threadIdx.x][k];
         job->partial[(int64_t)(m0 + threadIdx.x) * nseg + seg] = t;
     }
+}
+
+// one workgroup per (job, ROWS minibatch rows, column segment); b: its index
+template <int ROWS>
+__device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
+                                                   int64_t b, float (*red)[kThreads / 64]) {
+    const int groups = (B + ROWS - 1) / ROWS;
+    dense_margin_rows<ROWS>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
+                            (int)((b / nseg) % groups) * ROWS, red);
+}
+
+// The margin pass as a launch of its own: four minibatch rows per workgroup share every load of w (the L2 sees
+// 5 requests per 4 row pieces instead of 8); with few workgroups (kMarginFew) one row each, so that all CUs have rows in
+// flight (one minibatch of 128 x 65536: 14.1 -> 8.9 us; 3 records of 100 x 30 011: 36 -> 14 us, scalar loads before; waves of
+// 2 to 5 records of 128 x 65536: 4 % less than with four rows).
+// Rows by non-temporal loads: a wave's rows are new to every cache, and a cold stream runs faster without allocating in the memory-side cache (6.9 against 5.5 TB/s stand-alone).  Leaving
+// them there for the gradient pass with ordinary loads was measured on 16 workers x 65536 columns, B = 128:
+// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained.
+constexpr int kMarginRows = 4;
+constexpr int64_t kMarginFew = 768;
+
+template <int ROWS>
+__global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
+                                                                int nseg) {
+    __shared__ float red[ROWS][kThreads / 64];
+    dense_margin_block<ROWS>(jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
@@ -927,16 +920,16 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
                                                                     int64_t d, int64_t n_chunks,
                                                                     const HopGradJob* __restrict__ grad_jobs, int B,
                                                                     int nseg, int64_t margin_blocks) {
-    __shared__ float red[kThreads / 64];
+    __shared__ float red[1][kThreads / 64];
     if ((int64_t)blockIdx.x >= margin_blocks) {
         mix_block<VEC, NT, MAP, kThreads>(mix_jobs, n_mix, d, n_chunks, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block(grad_jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<1>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
-// One workgroup per (job, 1024-column chunk).  The hinge coefficients c_m = y_m / B if
+// One workgroup per (job, 256-column chunk).  The hinge coefficients c_m = y_m / B if
 // y_m <x_m, w> < 1 else 0 are rebuilt by every workgroup from the partial dot products (B values,
 // cheap) and the active rows are compacted in LDS in minibatch order.  Three endings: write g; apply -eta g to
 // a vector the wave's Reduce has already left in the result slot; or do the record's Reduce here as well
@@ -945,26 +938,30 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
 constexpr int kMaxB = 1024;
 constexpr int kRowUnroll = 8;
 
-// SPLIT > 1: that many groups of 256 threads share a column chunk and take alternate groups of 8 active rows; their
-// sums are joined through LDS in a fixed order.  For launches that leave most of the GPU idle (4 workers x 1024
-// columns: 4 workgroups), where the time is the chain of dependent row loads: 8 rounds become 2.
+// A column chunk is 256 columns; SPLIT wavefronts share it and take alternate groups of 8 active rows; their sums are
+// joined through LDS in a fixed order.  The time is the chain of dependent row loads, so a chunk is as narrow as a
+// wavefront's 1 KB of a row and its rows are split.  Per pass, chunks of 1024 columns with one group of 256 threads (four
+// in launches of up to 128 workgroups) -> this kernel: 8 workers x 30 011 columns, B = 100 (rows not 16-byte aligned,
+// scalar loads before): 6.91 -> 2.20 ms; 16 x 65536, B = 128: 3.86 -> 3.75 ms; 4 x 1024, B = 64: 392 -> 385 us; one
+// gradient of 128 x 65536: 14.4 -> 8.8 us.  4 against 8 wavefronts per chunk: 2.35 / 2.19 ms, 3.77 / 3.89 ms, 359 / 364 us.
+constexpr int64_t kGradFew = 768;                      // chunks up to which a launch takes 8 wavefronts for each
+
 template <int SPLIT>
-__global__ __launch_bounds__(kThreads * SPLIT) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs,
-                                                                      int B, int64_t d, int nseg, float lambda,
-                                                                      int loss, int64_t n_chunks) {
+__global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
+                                                                int64_t d, int nseg, float lambda, int loss,
+                                                                int64_t n_chunks) {
     __shared__ float coefS[kMaxB + kRowUnroll];
     __shared__ int rowS[kMaxB + kRowUnroll];
     __shared__ float allC[kMaxB];
     __shared__ int nactS;
-    __shared__ float4 joinS[SPLIT > 1 ? (SPLIT - 1) * kThreads : 1];
+    __shared__ float4 joinS[(SPLIT - 1) * 64];
     int j;
     int64_t chunk;
     if (!map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) return;
     const HopGradJob* job = jobs + j;
     const float invB = 1.0f / (float)B;
-    const int part = SPLIT > 1 ? (int)threadIdx.x / kThreads : 0;     // which share of the rows
-    const int col = SPLIT > 1 ? (int)threadIdx.x % kThreads : (int)threadIdx.x;
-    for (int m = threadIdx.x; m < B; m += kThreads * SPLIT) {
+    const int part = (int)threadIdx.x / 64, col = (int)threadIdx.x % 64;        // which share of the rows
+    for (int m = threadIdx.x; m < B; m += 64 * SPLIT) {
         float dot = 0.f;
         for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
         float c = loss_coef(job->y[job->rows[m]], dot, invB, loss);
@@ -1001,92 +998,53 @@ __global__ __launch_bounds__(kThreads * SPLIT) void dense_grad_kernel(const HopG
     const HopMixJob* red = job->reduce;                // set (with out): out = sum_a w'_a x_a - eta g, the Reduce done here
     float* vel = job->vel;
     const float neg_eta = -job->eta, mu = job->mu;
-    if ((d & 3) == 0) {
-        const int64_t n4 = d >> 2;
-        const int64_t i = chunk * kThreads + col;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i < n4) {
-            for (int n = part * kRowUnroll; n < nact; n += kRowUnroll * SPLIT) {
-                float4 v[kRowUnroll];
+    const int64_t c = (chunk * 64 + col) * 4;          // first of this thread's columns
+    const int n = (int)min((int64_t)4, d - c);         // how many of them exist
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n == 4) {
+        for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT) {
+            float4 v[kRowUnroll];
 #pragma unroll
-                for (int u = 0; u < kRowUnroll; ++u) v[u] = ld4(X + (int64_t)rowS[n + u] * d, i);
+            for (int u = 0; u < kRowUnroll; ++u) v[u] = ldu4(X + (int64_t)rowS[q + u] * d, c);
 #pragma unroll
-                for (int u = 0; u < kRowUnroll; ++u) {
-                    const float c = coefS[n + u];
-                    acc.x = fmaf(c, v[u].x, acc.x);
-                    acc.y = fmaf(c, v[u].y, acc.y);
-                    acc.z = fmaf(c, v[u].z, acc.z);
-                    acc.w = fmaf(c, v[u].w, acc.w);
-                }
-            }
+            for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], v[u], acc);
         }
-        if (SPLIT > 1) {                               // join the shares: ((part 0 + part 1) + part 2) + ...
-            if (part > 0) joinS[(part - 1) * kThreads + col] = acc;
-            __syncthreads();
-            if (part == 0) {
+    } else if (n > 0) {                                // the thread at the end of a vector with d mod 4 columns left
+        for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT)
+            for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], ldu4(X + (int64_t)rowS[q + u] * d, c, n), acc);
+    }
+    if (part > 0) joinS[(part - 1) * 64 + col] = acc;  // join the shares: ((part 0 + part 1) + part 2) + ...
+    __syncthreads();
+    if (part == 0) {
 #pragma unroll
-                for (int q = 1; q < SPLIT; ++q) {
-                    const float4 t = joinS[(q - 1) * kThreads + col];
-                    acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
-                }
-            }
-        }
-        if (i < n4 && part == 0) {
-            float4 wv = ld4(w, i);
-            float4 gv = make_float4(fmaf(lambda, wv.x, -acc.x), fmaf(lambda, wv.y, -acc.y),
-                                    fmaf(lambda, wv.z, -acc.z), fmaf(lambda, wv.w, -acc.w));
-            if (out == nullptr) {
-                st4(g, i, gv);
-            } else {
-                if (vel != nullptr) {
-                    const float4 v = ld4(vel, i);
-                    gv = make_float4(fmaf(mu, v.x, gv.x), fmaf(mu, v.y, gv.y), fmaf(mu, v.z, gv.z), fmaf(mu, v.w, gv.w));
-                    st4(vel, i, gv);
-                }
-                float4 o;
-                if (red != nullptr) {                  // the record's Reduce, in the order the mix kernels sum
-                    const int A = red->A;
-                    float4 v = ld4(red->src[0], i);
-                    float wa = red->w[0];
-                    o = make_float4(wa * v.x, wa * v.y, wa * v.z, wa * v.w);
-                    for (int a = 1; a < A; ++a) {
-                        v = ld4(red->src[a], i);
-                        wa = red->w[a];
-                        o = make_float4(fmaf(wa, v.x, o.x), fmaf(wa, v.y, o.y), fmaf(wa, v.z, o.z), fmaf(wa, v.w, o.w));
-                    }
-                } else {                               // already reduced into the result slot
-                    o = ld4(out, i);
-                }
-                st4(out, i, make_float4(fmaf(neg_eta, gv.x, o.x), fmaf(neg_eta, gv.y, o.y), fmaf(neg_eta, gv.z, o.z),
-                                        fmaf(neg_eta, gv.w, o.w)));
-            }
-        }
-    } else if (part == 0) {
-        for (int q = 0; q < 4; ++q) {
-            const int64_t c = (chunk * kThreads + col) * 4 + q;
-            if (c < d) {
-                float acc = 0.f;
-                for (int n = 0; n < nact; ++n) acc = fmaf(coefS[n], X[(int64_t)rowS[n] * d + c], acc);
-                float gv = fmaf(lambda, w[c], -acc);
-                if (out == nullptr) {
-                    g[c] = gv;
-                } else {
-                    if (vel != nullptr) {
-                        gv = fmaf(mu, vel[c], gv);
-                        vel[c] = gv;
-                    }
-                    float o;
-                    if (red != nullptr) {
-                        o = red->w[0] * red->src[0][c];
-                        for (int a = 1; a < red->A; ++a) o = fmaf(red->w[a], red->src[a][c], o);
-                    } else {
-                        o = out[c];
-                    }
-                    out[c] = fmaf(neg_eta, gv, o);
-                }
-            }
+        for (int q = 1; q < SPLIT; ++q) {
+            const float4 t = joinS[(q - 1) * 64 + col];
+            acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
         }
     }
+    if (n <= 0 || part != 0) return;
+    const float4 wv = ldu4(w, c, n);
+    float4 gv = make_float4(fmaf(lambda, wv.x, -acc.x), fmaf(lambda, wv.y, -acc.y), fmaf(lambda, wv.z, -acc.z),
+                            fmaf(lambda, wv.w, -acc.w));
+    if (out == nullptr) {
+        stu4(g, c, n, gv);
+        return;
+    }
+    if (vel != nullptr) {
+        gv = fma4(mu, ldu4(vel, c, n), gv);
+        stu4(vel, c, n, gv);
+    }
+    float4 o;
+    if (red != nullptr) {                              // the record's Reduce, in the order the mix kernels sum
+        const int A = red->A;
+        const float4 v = ldu4(red->src[0], c, n);
+        const float wa = red->w[0];
+        o = make_float4(wa * v.x, wa * v.y, wa * v.z, wa * v.w);
+        for (int a = 1; a < A; ++a) o = fma4(red->w[a], ldu4(red->src[a], c, n), o);
+    } else {                                           // already reduced into the result slot
+        o = ldu4(out, c, n);
+    }
+    stu4(out, c, n, fma4(neg_eta, gv, o));
 }
 
 // ------------------------------------------------------------------- CSR SVM: margins ----
@@ -1143,12 +1101,12 @@ __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPa
                                                                      int64_t d, int64_t n_chunks, int run, int reverse,
                                                                      const HopGradJob* __restrict__ grad_jobs, int B,
                                                                      int nseg, int64_t margin_blocks) {
-    __shared__ float red[kThreads / 64];
+    __shared__ float red[1][kThreads / 64];
     if ((int64_t)blockIdx.x >= margin_blocks) {
         pair_block(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block(grad_jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<1>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 template <int VEC, int NT, int MAP>
@@ -1290,11 +1248,25 @@ int hopk_dense_nseg(int64_t d) {
 int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     const int nseg = hopk_dense_nseg(d);
-    const int row_groups = (B + kMarginRows - 1) / kMarginRows;
-    const int64_t grid = (int64_t)n_jobs * row_groups * nseg;
+    const int64_t few = (int64_t)n_jobs * B * nseg;
+    const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
+    if (few > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    if (grid < kMarginFew)
+        hipLaunchKernelGGL(dense_margin_kernel<1>, dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, B,
+                           d, nseg);
+    else
+        hipLaunchKernelGGL(dense_margin_kernel<kMarginRows>, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream,
+                           jobs_dev, B, d, nseg);
+    return launch_status();
+}
+
+template <int SPLIT>
+static int launch_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, void* stream) {
+    const int64_t n_chunks = (d + 255) / 256;
+    const int64_t grid = grid_for(n_jobs, n_chunks);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(dense_margin4_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, B,
-                       d, nseg, row_groups);
+    hipLaunchKernelGGL(dense_grad_kernel<SPLIT>, dim3((unsigned)grid), dim3(64 * SPLIT), 0, (hipStream_t)stream,
+                       jobs_dev, n_jobs, B, d, hopk_dense_nseg(d), lambda, loss, n_chunks);
     return launch_status();
 }
 
@@ -1302,18 +1274,8 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
                     void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
-    int nseg = hopk_dense_nseg(d);
-    int64_t n_chunks = (d + 4 * kThreads - 1) / (4 * kThreads);
-    int64_t grid = grid_for(n_jobs, n_chunks);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    // a launch of fewer workgroups than the GPU has CUs is bound by each workgroup's chain of row loads
-    if (grid <= 128 && (d & 3) == 0)
-        hipLaunchKernelGGL(dense_grad_kernel<4>, dim3((unsigned)grid), dim3(kThreads * 4), 0, (hipStream_t)stream,
-                           jobs_dev, n_jobs, B, d, nseg, lambda, loss, n_chunks);
-    else
-        hipLaunchKernelGGL(dense_grad_kernel<1>, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev,
-                           n_jobs, B, d, nseg, lambda, loss, n_chunks);
-    return launch_status();
+    if (n_jobs * ((d + 255) / 256) <= kGradFew) return launch_dense_grad<8>(jobs_dev, n_jobs, B, d, lambda, loss, stream);
+    return launch_dense_grad<4>(jobs_dev, n_jobs, B, d, lambda, loss, stream);
 }
 
 int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, void* stream) {

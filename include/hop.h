@@ -301,7 +301,8 @@ int hop_profile(hop_ctx* ctx, int enable);
 int hop_profile_read(hop_ctx* ctx, int kernel, double* ms, int64_t* launches, double* bytes);
 
 /* Stand-alone kernels on caller-supplied device memory (same code the schedule runs).  Unlike
- * hop_step these calls are synchronous: they upload a small descriptor (hipMalloc / hipFree inside),
+ * hop_step these calls are synchronous: they pass their descriptor as a kernel argument (hop_mix with a
+ * velocity, with more jobs than fit or with more than 12 sources uploads it: hipMalloc / hipFree inside),
  * launch on the given stream and wait for it.  All vectors must be 16-byte aligned (when d is a
  * multiple of 4 this includes every row of X); a misaligned or NULL pointer, A outside 1..HOP_MAX_A
  * or B outside 1..1024 gives HOP_ERR_INVALID_ARG and nothing is launched.  The contents of device
@@ -319,8 +320,8 @@ int hop_svm_grad_dense(const float* X, const float* y, const float* w, const int
                        float* scratch, void* hip_stream);
 /* The same gradient for callers that cannot allocate device memory - a stream under graph capture, a tight
  * serving loop, a harness that forbids hipMalloc.  Same arguments and results as hop_svm_grad_dense without
- * the scratch argument: the descriptor and the partial dot products live in a fixed array of device memory
- * inside the library (256 KB + 256 B per GPU, held until the process ends), and the call only enqueues three
+ * the scratch argument: the partial dot products live in a fixed array of device memory
+ * inside the library (256 KB per GPU, held until the process ends), and the call only enqueues two
  * kernels on the stream and returns (no allocation, no copy, no wait: the caller synchronises).  Limit:
  * B x ceil(d / 16384) <= 65536, else HOP_ERR_ARENA_TOO_SMALL and nothing is launched.  All calls on one GPU
  * share that array: calls whose kernels could overlap (different streams, or a captured graph replayed

@@ -1185,6 +1185,32 @@ int hop_mix(const hop_mix_job* jobs, int32_t n_jobs, int64_t d, void* stream) {
     std::vector<HopPairJob> pairs;
     int n_sources = 0;
     if (!any_vel) n_sources = hop_pack_pairs(host.data(), n_jobs, pairs);    // the path hop_step takes without velocities
+    // a few narrow jobs travel as the kernel's argument
+    bool narrow = !any_vel && pairs.size() <= (size_t)kPairArgs;
+    for (const HopPairJob& pj : pairs) narrow = narrow && pj.U <= HOP_PAIR_U;
+    if (narrow) {
+        HopPairArg args[kPairArgs];
+        std::memset(args, 0, sizeof(args));
+        for (size_t q = 0; q < pairs.size(); ++q) {
+            const HopPairJob& pj = pairs[q];
+            HopPairArg& a = args[q];
+            a.U = (uint8_t)pj.U;
+            a.G = (uint8_t)pj.G;
+            a.eta = pj.eta;
+            for (int r = 0; r < 2; ++r) {
+                a.out[r] = pj.out[r];
+                a.g[r] = pj.g[r];
+                a.mask[r] = pj.mask[r];
+                std::copy(pj.w[r], pj.w[r] + HOP_PAIR_U, a.w[r]);
+            }
+            std::copy(pj.src, pj.src + HOP_PAIR_U, a.src);
+        }
+        const int rc = hopk_pair_args(args, (int)pairs.size(), n_sources, d, stream);
+        const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
+        if (rc) return hip_fail(nullptr, (hipError_t)rc, "mix launch");
+        if (e != hipSuccess) return hip_fail(nullptr, e, "hipStreamSynchronize");
+        return HOP_OK;
+    }
     const size_t bytes = any_vel ? host.size() * sizeof(HopMixJob) : pairs.size() * sizeof(HopPairJob);
     void* dev = nullptr;
     HOP_HIP(nullptr, hipMalloc(&dev, bytes));
@@ -1207,27 +1233,11 @@ int64_t hop_grad_scratch_floats(int64_t d, int32_t B) {
     return partial_floats(d, B);
 }
 
-static int run_one_grad(const HopGradJob& gj, int kind, int B, int64_t d, float lambda, int loss, void* stream) {
-    HopGradJob* dev = nullptr;
-    HOP_HIP(nullptr, hipMalloc((void**)&dev, sizeof(HopGradJob)));
-    hipError_t e = hipMemcpy(dev, &gj, sizeof(HopGradJob), hipMemcpyHostToDevice);
-    int rc = 0;
-    if (e == hipSuccess) {
-        if (kind == HOP_GRAD_SVM_DENSE) {
-            rc = hopk_dense_margin(dev, 1, B, d, stream);
-            if (!rc) rc = hopk_dense_grad(dev, 1, B, d, lambda, loss, stream);
-        } else if (kind == HOP_GRAD_SVM_CSR) {
-            rc = hopk_csr_margin(dev, 1, B, loss, stream);
-            if (!rc) rc = hopk_csr_dense_grad(dev, 1, B, d, lambda, stream);
-        } else {
-            rc = hopk_synth(dev, 1, 0, d, stream);
-        }
-    }
-    hipError_t e2 = hipStreamSynchronize((hipStream_t)stream);
-    (void)hipFree(dev);
-    if (e != hipSuccess) return hip_fail(nullptr, e, "hipMemcpy");
+static int run_one_grad(const HopGradJob& gj, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
+    const int rc = hopk_one_grad(gj, mode, B, d, lambda, loss, stream);
+    const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
     if (rc) return hip_fail(nullptr, (hipError_t)rc, "gradient launch");
-    if (e2 != hipSuccess) return hip_fail(nullptr, e2, "hipStreamSynchronize");
+    if (e != hipSuccess) return hip_fail(nullptr, e, "hipStreamSynchronize");
     return HOP_OK;
 }
 

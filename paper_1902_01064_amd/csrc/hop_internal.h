@@ -38,6 +38,19 @@ struct alignas(16) HopPairJob {
     float w[2][HOP_MAX_A];     // weight of src[u] in record r (0 where the record does not read it)
 };
 
+// What a stand-alone call's kernel argument holds of a pair job: up to HOP_PAIR_U vectors.
+struct alignas(8) HopPairArg {
+    float* out[2];
+    const float* g[2];
+    const float* src[HOP_PAIR_U];
+    float w[2][HOP_PAIR_U];
+    uint32_t mask[2];
+    uint8_t U, G;
+    float eta;
+};
+constexpr int kPairArgs = 16;           // of them in the 4 KB of arguments a kernel can have, beside the sizes
+static_assert(sizeof(HopPairArg) * kPairArgs <= 4096 - 64, "kernel arguments");
+
 struct alignas(16) HopGradJob {
     // dense: X row-major rows x d; csr: rowptr/col/val
     const float* X;
@@ -131,12 +144,14 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
 int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream);
 int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor, int into_velocity, void* stream);
-int hopk_csr_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, void* stream);
 int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int64_t first, int64_t nnz, int64_t d,
                    int* flag_dev, void* stream);
 int hopk_copy(void* dst, const void* src, size_t bytes, void* stream);
 // weak, so that the host files still link for checks that stub the launchers above and never reach a device
 __attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
+// one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out), the Reduce of up to kPairArgs jobs: descriptors on the host
+__attribute__((weak)) int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream);
+__attribute__((weak)) int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
 // ---- host-side random numbers (hop_sim.cpp) ---------------------------------------

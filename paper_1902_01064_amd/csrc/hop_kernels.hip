@@ -353,8 +353,8 @@ int launch_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
 constexpr int kPairU = HOP_PAIR_U;
 constexpr int kPairVec = 4;
 
-template <int U, bool FULL>
-__device__ __forceinline__ void pair_tile(const HopPairJob* __restrict__ job, int64_t first4, int64_t n4) {
+template <int U, bool FULL, class Job>
+__device__ __forceinline__ void pair_tile(Job job, int64_t first4, int64_t n4) {
     constexpr int VEC = kPairVec;
     const int G = job->G;
     const float* src[U];
@@ -421,7 +421,8 @@ __device__ __forceinline__ void pair_tile(const HopPairJob* __restrict__ job, in
 }
 
 // a single record with more than kPairU sources: a loop over the sources
-__device__ __forceinline__ void pair_tile_wide(const HopPairJob* __restrict__ job, int64_t first4, int64_t n4) {
+template <class Job>
+__device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t n4) {
     const int U = job->U;
     const float* g = job->g[0];
     const float neg_eta = -job->eta;
@@ -449,7 +450,9 @@ __device__ __forceinline__ void pair_tile_wide(const HopPairJob* __restrict__ jo
 }
 
 // Work of one workgroup; `bid` is its index among the launch's mix workgroups.
-__device__ __forceinline__ void pair_block(const HopPairJob* __restrict__ jobs, int n_jobs, int64_t d, int64_t n_chunks,
+// Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
+template <class Job>
+__device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int64_t n_chunks,
                                            int run, int reverse, int64_t bid) {
     const int xcd = (int)(bid % kXcd);
     const int64_t local = bid / kXcd;
@@ -470,7 +473,7 @@ __device__ __forceinline__ void pair_block(const HopPairJob* __restrict__ jobs, 
     // is still in the memory-side cache when the next launch begins there (1453 -> 1430 us per launch with the
     // gradient generator in between, 386 -> 381 us between launches of small waves)
     const int64_t chunk = reverse ? n_chunks - 1 - ahead : ahead;
-    const HopPairJob* job = jobs + j;
+    const Job job = jobs + j;
     const int64_t n4 = d >> 2;
     const int64_t first4 = chunk * (int64_t)(kThreads * kPairVec);
     const bool full = first4 + kThreads * kPairVec <= n4;
@@ -503,6 +506,20 @@ __device__ __forceinline__ void pair_block(const HopPairJob* __restrict__ jobs, 
 __global__ __launch_bounds__(kThreads) void pair_mix_kernel(const HopPairJob* __restrict__ jobs, int n_jobs, int64_t d,
                                                             int64_t n_chunks, int run, int reverse) {
     pair_block(jobs, n_jobs, d, n_chunks, run, reverse, blockIdx.x);
+}
+
+// The same for a stand-alone call: its descriptors travel as the kernel's argument, so the call allocates and copies
+// nothing (16 jobs of 5 sources and a gradient on 1 M columns, through the
+// Python binding: 76.8 -> 56.3 us a call, 34.8 us of them this kernel).
+struct HopPairArgs {
+    HopPairArg job[kPairArgs];
+};
+typedef const __attribute__((address_space(4))) HopPairArg* pair_args_in;
+
+__global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, int n_jobs, int64_t d, int64_t n_chunks,
+                                                                 int run) {
+    // the first argument where it lies: a copy indexed by job would go through scratch memory
+    pair_block((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), n_jobs, d, n_chunks, run, 0, blockIdx.x);
 }
 
 inline int64_t pair_chunks(int64_t d) {
@@ -560,13 +577,7 @@ constexpr int kSynthChunk4 = kThreads * kSynthVec;
 
 // `reverse`: walk the vectors from their end, so that the launch finishes where the Reduce + Apply that consumes
 // these gradients starts and finds their last-written part still in the memory-side cache.
-__global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __restrict__ jobs, int n_jobs,
-                                                         int64_t d, int64_t n_chunks, int reverse) {
-    int j;
-    int64_t chunk;
-    if (!map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) return;
-    if (reverse) chunk = n_chunks - 1 - chunk;
-    const HopGradJob* job = jobs + j;
+__device__ __forceinline__ void synth_chunk(const HopGradJob* __restrict__ job, int64_t d, int64_t n_chunks, int64_t chunk) {
     const uint32_t f0 = fold16(job->k0), f1 = fold16(job->k1), k2 = job->k2;
     const float scale = job->scale;
     float* g = job->g;
@@ -588,6 +599,18 @@ __global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __res
         int64_t c = (n4 << 2) + threadIdx.x;
         if (threadIdx.x < 4 && c < d) g[c] = synth_one(fold16((uint32_t)c), f0, f1, k2, scale);
     }
+}
+
+__global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __restrict__ jobs, int n_jobs,
+                                                         int64_t d, int64_t n_chunks, int reverse) {
+    int j;
+    int64_t chunk;
+    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
+        synth_chunk(jobs + j, d, n_chunks, reverse ? n_chunks - 1 - chunk : chunk);
+}
+
+__global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob job, int64_t d, int64_t n_chunks) {
+    synth_chunk(&job, d, n_chunks, blockIdx.x);
 }
 
 // ------------------------------------------------------------- a whole pass, column by column ----
@@ -912,6 +935,15 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob
     dense_margin_block<ROWS>(jobs, B, d, nseg, blockIdx.x, red);
 }
 
+// The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
+// allocated, copied or staged.  Per call: 128 x 65536 dense 42.5 -> 28.4 us, 64 x 1024 without allocation 10.4 -> 7.7 us
+// (one launch fewer), 256 samples of 64 non-zeros on 2^20 columns 33.0 -> 18.6 us (margins beside the dense part).
+template <int ROWS>
+__global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob job, int B, int64_t d, int nseg) {
+    __shared__ float red[ROWS][kThreads / 64];
+    dense_margin_rows<ROWS>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
+}
+
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
 // (the parallel approach of Section 3.2 runs Compute beside Reduce).  The Reduce leaves sum_a w'_a x_a
 // in the result slot; dense_grad_kernel then applies -eta g to it.
@@ -947,18 +979,13 @@ constexpr int kRowUnroll = 8;
 constexpr int64_t kGradFew = 768;                      // chunks up to which a launch takes 8 wavefronts for each
 
 template <int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
-                                                                int64_t d, int nseg, float lambda, int loss,
-                                                                int64_t n_chunks) {
+__device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
+                                                 int loss, int64_t chunk) {
     __shared__ float coefS[kMaxB + kRowUnroll];
     __shared__ int rowS[kMaxB + kRowUnroll];
     __shared__ float allC[kMaxB];
     __shared__ int nactS;
     __shared__ float4 joinS[(SPLIT - 1) * 64];
-    int j;
-    int64_t chunk;
-    if (!map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) return;
-    const HopGradJob* job = jobs + j;
     const float invB = 1.0f / (float)B;
     const int part = (int)threadIdx.x / 64, col = (int)threadIdx.x % 64;        // which share of the rows
     for (int m = threadIdx.x; m < B; m += 64 * SPLIT) {
@@ -1047,13 +1074,26 @@ __global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob
     stu4(out, c, n, fma4(neg_eta, gv, o));
 }
 
+template <int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
+                                                                int64_t d, int nseg, float lambda, int loss,
+                                                                int64_t n_chunks) {
+    int j;
+    int64_t chunk;
+    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) dense_grad_chunk<SPLIT>(jobs + j, B, d, nseg, lambda, loss, chunk);
+}
+
+template <int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
+                                                             int loss) {
+    dense_grad_chunk<SPLIT>(&job, B, d, nseg, lambda, loss, blockIdx.x);
+}
+
 // ------------------------------------------------------------------- CSR SVM: margins ----
 // One wavefront per (job, minibatch row): gather w[col], reduce across the 64 lanes.
-__device__ __forceinline__ void csr_margin_block(const HopGradJob* __restrict__ jobs, int B,
-                                                 int rows_per_job_blocks, int loss, int bid) {
+__device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int block) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const HopGradJob* job = jobs + bid / rows_per_job_blocks;
-    const int m = (bid % rows_per_job_blocks) * (kThreads / 64) + wv;
+    const int m = block * (kThreads / 64) + wv;
     if (m >= B) return;
     const int r = job->rows[m];
     const int64_t lo = job->rowptr[r], hi = job->rowptr[r + 1];
@@ -1062,6 +1102,27 @@ __device__ __forceinline__ void csr_margin_block(const HopGradJob* __restrict__ 
     for (int64_t p = lo + lane; p < hi; p += 64) acc = fmaf(job->val[p], w[job->col[p]], acc);
     acc = wave_sum(acc);
     if (lane == 0) job->coef[m] = loss_coef(job->y[r], acc, 1.0f / (float)B, loss);
+}
+
+__device__ __forceinline__ void csr_margin_block(const HopGradJob* __restrict__ jobs, int B,
+                                                 int rows_per_job_blocks, int loss, int bid) {
+    csr_margin_rows(jobs + bid / rows_per_job_blocks, B, loss, bid % rows_per_job_blocks);
+}
+
+// Margins and the dense part lambda w of a gradient that is wanted as a dense vector, side by side (the sparse part is
+// scattered into g afterwards).
+__global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJob job, int B, int64_t d, float lambda,
+                                                                 int loss, int margin_blocks) {
+    if ((int)blockIdx.x < margin_blocks) {
+        csr_margin_rows(&job, B, loss, (int)blockIdx.x);
+        return;
+    }
+    const int64_t c = ((int64_t)(blockIdx.x - margin_blocks) * kThreads + threadIdx.x) * 4;
+    const int n = (int)min((int64_t)4, d - c);
+    if (n > 0) {
+        const float4 w = ldu4(job.w, c, n);
+        stu4(job.out, c, n, make_float4(lambda * w.x, lambda * w.y, lambda * w.z, lambda * w.w));
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* __restrict__ jobs, int B,
@@ -1132,13 +1193,11 @@ constexpr int kScatterThreads = 1024;
 constexpr int kScatterRows = kScatterThreads / 64;
 constexpr int kHotCols = 1024;
 
-__global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopGradJob* __restrict__ jobs, int B,
-                                                                      int blocks_per_job, float factor,
-                                                                      int into_velocity) {
+__device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ job, int B, float factor,
+                                                 int into_velocity, int block) {
     __shared__ float hot[kHotCols];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const HopGradJob* job = jobs + blockIdx.x / blocks_per_job;
-    const int m = (blockIdx.x % blocks_per_job) * kScatterRows + wv;
+    const int m = block * kScatterRows + wv;
     for (int i = threadIdx.x; i < kHotCols; i += kScatterThreads) hot[i] = 0.f;
     __syncthreads();
     float* target = into_velocity ? job->vel : job->out;
@@ -1163,17 +1222,14 @@ __global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopG
     }
 }
 
-// g = lambda w, the dense part of a CSR gradient when a dense g is wanted.
-__global__ __launch_bounds__(kThreads) void scale_kernel(const HopGradJob* __restrict__ jobs, int n_jobs,
-                                                         int64_t d, float lambda, int64_t n_chunks) {
-    int j;
-    int64_t chunk;
-    if (!map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) return;
-    const HopGradJob* job = jobs + j;
-    for (int q = 0; q < 4; ++q) {
-        int64_t c = (chunk * 4 + q) * kThreads + threadIdx.x;
-        if (c < d) job->out[c] = lambda * job->w[c];
-    }
+__global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopGradJob* __restrict__ jobs, int B,
+                                                                      int blocks_per_job, float factor,
+                                                                      int into_velocity) {
+    csr_scatter_rows(jobs + blockIdx.x / blocks_per_job, B, factor, into_velocity, blockIdx.x % blocks_per_job);
+}
+
+__global__ __launch_bounds__(kScatterThreads) void csr_scatter_one(const HopGradJob job, int B, float factor) {
+    csr_scatter_rows(&job, B, factor, 0, blockIdx.x);
 }
 
 // Input check for CSR data: rowptr non-decreasing over [0, rows], every column id inside [0, d).
@@ -1367,16 +1423,55 @@ int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor
     return launch_status();
 }
 
-int hopk_csr_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, void* stream) {
+template <int SPLIT>
+static void launch_dense_grad_one(const HopGradJob& job, int B, int64_t d, int nseg, float lambda, int loss, void* stream) {
+    hipLaunchKernelGGL(dense_grad_one<SPLIT>, dim3((unsigned)((d + 255) / 256)), dim3(64 * SPLIT), 0, (hipStream_t)stream,
+                       job, B, d, nseg, lambda, loss);
+}
+
+int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
+    const hipStream_t st = (hipStream_t)stream;
+    if (mode == HOP_GRAD_SVM_DENSE) {
+        const int nseg = hopk_dense_nseg(d);
+        const int64_t few = (int64_t)B * nseg, grid = (int64_t)((B + kMarginRows - 1) / kMarginRows) * nseg;
+        if (B > kMaxB) return (int)hipErrorInvalidValue;
+        if (few > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+        if (grid < kMarginFew)
+            hipLaunchKernelGGL(dense_margin_one<1>, dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
+        else
+            hipLaunchKernelGGL(dense_margin_one<kMarginRows>, dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, nseg);
+        if (const int rc = launch_status()) return rc;
+        if ((d + 255) / 256 <= kGradFew) launch_dense_grad_one<8>(job, B, d, nseg, lambda, loss, stream);
+        else launch_dense_grad_one<4>(job, B, d, nseg, lambda, loss, stream);
+    } else if (mode == HOP_GRAD_SVM_CSR) {
+        const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
+        const int64_t grid = margin_blocks + (d + 4 * kThreads - 1) / (4 * kThreads);
+        if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(csr_margin_dense_one, dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, lambda, loss,
+                           margin_blocks);
+        if (const int rc = launch_status()) return rc;
+        hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)((B + kScatterRows - 1) / kScatterRows)), dim3(kScatterThreads), 0,
+                           st, job, B, -1.0f);
+    } else {
+        const int64_t n = ((d >> 2) + kSynthChunk4 - 1) / kSynthChunk4, n_chunks = n < 1 ? 1 : n;
+        if (n_chunks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(synth_one_kernel, dim3((unsigned)n_chunks), dim3(kThreads), 0, st, job, d, n_chunks);
+    }
+    return launch_status();
+}
+
+int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream) {
     if (n_jobs <= 0) return 0;
-    int64_t n_chunks = (d + 4 * kThreads - 1) / (4 * kThreads);
-    int64_t grid = grid_for(n_jobs, n_chunks);
+    if (n_jobs > kPairArgs) return (int)hipErrorInvalidValue;
+    HopPairArgs args;
+    memcpy(args.job, jobs, (size_t)n_jobs * sizeof(HopPairArg));
+    const int64_t n_chunks = pair_chunks(d);
+    const int run = pair_run(n_sources, n_chunks);
+    const int64_t grid = pair_grid(n_jobs, n_chunks, run);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(scale_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev,
-                       n_jobs, d, lambda, n_chunks);
-    int rc = launch_status();
-    if (rc) return rc;
-    return hopk_csr_scatter(jobs_dev, n_jobs, B, -1.0f, 0, stream);
+    hipLaunchKernelGGL(pair_mix_args_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args, n_jobs, d,
+                       n_chunks, run);
+    return launch_status();
 }
 
 int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int64_t first, int64_t nnz, int64_t d,
@@ -1402,21 +1497,16 @@ int hopk_copy(void* dst, const void* src, size_t bytes, void* stream) {
 
 // ------------------------------------------- dense SVM gradient without any allocation ----
 // For callers that cannot allocate (a stream being captured, a tight serving loop, a harness that forbids
-// hipMalloc): the job descriptor and the partial dot products, which hop_svm_grad_dense takes from a hipMalloc
-// of its own and from the caller's scratch argument, live in a fixed array in device memory instead.
+// hipMalloc): the partial dot products, which hop_svm_grad_dense keeps in the caller's scratch argument, live in a fixed
+// array in device memory instead.
 namespace {
 
-constexpr size_t kStaticDescBytes = 256;
 constexpr int64_t kStaticPartials = 65536;                 // most B x column segments (16384 columns each)
-static __device__ __align__(256) unsigned char scratch[kStaticDescBytes + kStaticPartials * sizeof(float)];
+static __device__ __align__(256) unsigned char scratch[kStaticPartials * sizeof(float)];
 
 constexpr int kMaxDevices = 64;
 void* g_scratch_ptr[kMaxDevices];                          // device address of `scratch` on each GPU, once known
 int g_scratch_state[kMaxDevices];                          // 0 unknown, 1 known
-
-__global__ void stage_job_kernel(HopGradJob job, HopGradJob* dst) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = job;
-}
 
 }  // namespace
 
@@ -1447,16 +1537,11 @@ extern "C" int hop_svm_grad_dense_static(const float* X, const float* y, const f
         g_scratch_state[dev] = 1;
     }
     unsigned char* base = (unsigned char*)g_scratch_ptr[dev];
-    HopGradJob* desc = (HopGradJob*)base;
-    static_assert(sizeof(HopGradJob) <= kStaticDescBytes, "descriptor must fit its slot");
     HopGradJob gj;
     memset(&gj, 0, sizeof(gj));
     gj.X = X; gj.y = y; gj.w = w; gj.rows = rows_dev; gj.g = g; gj.coef = coef;
-    gj.partial = (float*)(base + kStaticDescBytes);        // every entry is written by the margin pass before it is read
-    hipLaunchKernelGGL(stage_job_kernel, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, gj, desc);
-    int rc = launch_status();
-    if (!rc) rc = hopk_dense_margin(desc, 1, B, d, hip_stream);
-    if (!rc) rc = hopk_dense_grad(desc, 1, B, d, lambda, loss, hip_stream);
+    gj.partial = (float*)base;                             // every entry is written by the margin pass before it is read
+    const int rc = hopk_one_grad(gj, HOP_GRAD_SVM_DENSE, B, d, lambda, loss, hip_stream);
     if (rc) {
         fprintf(stderr, "libhop: hop_svm_grad_dense_static launch: %s\n", hipGetErrorString((hipError_t)rc));
         return HOP_ERR_HIP;

@@ -338,17 +338,18 @@ def hop_profile_read(ctx, kernel):
 def hop_mix(jobs, d, stream=0):
     """jobs: list of dicts {out, g (or None), eta, src: [ptr...], w: [float...]} (device pointers)."""
     arr = (hop_mix_job * len(jobs))()
-    for j, job in enumerate(jobs):
-        arr[j].out = job["out"]
-        arr[j].g = job.get("g") or None
-        arr[j].eta = float(job.get("eta", 0.0))
-        arr[j].A = len(job["src"])
-        arr[j].vel = job.get("vel") or None
-        arr[j].mu = float(job.get("mu", 0.0))
-        for a, (p, w) in enumerate(zip(job["src"], job["w"])):
-            if a < HOP_MAX_A:
-                arr[j].src[a] = p
-                arr[j].w[a] = float(w)
+    for a, job in zip(arr, jobs):
+        src, w = list(job["src"]), list(job["w"])
+        n = min(len(src), len(w), HOP_MAX_A)
+        a.out = job["out"]
+        a.g = job.get("g") or None
+        a.eta = float(job.get("eta", 0.0))
+        a.A = len(src)
+        if job.get("vel"):
+            a.vel = job["vel"]
+        a.mu = float(job.get("mu", 0.0))
+        a.src[:n] = src[:n]
+        a.w[:n] = w[:n]
     _check(load().hop_mix(arr, len(jobs), d, C.c_void_p(stream)), "hop_mix")
 
 

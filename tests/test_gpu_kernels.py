@@ -227,3 +227,32 @@ def test_mix_with_velocity_for_every_width():
     for out, vel, ref, vref in want:
         assert rel_err(out.cpu().numpy(), ref) <= 1e-5
         assert rel_err(vel.cpu().numpy(), vref) <= 1e-6
+
+
+@pytest.mark.parametrize("n_jobs,A", [(1, 1), (15, 3), (16, 12), (17, 5), (31, 5), (40, 2), (3, 13)])
+def test_mix_around_the_descriptors_that_fit_a_launch(n_jobs, A):
+    """Up to 16 pairs or singles of at most 12 vectors travel as the kernel's argument, more (or wider ones) through
+    device memory; jobs that share most sources are paired, so 31 jobs can still fit."""
+    d = 5003
+    rs = np.random.default_rng(n_jobs * 100 + A)
+    base = rs.normal(size=d)
+    host = [(base + 0.05 * rs.normal(size=d)).astype(np.float32) for _ in range(max(A, 14))]
+    pool = [aligned(d) for _ in host]
+    for t, h in zip(pool, host):
+        t.copy_(torch.from_numpy(h))
+    jobs, keep, want = [], [], []
+    for j in range(n_jobs):
+        pick = rs.choice(len(host), size=A, replace=False)
+        w = rs.dirichlet(np.ones(A)).astype(np.float32)
+        g, out = aligned(d), aligned(d)
+        gh = (0.03 * rs.normal(size=d)).astype(np.float32)
+        g.copy_(torch.from_numpy(gh))
+        keep += [g, out]
+        use_g = j % 3 != 1
+        jobs.append(dict(out=out.data_ptr(), g=g.data_ptr() if use_g else None, eta=0.05,
+                         src=[pool[p].data_ptr() for p in pick], w=w))
+        want.append((out, arith.reduce_apply([host[p] for p in pick], w, gh if use_g else None, 0.05)))
+    hop.hop_mix(jobs, d, stream())
+    torch.cuda.synchronize()
+    for out, ref in want:
+        assert rel_err(out.cpu().numpy(), ref) <= 1e-5

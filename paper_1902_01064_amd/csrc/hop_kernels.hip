@@ -339,7 +339,8 @@ int launch_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
 // ---------------------------------------------------------- Reduce + Apply, records in pairs ----
 // The plain path (no velocity).  Neighbouring workers average almost the same vectors (on a ring i and
 // i + 1 share x_i and x_{i+1}), so the host packs a wave's records two by two where their source sets
-// overlap and the union has at most kPairU vectors.  One workgroup loads the union for a 16 KB column chunk
+// overlap and the union has at most kPairU vectors.  One workgroup loads the union for a column chunk (16 KB
+// in long launches, pair_vec)
 // once into registers and forms both sums from there; a source shared inside the pair then costs one L2
 // request instead of two.  Against the record-by-record kernel above this also changes how the work is issued:
 //  - the union size is a compile-time constant (switch over U), every pointer and weight is read by one batch
@@ -351,11 +352,9 @@ int launch_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
 // Terms are added in the order of the union (the first record's own order; the second record's sources fall
 // where the union has them), in fp32 FMAs starting from zero.
 constexpr int kPairU = HOP_PAIR_U;
-constexpr int kPairVec = 4;
 
-template <int U, bool FULL, class Job>
+template <int VEC, int U, bool FULL, class Job>
 __device__ __forceinline__ void pair_tile(Job job, int64_t first4, int64_t n4) {
-    constexpr int VEC = kPairVec;
     const int G = job->G;
     const float* src[U];
 #pragma unroll
@@ -421,12 +420,12 @@ __device__ __forceinline__ void pair_tile(Job job, int64_t first4, int64_t n4) {
 }
 
 // a single record with more than kPairU sources: a loop over the sources
-template <class Job>
+template <int VEC, class Job>
 __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t n4) {
     const int U = job->U;
     const float* g = job->g[0];
     const float neg_eta = -job->eta;
-    for (int v = 0; v < kPairVec; ++v) {
+    for (int v = 0; v < VEC; ++v) {
         const int64_t i = first4 + (int64_t)v * kThreads + threadIdx.x;
         if (i >= n4) continue;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -451,7 +450,7 @@ __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t 
 
 // Work of one workgroup; `bid` is its index among the launch's mix workgroups.
 // Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
-template <class Job>
+template <int VEC, class Job>
 __device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int64_t n_chunks,
                                            int run, int reverse, int64_t bid) {
     const int xcd = (int)(bid % kXcd);
@@ -475,18 +474,18 @@ __device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int6
     const int64_t chunk = reverse ? n_chunks - 1 - ahead : ahead;
     const Job job = jobs + j;
     const int64_t n4 = d >> 2;
-    const int64_t first4 = chunk * (int64_t)(kThreads * kPairVec);
-    const bool full = first4 + kThreads * kPairVec <= n4;
+    const int64_t first4 = chunk * (int64_t)(kThreads * VEC);
+    const bool full = first4 + kThreads * VEC <= n4;
     static_assert(kPairU == 12, "the switch below unrolls unions of 1..12 vectors");
 #define HOP_PAIR_CASE(UU)                                      \
     case UU:                                                   \
-        if (full) pair_tile<UU, true>(job, first4, n4);        \
-        else pair_tile<UU, false>(job, first4, n4);            \
+        if (full) pair_tile<VEC, UU, true>(job, first4, n4);   \
+        else pair_tile<VEC, UU, false>(job, first4, n4);       \
         break;
     switch (job->U) {
         HOP_PAIR_CASE(1) HOP_PAIR_CASE(2) HOP_PAIR_CASE(3) HOP_PAIR_CASE(4) HOP_PAIR_CASE(5) HOP_PAIR_CASE(6)
         HOP_PAIR_CASE(7) HOP_PAIR_CASE(8) HOP_PAIR_CASE(9) HOP_PAIR_CASE(10) HOP_PAIR_CASE(11) HOP_PAIR_CASE(12)
-        default: pair_tile_wide(job, first4, n4); break;
+        default: pair_tile_wide<VEC>(job, first4, n4); break;
     }
 #undef HOP_PAIR_CASE
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
@@ -503,9 +502,10 @@ __device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int6
     }
 }
 
+template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_mix_kernel(const HopPairJob* __restrict__ jobs, int n_jobs, int64_t d,
                                                             int64_t n_chunks, int run, int reverse) {
-    pair_block(jobs, n_jobs, d, n_chunks, run, reverse, blockIdx.x);
+    pair_block<VEC>(jobs, n_jobs, d, n_chunks, run, reverse, blockIdx.x);
 }
 
 // The same for a stand-alone call: its descriptors travel as the kernel's argument, so the call allocates and copies
@@ -516,23 +516,32 @@ struct HopPairArgs {
 };
 typedef const __attribute__((address_space(4))) HopPairArg* pair_args_in;
 
+template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, int n_jobs, int64_t d, int64_t n_chunks,
                                                                  int run) {
     // the first argument where it lies: a copy indexed by job would go through scratch memory
-    pair_block((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), n_jobs, d, n_chunks, run, 0, blockIdx.x);
+    pair_block<VEC>((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), n_jobs, d, n_chunks, run, 0, blockIdx.x);
 }
 
-inline int64_t pair_chunks(int64_t d) {
-    const int64_t per = (int64_t)kThreads * kPairVec;
+// float4 per thread and vector, and with it the columns of a chunk.  Long launches: 4, 16 KB of every vector per workgroup
+// (25 M columns: 8 and 32 KB are 1 to 3 % slower).  Short ones finish in one or two turns of the 2 workgroups per CU that
+// the registers of that form allow, so they take smaller workgroups, more of them at a time: 16 workers x 4 M columns
+// 36.5 -> 35.6 us per launch with 2, 16 x 1 M columns with CSR margins beside 12.3 -> 11.8 with 2 and 11.4 with 1; waves of
+// 7 records of 2^24 columns: no difference.
+constexpr int64_t kPairShort = 8192;                   // workgroups of 16 KB chunks
+inline int pair_vec(int n_jobs, int64_t d, bool margins) { return n_jobs * (d >> 12) >= kPairShort ? 4 : margins ? 1 : 2; }
+
+inline int64_t pair_chunks(int64_t d, int vec) {
+    const int64_t per = (int64_t)kThreads * vec;
     const int64_t n = ((d >> 2) + per - 1) / per;
     return n < 1 ? 1 : n;
 }
 
-// chunks an XCD walks per job group: run x 16 KB x distinct sources near 3 MB of its 4 MB L2 (measured on 32
+// chunks an XCD walks per job group: run x chunk x distinct sources near 3 MB of its 4 MB L2 (measured on 32
 // sources: runs of 5 to 7 equal, 4 and 8 1.3 % slower, 12 10 % slower), never more than the vector has
-inline int pair_run(int n_sources, int64_t n_chunks) {
-    int run = (192 + n_sources / 2) / (n_sources < 1 ? 1 : n_sources);
-    if (run > 8) run = 8;
+inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
+    int run = (192 * 4 / vec + n_sources / 2) / (n_sources < 1 ? 1 : n_sources);
+    if (run > 8 * 4 / vec) run = 8 * 4 / vec;
     const int64_t room = n_chunks / kXcd;
     if (run > room) run = (int)room;
     return run < 1 ? 1 : run;
@@ -864,7 +873,7 @@ constexpr int64_t kSegCols = (int64_t)kSeg4 * 4;
 
 // ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t.
 // Each row is summed in the same order whatever ROWS is.
-template <int ROWS>
+template <int ROWS, bool STREAM>
 __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, int seg,
                                                   int m0, float (*red)[kThreads / 64]) {
     const float* w = job->w;
@@ -883,7 +892,7 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
         const float4 wv = ldu4(w, i << 2);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const float4 xv = ldu4_stream(x[r], i << 2);
+            const float4 xv = STREAM ? ldu4_stream(x[r], i << 2) : ldu4(x[r], i << 2);
             a[r][0] = fmaf(xv.x, wv.x, a[r][0]);
             a[r][1] = fmaf(xv.y, wv.y, a[r][1]);
             a[r][2] = fmaf(xv.z, wv.z, a[r][2]);
@@ -910,11 +919,11 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
 }
 
 // one workgroup per (job, ROWS minibatch rows, column segment); b: its index
-template <int ROWS>
+template <int ROWS, bool STREAM>
 __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
                                                    int64_t b, float (*red)[kThreads / 64]) {
     const int groups = (B + ROWS - 1) / ROWS;
-    dense_margin_rows<ROWS>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
+    dense_margin_rows<ROWS, STREAM>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
                             (int)((b / nseg) % groups) * ROWS, red);
 }
 
@@ -922,26 +931,29 @@ __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict_
 // 5 requests per 4 row pieces instead of 8); with few workgroups (kMarginFew) one row each, so that all CUs have rows in
 // flight (one minibatch of 128 x 65536: 14.1 -> 8.9 us; 3 records of 100 x 30 011: 36 -> 14 us, scalar loads before; waves of
 // 2 to 5 records of 128 x 65536: 4 % less than with four rows).
-// Rows by non-temporal loads: a wave's rows are new to every cache, and a cold stream runs faster without allocating in the memory-side cache (6.9 against 5.5 TB/s stand-alone).  Leaving
-// them there for the gradient pass with ordinary loads was measured on 16 workers x 65536 columns, B = 128:
-// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained.
+// Rows by non-temporal loads: a wave's rows are new to every cache, and a cold stream
+// runs faster without allocating in the memory-side cache (6.9 against 5.5 TB/s stand-alone).  Leaving
+// them there for the gradient pass with ordinary loads was measured on 16 workers x 65536 columns, B = 128, 6.6 records:
+// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained; where a launch reads no more than half of
+// that cache (kMarginNear) ordinary loads pay: 3 to 4 records of 100 x 30 011 2.20 -> 2.12 ms per pass.
 constexpr int kMarginRows = 4;
 constexpr int64_t kMarginFew = 768;
+constexpr int64_t kMarginNear = 128ll << 20;           // bytes of rows in a launch up to which they are left in the caches
 
-template <int ROWS>
+template <int ROWS, bool STREAM>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
                                                                 int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_block<ROWS>(jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<ROWS, STREAM>(jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
 // allocated, copied or staged.  Per call: 128 x 65536 dense 42.5 -> 28.4 us, 64 x 1024 without allocation 10.4 -> 7.7 us
 // (one launch fewer), 256 samples of 64 non-zeros on 2^20 columns 33.0 -> 18.6 us (margins beside the dense part).
-template <int ROWS>
+template <int ROWS, bool STREAM>
 __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob job, int B, int64_t d, int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_rows<ROWS>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
+    dense_margin_rows<ROWS, STREAM>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
 }
 
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
@@ -957,7 +969,7 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
         mix_block<VEC, NT, MAP, kThreads>(mix_jobs, n_mix, d, n_chunks, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block<1>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<1, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
@@ -974,10 +986,12 @@ constexpr int kRowUnroll = 8;
 // joined through LDS in a fixed order.  The time is the chain of dependent row loads, so a chunk is as narrow as a
 // wavefront's 1 KB of a row and its rows are split.  Per pass, chunks of 1024 columns with one group of 256 threads (four
 // in launches of up to 128 workgroups) -> this kernel: 8 workers x 30 011 columns, B = 100 (rows not 16-byte aligned,
-// scalar loads before): 6.91 -> 2.20 ms; 16 x 65536, B = 128: 3.86 -> 3.75 ms; 4 x 1024, B = 64: 392 -> 385 us; one
+// scalar loads before): 6.91 -> 2.20 ms; 16 x 65536, B = 128: 3.86 -> 3.75 ms; 4 x 1024, B = 64: 392 -> 360 us; one
 // gradient of 128 x 65536: 14.4 -> 8.8 us.  4 against 8 wavefronts per chunk: 2.35 / 2.19 ms, 3.77 / 3.89 ms, 359 / 364 us.
 constexpr int64_t kGradFew = 768;                      // chunks up to which a launch takes 8 wavefronts for each
 
+// (Loading a wavefront's 8 rows at once, active or not, while the coefficients are still being worked out - one chain of
+// loads instead of two, for minibatches of up to 8 SPLIT rows - was slower: 4 x 1024, B = 64: 364 -> 460 us per pass.)
 template <int SPLIT>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
@@ -988,29 +1002,50 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     __shared__ float4 joinS[(SPLIT - 1) * 64];
     const float invB = 1.0f / (float)B;
     const int part = (int)threadIdx.x / 64, col = (int)threadIdx.x % 64;        // which share of the rows
+    const float* X = job->X;
+    const float* w = job->w;
+    float* out = job->out;                             // set: apply -eta g (or -eta v) to it instead of writing g
+    const HopMixJob* red = job->reduce;                // set (with out): out = sum_a w'_a x_a - eta g, the Reduce done here
+    const int64_t c = (chunk * 64 + col) * 4;          // first of this thread's columns
+    const int n = (int)min((int64_t)4, d - c);         // how many of them exist
+    // what the ending needs beside the sum, loaded ahead of the rows
+    float4 wv = make_float4(0.f, 0.f, 0.f, 0.f), o = wv;
+    if (part == 0 && n > 0) {
+        wv = ldu4(w, c, n);
+        if (red != nullptr) {                          // the record's Reduce, in the order the mix kernels sum
+            const int A = red->A;
+            const float4 x0 = ldu4(red->src[0], c, n);
+            const float wa = red->w[0];
+            o = make_float4(wa * x0.x, wa * x0.y, wa * x0.z, wa * x0.w);
+            for (int a = 1; a < A; ++a) o = fma4(red->w[a], ldu4(red->src[a], c, n), o);
+        } else if (out != nullptr) {                   // already reduced into the result slot
+            o = ldu4(out, c, n);
+        }
+    }
     for (int m = threadIdx.x; m < B; m += 64 * SPLIT) {
         float dot = 0.f;
         for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
-        float c = loss_coef(job->y[job->rows[m]], dot, invB, loss);
-        allC[m] = c;
-        if (chunk == 0) job->coef[m] = c;
+        const float cm = loss_coef(job->y[job->rows[m]], dot, invB, loss);
+        allC[m] = cm;
+        if (chunk == 0) job->coef[m] = cm;
     }
     __syncthreads();
-    if (threadIdx.x < 64) {                            // first wavefront compacts, keeping order
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (threadIdx.x < 64) {                        // first wavefront compacts the active rows, keeping order
         int count = 0;
         for (int base = 0; base < B; base += 64) {
-            int m = base + threadIdx.x;
-            float c = m < B ? allC[m] : 0.f;
-            bool act = c != 0.f;
-            unsigned long long mask = __ballot(act);
-            int pos = count + __popcll(mask & ((1ull << threadIdx.x) - 1ull));
+            const int m = base + threadIdx.x;
+            const float cm = m < B ? allC[m] : 0.f;
+            const bool act = cm != 0.f;
+            const unsigned long long mask = __ballot(act);
+            const int pos = count + __popcll(mask & ((1ull << threadIdx.x) - 1ull));
             if (act) {
-                coefS[pos] = c;
+                coefS[pos] = cm;
                 rowS[pos] = job->rows[m];
             }
             count += __popcll(mask);
         }
-        if (threadIdx.x < kRowUnroll) {                // pad to a multiple of the unroll with zeros
+        if (threadIdx.x < kRowUnroll) {            // pad to a multiple of the unroll with zeros
             coefS[count + threadIdx.x] = 0.f;
             rowS[count + threadIdx.x] = job->rows[0];
         }
@@ -1018,16 +1053,6 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     }
     __syncthreads();
     const int nact = nactS;
-    const float* X = job->X;
-    const float* w = job->w;
-    float* g = job->g;
-    float* out = job->out;                             // set: apply -eta g (or -eta v) to it instead of writing g
-    const HopMixJob* red = job->reduce;                // set (with out): out = sum_a w'_a x_a - eta g, the Reduce done here
-    float* vel = job->vel;
-    const float neg_eta = -job->eta, mu = job->mu;
-    const int64_t c = (chunk * 64 + col) * 4;          // first of this thread's columns
-    const int n = (int)min((int64_t)4, d - c);         // how many of them exist
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (n == 4) {
         for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT) {
             float4 v[kRowUnroll];
@@ -1036,42 +1061,31 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
 #pragma unroll
             for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], v[u], acc);
         }
-    } else if (n > 0) {                                // the thread at the end of a vector with d mod 4 columns left
+    } else if (n > 0) {                            // the thread at the end of a vector with d mod 4 columns left
         for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT)
-            for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], ldu4(X + (int64_t)rowS[q + u] * d, c, n), acc);
+            for (int u = 0; u < kRowUnroll; ++u)
+                acc = fma4(coefS[q + u], ldu4(X + (int64_t)rowS[q + u] * d, c, n), acc);
     }
     if (part > 0) joinS[(part - 1) * 64 + col] = acc;  // join the shares: ((part 0 + part 1) + part 2) + ...
     __syncthreads();
-    if (part == 0) {
-#pragma unroll
-        for (int q = 1; q < SPLIT; ++q) {
-            const float4 t = joinS[(q - 1) * 64 + col];
-            acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
-        }
-    }
     if (n <= 0 || part != 0) return;
-    const float4 wv = ldu4(w, c, n);
+#pragma unroll
+    for (int q = 1; q < SPLIT; ++q) {
+        const float4 t = joinS[(q - 1) * 64 + col];
+        acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
+    }
     float4 gv = make_float4(fmaf(lambda, wv.x, -acc.x), fmaf(lambda, wv.y, -acc.y), fmaf(lambda, wv.z, -acc.z),
                             fmaf(lambda, wv.w, -acc.w));
     if (out == nullptr) {
-        stu4(g, c, n, gv);
+        stu4(job->g, c, n, gv);
         return;
     }
+    float* vel = job->vel;
     if (vel != nullptr) {
-        gv = fma4(mu, ldu4(vel, c, n), gv);
+        gv = fma4(job->mu, ldu4(vel, c, n), gv);
         stu4(vel, c, n, gv);
     }
-    float4 o;
-    if (red != nullptr) {                              // the record's Reduce, in the order the mix kernels sum
-        const int A = red->A;
-        const float4 v = ldu4(red->src[0], c, n);
-        const float wa = red->w[0];
-        o = make_float4(wa * v.x, wa * v.y, wa * v.z, wa * v.w);
-        for (int a = 1; a < A; ++a) o = fma4(red->w[a], ldu4(red->src[a], c, n), o);
-    } else {                                           // already reduced into the result slot
-        o = ldu4(out, c, n);
-    }
-    stu4(out, c, n, fma4(neg_eta, gv, o));
+    stu4(out, c, n, fma4(-job->eta, gv, o));
 }
 
 template <int SPLIT>
@@ -1080,7 +1094,8 @@ __global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob
                                                                 int64_t n_chunks) {
     int j;
     int64_t chunk;
-    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk)) dense_grad_chunk<SPLIT>(jobs + j, B, d, nseg, lambda, loss, chunk);
+    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
+        dense_grad_chunk<SPLIT>(jobs + j, B, d, nseg, lambda, loss, chunk);
 }
 
 template <int SPLIT>
@@ -1147,6 +1162,7 @@ __global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJo
 }
 
 // the same two fusions for the paired Reduce + Apply
+template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int n_mix,
                                                                    int64_t d, int64_t n_chunks, int run, int reverse,
                                                                    const HopGradJob* __restrict__ grad_jobs, int B,
@@ -1155,19 +1171,20 @@ __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPair
         csr_margin_block(grad_jobs, B, rows_per_job_blocks, loss, (int)blockIdx.x);
         return;
     }
-    pair_block(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
+    pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
 }
 
+template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int n_mix,
                                                                      int64_t d, int64_t n_chunks, int run, int reverse,
                                                                      const HopGradJob* __restrict__ grad_jobs, int B,
                                                                      int nseg, int64_t margin_blocks) {
     __shared__ float red[1][kThreads / 64];
     if ((int64_t)blockIdx.x >= margin_blocks) {
-        pair_block(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
+        pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block<1>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<1, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 template <int VEC, int NT, int MAP>
@@ -1255,6 +1272,13 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float4* __restrict__ dst
         if (i < n16) dst[i] = src[i];
 }
 
+#define HOP_PAIR_LAUNCH(KERNEL, ...)                                   \
+    do {                                                               \
+        if (vec == 4) hipLaunchKernelGGL(KERNEL<4>, __VA_ARGS__);      \
+        else if (vec == 2) hipLaunchKernelGGL(KERNEL<2>, __VA_ARGS__); \
+        else hipLaunchKernelGGL(KERNEL<1>, __VA_ARGS__);               \
+    } while (0)
+
 inline int launch_status() { return (int)hipGetLastError(); }
 
 }  // namespace
@@ -1307,22 +1331,16 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int64_t few = (int64_t)n_jobs * B * nseg;
     const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
     if (few > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    if (grid < kMarginFew)
-        hipLaunchKernelGGL(dense_margin_kernel<1>, dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, B,
-                           d, nseg);
-    else
-        hipLaunchKernelGGL(dense_margin_kernel<kMarginRows>, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream,
+    const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
+    if (grid < kMarginFew && near)
+        hipLaunchKernelGGL((dense_margin_kernel<1, false>), dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream,
                            jobs_dev, B, d, nseg);
-    return launch_status();
-}
-
-template <int SPLIT>
-static int launch_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, void* stream) {
-    const int64_t n_chunks = (d + 255) / 256;
-    const int64_t grid = grid_for(n_jobs, n_chunks);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(dense_grad_kernel<SPLIT>, dim3((unsigned)grid), dim3(64 * SPLIT), 0, (hipStream_t)stream,
-                       jobs_dev, n_jobs, B, d, hopk_dense_nseg(d), lambda, loss, n_chunks);
+    else if (grid < kMarginFew)
+        hipLaunchKernelGGL((dense_margin_kernel<1, true>), dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream,
+                           jobs_dev, B, d, nseg);
+    else
+        hipLaunchKernelGGL((dense_margin_kernel<kMarginRows, true>), dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream,
+                           jobs_dev, B, d, nseg);
     return launch_status();
 }
 
@@ -1330,8 +1348,17 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
                     void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
-    if (n_jobs * ((d + 255) / 256) <= kGradFew) return launch_dense_grad<8>(jobs_dev, n_jobs, B, d, lambda, loss, stream);
-    return launch_dense_grad<4>(jobs_dev, n_jobs, B, d, lambda, loss, stream);
+    const int64_t n_chunks = (d + 255) / 256;
+    const int64_t grid = grid_for(n_jobs, n_chunks);
+    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    const int nseg = hopk_dense_nseg(d);
+    if (n_jobs * n_chunks <= kGradFew)
+        hipLaunchKernelGGL(dense_grad_kernel<8>, dim3((unsigned)grid), dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B,
+                           d, nseg, lambda, loss, n_chunks);
+    else
+        hipLaunchKernelGGL(dense_grad_kernel<4>, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs, B,
+                           d, nseg, lambda, loss, n_chunks);
+    return launch_status();
 }
 
 int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, void* stream) {
@@ -1375,11 +1402,12 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
 
 int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream) {
     if (n_jobs <= 0) return 0;
-    const int64_t n_chunks = pair_chunks(d);
-    const int run = pair_run(n_sources, n_chunks);
+    const int vec = pair_vec(n_jobs, d, false);
+    const int64_t n_chunks = pair_chunks(d, vec);
+    const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_jobs, n_chunks, run);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(pair_mix_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs, d,
+    HOP_PAIR_LAUNCH(pair_mix_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs, d,
                        n_chunks, run, reverse);
     return launch_status();
 }
@@ -1388,13 +1416,14 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
                          const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
-    const int64_t n_chunks = pair_chunks(d);
-    const int run = pair_run(n_sources, n_chunks);
+    const int vec = pair_vec(n_mix, d, true);
+    const int64_t n_chunks = pair_chunks(d, vec);
+    const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_mix, n_chunks, run);
     const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
     const int64_t margin_blocks = (int64_t)n_grad * per;
     if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(pair_csr_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
+    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
                        (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, per, loss,
                        (int)margin_blocks);
     return launch_status();
@@ -1404,13 +1433,14 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
-    const int64_t n_chunks = pair_chunks(d);
-    const int run = pair_run(n_sources, n_chunks);
+    const int vec = pair_vec(n_mix, d, true);
+    const int64_t n_chunks = pair_chunks(d, vec);
+    const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_mix, n_chunks, run);
     const int nseg = hopk_dense_nseg(d);
     const int64_t margin_blocks = (int64_t)n_grad * B * nseg;
     if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(pair_dense_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
+    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
                        (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, nseg, margin_blocks);
     return launch_status();
 }
@@ -1423,12 +1453,6 @@ int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor
     return launch_status();
 }
 
-template <int SPLIT>
-static void launch_dense_grad_one(const HopGradJob& job, int B, int64_t d, int nseg, float lambda, int loss, void* stream) {
-    hipLaunchKernelGGL(dense_grad_one<SPLIT>, dim3((unsigned)((d + 255) / 256)), dim3(64 * SPLIT), 0, (hipStream_t)stream,
-                       job, B, d, nseg, lambda, loss);
-}
-
 int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
     const hipStream_t st = (hipStream_t)stream;
     if (mode == HOP_GRAD_SVM_DENSE) {
@@ -1436,13 +1460,18 @@ int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambd
         const int64_t few = (int64_t)B * nseg, grid = (int64_t)((B + kMarginRows - 1) / kMarginRows) * nseg;
         if (B > kMaxB) return (int)hipErrorInvalidValue;
         if (few > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-        if (grid < kMarginFew)
-            hipLaunchKernelGGL(dense_margin_one<1>, dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
+        if (grid < kMarginFew && (int64_t)B * d * 4 <= kMarginNear)
+            hipLaunchKernelGGL((dense_margin_one<1, false>), dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
+        else if (grid < kMarginFew)
+            hipLaunchKernelGGL((dense_margin_one<1, true>), dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
         else
-            hipLaunchKernelGGL(dense_margin_one<kMarginRows>, dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, nseg);
+            hipLaunchKernelGGL((dense_margin_one<kMarginRows, true>), dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, nseg);
         if (const int rc = launch_status()) return rc;
-        if ((d + 255) / 256 <= kGradFew) launch_dense_grad_one<8>(job, B, d, nseg, lambda, loss, stream);
-        else launch_dense_grad_one<4>(job, B, d, nseg, lambda, loss, stream);
+        const int64_t n_chunks = (d + 255) / 256;
+        if (n_chunks <= kGradFew)
+            hipLaunchKernelGGL(dense_grad_one<8>, dim3((unsigned)n_chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
+        else
+            hipLaunchKernelGGL(dense_grad_one<4>, dim3((unsigned)n_chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
         const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
         const int64_t grid = margin_blocks + (d + 4 * kThreads - 1) / (4 * kThreads);
@@ -1465,11 +1494,12 @@ int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d,
     if (n_jobs > kPairArgs) return (int)hipErrorInvalidValue;
     HopPairArgs args;
     memcpy(args.job, jobs, (size_t)n_jobs * sizeof(HopPairArg));
-    const int64_t n_chunks = pair_chunks(d);
-    const int run = pair_run(n_sources, n_chunks);
+    const int vec = pair_vec(n_jobs, d, false);
+    const int64_t n_chunks = pair_chunks(d, vec);
+    const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_jobs, n_chunks, run);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(pair_mix_args_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args, n_jobs, d,
+    HOP_PAIR_LAUNCH(pair_mix_args_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args, n_jobs, d,
                        n_chunks, run);
     return launch_status();
 }

@@ -1024,8 +1024,7 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
         if (timed && (rc = prof_end(c))) return rc;
         if (csr) {
             if (timed && (rc = prof_begin(c, HOP_KERNEL_GRAD, s->wave_grad_bytes[w]))) return rc;
-            HOP_LAUNCH(c, hopk_csr_scatter(gj, ng, B, c->opts.lr, 0, stream));
-            if (c->vel) HOP_LAUNCH(c, hopk_csr_scatter(gj, ng, B, -1.0f, 1, stream));
+            HOP_LAUNCH(c, hopk_csr_scatter(gj, ng, B, c->opts.lr, c->vel != nullptr, stream));
             if (timed && (rc = prof_end(c))) return rc;
         }
     }

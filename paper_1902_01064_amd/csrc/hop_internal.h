@@ -143,6 +143,7 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
                          const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream);
 int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream);
+// out += factor c_m x_m over the active rows; into_velocity: vel -= c_m x_m too
 int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor, int into_velocity, void* stream);
 int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int64_t first, int64_t nnz, int64_t d,
                    int* flag_dev, void* stream);

@@ -170,16 +170,30 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         reader_after[op.out_slot] = 0;
         for (const auto& t : op.terms) reader_after[t.first] = 1;
     }
-    // by kind inside a wave, beginning with the kind that the wave before ended on: long runs
+    // by kind inside a wave, beginning with the kind that the wave before ended on: long runs; returns their number
     std::vector<int> order((size_t)R);
-    for (int b = 0; b < R;) {
-        int e = b;
-        for (; e < R && given[e].wave == given[b].wave; ++e) order[e] = e;
-        const int open = b ? kind[order[b - 1]] : 0;
-        std::stable_sort(order.begin() + b, order.begin() + e, [&](int x, int y) {
-            return std::make_pair(kind[x] != open, kind[x]) < std::make_pair(kind[y] != open, kind[y]);
-        });
-        b = e;
+    auto arrange = [&] {
+        int runs = 0;
+        for (int b = 0; b < R;) {
+            int e = b;
+            for (; e < R && given[e].wave == given[b].wave; ++e) order[e] = e;
+            const int open = b ? kind[order[b - 1]] : 0;
+            std::stable_sort(order.begin() + b, order.begin() + e, [&](int x, int y) {
+                return std::make_pair(kind[x] != open, kind[x]) < std::make_pair(kind[y] != open, kind[y]);
+            });
+            for (; b < e; ++b) runs += b == 0 || kind[order[b]] != kind[order[b - 1]];
+        }
+        return runs;
+    };
+    // A run starts with a load that nothing covers.  Where runs are short, records with an odd number of sources take a
+    // zero with weight 0 as one more: half as many kinds (32 workers x 25 M columns, 4.5 -> 8.5 records per run: 88.4 ->
+    // 82 ms; 16 x 2 M with momentum, 1.7 -> 2.3: 1.75 -> 1.63 ms).  Where they are long that only costs the source and a
+    // local slot (64 workers with 5 sources each in lock-step: 5.47 -> 6.74 ms).
+    const bool even = arrange() * 8 > R;
+    if (even) {
+        for (int& k : kind)
+            if (k != kSweepOther) k += k & 1;
+        arrange();
     }
     auto op_at = [&](int r) -> const HopSweepOp& { return given[order[r]]; };
     std::vector<int> holds((size_t)n_ring_slots, -1);
@@ -218,7 +232,7 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
             vel[op.worker] = take();
             ++n_vel;
         }
-    if (n_local > kSweepMaxLocal) return false;
+    if (n_local >= kSweepMaxLocal) return false;
     auto bits = [](float f) {
         uint32_t u;
         std::memcpy(&u, &f, sizeof(u));
@@ -235,12 +249,14 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
     plan->n_runs = (int)prog.size();
     prog.resize((prog.size() + 4) / 4 * 4, 0u);      // at least one word of padding: the next run is read ahead
     plan->first_record = (int)prog.size();
+    std::vector<size_t> padded;                      // where a source is missing to an even number: the zero, weight 0
     for (int r = 0; r < R; ++r) {
         const HopSweepOp& op = op_at(r);
         const size_t A = op.terms.size(), at = prog.size();
         prog.resize(at + hop_sweep_words((int)A), 0u);
         uint32_t* p = prog.data() + at;
         p[7] = (uint32_t)A;
+        if (even && A % 2 && A <= (size_t)kSweepInline) padded.push_back(at + kSweepHead + 2 * A);
         for (size_t t = 0; t < A; ++t) {
             p[kSweepHead + 2 * t] = (uint32_t)local[reads[r][t]] * kLane;
             p[kSweepHead + 2 * t + 1] = bits(op.terms[t].second);
@@ -253,7 +269,7 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         const int v = result[r];
         if (last_use[v] >= 0) {
             local[v] = take();
-            if (n_local > kSweepMaxLocal) return false;
+            if (n_local >= kSweepMaxLocal) return false;
             p[0] |= kSweepKeep;
             p[1] = (uint32_t)local[v] * kLane;
         }
@@ -278,6 +294,7 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         following = op.worker;
     }
     plan->first_external = std::max(following, 0);
+    for (size_t q : padded) prog[q] = (uint32_t)n_local * kLane;
     plan->first_load = (int)prog.size();
     // the initial values were given the first local slots, in this order
     for (size_t i = 0; i < initial.size(); ++i) {
@@ -289,7 +306,8 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
             prog.push_back((uint32_t)w);
             prog.push_back((uint32_t)vel[w] * kLane);
         }
-    plan->n_local = std::max(n_local, 1);
+    plan->n_local = std::max(n_local + (even ? 1 : 0), 1);
+    plan->zero = even ? n_local * (int)kLane : -1;
     plan->n_loads = (int)initial.size();
     plan->n_vel = n_vel;
     return true;
@@ -309,8 +327,23 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
                 char* room, size_t room_bytes) {
     const int mode = c->grad_mode;
     if (!hopk_sweep || (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL)) return HOP_OK;
-    auto slot_of = [c](const float* p) { return (int)((p - c->ring) / c->stride); };
     const int R = (int)mix.size();
+    // The more local slots, the fewer wavefronts per CU there are to hide each other's latency: 2 M columns and 64, 81
+    // and 100 workers in lock-step (80, 99 and 120 slots) take, wave by wave against sweep, 1.5, 1.1 and 0.94 times as
+    // long without a gradient, 1.05, 0.74 and 0.64 with external ones (loads on the way), 2.5, 2 and 1.6 with synthetic
+    // ones (arithmetic on the way).
+    const int most_local = mode == HOP_GRAD_SYNTH ? kSweepMaxLocal : mode == HOP_GRAD_ZERO ? 112 : 84;
+    // Narrow models leave most of the GPU idle in a sweep, whose records then follow each other at 0.14 us; a wave of
+    // its own takes 3.5 to 5 us (two launches with synthetic gradients: 6 to 9), whatever its records.  1024 columns in
+    // lock-step, wave by wave against sweep: 16 records per wave 2 to 3 times, 32 records 0.84 (synthetic 1.3), 64
+    // records 0.5 (0.86).  From 65536 columns on the sweep is ahead in every case above.
+    const int most_per_wave = mode == HOP_GRAD_SYNTH ? 40 : 24;
+    // (with over 112 slots - 64 workers with velocities, 54 000 columns, 21 records per wave - 641 us against 622)
+    const bool narrow = c->d < 65536;
+    const int limit = narrow ? std::min(most_local, 112) : most_local;
+    // a slot per worker and one per velocity are needed in any case
+    if ((narrow && R > most_per_wave * s->n_waves) || c->N * (c->vel ? 2 : 1) > limit) return HOP_OK;
+    auto slot_of = [c](const float* p) { return (int)((p - c->ring) / c->stride); };
     std::vector<HopSweepOp> ops((size_t)R);
     std::vector<int> at((size_t)c->N * c->slots, -1);            // position of the record that writes a slot, this wave
     for (int w = 0; w < s->n_waves; ++w) {
@@ -345,24 +378,14 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
         }
     }
     HopSweepPlan plan;
-    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan)) return HOP_OK;
-    // The more local slots, the fewer wavefronts per CU there are to hide each other's latency: 2 M columns and 64, 81
-    // and 100 workers in lock-step (80, 99 and 120 slots) take, wave by wave against sweep, 1.5, 1.1 and 0.94 times as
-    // long without a gradient, 1.05, 0.74 and 0.64 with external ones (loads on the way), 2.5, 2 and 1.6 with synthetic
-    // ones (arithmetic on the way).
-    const int most_local = mode == HOP_GRAD_SYNTH ? kSweepMaxLocal : mode == HOP_GRAD_ZERO ? 112 : 84;
-    // Narrow models leave most of the GPU idle in a sweep, whose records then follow each other at 0.14 us; a wave of
-    // its own takes 3.5 to 5 us (two launches with synthetic gradients: 6 to 9), whatever its records.  1024 columns in
-    // lock-step, wave by wave against sweep: 16 records per wave 2 to 3 times, 32 records 0.84 (synthetic 1.3), 64
-    // records 0.5 (0.86).  From 65536 columns on the sweep is ahead in every case above.
-    const int most_per_wave = mode == HOP_GRAD_SYNTH ? 40 : 24;
-    if (plan.n_local > most_local || (c->d < 65536 && R > most_per_wave * s->n_waves)) return HOP_OK;
+    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan) || plan.n_local > limit) return HOP_OK;
     const size_t bytes = plan.program.size() * sizeof(uint32_t);
     if (bytes > room_bytes) return HOP_OK;
     HOP_HIP(c, hipMemcpy(room, plan.program.data(), bytes, hipMemcpyHostToDevice));
     HopSweepArgs& a = s->sweep;
     a.program = (const uint32_t*)room;
     a.n_runs = plan.n_runs;
+    a.zero = plan.zero;
     a.first_record = plan.first_record;
     a.first_load = plan.first_load;
     a.first_external = plan.first_external;

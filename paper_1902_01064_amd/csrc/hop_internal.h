@@ -77,13 +77,14 @@ struct alignas(16) HopGradJob {
 // ---- a whole pass as a program for sweep_kernel ------------------------------------
 // The records of a pass in an order that respects their dependences, for gradients that need no sum over the columns
 // (none, synthetic, external): every column can then run the whole pass by itself.  Words of 32 bits:
-//   runs     count << 8 | kind for every run of records of one kind: the number of sources, + kSweepGrad << 4 with a
-//            gradient, + kSweepStore << 4 where a result is not just kept in a local slot (the flags of each record say);
-//            kSweepOther: more sources than are unrolled
+//   runs     count << 8 | kind for every run of records of one kind: the number of sources (possibly rounded up to an even
+//            one), + kSweepGrad << 4 with a gradient, + kSweepStore << 4 where a result is not just kept in a local slot
+//            (the flags of each record say); kSweepOther: more sources than are unrolled
 //   records  0 flags, 1 local slot of the result, 2 ring slot it is stored to, 3 local slot of the velocity, 4..6 key[]
 //            (synthetic: hash keys, the first two folded; external: the worker, and the worker of
 //            the next record with a gradient, whose load is issued ahead), 7 number of sources, then (local slot,
-//            weight) of every source, padded to whole fours; one empty record behind the last
+//            weight) of every source, padded to whole fours; one empty record behind the last.  Where the
+//            number is rounded up, the local slot `zero`, which holds zero, follows with weight 0
 //   loads    (ring slot, local slot) of the values read from the rings, then (worker, local slot) of the velocities
 // A local slot is written as its byte offset.
 constexpr int kSweepHead = 8;
@@ -103,7 +104,7 @@ struct HopSweepOp {                     // one record, in ring-slot terms (host 
 struct HopSweepPlan {
     int n_runs = 0, n_local = 0, n_loads = 0, n_vel = 0;
     int first_record = 0, first_load = 0;       // words
-    int first_external = 0;
+    int first_external = 0, zero = -1;          // zero: -1 if no record uses it
     std::vector<uint32_t> program;
 };
 
@@ -119,6 +120,7 @@ struct HopSweepArgs {
     float* vel;                         // null: no velocities
     const float* external;              // n_workers x d
     int32_t first_external;             // worker of the first record with a gradient
+    int32_t zero;
     int64_t stride, d;
     float eta, mu, scale;
 };

@@ -629,11 +629,12 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 // vectors per worker, whatever the ring depth), gradients in registers; a ring slot is read once if its old content is
 // used and written once if its content survives the pass.  Lanes never exchange data: one wavefront is a workgroup.
 // Bound by instruction issue: 20 integer instructions (4 of them half-rate multiplies) for a synthetic gradient and two
-// vector instructions per source, at 87 % of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x 25 M
-// columns x 3136 records (52 local slots): 246.7 ms wave by wave -> 87.3 to 91.8 ms; 16 workers x 2 M columns x 640 records with
-// momentum: 7.87 -> 1.78 ms.  On the way there: words unpacked from bytes 180 ms (scalar unit), flags tested per record
-// 110 ms, next words loaded where the compiler moves them 99 ms; 2 and 4 columns per lane (fewer wavefronts per CU: the
-// local slots fill LDS either way) 115 and 190 ms; several wavefronts per workgroup 109 to 130 ms.
+// vector instructions per source, at 90 % of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x 25 M
+// columns x 3136 records (52 local slots): 242.1 ms wave by wave -> 83.1 ms; 16 workers x 2 M columns x 640 records with
+// momentum: 7.93 -> 1.58 ms.  On the way there: words unpacked from bytes 180 ms (scalar unit), flags tested per record
+// 110 ms, next words loaded where the compiler moves them 99 ms, a kind for every number of sources 88 ms; 2 and 4 columns
+// per lane (fewer wavefronts per CU: the local slots fill LDS either way) 115 and 190 ms; several wavefronts per workgroup
+// 109 to 130 ms.
 typedef const __attribute__((address_space(4))) uint32_t* sweep_words;     // scalar loads
 
 // N program words (a multiple of 4, at most 32) by as few scalar loads as there can be
@@ -808,6 +809,7 @@ __device__ __forceinline__ void sweep_columns(const HopSweepArgs& a, SweepLane& 
     lists += 2 * a.n_loads;
     if (MOM) sweep_fill<FULL>(lists, a.n_vel, a.vel, a.stride, l);
     if (MODE == HOP_GRAD_EXTERNAL) l.ahead = sweep_external<FULL>(a, (uint32_t)a.first_external, l);
+    if (a.zero >= 0) sweep_local(l, (uint32_t)a.zero) = 0.f;            // the missing source of an odd record
     const sweep_words runs = (sweep_words)a.program;
     sweep_words rec = runs + a.first_record;
     uint32_t ahead = runs[0];

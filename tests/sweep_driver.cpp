@@ -38,11 +38,12 @@ static float grad_of(const uint32_t* key) { return (float)((key[0] * 2654435761u
 int main() {
     std::mt19937 gen(3);
     auto below = [&](int n) { return (int)(gen() % (unsigned)n); };
-    int wide = 0, refused = 0, kinds[4] = {0, 0, 0, 0};
+    int wide = 0, refused = 0, evens = 0, planned = 0, kinds[4] = {0, 0, 0, 0};
     for (int run = 0; run < 400; ++run) {
         const int N = 1 + below(run % 7 == 0 ? 90 : 12), depth = 1 + below(5), slots = N * depth, waves = 1 + below(12);
         const int mode = below(3);                                   // 0 none, 1 keys, 2 external
         const bool mom = below(3) == 0;
+        const int uniform = run % 4 == 0 ? 1 + below(9) : 0;           // long runs: the same number of sources everywhere
         const float eta = 0.125f, mu = 0.9f;
         std::vector<HopSweepOp> ops;
         for (int w = 0; w < waves; ++w) {
@@ -57,17 +58,17 @@ int main() {
                 for (const HopSweepOp& o : ops) seen = seen || (o.wave == w && o.worker == op.worker);
                 const int me = (int)ops.size();
                 if (seen || written_by[op.out_slot] >= 0 || read_by[op.out_slot] >= 0) continue;
-                const int A = 1 + below(below(6) == 0 ? 20 : 8);
+                const int A = uniform ? uniform : 1 + below(below(6) == 0 ? 20 : 8);
                 for (int t = 0; t < A; ++t) {
                     const int src = below(slots);
-                    if (written_by[src] >= 0) continue;
+                    if (written_by[src] >= 0) { t -= uniform && below(8) ? 1 : 0; continue; }
                     op.terms.emplace_back(src, 0.0625f * (1 + below(9)));
-                    if (below(12) == 0) op.terms.push_back(op.terms.back());       // listed twice
+                    if (!uniform && below(12) == 0) op.terms.push_back(op.terms.back());       // listed twice
                 }
                 if (op.terms.empty()) continue;
                 for (auto& t : op.terms) if (t.first != op.out_slot) read_by[t.first] = me;
                 written_by[op.out_slot] = me;
-                op.grad = mode != 0 && below(5) != 0;
+                op.grad = mode != 0 && (uniform || below(5) != 0);
                 op.vel = mom && op.grad;
                 op.external = op.grad && mode == 2;
                 if (op.grad && mode == 1) for (uint32_t& k : op.key) k = gen();
@@ -96,6 +97,7 @@ int main() {
         HopSweepPlan plan;
         if (!hop_plan_sweep(ops, slots, N, &plan)) { ++refused; continue; }
         EXPECT(plan.n_local <= kSweepMaxLocal);
+        ++planned;
         std::vector<float> got = ring0, gvel = vel0, local((size_t)plan.n_local, NAN);
         const std::vector<uint32_t>& P = plan.program;
         auto at = [&](uint32_t off) -> float& { return local.at(off / 256); };
@@ -104,6 +106,9 @@ int main() {
         const size_t vels = list;
         for (int k = 0; k < plan.n_vel; ++k, list += 2) at(P.at(list + 1)) = vel0.at(P.at(list));
         EXPECT(list == P.size());
+        const bool even = plan.zero >= 0;                            // odd records read a zero more
+        if (even) at((uint32_t)plan.zero) = 0.f;
+        evens += even;
         std::vector<char> stored((size_t)slots, 0);
         size_t rec = (size_t)plan.first_record;
         int done = 0;
@@ -116,10 +121,10 @@ int main() {
                 EXPECT(rec % 4 == 0 && rec + hop_sweep_words(A) + hop_sweep_words(kSweepInline) <= (size_t)plan.first_load);
                 const bool kept = (h[0] & kSweepKeep) && !(h[0] & kSweepStore);
                 if (kind == (uint32_t)kSweepOther) EXPECT(A > kSweepInline);
-                else EXPECT(kind == A + ((h[0] & kSweepGrad) << 4) + (kept ? 0u : kSweepStore << 4));
+                else EXPECT(kind == (even ? (A + 1) / 2 * 2 : A) + ((h[0] & kSweepGrad) << 4) + (kept ? 0u : kSweepStore << 4));
                 if (kind != (uint32_t)kSweepOther) kinds[kind >> 4]++;
                 float acc = 0.f;
-                for (int t = 0; t < A; ++t) {
+                for (int t = 0; t < (even && A <= kSweepInline ? (A + 1) / 2 * 2 : A); ++t) {
                     EXPECT(!std::isnan(at(h[kSweepHead + 2 * t])));
                     acc = std::fmaf(as_float(h[kSweepHead + 2 * t + 1]), at(h[kSweepHead + 2 * t]), acc);
                 }
@@ -149,7 +154,7 @@ int main() {
         for (int q = 0; q < slots; ++q) EXPECT(got[q] == ring[q]);
         for (int q = 0; q < N; ++q) EXPECT(gvel[q] == vel[q]);
     }
-    EXPECT(wide > 50 && refused > 0 && kinds[0] && kinds[1] && kinds[2] && kinds[3]);
+    EXPECT(wide > 50 && refused > 0 && evens > 20 && planned - evens > 20 && kinds[0] && kinds[1] && kinds[2] && kinds[3]);
     std::printf("ok wide=%d refused=%d\n", wide, refused);
     return 0;
 }

@@ -159,6 +159,7 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
 // this record reads for the last time: a lane reads all its sources before it writes.
 bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int n_workers, HopSweepPlan* plan) {
     const int R = (int)given.size();
+    if (R >= 1 << 24) return false;                  // a run's length has 24 bits
     std::vector<int> last_writer((size_t)n_ring_slots, -1), reader_after((size_t)n_ring_slots, 0);
     std::vector<int> kind((size_t)R);                // what the record's run is written down as
     for (int r = 0; r < R; ++r) last_writer[given[r].out_slot] = r;

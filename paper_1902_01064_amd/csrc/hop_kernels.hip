@@ -1517,10 +1517,18 @@ int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambd
             hipLaunchKernelGGL(dense_grad_one<4>, dim3((unsigned)n_chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
         const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
-        const int64_t grid = margin_blocks + (d + 4 * kThreads - 1) / (4 * kThreads);
+        const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;
         if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL(csr_margin_dense_one, dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, lambda, loss,
-                           margin_blocks);
+        const uintptr_t w0 = (uintptr_t)job.w, g0 = (uintptr_t)job.out, bytes = (uintptr_t)d * sizeof(float);
+        if (w0 < g0 + bytes && g0 < w0 + bytes) {          // g over w: the margins read w first
+            hipLaunchKernelGGL(csr_margin_dense_one, dim3((unsigned)margin_blocks), dim3(kThreads), 0, st, job, B, d, lambda,
+                               loss, margin_blocks);
+            hipLaunchKernelGGL(csr_margin_dense_one, dim3((unsigned)dense_blocks), dim3(kThreads), 0, st, job, B, d, lambda,
+                               loss, 0);
+        } else {
+            hipLaunchKernelGGL(csr_margin_dense_one, dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, lambda, loss,
+                               margin_blocks);
+        }
         if (const int rc = launch_status()) return rc;
         hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)((B + kScatterRows - 1) / kScatterRows)), dim3(kScatterThreads), 0,
                            st, job, B, -1.0f);

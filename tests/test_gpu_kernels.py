@@ -256,3 +256,24 @@ def test_mix_around_the_descriptors_that_fit_a_launch(n_jobs, A):
     torch.cuda.synchronize()
     for out, ref in want:
         assert rel_err(out.cpu().numpy(), ref) <= 1e-5
+
+
+def test_svm_grad_csr_may_overwrite_its_parameters():
+    """g over w: the margins have to be taken before the dense part lambda w is written."""
+    d, nnz, B, rows = 40000, 16, 64, 128
+    ws = inputs.hidden_w(9, d)
+    rowptr, col, val, y = inputs.csr_svm_data(9, 0, rows, d, nnz, 1.1, ws)
+    w = (inputs.initial_params(9, d, 0.01) + 0.05 * ws).contiguous()
+    dv = [t.to(DEV) for t in (rowptr, col, val, y)]
+    rd = torch.from_numpy(rng.batch_rows(9, 0, 2, B, rows).astype(np.int32)).to(DEV)
+    got = []
+    for over in (False, True):
+        wd, g, coef = w.to(DEV), aligned(d), aligned(B)
+        if over:
+            g = wd
+        hop.hop_svm_grad_csr(*[t.data_ptr() for t in dv], wd.data_ptr(), rd.data_ptr(), B, d, 1e-3, g.data_ptr(),
+                             coef.data_ptr(), stream(), hop.HOP_LOSS_LOG)
+        torch.cuda.synchronize()
+        got.append((g.cpu().numpy(), coef.cpu().numpy()))
+    assert np.array_equal(got[0][1], got[1][1])
+    assert rel_err(got[1][0], got[0][0]) <= 1e-6                # the scatter's atomics have no fixed order

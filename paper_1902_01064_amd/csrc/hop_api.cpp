@@ -91,7 +91,8 @@ size_t workspace_need(size_t R, size_t B) {
 
 // Pack the Reduce jobs of one wave two by two: a record is joined with the later record (among the next 64 still
 // single) that shares the most sources with it, provided the union stays within HOP_PAIR_U vectors.  Union order:
-// the first record's sources in its own order, then what the second adds.  Only waves whose records read every
+// the first record's sources in its own order, then what the second adds.  A pair has one eta: two records with a
+// gradient each are joined only if theirs is the same.  Only waves whose records read every
 // distinct vector at least twice on average are paired: there a shared load in registers saves an L2 request that
 // matters (32 workers, 23 records of ~7 sources per wave: 1472 -> 1434 us per launch); where records share little
 // (64 workers, 9 records of ~5 sources per wave) single records run 3 % faster than pairs, which halve the number
@@ -115,6 +116,7 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
                 if (used[k]) continue;
                 ++seen;
                 const HopMixJob& b = jobs[k];
+                if (a.g && b.g && !(a.eta == b.eta)) continue;
                 int overlap = 0;
                 for (int q = 0; q < b.A; ++q)
                     if (std::find(a.src, a.src + a.A, b.src[q]) != a.src + a.A) ++overlap;
@@ -140,6 +142,7 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
             used[best] = 1;
             const HopMixJob& b = jobs[best];
             pj.G = 2;
+            if (!a.g) pj.eta = b.eta;      // without a gradient a record has no use for its own
             pj.out[1] = b.out;
             pj.g[1] = b.g;
             for (int q = 0; q < b.A; ++q) {

@@ -135,8 +135,61 @@ static int test_pack_pairs() {
     return 0;
 }
 
+// Records of one call may differ in eta: whoever has a gradient keeps its own, inside a pair too.
+static int test_pack_pairs_with_several_etas() {
+    std::vector<float> pool(16), outs(8);
+    int pairs_of_both = 0, pairs_of_one = 0;
+    for (int code = 0; code < 2 * 81; ++code) {                      // 4 records: eta 0 / 0.5 / 0.25, every choice
+        const bool no_g_first = code >= 81;
+        HopMixJob jobs[4];
+        int z = code % 81;
+        for (int i = 0; i < 4; ++i, z /= 3) {
+            std::memset(&jobs[i], 0, sizeof(jobs[i]));
+            jobs[i].out = &outs[(size_t)i];
+            jobs[i].eta = z % 3 == 0 ? 0.f : z % 3 == 1 ? 0.5f : 0.25f;
+            jobs[i].g = no_g_first && i < 2 ? nullptr : &pool[8 + (size_t)i];
+            jobs[i].A = 3;
+            for (int a = 0; a < 3; ++a) {
+                jobs[i].src[a] = &pool[(size_t)a];
+                jobs[i].w[a] = 0.25f * (float)(i + 1);
+            }
+        }
+        std::vector<HopPairJob> out;
+        EXPECT(hop_pack_pairs(jobs, 4, out) == 3);
+        int seen = 0;
+        for (const HopPairJob& pj : out) {
+            int with_g = 0;
+            for (int r = 0; r < pj.G; ++r, ++seen) {
+                const HopMixJob& j = jobs[pj.out[r] - outs.data()];
+                EXPECT(pj.g[r] == j.g);
+                if (j.g) EXPECT(pj.eta == j.eta);
+                with_g += j.g != nullptr;
+            }
+            if (pj.G == 2) (with_g == 2 ? pairs_of_both : pairs_of_one) += with_g > 0;
+        }
+        EXPECT(seen == 4);
+    }
+    EXPECT(pairs_of_both > 0 && pairs_of_one == 0);                  // the two without a gradient find each other first
+    HopMixJob mixed[2];
+    for (int i = 0; i < 2; ++i) {
+        std::memset(&mixed[i], 0, sizeof(mixed[i]));
+        mixed[i].out = &outs[(size_t)i];
+        mixed[i].A = 2;
+        for (int a = 0; a < 2; ++a) { mixed[i].src[a] = &pool[(size_t)a]; mixed[i].w[a] = 0.5f; }
+    }
+    for (int with = 0; with < 2; ++with) {                           // one of the two has a gradient: still a pair
+        mixed[with].g = &pool[8];
+        mixed[with].eta = 0.125f;
+        mixed[1 - with].g = nullptr;
+        mixed[1 - with].eta = 0.f;
+        std::vector<HopPairJob> out;
+        EXPECT(hop_pack_pairs(mixed, 2, out) == 2 && out.size() == 1 && out[0].G == 2 && out[0].eta == 0.125f);
+    }
+    return 0;
+}
+
 int main() {
-    if (test_pack_pairs() != 0) return 1;
+    if (test_pack_pairs() != 0 || test_pack_pairs_with_several_etas() != 0) return 1;
     hop_opts o;
     EXPECT(hop_opts_default(&o) == HOP_OK && hop_opts_default(nullptr) == HOP_ERR_INVALID_ARG);
     EXPECT(std::strcmp(hop_strerror(HOP_ERR_DEADLOCK), "unknown error") != 0 && hop_strerror(-99) != nullptr);

@@ -277,3 +277,31 @@ def test_svm_grad_csr_may_overwrite_its_parameters():
         got.append((g.cpu().numpy(), coef.cpu().numpy()))
     assert np.array_equal(got[0][1], got[1][1])
     assert rel_err(got[1][0], got[0][0]) <= 1e-6                # the scatter's atomics have no fixed order
+
+
+@pytest.mark.parametrize("n_jobs", [2, 15, 40])
+@pytest.mark.parametrize("first", ["no gradient", "eta 0", "eta 0.2"])
+def test_mix_jobs_that_differ_in_eta(n_jobs, first):
+    """Jobs that average the same vectors but step by different eta: the first one without a gradient, with a gradient
+    that it does not apply, or with a longer step than the others; as kernel arguments and through device memory."""
+    d = 2053
+    rs = np.random.default_rng(n_jobs)
+    host = [rs.normal(size=d).astype(np.float32) for _ in range(4)]
+    pool = [aligned(d) for _ in host]
+    for t, h in zip(pool, host):
+        t.copy_(torch.from_numpy(h))
+    jobs, keep, want = [], [], []
+    for j in range(n_jobs):
+        w = rs.dirichlet(np.ones(4)).astype(np.float32)
+        g, out = aligned(d), aligned(d)
+        gh = rs.normal(size=d).astype(np.float32)
+        g.copy_(torch.from_numpy(gh))
+        keep += [g, out]
+        eta = {"no gradient": 0.0, "eta 0": 0.0, "eta 0.2": 0.2}[first] if j == 0 else 0.01 * (1 + j % 3)
+        use_g = j > 0 or first != "no gradient"
+        jobs.append(dict(out=out.data_ptr(), g=g.data_ptr() if use_g else None, eta=eta, src=[p.data_ptr() for p in pool], w=w))
+        want.append((out, arith.reduce_apply(host, w, gh if use_g else None, eta)))
+    hop.hop_mix(jobs, d, stream())
+    torch.cuda.synchronize()
+    for out, ref in want:
+        assert rel_err(out.cpu().numpy(), ref) <= 1e-5

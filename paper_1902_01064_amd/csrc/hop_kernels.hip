@@ -1002,13 +1002,14 @@ constexpr int64_t kGradFew = 768;                      // chunks up to which a l
 template <int SPLIT>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
-    __shared__ float coefS[kMaxB + kRowUnroll];
+    __shared__ float coefS[kMaxB];
     __shared__ int rowS[kMaxB + kRowUnroll];
     __shared__ float allC[kMaxB];
     __shared__ int nactS;
     __shared__ float4 joinS[(SPLIT - 1) * 64];
     const float invB = 1.0f / (float)B;
-    const int part = (int)threadIdx.x / 64, col = (int)threadIdx.x % 64;        // which share of the rows
+    const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);     // which share of the rows
+    const int col = (int)threadIdx.x % 64;
     const float* X = job->X;
     const float* w = job->w;
     float* out = job->out;                             // set: apply -eta g (or -eta v) to it instead of writing g
@@ -1039,40 +1040,44 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     __syncthreads();
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (threadIdx.x < 64) {                        // first wavefront compacts the active rows, keeping order
-        int count = 0;
+        int count = 0, any = 0;
         for (int base = 0; base < B; base += 64) {
             const int m = base + threadIdx.x;
             const float cm = m < B ? allC[m] : 0.f;
             const bool act = cm != 0.f;
             const unsigned long long mask = __ballot(act);
             const int pos = count + __popcll(mask & ((1ull << threadIdx.x) - 1ull));
+            const int row = act ? job->rows[m] : 0;
             if (act) {
                 coefS[pos] = cm;
-                rowS[pos] = job->rows[m];
+                rowS[pos] = row;
             }
+            if (mask) any = __builtin_amdgcn_readlane(row, __ffsll(mask) - 1);
             count += __popcll(mask);
         }
-        if (threadIdx.x < kRowUnroll) {            // pad to a multiple of the unroll with zeros
-            coefS[count + threadIdx.x] = 0.f;
-            rowS[count + threadIdx.x] = job->rows[0];
-        }
+        if (threadIdx.x < kRowUnroll) rowS[count + threadIdx.x] = any;     // loaded with the last rows, not added
         if (threadIdx.x == 0) nactS = count;
     }
     __syncthreads();
-    const int nact = nactS;
-    if (n == 4) {
+    const int nact = __builtin_amdgcn_readfirstlane(nactS);
+    // active rows only, each once: a zero times an infinity in a row that takes no part would be a NaN in the sum
+    auto add_rows = [&](auto row_at) {
         for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT) {
             float4 v[kRowUnroll];
 #pragma unroll
-            for (int u = 0; u < kRowUnroll; ++u) v[u] = ldu4(X + (int64_t)rowS[q + u] * d, c);
+            for (int u = 0; u < kRowUnroll; ++u) v[u] = row_at(X + (int64_t)rowS[q + u] * d);
+            if (q + kRowUnroll <= nact) {
 #pragma unroll
-            for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], v[u], acc);
+                for (int u = 0; u < kRowUnroll; ++u) acc = fma4(coefS[q + u], v[u], acc);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kRowUnroll - 1; ++u)
+                    if (q + u < nact) acc = fma4(coefS[q + u], v[u], acc);
+            }
         }
-    } else if (n > 0) {                            // the thread at the end of a vector with d mod 4 columns left
-        for (int q = part * kRowUnroll; q < nact; q += kRowUnroll * SPLIT)
-            for (int u = 0; u < kRowUnroll; ++u)
-                acc = fma4(coefS[q + u], ldu4(X + (int64_t)rowS[q + u] * d, c, n), acc);
-    }
+    };
+    if (n == 4) add_rows([&](const float* x) { return ldu4(x, c); });
+    else if (n > 0) add_rows([&](const float* x) { return ldu4(x, c, n); });     // the end of a vector, d mod 4 columns left
     if (part > 0) joinS[(part - 1) * 64 + col] = acc;  // join the shares: ((part 0 + part 1) + part 2) + ...
     __syncthreads();
     if (n <= 0 || part != 0) return;

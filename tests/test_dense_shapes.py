@@ -58,3 +58,35 @@ def test_dense_gradient_at_the_edges(d, B, shift, loss):
         slack += min(d, 4096) * 2.0 ** -24 * (1.0 + np.abs(Xn[ids].astype(np.float64) * wn).sum(1).max())
     assert np.all(np.abs(got - ref) <= slack * mag + 1e-30)
     assert (gbuf[:shift] == 7.0).all() and (gbuf[shift + d:] == 7.0).all()           # nothing written beside the result
+
+
+@pytest.mark.parametrize("loss", ["hinge", "log"])
+@pytest.mark.parametrize("d,B", [(1024, 8), (1021, 8), (4, 5), (3, 5), (258, 64), (4096, 100), (16390, 33)])
+def test_samples_that_are_not_finite(d, B, loss):
+    """The first sample of the minibatch has an infinite margin on the right side (hinge: one that is no number): it takes
+    no part, and what it holds stays out of the gradient.  The second has an infinite margin on the wrong side: it takes
+    part, in column 0 with an infinity."""
+    print("not finite d=%d B=%d %s" % (d, B, loss), flush=True)
+    gen = torch.Generator().manual_seed(d + B)
+    X = torch.randn(B, d, generator=gen)
+    y = torch.sign(torch.randn(B, generator=gen))
+    w = 0.1 + torch.rand(d, generator=gen) / np.sqrt(d)
+    y[0], y[1] = 1.0, 1.0
+    X[0, d // 2], X[0, d - 1] = float("nan" if loss == "hinge" else "inf"), float("inf")
+    X[1, 0] = float("-inf")                                       # active: -c * -inf = +inf in column 0
+    ids = np.arange(B)
+    Xd, yd, wd, rd = X.to(DEV), y.to(DEV), w.to(DEV), torch.from_numpy(ids.astype(np.int32)).to(DEV)
+    g, coef = torch.empty(d, device=DEV), torch.zeros(B, device=DEV)
+    scratch = torch.empty(hop.hop_grad_scratch_floats(d, B), device=DEV)
+    hop.hop_svm_grad_dense(Xd.data_ptr(), yd.data_ptr(), wd.data_ptr(), rd.data_ptr(), B, d, 1e-3, g.data_ptr(),
+                           coef.data_ptr(), scratch.data_ptr(), torch.cuda.current_stream().cuda_stream,
+                           1 if loss == "log" else 0)
+    torch.cuda.synchronize()
+    cg, got = coef.cpu().numpy(), g.cpu().numpy().astype(np.float64)
+    assert cg[0] == 0.0 and abs(cg[1] - 1.0 / B) <= 1e-7
+    part = cg != 0
+    ref = 1e-3 * w.numpy().astype(np.float64) - cg[part].astype(np.float64) @ X.numpy()[part].astype(np.float64)
+    assert ref[0] == np.inf and got[0] == np.inf
+    mag = 1e-3 * np.abs(w.numpy()) + np.abs(cg[part]) @ np.abs(X.numpy()[part].astype(np.float64))
+    # an fp32 sum of B + 1 products is within (B + 3) 2^-24 of the sum of magnitudes
+    assert np.all(np.abs(got[1:] - ref[1:]) <= (B + 3) * 2.0 ** -24 * mag[1:])

@@ -190,7 +190,7 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         return runs;
     };
     // A run starts with a load that nothing covers.  Where runs are short, records with an odd number of sources take a
-    // zero with weight 0 as one more: half as many kinds (32 workers x 25 M columns, 4.5 -> 8.5 records per run: 88.4 ->
+    // zero with weight -0 as one more: half as many kinds (32 workers x 25 M columns, 4.5 -> 8.5 records per run: 88.4 ->
     // 82 ms; 16 x 2 M with momentum, 1.7 -> 2.3: 1.75 -> 1.63 ms).  Where they are long that only costs the source and a
     // local slot (64 workers with 5 sources each in lock-step: 5.47 -> 6.74 ms).
     const bool even = arrange() * 8 > R;
@@ -253,7 +253,7 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
     plan->n_runs = (int)prog.size();
     prog.resize((prog.size() + 4) / 4 * 4, 0u);      // at least one word of padding: the next run is read ahead
     plan->first_record = (int)prog.size();
-    std::vector<size_t> padded;                      // where a source is missing to an even number: the zero, weight 0
+    std::vector<size_t> padded;                      // where a source is missing to an even number: the zero, weight -0
     for (int r = 0; r < R; ++r) {
         const HopSweepOp& op = op_at(r);
         const size_t A = op.terms.size(), at = prog.size();
@@ -298,7 +298,10 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         following = op.worker;
     }
     plan->first_external = std::max(following, 0);
-    for (size_t q : padded) prog[q] = (uint32_t)n_local * kLane;
+    for (size_t q : padded) {
+        prog[q] = (uint32_t)n_local * kLane;
+        prog[q + 1] = bits(-0.f);                    // -0 * 0 = -0, which changes no sum: not even one of -0
+    }
     plan->first_load = (int)prog.size();
     // the initial values were given the first local slots, in this order
     for (size_t i = 0; i < initial.size(); ++i) {

@@ -84,7 +84,7 @@ struct alignas(16) HopGradJob {
 //            (synthetic: hash keys, the first two folded; external: the worker, and the worker of
 //            the next record with a gradient, whose load is issued ahead), 7 number of sources, then (local slot,
 //            weight) of every source, padded to whole fours; one empty record behind the last.  Where the
-//            number is rounded up, the local slot `zero`, which holds zero, follows with weight 0
+//            number is rounded up, the local slot `zero`, which holds zero, follows with weight -0
 //   loads    (ring slot, local slot) of the values read from the rings, then (worker, local slot) of the velocities
 // A local slot is written as its byte offset.
 constexpr int kSweepHead = 8;

@@ -126,6 +126,7 @@ int main() {
                 float acc = 0.f;
                 for (int t = 0; t < (even && A <= kSweepInline ? (A + 1) / 2 * 2 : A); ++t) {
                     EXPECT(!std::isnan(at(h[kSweepHead + 2 * t])));
+                    if (t >= A) EXPECT(h[kSweepHead + 2 * t + 1] == 0x80000000u);     // -0 * 0: no change to a sum of -0
                     acc = std::fmaf(as_float(h[kSweepHead + 2 * t + 1]), at(h[kSweepHead + 2 * t]), acc);
                 }
                 if (h[0] & kSweepGrad) {

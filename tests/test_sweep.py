@@ -74,3 +74,26 @@ def test_pass_equals_the_waves_bit_for_bit(mode, graph, over):
         finally:
             sess.close()
     assert np.isfinite(got["waves"]).all() and np.array_equal(got["pass"], got["waves"])
+
+
+@pytest.mark.gpu
+def test_pass_keeps_the_sign_of_zero():
+    """Parameters of -0: with a velocity a sum starts with a product, so every average is -0 again, also where a record
+    with an odd number of sources is filled up with a zero."""
+    nb = inputs.ring_with_chords(32, 2, 7)
+    c = dict(inputs.config(4, d=130, K=8), in_nbrs=nb, W=inputs.uniform_weights(nb), N=32, s=2, b=1, skip_on=False, mult=None,
+             delay_kind=inputs.DELAY_EXP1, momentum=0.9)
+    from paper_1902_01064_amd.session import Session
+    sess = Session(c)
+    try:
+        hop.hop_set_grad_source(sess.ctx, hop.HOP_GRAD_ZERO)
+        sess.arena.fill_(-0.0)
+        sess.set_params(torch.full((c["d"],), -0.0))
+        sched = sess.simulate()
+        sources = np.diff(sched.src_begin)
+        assert (sources % 2 == 1).any() and (sources % 2 == 0).any()
+        sess.step()
+        sess.sync()
+        assert np.array_equal(sess.ring_snapshot().view(np.uint32), np.full_like(sess.ring_snapshot(), -0.0).view(np.uint32))
+    finally:
+        sess.close()

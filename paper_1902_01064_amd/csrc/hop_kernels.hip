@@ -980,7 +980,7 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
-// One workgroup per (job, 256-column chunk).  The hinge coefficients c_m = y_m / B if
+// One workgroup per (job, column chunk).  The hinge coefficients c_m = y_m / B if
 // y_m <x_m, w> < 1 else 0 are rebuilt by every workgroup from the partial dot products (B values,
 // cheap) and the active rows are compacted in LDS in minibatch order.  Three endings: write g; apply -eta g to
 // a vector the wave's Reduce has already left in the result slot; or do the record's Reduce here as well
@@ -989,32 +989,46 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
 constexpr int kMaxB = 1024;
 constexpr int kRowUnroll = 8;
 
-// A column chunk is 256 columns; SPLIT wavefronts share it and take alternate groups of 8 active rows; their sums are
-// joined through LDS in a fixed order.  The time is the chain of dependent row loads, so a chunk is as narrow as a
+// A column chunk is 256 columns times WIDE wavefronts side by side; SPLIT such groups share it and take alternate groups
+// of 8 active rows, their sums joined through LDS in a fixed order.
+// Up to a few chunks of 256 columns per CU the time is the chain of dependent row loads, so a chunk is as narrow as a
 // wavefront's 1 KB of a row and its rows are split.  Per pass, chunks of 1024 columns with one group of 256 threads (four
-// in launches of up to 128 workgroups) -> this kernel: 8 workers x 30 011 columns, B = 100 (rows not 16-byte aligned,
-// scalar loads before): 6.91 -> 2.20 ms; 16 x 65536, B = 128: 3.86 -> 3.75 ms; 4 x 1024, B = 64: 392 -> 360 us; one
-// gradient of 128 x 65536: 14.4 -> 8.8 us.  4 against 8 wavefronts per chunk: 2.35 / 2.19 ms, 3.77 / 3.89 ms, 359 / 364 us.
-constexpr int64_t kGradFew = 768;                      // chunks up to which a launch takes 8 wavefronts for each
+// in launches of up to 128 workgroups) -> this: 8 workers x 30 011 columns, B = 100 (rows not 16-byte aligned, scalar
+// loads before): 6.91 -> 2.20 ms; 16 x 65536, B = 128: 3.86 -> 3.75 ms; 4 x 1024, B = 64: 392 -> 360 us; one gradient of
+// 128 x 65536: 14.4 -> 8.8 us.  4 against 8 wavefronts per chunk, log loss (all rows active), 4 x 1024 columns, B = 64
+// and 128: 164 / 162, 186 / 174 us; 16 x 16384, B = 128: 703 / 682; 16 x 65536, B = 16: 601 / 636 us.
+// With more chunks the row loads of other workgroups fill the wait, and what counts is that every workgroup sums up the
+// coefficients of all rows again, from a partial product per 16384 columns: four times as many of them cost more than
+// the split gives.  SPLIT = WIDE = 4, 1 against 1, 4: one gradient of 2^20 columns, B = 128: 238 / 210 us, 4 M columns
+// 1564 / 962, 2^24 columns and B = 64 10.8 / 3.2 ms; a pass of 16 workers x 400 000 columns, B = 16: 1943 / 1487 us; of
+// 64 x 65536, B = 128, 13 records a wave: 3973 / 3813 us; the other way round 64 x 16384, B = 128: 1461 / 1543 us.
+constexpr int64_t kGradFew = 768;                      // chunks of 256 columns up to which a launch takes 8 wavefronts for each
+constexpr int64_t kGradMany = 2048;                    // over that many, or
+constexpr int kGradSegs = 16;                          // from that many partial products per row on: 1024 columns, rows not split
+// From 65 partial products per row on a wavefront sums them up, not a thread: 4 M columns, B = 1 and 128: 54 -> 20,
+// 962 -> 842 us; 2^24 columns, B = 1 and 64: 635 -> 89 us, 3.2 -> 1.95 ms (2^20 columns, 64 of them, B = 8 and 128:
+// 20.5 -> 17.3, 211 -> 216).
+constexpr int kSegThread = 64;
 
 // (Loading a wavefront's 8 rows at once, active or not, while the coefficients are still being worked out - one chain of
 // loads instead of two, for minibatches of up to 8 SPLIT rows - was slower: 4 x 1024, B = 64: 364 -> 460 us per pass.)
-template <int SPLIT>
+template <int SPLIT, int WIDE>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
     __shared__ float coefS[kMaxB];
     __shared__ int rowS[kMaxB + kRowUnroll];
     __shared__ float allC[kMaxB];
     __shared__ int nactS;
-    __shared__ float4 joinS[(SPLIT - 1) * 64];
+    constexpr int kCols = 64 * WIDE;                   // threads side by side
+    __shared__ float4 joinS[SPLIT > 1 ? (SPLIT - 1) * kCols : 1];
     const float invB = 1.0f / (float)B;
-    const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);     // which share of the rows
-    const int col = (int)threadIdx.x % 64;
+    const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kCols);  // which share of the rows
+    const int col = (int)threadIdx.x % kCols;
     const float* X = job->X;
     const float* w = job->w;
     float* out = job->out;                             // set: apply -eta g (or -eta v) to it instead of writing g
     const HopMixJob* red = job->reduce;                // set (with out): out = sum_a w'_a x_a - eta g, the Reduce done here
-    const int64_t c = (chunk * 64 + col) * 4;          // first of this thread's columns
+    const int64_t c = (chunk * kCols + col) * 4;       // first of this thread's columns
     const int n = (int)min((int64_t)4, d - c);         // how many of them exist
     // what the ending needs beside the sum, loaded ahead of the rows
     float4 wv = make_float4(0.f, 0.f, 0.f, 0.f), o = wv;
@@ -1030,12 +1044,24 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
             o = ldu4(out, c, n);
         }
     }
-    for (int m = threadIdx.x; m < B; m += 64 * SPLIT) {
-        float dot = 0.f;
-        for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
+    auto put_coef = [&](int m, float dot) {
         const float cm = loss_coef(job->y[job->rows[m]], dot, invB, loss);
         allC[m] = cm;
         if (chunk == 0) job->coef[m] = cm;
+    };
+    if (WIDE == 1 || nseg <= kSegThread) {
+        for (int m = threadIdx.x; m < B; m += kCols * SPLIT) {
+            float dot = 0.f;
+            for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
+            put_coef(m, dot);
+        }
+    } else {                                           // a wavefront per row
+        for (int m = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64); m < B; m += WIDE * SPLIT) {
+            float dot = 0.f;
+            for (int sg = (int)threadIdx.x % 64; sg < nseg; sg += 64) dot += job->partial[(int64_t)m * nseg + sg];
+            dot = wave_sum(dot);
+            if (threadIdx.x % 64 == 0) put_coef(m, dot);
+        }
     }
     __syncthreads();
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1078,14 +1104,17 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     };
     if (n == 4) add_rows([&](const float* x) { return ldu4(x, c); });
     else if (n > 0) add_rows([&](const float* x) { return ldu4(x, c, n); });     // the end of a vector, d mod 4 columns left
-    if (part > 0) joinS[(part - 1) * 64 + col] = acc;  // join the shares: ((part 0 + part 1) + part 2) + ...
-    __syncthreads();
-    if (n <= 0 || part != 0) return;
+    if constexpr (SPLIT > 1) {                     // join the shares: ((part 0 + part 1) + part 2) + ...
+        if (part > 0) joinS[(part - 1) * kCols + col] = acc;
+        __syncthreads();
 #pragma unroll
-    for (int q = 1; q < SPLIT; ++q) {
-        const float4 t = joinS[(q - 1) * 64 + col];
-        acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
+        for (int q = 1; q < SPLIT; ++q) {
+            if (part != 0) break;
+            const float4 t = joinS[(q - 1) * kCols + col];
+            acc = make_float4(acc.x + t.x, acc.y + t.y, acc.z + t.z, acc.w + t.w);
+        }
     }
+    if (n <= 0 || part != 0) return;
     float4 gv = make_float4(fmaf(lambda, wv.x, -acc.x), fmaf(lambda, wv.y, -acc.y), fmaf(lambda, wv.z, -acc.z),
                             fmaf(lambda, wv.w, -acc.w));
     if (out == nullptr) {
@@ -1100,20 +1129,20 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     stu4(out, c, n, fma4(-job->eta, gv, o));
 }
 
-template <int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
+template <int SPLIT, int WIDE>
+__global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
                                                                 int64_t d, int nseg, float lambda, int loss,
                                                                 int64_t n_chunks) {
     int j;
     int64_t chunk;
     if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
-        dense_grad_chunk<SPLIT>(jobs + j, B, d, nseg, lambda, loss, chunk);
+        dense_grad_chunk<SPLIT, WIDE>(jobs + j, B, d, nseg, lambda, loss, chunk);
 }
 
-template <int SPLIT>
-__global__ __launch_bounds__(64 * SPLIT) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
+template <int SPLIT, int WIDE>
+__global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
                                                              int loss) {
-    dense_grad_chunk<SPLIT>(&job, B, d, nseg, lambda, loss, blockIdx.x);
+    dense_grad_chunk<SPLIT, WIDE>(&job, B, d, nseg, lambda, loss, blockIdx.x);
 }
 
 // ------------------------------------------------------------------- CSR SVM: margins ----
@@ -1372,7 +1401,7 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int nseg = hopk_dense_nseg(d);
     const int64_t few = (int64_t)n_jobs * B * nseg;
     const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
-    if (few > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;      // few is used only where grid is small
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
     if (grid < kMarginFew && near)
         hipLaunchKernelGGL((dense_margin_kernel<1, false>), dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream,
@@ -1386,20 +1415,30 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     return launch_status();
 }
 
+enum class GradShape { few, some, many };
+static GradShape grad_shape(int n_jobs, int64_t d, int nseg) {
+    const int64_t chunks = n_jobs * ((d + 255) / 256);
+    return chunks > kGradMany || nseg >= kGradSegs ? GradShape::many : chunks > kGradFew ? GradShape::some : GradShape::few;
+}
+
 int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss,
                     void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
-    const int64_t n_chunks = (d + 255) / 256;
+    const int nseg = hopk_dense_nseg(d);
+    const GradShape shape = grad_shape(n_jobs, d, nseg);
+    const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;
     const int64_t grid = grid_for(n_jobs, n_chunks);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    const int nseg = hopk_dense_nseg(d);
-    if (n_jobs * n_chunks <= kGradFew)
-        hipLaunchKernelGGL(dense_grad_kernel<8>, dim3((unsigned)grid), dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B,
-                           d, nseg, lambda, loss, n_chunks);
+    if (shape == GradShape::few)
+        hipLaunchKernelGGL((dense_grad_kernel<8, 1>), dim3((unsigned)grid), dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs,
+                           B, d, nseg, lambda, loss, n_chunks);
+    else if (shape == GradShape::some)
+        hipLaunchKernelGGL((dense_grad_kernel<4, 1>), dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs,
+                           B, d, nseg, lambda, loss, n_chunks);
     else
-        hipLaunchKernelGGL(dense_grad_kernel<4>, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs, B,
-                           d, nseg, lambda, loss, n_chunks);
+        hipLaunchKernelGGL((dense_grad_kernel<1, 4>), dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs,
+                           B, d, nseg, lambda, loss, n_chunks);
     return launch_status();
 }
 
@@ -1507,7 +1546,7 @@ int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambd
         const int nseg = hopk_dense_nseg(d);
         const int64_t few = (int64_t)B * nseg, grid = (int64_t)((B + kMarginRows - 1) / kMarginRows) * nseg;
         if (B > kMaxB) return (int)hipErrorInvalidValue;
-        if (few > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+        if (grid > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         if (grid < kMarginFew && (int64_t)B * d * 4 <= kMarginNear)
             hipLaunchKernelGGL((dense_margin_one<1, false>), dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
         else if (grid < kMarginFew)
@@ -1515,11 +1554,14 @@ int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambd
         else
             hipLaunchKernelGGL((dense_margin_one<kMarginRows, true>), dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, nseg);
         if (const int rc = launch_status()) return rc;
-        const int64_t n_chunks = (d + 255) / 256;
-        if (n_chunks <= kGradFew)
-            hipLaunchKernelGGL(dense_grad_one<8>, dim3((unsigned)n_chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
+        const GradShape shape = grad_shape(1, d, nseg);
+        const unsigned chunks = (unsigned)((d + 255) / 256);
+        if (shape == GradShape::few)
+            hipLaunchKernelGGL((dense_grad_one<8, 1>), dim3(chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
+        else if (shape == GradShape::some)
+            hipLaunchKernelGGL((dense_grad_one<4, 1>), dim3(chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
         else
-            hipLaunchKernelGGL(dense_grad_one<4>, dim3((unsigned)n_chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
+            hipLaunchKernelGGL((dense_grad_one<1, 4>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
         const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
         const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;

@@ -1,6 +1,7 @@
 """The dense SVM gradient where its kernels change path: column counts around a 256-column chunk, a wavefront's last lane
-and a 16384-column segment with every remainder mod 4, minibatches around the 8 rows a wavefront takes at a time, data
-sets, parameters and results at any multiple of 4 bytes when d is no multiple of four."""
+and a 16384-column segment with every remainder mod 4, minibatches around the 8 rows a wavefront takes at a time, 15, 16,
+64 and 65 partial products per row, data sets, parameters and results at any multiple of 4 bytes when d is no multiple of
+four."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +23,8 @@ def _at(host, shift):
 
 @pytest.mark.parametrize("loss", ["hinge", "log"])
 @pytest.mark.parametrize("d,B,shift", [(1, 1, 1), (2, 9, 3), (3, 64, 2), (255, 8, 1), (256, 7, 0), (257, 65, 3), (1021, 1024, 1),
-                                       (16383, 33, 2), (16385, 16, 1), (16390, 100, 0), (196612, 40, 0)])
+                                       (16383, 33, 2), (16385, 16, 1), (16390, 100, 0), (196612, 40, 0),
+                                       (245758, 9, 2), (245761, 17, 1), (524288, 8, 0), (1048577, 5, 3), (1048580, 33, 0)])
 def test_dense_gradient_at_the_edges(d, B, shift, loss):
     print("dense d=%d B=%d shift=%d %s" % (d, B, shift, loss), flush=True)
     gen = torch.Generator().manual_seed(d * 7 + B)

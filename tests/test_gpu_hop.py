@@ -496,6 +496,8 @@ def test_momentum_and_log_loss(cfgn, over):
     dict(d=4037, batch=130, rows=256, K=16),                   # minibatch not a multiple of the margin kernel's 4 rows
     dict(d=4098, rows=256, K=16, momentum=0.9),
     dict(d=4037, batch=131, rows=256, K=12, serial=True),
+    dict(d=99003, batch=9, rows=64, K=6),                      # waves of more than 2048 chunks of 256 columns
+    dict(d=99003, batch=9, rows=64, K=6, momentum=0.9, loss=1),
 ])
 def test_large_dense_minibatch_ragged_shapes(over):
     """Minibatches just above 2 MB per record take the path where the gradient kernel also reduces and applies:

@@ -893,19 +893,26 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) a[r][0] = a[r][1] = a[r][2] = a[r][3] = 0.f;
     const int64_t hi4 = hi >> 2;
-    constexpr int kAhead = ROWS == 1 ? 8 : 4;
-#pragma unroll kAhead
-    for (int64_t i = (lo >> 2) + threadIdx.x; i < hi4; i += kThreads) {
-        const float4 wv = ldu4(w, i << 2);
+    int64_t i = (lo >> 2) + threadIdx.x;
+    auto piece = [&](int64_t k) {
+        const float4 wv = ldu4(w, k << 2);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const float4 xv = STREAM ? ldu4_stream(x[r], i << 2) : ldu4(x[r], i << 2);
+            const float4 xv = STREAM ? ldu4_stream(x[r], k << 2) : ldu4(x[r], k << 2);
             a[r][0] = fmaf(xv.x, wv.x, a[r][0]);
             a[r][1] = fmaf(xv.y, wv.y, a[r][1]);
             a[r][2] = fmaf(xv.z, wv.z, a[r][2]);
             a[r][3] = fmaf(xv.w, wv.w, a[r][3]);
         }
+    };
+    if (ROWS == 1) {                                               // eight pieces in flight; what is left by fours, not singly
+        for (; i + 7 * kThreads < hi4; i += 8 * kThreads) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) piece(i + u * kThreads);
+        }
     }
+#pragma unroll 4
+    for (; i < hi4; i += kThreads) piece(i);
     if (const int64_t c = (hi4 << 2) + threadIdx.x; c < hi) {      // the d mod 4 last columns
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) a[r][0] = fmaf(x[r][c], w[c], a[r][0]);

@@ -943,15 +943,16 @@ __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict_
 
 // The margin pass as a launch of its own: four minibatch rows per workgroup share every load of w (the L2 sees
 // 5 requests per 4 row pieces instead of 8); with few workgroups (kMarginFew) one row each, so that all CUs have rows in
-// flight (one minibatch of 128 x 65536: 14.1 -> 8.9 us; 3 records of 100 x 30 011: 36 -> 14 us, scalar loads before; waves of
-// 2 to 5 records of 128 x 65536: 4 % less than with four rows).
+// flight (one minibatch of 128 x 65536: 14.1 -> 8.9 us; 3 records of 100 x 30 011: 36 -> 14 us, scalar loads before).
+// The line: 16 workers x 65536 columns, B = 128 (128 workgroups of four rows per record) 3627 us per pass with one row
+// up to 767 workgroups, 3529 up to 383; 16 x 400 000, B = 16, momentum 1587 and 1486 us.
 // Rows by non-temporal loads: a wave's rows are new to every cache, and a cold stream
 // runs faster without allocating in the memory-side cache (6.9 against 5.5 TB/s stand-alone).  Leaving
 // them there for the gradient pass with ordinary loads was measured on 16 workers x 65536 columns, B = 128, 6.6 records:
-// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained; where a launch reads no more than half of
-// that cache (kMarginNear) ordinary loads pay: 3 to 4 records of 100 x 30 011 2.20 -> 2.12 ms per pass.
+// margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained; where a launch of few workgroups reads no
+// more than half of that cache (kMarginNear) ordinary loads pay: 3 to 4 records of 100 x 30 011 2.20 -> 2.12 ms per pass.
 constexpr int kMarginRows = 4;
-constexpr int64_t kMarginFew = 768;
+constexpr int64_t kMarginFew = 384;
 constexpr int64_t kMarginNear = 128ll << 20;           // bytes of rows in a launch up to which they are left in the caches
 
 template <int ROWS, bool STREAM>

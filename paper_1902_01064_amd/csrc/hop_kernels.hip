@@ -674,37 +674,29 @@ struct SweepWords {
 struct SweepLane {
     char* lds;
     int64_t c;
-    bool exists;             // c < d
     uint32_t folded;         // fold16(c)
     float ahead;             // external gradients: that of the next record with one
 };
 __device__ __forceinline__ float& sweep_local(const SweepLane& l, uint32_t offset) { return *(float*)(l.lds + offset); }
 
-// FULL: all 64 columns exist
-template <bool FULL>
 __device__ __forceinline__ float sweep_load(const float* p, const SweepLane& l) {
-    if (FULL) return __builtin_nontemporal_load((const HOP_GLOBAL float*)p + l.c);
-    return l.exists ? p[l.c] : 0.f;
+    return __builtin_nontemporal_load((const HOP_GLOBAL float*)p + l.c);
 }
-template <bool FULL>
 __device__ __forceinline__ void sweep_store(float* p, const SweepLane& l, float v) {
-    if (FULL) __builtin_nontemporal_store(v, (HOP_GLOBAL float*)p + l.c);
-    else if (l.exists) p[l.c] = v;
+    __builtin_nontemporal_store(v, (HOP_GLOBAL float*)p + l.c);
 }
 
 // a worker's external gradient; its next record reads it again: ordinary loads
-template <bool FULL>
 __device__ __forceinline__ float sweep_external(const HopSweepArgs& a, uint32_t worker, const SweepLane& l) {
-    const float* p = a.external + (int64_t)worker * a.d;
-    return FULL ? ((const HOP_GLOBAL float*)p)[l.c] : sweep_load<false>(p, l);
+    return ((const HOP_GLOBAL float*)(a.external + (int64_t)worker * a.d))[l.c];
 }
 
-template <int MODE, bool FULL, class Words>
+template <int MODE, class Words>
 __device__ __forceinline__ float sweep_grad(const HopSweepArgs& a, const Words& h, SweepLane& l) {
     if (MODE == HOP_GRAD_SYNTH) return synth_one(l.folded, h[4], h[5], h[6], a.scale);
     if (MODE == HOP_GRAD_EXTERNAL) {
         const float g = l.ahead;
-        l.ahead = sweep_external<FULL>(a, h[5], l);
+        l.ahead = sweep_external(a, h[5], l);
         return g;
     }
     return 0.f;
@@ -728,10 +720,10 @@ __device__ __forceinline__ float sweep_first(uint32_t w, float x) {
 }
 
 // the result of a record to where it is read from or stays
-template <bool FULL, class Words>
+template <class Words>
 __device__ __forceinline__ void sweep_put(const HopSweepArgs& a, const Words& h, const SweepLane& l, float acc) {
     if (h[0] & kSweepKeep) sweep_local(l, h[1]) = acc;
-    if (h[0] & kSweepStore) sweep_store<FULL>(a.ring + (int64_t)h[2] * a.stride, l, acc);
+    if (h[0] & kSweepStore) sweep_store(a.ring + (int64_t)h[2] * a.stride, l, acc);
 }
 
 // One record with A sources, while the words of the next are loaded; KEPT: the result goes to a local slot and nowhere
@@ -745,7 +737,7 @@ __device__ __forceinline__ void sweep_record(const HopSweepArgs& a, const SweepW
 #pragma unroll
     for (int t = 0; t < A; ++t) x[t] = sweep_local(l, h[kSweepHead + 2 * t]);
     __builtin_amdgcn_sched_barrier(0);
-    if (GRAD) g = sweep_grad<MODE, true>(a, h, l);
+    if (GRAD) g = sweep_grad<MODE>(a, h, l);
     if (GRAD && MODE == HOP_GRAD_SYNTH) asm volatile("" : "+v"(g));        // computed here, not where it is used
     __builtin_amdgcn_sched_barrier(0);
     float acc = sweep_first<MOM>(h[kSweepHead + 1], x[0]);
@@ -754,7 +746,7 @@ __device__ __forceinline__ void sweep_record(const HopSweepArgs& a, const SweepW
     if (GRAD) acc = sweep_apply<MOM>(a, h, l, g, acc);
     next.hold();                                           // else the compiler loads them where they are first needed
     if (KEPT) sweep_local(l, h[1]) = acc;
-    else sweep_put<true>(a, h, l, acc);
+    else sweep_put(a, h, l, acc);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -776,7 +768,7 @@ __device__ __forceinline__ sweep_words sweep_run(const HopSweepArgs& a, sweep_wo
 }
 
 // a run of any records
-template <int MODE, bool MOM, bool FULL>
+template <int MODE, bool MOM>
 __device__ sweep_words sweep_run_any(const HopSweepArgs& a, sweep_words rec, uint32_t count, SweepLane& l) {
     do {
         SweepWords<kSweepHead> h;
@@ -785,35 +777,34 @@ __device__ sweep_words sweep_run_any(const HopSweepArgs& a, sweep_words rec, uin
         float acc = sweep_first<MOM>(term[1], sweep_local(l, term[0]));
         for (uint32_t t = 1; t < h[7]; ++t) acc = fmaf(__uint_as_float(term[2 * t + 1]), sweep_local(l, term[2 * t]), acc);
         if (MODE != HOP_GRAD_ZERO && (h[0] & kSweepGrad))
-            acc = sweep_apply<MOM>(a, h, l, sweep_grad<MODE, FULL>(a, h, l), acc);
-        sweep_put<FULL>(a, h, l, acc);
+            acc = sweep_apply<MOM>(a, h, l, sweep_grad<MODE>(a, h, l), acc);
+        sweep_put(a, h, l, acc);
         rec += hop_sweep_words((int)h[7]);
     } while (--count);
     return rec;
 }
 
 // `n` vectors (rows of `base`) into their local slots, eight loads in flight
-template <bool FULL>
 __device__ __forceinline__ void sweep_fill(const uint32_t* __restrict__ list, int n, const float* base, int64_t stride,
                                            const SweepLane& l) {
     for (int k = 0; k < n; k += 8) {
         float t[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-            if (k + q < n) t[q] = sweep_load<FULL>(base + (int64_t)list[2 * (k + q)] * stride, l);
+            if (k + q < n) t[q] = sweep_load(base + (int64_t)list[2 * (k + q)] * stride, l);
 #pragma unroll
         for (int q = 0; q < 8; ++q)
             if (k + q < n) sweep_local(l, list[2 * (k + q) + 1]) = t[q];
     }
 }
 
-template <int MODE, bool MOM, bool FULL>
+template <int MODE, bool MOM>
 __device__ __forceinline__ void sweep_columns(const HopSweepArgs& a, SweepLane& l) {
     const uint32_t* lists = a.program + a.first_load;
-    sweep_fill<FULL>(lists, a.n_loads, a.ring, a.stride, l);
+    sweep_fill(lists, a.n_loads, a.ring, a.stride, l);
     lists += 2 * a.n_loads;
-    if (MOM) sweep_fill<FULL>(lists, a.n_vel, a.vel, a.stride, l);
-    if (MODE == HOP_GRAD_EXTERNAL) l.ahead = sweep_external<FULL>(a, (uint32_t)a.first_external, l);
+    if (MOM) sweep_fill(lists, a.n_vel, a.vel, a.stride, l);
+    if (MODE == HOP_GRAD_EXTERNAL) l.ahead = sweep_external(a, (uint32_t)a.first_external, l);
     if (a.zero >= 0) sweep_local(l, (uint32_t)a.zero) = 0.f;            // the missing source of an odd record
     const sweep_words runs = (sweep_words)a.program;
     sweep_words rec = runs + a.first_record;
@@ -828,34 +819,32 @@ __device__ __forceinline__ void sweep_columns(const HopSweepArgs& a, SweepLane& 
 #define HOP_SWEEP_GRAD(AA)                                                                     \
     case AA + 16: rec = sweep_run<AA, true, true, MODE, MOM>(a, rec, count, l); continue;      \
     case AA + 48: rec = sweep_run<AA, true, false, MODE, MOM>(a, rec, count, l); continue;
-        if (FULL) {                                        // the wavefront at the end of the vectors takes the plain way
-            switch (run & 0xFFu) {
-                HOP_SWEEP_CASE(1) HOP_SWEEP_CASE(2) HOP_SWEEP_CASE(3) HOP_SWEEP_CASE(4) HOP_SWEEP_CASE(5) HOP_SWEEP_CASE(6)
-                HOP_SWEEP_CASE(7) HOP_SWEEP_CASE(8) HOP_SWEEP_CASE(9) HOP_SWEEP_CASE(10) HOP_SWEEP_CASE(11) HOP_SWEEP_CASE(12)
-                default: break;
-            }
-            if (MODE != HOP_GRAD_ZERO) switch (run & 0xFFu) {
-                HOP_SWEEP_GRAD(1) HOP_SWEEP_GRAD(2) HOP_SWEEP_GRAD(3) HOP_SWEEP_GRAD(4) HOP_SWEEP_GRAD(5) HOP_SWEEP_GRAD(6)
-                HOP_SWEEP_GRAD(7) HOP_SWEEP_GRAD(8) HOP_SWEEP_GRAD(9) HOP_SWEEP_GRAD(10) HOP_SWEEP_GRAD(11) HOP_SWEEP_GRAD(12)
-                default: break;
-            }
+        switch (run & 0xFFu) {
+            HOP_SWEEP_CASE(1) HOP_SWEEP_CASE(2) HOP_SWEEP_CASE(3) HOP_SWEEP_CASE(4) HOP_SWEEP_CASE(5) HOP_SWEEP_CASE(6)
+            HOP_SWEEP_CASE(7) HOP_SWEEP_CASE(8) HOP_SWEEP_CASE(9) HOP_SWEEP_CASE(10) HOP_SWEEP_CASE(11) HOP_SWEEP_CASE(12)
+            default: break;
         }
-        rec = sweep_run_any<MODE, MOM, FULL>(a, rec, count, l);
+        if (MODE != HOP_GRAD_ZERO) switch (run & 0xFFu) {
+            HOP_SWEEP_GRAD(1) HOP_SWEEP_GRAD(2) HOP_SWEEP_GRAD(3) HOP_SWEEP_GRAD(4) HOP_SWEEP_GRAD(5) HOP_SWEEP_GRAD(6)
+            HOP_SWEEP_GRAD(7) HOP_SWEEP_GRAD(8) HOP_SWEEP_GRAD(9) HOP_SWEEP_GRAD(10) HOP_SWEEP_GRAD(11) HOP_SWEEP_GRAD(12)
+            default: break;
+        }
+        rec = sweep_run_any<MODE, MOM>(a, rec, count, l);
 #undef HOP_SWEEP_CASE
 #undef HOP_SWEEP_GRAD
     }
     if (MOM)
         for (int n = 0; n < a.n_vel; ++n)
-            sweep_store<FULL>(a.vel + (int64_t)lists[2 * n] * a.stride, l, sweep_local(l, lists[2 * n + 1]));
+            sweep_store(a.vel + (int64_t)lists[2 * n] * a.stride, l, sweep_local(l, lists[2 * n + 1]));
 }
 
 template <int MODE, bool MOM>
 __global__ __launch_bounds__(64) void sweep_kernel(const HopSweepArgs a) {
     extern __shared__ float sweep_lds[];
-    const int64_t first = (int64_t)blockIdx.x * 64, c = first + threadIdx.x;
-    SweepLane l{(char*)(sweep_lds + threadIdx.x), c, c < a.d, fold16((uint32_t)c), 0.f};
-    if (first + 64 <= a.d) sweep_columns<MODE, MOM, true>(a, l);
-    else sweep_columns<MODE, MOM, false>(a, l);
+    const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (c >= a.d) return;                              // the wavefront at the end of the vectors: fewer lanes, the same way
+    SweepLane l{(char*)(sweep_lds + threadIdx.x), c, fold16((uint32_t)c), 0.f};
+    sweep_columns<MODE, MOM>(a, l);
 }
 
 // ------------------------------------------------------------------ wavefront reductions ----

@@ -65,6 +65,12 @@ enum {
     HOP_DELAY_BERNOULLI6 = 2,     /* 6 units with probability 1/N, else 1 (Section 7.3.1)     */
     HOP_DELAY_TABLE = 3           /* ticks given per (worker, iteration)                      */
 };
+/* How an unprofiled hop_step over a whole schedule is launched, see hop_pass_path. */
+enum {
+    HOP_PASS_WAVES = 0,           /* kernel by kernel, wave by wave                           */
+    HOP_PASS_GRAPH = 1,           /* the same launches replayed as one HIP graph              */
+    HOP_PASS_ONE_LAUNCH = 2       /* one kernel, column by column                             */
+};
 #define HOP_TICKS_NEVER (1ull << 62)   /* a duration at or above this never completes */
 
 enum {
@@ -264,8 +270,8 @@ int hop_schedule_bind(hop_ctx* ctx, hop_schedule* s, void* workspace, size_t byt
  * and the Reduce launch only holds the records without a gradient; synthetic gradients of up to
  * hop_opts.grad_ahead consecutive waves are generated in front of the first of them.  A call that covers the
  * whole schedule (wave_begin 0, wave_end -1 or n_waves) and is not being profiled runs as ONE launch when
- * gradients are absent, synthetic or external and the schedule suits it (not too many workers, nor many
- * records per wave on a narrow model): every column then goes through all records by itself, no gradient is
+ * gradients are absent, synthetic or external and an estimate of both ways has it ahead (it is not with very
+ * many workers, nor with many or wide records per wave on a narrow model): every column then goes through all records by itself, no gradient is
  * written to memory, and the results are those of the waves bit for bit.  The results are the same in every
  * arrangement up to the rounding of the sums.  The first call for a schedule (and the first after the gradient
  * source or a data set changed) copies the descriptors into the schedule's workspace with synchronous
@@ -283,6 +289,10 @@ int hop_step(hop_ctx* ctx, const hop_schedule* s, int32_t wave_begin, int32_t wa
  * ranges and profiled passes always run kernel by kernel.  Off by default; without effect where a whole
  * pass is a single launch anyway (see hop_step). */
 int hop_use_graph(hop_ctx* ctx, int enable);
+
+/* Which way hop_step takes for the whole schedule (HOP_PASS_*) with the current gradient source and data; HOP_ERR_STATE
+ * before the first hop_step of the schedule with them, which is where that is decided. */
+int hop_pass_path(hop_ctx* ctx, const hop_schedule* s, int32_t* path);
 
 /* Newest parameter vector of a worker (device, d floats) and its iteration number. */
 int hop_params(hop_ctx* ctx, int32_t worker, const float** dev_ptr, int32_t* iter);

@@ -326,6 +326,83 @@ float* slot_ptr(const hop_ctx* c, int worker, int slot) {
     return c->ring + ((int64_t)worker * c->slots + slot) * c->stride;
 }
 
+// A pass in microseconds as one sweep and wave by wave, to choose between the two.  Fitted to 5082 passes on MI355X: rings,
+// tori, rings with chords and complete graphs of 4 to 100 workers, 64 to 4 M columns, each gradient, with and without a
+// velocity, in lock-step, with Exp(1) delays and with a straggler.  Of the 4010 that these estimates give to the sweep 13
+// were more than 4 % faster in waves; of those they refuse it 61 would have been faster in it, by 9 % at the median.
+struct SweepCost {
+    int64_t d = 0;
+    int waves = 0, records = 0, gradients = 0, mode = 0;
+    bool vel = false;                    // the context has velocities
+    int wide = 0;                        // records with more sources than the sweep unrolls
+    double terms = 0, wide_terms = 0;    // sources of the other records and of these
+    double wide_chain = 0;               // over the waves: the most sources a wide record of the wave has
+    double bytes = 0;                    // that reach the CUs wave by wave
+    double distinct = 0;                 // over the waves: vectors read, each once per wave
+    double ring_bytes = 0;
+
+    // A wavefront takes its records one after the other: 0.16 us each with five sources, 68 ns per source where they are
+    // not unrolled, 0.13 us where a run of another kind begins.  The columns run side by side until LDS is full of local
+    // slots; beyond that they take turns, and loads of gradients on the way are no longer hidden.
+    double sweep_us(int n_local, int n_runs) const {
+        const double at_a_time = 256.0 * std::min(32, 160 * 1024 / (n_local * 256));
+        const double turns = std::max(1.0, std::ceil((double)((d + 63) / 64) / at_a_time));
+        double us = 0.12 * (records - wide) + 0.0075 * terms + 0.068 * wide_terms + 0.13 * n_runs;
+        if (vel) us += 0.02 * gradients;
+        if (mode == HOP_GRAD_EXTERNAL && turns > 1) us += 0.1 * gradients;
+        return 2.5 + us * turns;
+    }
+
+    // Launches (one per wave, two with synthetic gradients) that partly hide behind what they move: every source to the
+    // CUs, every distinct vector from where the rings are.  A wide record reads one source after the other, 0.13 us for
+    // each 1024 of up to 4096 columns.
+    double waves_us() const {
+        const bool mostly_wide = 2 * wide > records, cached = ring_bytes < 30e6 && !mostly_wide, moved = vel && gradients > 0;
+        const double sources = terms + wide_terms, mean = std::min(sources / records, 8.0);
+        double launch = waves * (vel ? 2.9 : 2.1 + 0.31 * mean);
+        if (d >= 4096) launch += records * (moved ? 0.062 : 0.012);
+        if (d >= 16384 && !vel) launch += 1.3 * waves;
+        const double chain = 0.13 * (double)std::min<int64_t>(4, (d + 1023) / 1024) * wide_chain;
+        double rate = moved ? 9.3e6 : vel ? 13e6 : 12e6 + 0.54e6 * mean;
+        if (cached) rate *= 2;
+        if (mostly_wide && ring_bytes > 450e6) rate *= 0.73;
+        const double from = cached ? 20e6 : mostly_wide && ring_bytes > 95e6 ? 1.8e6 : 7e6;
+        const double own = bytes - 4.0 * d * sources;
+        const double move = std::max(chain, std::max(bytes / rate, (4.0 * d * distinct + own) / from));
+        const double us = std::max(launch + 0.72 * move, move + 0.72 * launch);
+        return mode == HOP_GRAD_SYNTH ? us + 2.4 * waves + 4.0 * d * gradients / 8e6 : us;
+    }
+};
+
+SweepCost sweep_cost(const hop_ctx* c, const hop_schedule* s, const std::vector<HopMixJob>& mix) {
+    SweepCost k;
+    k.d = c->d;
+    k.waves = s->n_waves;
+    k.records = (int)s->kind.size();
+    k.mode = c->grad_mode;
+    k.vel = c->vel != nullptr;
+    k.ring_bytes = 4.0 * (double)c->N * c->slots * c->d;
+    std::vector<const float*> seen;
+    for (int w = 0; w < s->n_waves; ++w) {
+        int widest = 0;
+        seen.clear();
+        for (int p = s->wave_begin[w]; p < s->wave_begin[w + 1]; ++p) {
+            const HopMixJob& j = mix[p];
+            const bool wide = j.A > kSweepInline;
+            k.gradients += j.g != nullptr;
+            k.wide += wide;
+            (wide ? k.wide_terms : k.terms) += j.A;
+            if (wide) widest = std::max(widest, j.A);
+            seen.insert(seen.end(), j.src, j.src + j.A);
+        }
+        std::sort(seen.begin(), seen.end());
+        k.distinct += (double)(std::unique(seen.begin(), seen.end()) - seen.begin());
+        k.wide_chain += widest;
+        k.bytes += s->wave_mix_bytes[w];
+    }
+    return k;
+}
+
 // The whole pass as one program, where no gradient needs a sum over the columns.  Sums are taken in the order in which
 // the wave-by-wave kernels take them (that of the union of a pair), so both ways give the same bits.  The program goes
 // into the part of the workspace that this kind of context leaves unused: the record-by-record Reduce descriptors, or
@@ -335,21 +412,11 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     const int mode = c->grad_mode;
     if (!hopk_sweep || (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL)) return HOP_OK;
     const int R = (int)mix.size();
-    // The more local slots, the fewer wavefronts per CU there are to hide each other's latency: 2 M columns and 64, 81
-    // and 100 workers in lock-step (80, 99 and 120 slots) take, wave by wave against sweep, 1.5, 1.1 and 0.94 times as
-    // long without a gradient, 1.05, 0.74 and 0.64 with external ones (loads on the way), 2.5, 2 and 1.6 with synthetic
-    // ones (arithmetic on the way).
-    const int most_local = mode == HOP_GRAD_SYNTH ? kSweepMaxLocal : mode == HOP_GRAD_ZERO ? 112 : 84;
-    // Narrow models leave most of the GPU idle in a sweep, whose records then follow each other at 0.14 us; a wave of
-    // its own takes 3.5 to 5 us (two launches with synthetic gradients: 6 to 9), whatever its records.  1024 columns in
-    // lock-step, wave by wave against sweep: 16 records per wave 2 to 3 times, 32 records 0.84 (synthetic 1.3), 64
-    // records 0.5 (0.86).  From 65536 columns on the sweep is ahead in every case above.
-    const int most_per_wave = mode == HOP_GRAD_SYNTH ? 40 : 24;
-    // (with over 112 slots - 64 workers with velocities, 54 000 columns, 21 records per wave - 641 us against 622)
-    const bool narrow = c->d < 65536;
-    const int limit = narrow ? std::min(most_local, 112) : most_local;
-    // a slot per worker and one per velocity are needed in any case
-    if ((narrow && R > most_per_wave * s->n_waves) || c->N * (c->vel ? 2 : 1) > limit) return HOP_OK;
+    // the cheapest that a sweep can be: a local slot per worker (and velocity), one run
+    const SweepCost cost = sweep_cost(c, s, mix);
+    const double waves_us = cost.waves_us();
+    const bool vel_slots = c->vel && mode != HOP_GRAD_ZERO;
+    if (c->N * (vel_slots ? 2 : 1) > kSweepMaxLocal || cost.sweep_us(c->N * (vel_slots ? 2 : 1), 1) > waves_us) return HOP_OK;
     auto slot_of = [c](const float* p) { return (int)((p - c->ring) / c->stride); };
     std::vector<HopSweepOp> ops((size_t)R);
     std::vector<int> at((size_t)c->N * c->slots, -1);            // position of the record that writes a slot, this wave
@@ -385,7 +452,7 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
         }
     }
     HopSweepPlan plan;
-    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan) || plan.n_local > limit) return HOP_OK;
+    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan) || cost.sweep_us(plan.n_local, plan.n_runs) > waves_us) return HOP_OK;
     const size_t bytes = plan.program.size() * sizeof(uint32_t);
     if (bytes > room_bytes) return HOP_OK;
     HOP_HIP(c, hipMemcpy(room, plan.program.data(), bytes, hipMemcpyHostToDevice));
@@ -1135,6 +1202,15 @@ int hop_use_graph(hop_ctx* c, int enable) {
     if (!c) return HOP_ERR_INVALID_ARG;
     if (!c->has_device) return HOP_ERR_NO_DEVICE;
     c->use_graph = enable != 0;
+    return HOP_OK;
+}
+
+int hop_pass_path(hop_ctx* c, const hop_schedule* s, int32_t* path) {
+    if (!c || !s || !path) return HOP_ERR_INVALID_ARG;
+    if (!c->has_device) return HOP_ERR_NO_DEVICE;
+    if (s->owner != c) return HOP_ERR_INVALID_ARG;
+    if (s->built_mode != c->grad_mode || s->built_epoch != c->epoch) return HOP_ERR_STATE;
+    *path = s->sweep.program ? HOP_PASS_ONE_LAUNCH : c->use_graph && s->n_waves > 0 ? HOP_PASS_GRAPH : HOP_PASS_WAVES;
     return HOP_OK;
 }
 

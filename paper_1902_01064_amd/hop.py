@@ -19,6 +19,7 @@ HOP_GRAD_ZERO, HOP_GRAD_SVM_DENSE, HOP_GRAD_SVM_CSR, HOP_GRAD_SYNTH, HOP_GRAD_EX
 HOP_STEP, HOP_JUMP, HOP_APPLY, HOP_REDUCE = 0, 1, 2, 3
 HOP_KERNEL_MIX, HOP_KERNEL_GRAD, HOP_KERNEL_SYNTH = 0, 1, 2
 HOP_LOSS_HINGE, HOP_LOSS_LOG = 0, 1
+HOP_PASS_WAVES, HOP_PASS_GRAPH, HOP_PASS_ONE_LAUNCH = 0, 1, 2
 HOP_TICKS_NEVER = 1 << 62
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libhop.so")
@@ -30,7 +31,7 @@ EXPORTS = [
     "hop_params", "hop_slot", "hop_coef", "hop_profile", "hop_profile_read", "hop_mix",
     "hop_grad_scratch_floats", "hop_svm_grad_dense", "hop_svm_grad_csr", "hop_synth_grad", "hop_copy",
     "hop_download", "hop_use_graph", "hop_schedule_bytes", "hop_schedule_bind",
-    "hop_svm_grad_dense_static",
+    "hop_svm_grad_dense_static", "hop_pass_path",
 ]
 
 
@@ -119,6 +120,7 @@ def load():
         "hop_schedule_bytes": (C.c_size_t, [vp]),
         "hop_schedule_bind": (C.c_int, [vp, vp, vp, C.c_size_t]),
         "hop_step": (C.c_int, [vp, vp, i32, i32]),
+        "hop_pass_path": (C.c_int, [vp, vp, C.POINTER(i32)]),
         "hop_params": (C.c_int, [vp, i32, C.POINTER(vp), C.POINTER(i32)]),
         "hop_slot": (C.c_int, [vp, i32, i32, C.POINTER(vp)]),
         "hop_coef": (C.c_int, [vp, vp, i32, C.POINTER(vp)]),
@@ -323,6 +325,12 @@ def hop_coef(ctx, sched, record):
 
 def hop_use_graph(ctx, enable):
     _check(load().hop_use_graph(ctx, int(enable)), "hop_use_graph")
+
+
+def hop_pass_path(ctx, sched):
+    path = C.c_int32()
+    _check(load().hop_pass_path(ctx, sched.handle, C.byref(path)), "hop_pass_path")
+    return path.value
 
 
 def hop_profile(ctx, enable):

@@ -274,6 +274,9 @@ int main() {
         int32_t it = 0;
         EXPECT(hop_params(c, 0, &p, &it) == HOP_ERR_NO_DEVICE && hop_params(c, -1, &p, &it) == HOP_ERR_INVALID_ARG);
         EXPECT(hop_use_graph(c, 1) == HOP_ERR_NO_DEVICE && hop_profile(c, 1) == HOP_ERR_NO_DEVICE);
+        int32_t path = -1;
+        EXPECT(hop_pass_path(c, s1, &path) == HOP_ERR_NO_DEVICE && hop_pass_path(c, nullptr, &path) == HOP_ERR_INVALID_ARG &&
+               hop_pass_path(c, s1, nullptr) == HOP_ERR_INVALID_ARG && path == -1);
         if (n >= 2) {                                   // a frozen worker: the stall is reported, the schedule returned
             std::vector<uint64_t> table((size_t)n * 5, 1u << 20);
             for (int k = 0; k < 5; ++k) table[k] = HOP_TICKS_NEVER;

@@ -196,6 +196,8 @@ def run_parity(c, per_wave_check=True, strict=False, strict_run_tol=None):
         # ---- the run as a whole: both sides from p0, the oracle in sequence order ----
         sess.step()
         sess.sync()
+        if "pass_path" in c:
+            assert hop.hop_pass_path(sess.ctx, sched) == c["pass_path"]
         gpu_active = read_active(sess, sched, recs) if has_hinge else {}
         rings = arith.init_rings(p0.numpy(), N, h.slots, serial)
         grad = FollowKernelAtTies(base, gpu_active, scale_of) if has_hinge else base
@@ -359,15 +361,26 @@ def test_cfg4_full_size_sampled_columns():
         sess.close()
 
 
+def lock_step_81(**over):
+    """Synthetic gradients on a narrow model with 81 records in every wave: a whole pass stays with the waves (generator
+    launches, then Reduce + Apply), it does not run as one launch."""
+    nb = inputs.torus(9, 9)
+    return dict(dict(d=1500, K=10), in_nbrs=nb, W=inputs.uniform_weights(nb), N=81, s=2, b=0, skip_on=False, mult=None,
+                delay_kind=hop.HOP_DELAY_NONE, **over)
+
+
 @pytest.mark.parametrize("cfgn,over,exact", [(1, dict(), True), (4, dict(d=(1 << 14) + 8, K=40), True),
                                             (3, dict(d=1 << 13, rows=512, K=25), False),
-                                            (2, dict(d=8192 + 4, rows=512, K=30), True)])
+                                            (2, dict(d=8192 + 4, rows=512, K=30), True),
+                                            (4, lock_step_81(), True), (4, lock_step_81(grad_ahead=3), True),
+                                            (4, lock_step_81(momentum=0.9), True)])
 def test_graph_replay_equals_kernel_by_kernel(cfgn, over, exact):
     """hop_use_graph: the recorded graph is replayed several times, with other GPU work and
     synchronisations in between, and every replay must leave the rings exactly as the same pass run
     kernel by kernel does (CSR scatters use atomics, so there to rounding).  The fourth case has dense
-    minibatches of 4 MB per record, which take the two-launch margin + gradient path."""
-    c = inputs.config(cfgn, **over)
+    minibatches of 4 MB per record, which take the two-launch margin + gradient path.  The last three capture generator
+    launches (16 waves ahead, 3, and with velocities); the second is one launch either way."""
+    c = dict(inputs.config(cfgn), **over)
     p0, data = make_data(c)
     snaps = {}
     for mode in ("eager", "graph"):
@@ -380,6 +393,9 @@ def test_graph_replay_equals_kernel_by_kernel(cfgn, over, exact):
             for rep in range(4):
                 sess.step()
                 sess.sync()
+                assert hop.hop_pass_path(sess.ctx, sess.sched) == (
+                    hop.HOP_PASS_ONE_LAUNCH if cfgn == 4 and "in_nbrs" not in over else
+                    hop.HOP_PASS_GRAPH if mode == "graph" else hop.HOP_PASS_WAVES)
                 snaps[mode].append(sess.ring_snapshot())
                 junk = torch.randn(1 << 16, device=sess.dev)          # unrelated eager work between replays
                 junk = (junk * 2).sum()
@@ -510,8 +526,10 @@ def test_large_dense_minibatch_ragged_shapes(over):
 @pytest.mark.parametrize("ahead", [1, 3, 8])
 def test_gradients_generated_several_waves_ahead(ahead):
     """hop_opts.grad_ahead: one generator launch for that many waves, a rotating set of gradient buffers per worker.
-    Same records, same values (the per-wave part of run_parity also starts passes in the middle of a group)."""
+    Same records, same values (the per-wave part of run_parity also starts passes in the middle of a group; the second
+    schedule keeps its waves when it runs as a whole)."""
     run_parity(inputs.config(4, d=(1 << 13) + 12, K=30, grad_ahead=ahead), strict=True)
+    run_parity(dict(inputs.config(4), grad_ahead=ahead, pass_path=hop.HOP_PASS_WAVES, **lock_step_81()), strict=True)
 
 
 def test_data_set_swapped_after_simulate_is_refused():

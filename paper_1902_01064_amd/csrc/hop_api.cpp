@@ -410,7 +410,7 @@ SweepCost sweep_cost(const hop_ctx* c, const hop_schedule* s, const std::vector<
 int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, const std::vector<HopPairJob>& pairs,
                 char* room, size_t room_bytes) {
     const int mode = c->grad_mode;
-    if (!hopk_sweep || (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL)) return HOP_OK;
+    if (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL) return HOP_OK;
     const int R = (int)mix.size();
     // the cheapest that a sweep can be: a local slot per worker (and velocity), one run
     const SweepCost cost = sweep_cost(c, s, mix);
@@ -452,7 +452,8 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
         }
     }
     HopSweepPlan plan;
-    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan) || cost.sweep_us(plan.n_local, plan.n_runs) > waves_us) return HOP_OK;
+    if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan)) return HOP_OK;
+    if (cost.sweep_us(plan.n_local, plan.n_runs) > waves_us) return HOP_OK;
     const size_t bytes = plan.program.size() * sizeof(uint32_t);
     if (bytes > room_bytes) return HOP_OK;
     HOP_HIP(c, hipMemcpy(room, plan.program.data(), bytes, hipMemcpyHostToDevice));

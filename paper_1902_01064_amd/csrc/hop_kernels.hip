@@ -530,10 +530,11 @@ __global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, in
 // 7 records of 2^24 columns: no difference.
 // Plain launches that fit one turn stay (64 records in 32 pairs, 32768 columns: 6.9 us per wave against 7.5 with 2).
 constexpr int64_t kPairShort = 8192, kPairTurn = 512;  // workgroups of 16 KB chunks
+constexpr int kPairPlain = 2, kPairMargin = 1;         // the short width alone, and with margins beside
 inline int pair_vec(int n_jobs, int64_t d, bool margins) {
     const int64_t blocks = n_jobs * ((d + 4095) / 4096);
     if (blocks >= kPairShort) return 4;
-    return margins ? 1 : blocks <= kPairTurn ? 4 : 2;
+    return margins ? kPairMargin : blocks <= kPairTurn ? 4 : kPairPlain;
 }
 
 inline int64_t pair_chunks(int64_t d, int vec) {
@@ -1001,7 +1002,7 @@ constexpr int kRowUnroll = 8;
 // 64 x 65536, B = 128, 13 records a wave: 3973 / 3813 us; the other way round 64 x 16384, B = 128: 1461 / 1543 us.
 constexpr int64_t kGradFew = 768;                      // chunks of 256 columns up to which a launch takes 8 wavefronts for each
 constexpr int64_t kGradMany = 2048;                    // over that many, or
-constexpr int kGradSegs = 16;                          // from that many partial products per row on: 1024 columns, rows not split
+constexpr int kGradSegs = 16;                          // from that many partial products per row on: 1024 columns, rows whole
 // From 65 partial products per row on a wavefront sums them up, not a thread: 4 M columns, B = 1 and 128: 54 -> 20,
 // 962 -> 842 us; 2^24 columns, B = 1 and 64: 635 -> 89 us, 3.2 -> 1.95 ms (2^20 columns, 64 of them, B = 8 and 128:
 // 20.5 -> 17.3, 211 -> 216).
@@ -1340,11 +1341,11 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float4* __restrict__ dst
         if (i < n16) dst[i] = src[i];
 }
 
-#define HOP_PAIR_LAUNCH(KERNEL, ...)                                   \
-    do {                                                               \
-        if (vec == 4) hipLaunchKernelGGL(KERNEL<4>, __VA_ARGS__);      \
-        else if (vec == 2) hipLaunchKernelGGL(KERNEL<2>, __VA_ARGS__); \
-        else hipLaunchKernelGGL(KERNEL<1>, __VA_ARGS__);               \
+// the widths that pair_vec chooses from: 4, or SHORT
+#define HOP_PAIR_LAUNCH(KERNEL, SHORT, ...)                              \
+    do {                                                                 \
+        if (vec == 4) hipLaunchKernelGGL(KERNEL<4>, __VA_ARGS__);        \
+        else hipLaunchKernelGGL(KERNEL<SHORT>, __VA_ARGS__);             \
     } while (0)
 
 inline int launch_status() { return (int)hipGetLastError(); }
@@ -1485,8 +1486,8 @@ int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse
     const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_jobs, n_chunks, run);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_mix_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs, d,
-                       n_chunks, run, reverse);
+    HOP_PAIR_LAUNCH(pair_mix_kernel, kPairPlain, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs,
+                    d, n_chunks, run, reverse);
     return launch_status();
 }
 
@@ -1501,9 +1502,9 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
     const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
     const int64_t margin_blocks = (int64_t)n_grad * per;
     if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                       (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, per, loss,
-                       (int)margin_blocks);
+    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, kPairMargin, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
+                    (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, per, loss,
+                    (int)margin_blocks);
     return launch_status();
 }
 
@@ -1518,8 +1519,8 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
     const int nseg = hopk_dense_nseg(d);
     const int64_t margin_blocks = (int64_t)n_grad * B * nseg;
     if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                       (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, nseg, margin_blocks);
+    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, kPairMargin, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
+                    (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, nseg, margin_blocks);
     return launch_status();
 }
 
@@ -1594,8 +1595,8 @@ int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d,
     const int run = pair_run(n_sources, n_chunks, vec);
     const int64_t grid = pair_grid(n_jobs, n_chunks, run);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_mix_args_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args, n_jobs, d,
-                       n_chunks, run);
+    HOP_PAIR_LAUNCH(pair_mix_args_kernel, kPairPlain, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args,
+                    n_jobs, d, n_chunks, run);
     return launch_status();
 }
 

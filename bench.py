@@ -124,6 +124,17 @@ def wave_compulsory_bytes(sched, d, mode, momentum):
     return out
 
 
+def pass_compulsory_bytes(sched, d, momentum):
+    """HBM bytes a whole pass cannot avoid where no gradient is read: every vector whose content from before the pass is
+    read, once, every slot written, once, with momentum a velocity read and written per worker."""
+    written, read = set(), set()
+    for e in sched.wave_order.tolist():
+        a0, a1 = int(sched.src_begin[e]), int(sched.src_begin[e + 1])
+        read.update(v for v in zip(sched.src_worker[a0:a1].tolist(), sched.src_slot[a0:a1].tolist()) if v not in written)
+        written.add((int(sched.worker[e]), int(sched.out_slot[e])))
+    return 4.0 * d * (len(read) + len(written) + (2 * int(sched.n_workers) if momentum else 0))
+
+
 def run_config(cfgn, steps, warmup, graph, over=None, external=False):
     """Sets one workload up on cuda:0, times `steps` passes, returns (result dict, config, p0).
     external: gradients from a buffer the caller filled once (config 4 only), so no generator kernel runs."""
@@ -177,6 +188,8 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
         syn_ms, syn_n, syn_bytes = hop.hop_profile_read(sess.ctx, hop.HOP_KERNEL_SYNTH)
         hop.hop_profile(sess.ctx, 0)
         elapsed = t1 - t0
+        way = {hop.HOP_PASS_ONE_LAUNCH: "one launch per pass (sweep_kernel)", hop.HOP_PASS_GRAPH: "hip graph replay",
+               hop.HOP_PASS_WAVES: "kernel by kernel"}[hop.hop_pass_path(sess.ctx, sched)]
 
         def rate(b, ms):
             return b / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
@@ -191,8 +204,7 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
                 "records_per_wave": float(len(A)) / max(int(sched.n_waves), 1),
                 "simulated_makespan_units": float(max(sched.finish_time)) / float(1 << 20),
                 "step_definition": "one pass of hop_step over the whole schedule",
-                "launch": ("one launch per pass (sweep_kernel) where no gradient couples the columns"
-                           if c["model"] == "synth" or external else "hip graph replay" if graph else "kernel by kernel"),
+                "launch": way,
             },
             "mix": {"ms": mix_ms, "launches": int(mix_n), "bytes": mix_bytes, "GBps": rate(mix_bytes, mix_ms),
                     "compulsory_bytes_per_pass": float(compulsory.sum()),
@@ -200,6 +212,12 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
             "grad": {"ms": grad_ms, "launches": int(grad_n), "GBps": rate(grad_bytes, grad_ms)},
             "synth": {"ms": syn_ms, "launches": int(syn_n), "GBps": rate(syn_bytes, syn_ms)},
         }
+        if "sweep_kernel" in way and not external:
+            need = pass_compulsory_bytes(sched, c["d"], c.get("momentum", 0.0) > 0)
+            res["timed_kernel"] = {
+                "kernel": "sweep_kernel", "bound": "instruction issue", "launches_per_pass": 1,
+                "compulsory_bytes": need, "hbm_GBps": rate(need, res["ms_per_step"]),
+                "records_per_us": len(A) / (res["ms_per_step"] * 1e3)}
         return res, c, p0
     finally:
         sess.close()
@@ -286,13 +304,16 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": res["config"],
-        # The Reduce + Apply of one wave as a launch of its own, from the extra wave-by-wave passes of this run (the timed
-        # passes run all waves in one launch, which reads and writes a ring slot once per pass).
+        # The Reduce + Apply of one wave as a launch of its own, from the extra wave-by-wave passes of this run.  Where the
+        # timed passes are one launch each ("timed_kernel"), which reads and writes a ring slot once per pass, these
+        # launches are no part of the timed region.
         # HBM side: the bytes a launch cannot avoid (every distinct source of the wave once, one gradient and one
         # result per record; from this run's schedule) over the launch time measured in this run.  The rate at which
         # the records' 4 d (A + 2) bytes reach the CUs is higher (sources shared through L2) and is no HBM figure.
         "roofline": {
-            "bound": "hbm", "kernel": "pair_mix_kernel", "achieved": hbm_GBps, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "bound": "hbm",
+            "kernel": ("mix" if c.get("momentum") else "pair_mix") + "_kernel" + (" beside CSR margins" if c["model"] == "csr" else ""),
+            "passes": "wave by wave, behind the timed region", "achieved": hbm_GBps, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": hbm_GBps / HBM_PEAK_GBS,
             "traffic": counters,
             "launches": mix["launches"], "avg_launch_us": avg_us,
@@ -303,6 +324,8 @@ def main():
         "kernels": {k: {kk: vv for kk, vv in res[k].items() if kk not in ("bytes", "compulsory_bytes_per_pass", "passes_timed")}
                     for k in ("mix", "grad", "synth")},
     }
+    if "timed_kernel" in res:
+        out["timed_kernel"] = res["timed_kernel"]
     r = out["roofline"]
     grad = res["grad"]
     if grad["ms"] > res["mix"]["ms"] and c["model"] == "dense":

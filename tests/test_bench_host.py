@@ -33,6 +33,9 @@ def test_compulsory_bytes_of_a_lock_step_ring():
         assert np.all(bench.wave_compulsory_bytes(s, d, "none", False) == 4.0 * d * 8)
         assert np.all(bench.wave_compulsory_bytes(s, d, "synth", True) == 4.0 * d * 20)     # + velocity read and written
         assert np.all(bench.wave_compulsory_bytes(s, d, "dense_fused", False) == 0)        # no record left for the mix
+        # a whole pass: the 4 vectors of version 0 are read, both slots of every ring written
+        assert s.depth == 2 and bench.pass_compulsory_bytes(s, d, False) == 4.0 * d * (4 + 8)
+        assert bench.pass_compulsory_bytes(s, d, True) == 4.0 * d * (4 + 8 + 8)
         s.free()
     finally:
         hop.hop_destroy(ctx)

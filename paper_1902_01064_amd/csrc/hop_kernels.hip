@@ -1,7 +1,8 @@
 // HIP kernels of the Hop hot path for gfx950 (CDNA4, 64-wide wavefronts, 256 CUs in 8 XCDs).
 //
-// Every kernel here is bound by HBM bandwidth (about half a flop per byte), so none uses MFMA:
-// the work is coalesced 128-bit streaming, wavefront reductions and LDS staging of small tables.
+// About half a flop per byte, so none uses MFMA: the kernels of one wave are bound by HBM (small ones by their launch
+// and their chain of dependent loads) and do coalesced 128-bit streaming, wavefront reductions and LDS staging of small
+// tables; the generator of synthetic gradients and the whole pass in one launch are bound by instruction issue.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -635,12 +636,13 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 // vectors per worker, whatever the ring depth), gradients in registers; a ring slot is read once if its old content is
 // used and written once if its content survives the pass.  Lanes never exchange data: one wavefront is a workgroup.
 // Bound by instruction issue: 20 integer instructions (4 of them half-rate multiplies) for a synthetic gradient and two
-// vector instructions per source, at 90 % of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x 25 M
-// columns x 3136 records (52 local slots): 242.1 ms wave by wave -> 83.1 ms; 16 workers x 2 M columns x 640 records with
+// vector instructions per source, at nine tenths of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x
+// 25 M columns x 3136 records (52 local slots): 242.1 ms wave by wave -> 83.1 ms; 16 workers x 2 M columns x 640 records with
 // momentum: 7.93 -> 1.58 ms.  On the way there: words unpacked from bytes 180 ms (scalar unit), flags tested per record
 // 110 ms, next words loaded where the compiler moves them 99 ms, a kind for every number of sources 88 ms; 2 and 4 columns
 // per lane (fewer wavefronts per CU: the local slots fill LDS either way) 115 and 190 ms; several wavefronts per workgroup
-// 109 to 130 ms.
+// 109 to 130 ms.  Lanes past the end of the vectors end at once; with a loop over the sources for the last wavefront the
+// launch waited for it (16 workers x 2500 columns, 160 records: 78.5 us against 24.8).
 typedef const __attribute__((address_space(4))) uint32_t* sweep_words;     // scalar loads
 
 // N program words (a multiple of 4, at most 32) by as few scalar loads as there can be

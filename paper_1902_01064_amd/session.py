@@ -13,9 +13,10 @@ class Session:
         self.c = c
         self.dev = torch.device(device)
         torch.cuda.set_device(self.dev)
-        # synthetic gradients: up to sixteen waves' worth generated back to back (the mix runs slower right behind
-        # the arithmetic-bound generator), one buffer per worker and wave, as far as a quarter of the free memory
-        # (at most 64 GiB) holds them
+        # synthetic gradients of passes that run wave by wave (parts of a schedule, profiled passes, schedules that do not
+        # suit the single launch, which needs no gradient buffer): up to sixteen waves' worth generated back to back (the
+        # mix runs slower right behind the arithmetic-bound generator), one buffer per worker and wave, as far as a
+        # quarter of the free memory (at most 64 GiB) holds them; grad_ahead=1 keeps one buffer per worker
         ahead = c.get("grad_ahead", 16 if c["model"] == "synth" else 1)
         if "grad_ahead" not in c and ahead > 1:
             room = min(torch.cuda.mem_get_info(self.dev)[0] // 4, 64 << 30)

@@ -29,7 +29,7 @@ constexpr int HOP_PAIR_U = 12;   // most vectors in the union of a pair of recor
 // record may have up to HOP_MAX_A sources; a pair at most 12 in the union.  Records with a velocity keep HopMixJob.
 struct alignas(16) HopPairJob {
     int32_t U, G;              // vectors in the union, records (1 or 2)
-    float eta;
+    float eta;                 // of the records with a gradient
     int32_t reserved;
     float* out[2];
     const float* g[2];         // null: no gradient term

@@ -320,37 +320,120 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
     return true;
 }
 
+void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors& at, HopSweepArgs* args,
+                     std::vector<uint32_t>* words) {
+    constexpr uint32_t kLane = 64 * sizeof(float);
+    constexpr uint32_t kOne = 0x3F800000u;
+    std::vector<uint32_t>& out = *words;
+    out.clear();
+    args->n_local = 0;
+    auto local = [&](uint32_t slot) {
+        args->n_local = std::max(args->n_local, (int)slot + 1);
+        return slot;
+    };
+    auto put_address = [&](size_t word, const float* v) {
+        out[word] = (uint32_t)(uintptr_t)v;
+        out[word + 1] = (uint32_t)((uint64_t)(uintptr_t)v >> 32);
+    };
+    const bool external = args->mode == HOP_GRAD_EXTERNAL, none = args->mode == HOP_GRAD_ZERO;
+    const uint32_t partial = (uint32_t)plan.n_local;         // the sum so far of a record in parts
+    std::vector<std::pair<uint32_t, uint32_t>> terms;
+    const uint32_t* p = plan.program.data() + plan.first_record;
+    for (int r = 0; r < n_ops; ++r, p += hop_sweep_words((int)p[7])) {
+        terms.clear();
+        for (uint32_t t = 0; t < p[7]; ++t)
+            terms.emplace_back(p[kSweepHead + 2 * t] / kLane, p[kSweepHead + 2 * t + 1]);
+        for (size_t first = 0, n = 0; first < terms.size(); first += n) {
+            n = std::min(terms.size() - first, (size_t)kSweepInline);
+            const bool last = first + n == terms.size();
+            const size_t w = out.size();
+            out.resize(w + kSweepRecord, 0u);
+            for (size_t k = 0; k < n; ++k) {
+                const size_t place = w + (size_t)hop_sweep_source(k == 0 ? 0 : (int)(n - k));
+                out[place] = local(terms[first + k].first);
+                out[place + 1] = terms[first + k].second;
+            }
+            const bool grad = last && (p[0] & kSweepGrad), keep = !last || (p[0] & kSweepKeep), store = last && (p[0] & kSweepStore);
+            const bool on_its_way = keep && !store && (grad || none);
+            out[w] = (uint32_t)(kSweepInline + 1 - n) * kSweepStep + (on_its_way ? 0u : kSweepLong) +
+                     (w / kSweepRecord % 2 ? kSweepOdd : 0u);
+            out[w + 1] = (grad ? kSweepWithGrad : 0u) | (keep ? kSweepToLocal | local(last ? p[1] / kLane : partial) : 0u) |
+                         (store ? kSweepToRing : 0u);
+            if (w && (n > 5 || !on_its_way)) out[w - kSweepRecord + 1] |= kSweepNextWhole;
+            if (grad && external) put_address(w + 2, at.external + (int64_t)p[5] * at.d);
+            else if (grad) std::copy(p + 4, p + 7, out.begin() + (std::ptrdiff_t)w + 2);
+            out[w + 15] = p[3] / kLane;
+            if (store) put_address(w + 30, at.ring + (int64_t)p[2] * at.stride);
+            if (!last) terms[first + --n] = std::make_pair(partial, kOne);    // first source of the next part
+        }
+    }
+    args->n_records = (int)(out.size() / kSweepRecord);
+    out.resize(out.size() + kSweepRecord, 0u);
+    out[out.size() - kSweepRecord] = args->n_records % 2 ? kSweepOdd : 0u;
+    args->first_list = (int)out.size();
+    auto list = [&](const uint32_t* pairs, int n, const float* base) {
+        for (int k = 0; k < n; ++k) {
+            const size_t w = out.size();
+            out.resize(w + 4, 0u);
+            put_address(w, base + (int64_t)pairs[2 * k] * at.stride);
+            out[w + 2] = local(pairs[2 * k + 1] / kLane);
+        }
+    };
+    auto groups = [&](size_t from) {                         // filled up to eights
+        out.resize(from + (out.size() - from + 31) / 32 * 32, 0u);
+        return (int)((out.size() - from) / 32);
+    };
+    const uint32_t *loads = plan.program.data() + plan.first_load, *velocities = loads + 2 * plan.n_loads;
+    list(loads, plan.n_loads, at.ring);
+    list(velocities, plan.n_vel, at.vel);
+    args->n_load_groups = groups((size_t)args->first_list);
+    const size_t stores = out.size();
+    list(velocities, plan.n_vel, at.vel);
+    args->n_store_groups = groups(stores);
+    if (external) args->first_external = (uint64_t)(uintptr_t)(at.external + (int64_t)plan.first_external * at.d);
+}
+
 namespace {
 
 float* slot_ptr(const hop_ctx* c, int worker, int slot) {
     return c->ring + ((int64_t)worker * c->slots + slot) * c->stride;
 }
 
-// A pass in microseconds as one sweep and wave by wave, to choose between the two.  Fitted to 5082 passes on MI355X: rings,
-// tori, rings with chords and complete graphs of 4 to 100 workers, 64 to 4 M columns, each gradient, with and without a
-// velocity, in lock-step, with Exp(1) delays and with a straggler.  Of the 4010 that these estimates give to the sweep 13
-// were more than 4 % faster in waves; of those they refuse it 61 would have been faster in it, by 9 % at the median.
+// A pass in microseconds as one sweep and wave by wave, to choose between the two.  The waves' side is fitted to 5082 passes
+// on MI355X (rings, tori, rings with chords and complete graphs of 4 to 100 workers, 64 to 4 M columns, each gradient, with
+// and without a velocity, in lock-step, with Exp(1) delays and with a straggler), the sweep's to 1300 like them: half of
+// them within 10 %, nine in ten within 30 %.
 struct SweepCost {
     int64_t d = 0;
-    int waves = 0, records = 0, gradients = 0, mode = 0;
+    int waves = 0, records = 0, gradients = 0, mode = 0, workers = 0;
     bool vel = false;                    // the context has velocities
-    int wide = 0;                        // records with more sources than the sweep unrolls
+    int wide = 0;                        // records with more sources than the sweep's chain has
     double terms = 0, wide_terms = 0;    // sources of the other records and of these
     double wide_chain = 0;               // over the waves: the most sources a wide record of the wave has
     double bytes = 0;                    // that reach the CUs wave by wave
     double distinct = 0;                 // over the waves: vectors read, each once per wave
     double ring_bytes = 0;
 
-    // A wavefront takes its records one after the other: 0.16 us each with five sources, 68 ns per source where they are
-    // not unrolled, 0.13 us where a run of another kind begins.  The columns run side by side until LDS is full of local
-    // slots; beyond that they take turns, and loads of gradients on the way are no longer hidden.
-    double sweep_us(int n_local, int n_runs) const {
-        const double at_a_time = 256.0 * std::min(32, 160 * 1024 / (n_local * 256));
-        const double turns = std::max(1.0, std::ceil((double)((d + 63) / 64) / at_a_time));
-        double us = 0.12 * (records - wide) + 0.0075 * terms + 0.068 * wide_terms + 0.13 * n_runs;
-        if (vel) us += 0.02 * gradients;
-        if (mode == HOP_GRAD_EXTERNAL && turns > 1) us += 0.1 * gradients;
-        return 2.5 + us * turns;
+    // `one`: a wavefront takes its records one after the other, 0.14 us each with five sources and a synthetic gradient.
+    // Alone on its SIMD it waits most of that time (the words of the next record, jumps); what it issues is a fifth to a
+    // half, and the wavefronts there are registers for fill the rest.  A pass is the larger of the two, or what it reads and
+    // writes.  External gradients are read while the record before is at work, which is too short where wavefronts take turns.
+    // Wide records count about 1.7 times what their parts take (complete graphs of 13 to 32 workers in lock-step: 0.016 to
+    // 0.022 us a source): there the waves' estimate is at its weakest, and a refusal costs at most as much (24 workers x
+    // 65 540 columns: 285 us in waves, 179 in the sweep, which is refused).
+    double sweep_us(int n_local) const {
+        const double per_simd = std::max(1.0, (double)((d + 255) / 256) / 256.0);
+        const int at_a_time = n_local <= 48 ? 8 : n_local <= 80 ? 5 : n_local <= 112 ? 4 : 2;
+        const double turns = std::ceil(per_simd / at_a_time);
+        const bool synth = mode == HOP_GRAD_SYNTH, external = mode == HOP_GRAD_EXTERNAL;
+        double one = 0.069 * (records - wide) + 0.0043 * terms + 0.036 * wide_terms + 0.94 * ((n_local + 7) / 8);
+        one += gradients * (synth ? 0.047 : external ? turns > 1 ? 0.17 : 0.011 : 0.0);
+        double issue = 0.017 * (records - wide) + 0.002 * terms + 0.01 * wide_terms;
+        issue += gradients * ((synth ? 0.021 : 0.0) + (vel ? 0.0094 : 0.0));
+        double vectors = 4.0 * workers;                          // read at the start and stored, about
+        if (vel && gradients) vectors += 2.0 * workers;
+        if (external) vectors += gradients;
+        return 3.8 + std::max(one * turns, std::max(issue * per_simd, 4.0 * (double)d * vectors / 7.2e6) + 0.69 * one);
     }
 
     // Launches (one per wave, two with synthetic gradients) that partly hide behind what they move: every source to the
@@ -381,6 +464,7 @@ SweepCost sweep_cost(const hop_ctx* c, const hop_schedule* s, const std::vector<
     k.records = (int)s->kind.size();
     k.mode = c->grad_mode;
     k.vel = c->vel != nullptr;
+    k.workers = c->N;
     k.ring_bytes = 4.0 * (double)c->N * c->slots * c->d;
     std::vector<const float*> seen;
     for (int w = 0; w < s->n_waves; ++w) {
@@ -412,11 +496,11 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     const int mode = c->grad_mode;
     if (mode != HOP_GRAD_ZERO && mode != HOP_GRAD_SYNTH && mode != HOP_GRAD_EXTERNAL) return HOP_OK;
     const int R = (int)mix.size();
-    // the cheapest that a sweep can be: a local slot per worker (and velocity), one run
+    // the cheapest that a sweep can be: a local slot per worker (and velocity)
     const SweepCost cost = sweep_cost(c, s, mix);
     const double waves_us = cost.waves_us();
     const bool vel_slots = c->vel && mode != HOP_GRAD_ZERO;
-    if (c->N * (vel_slots ? 2 : 1) > kSweepMaxLocal || cost.sweep_us(c->N * (vel_slots ? 2 : 1), 1) > waves_us) return HOP_OK;
+    if (c->N * (vel_slots ? 2 : 1) > kSweepMaxLocal || cost.sweep_us(c->N * (vel_slots ? 2 : 1)) > waves_us) return HOP_OK;
     auto slot_of = [c](const float* p) { return (int)((p - c->ring) / c->stride); };
     std::vector<HopSweepOp> ops((size_t)R);
     std::vector<int> at((size_t)c->N * c->slots, -1);            // position of the record that writes a slot, this wave
@@ -453,29 +537,27 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     }
     HopSweepPlan plan;
     if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan)) return HOP_OK;
-    if (cost.sweep_us(plan.n_local, plan.n_runs) > waves_us) return HOP_OK;
-    const size_t bytes = plan.program.size() * sizeof(uint32_t);
-    if (bytes > room_bytes) return HOP_OK;
-    HOP_HIP(c, hipMemcpy(room, plan.program.data(), bytes, hipMemcpyHostToDevice));
-    HopSweepArgs& a = s->sweep;
-    a.program = (const uint32_t*)room;
-    a.n_runs = plan.n_runs;
-    a.zero = plan.zero;
-    a.first_record = plan.first_record;
-    a.first_load = plan.first_load;
-    a.first_external = plan.first_external;
-    a.n_local = plan.n_local;
-    a.n_loads = plan.n_loads;
-    a.n_vel = plan.n_vel;
+    if (cost.sweep_us(plan.n_local) > waves_us) return HOP_OK;
+    HopSweepArgs a;
     a.mode = mode;
-    a.ring = c->ring;
-    a.vel = c->vel;
-    a.external = c->external;
-    a.stride = c->stride;
+    HopSweepVectors vectors;
+    vectors.ring = c->ring;
+    vectors.vel = c->vel;
+    vectors.external = c->external;
+    vectors.stride = c->stride;
+    vectors.d = c->d;
+    std::vector<uint32_t> words;
+    hop_lower_sweep(plan, R, vectors, &a, &words);
+    const size_t bytes = words.size() * sizeof(uint32_t);
+    if (bytes > room_bytes) return HOP_OK;
+    HOP_HIP(c, hipMemcpy(room, words.data(), bytes, hipMemcpyHostToDevice));
+    a.program = (const uint32_t*)room;
+    a.velocities = c->vel != nullptr;
     a.d = c->d;
     a.eta = c->opts.lr;
     a.mu = c->opts.momentum;
     a.scale = hoprng::synth_scale(c->synth_variance);
+    s->sweep = a;
     return HOP_OK;
 }
 

@@ -74,7 +74,9 @@ struct alignas(16) HopGradJob {
     float scale;               // synth: fp32 factor
 };
 
-// ---- a whole pass as a program for sweep_kernel ------------------------------------
+// ---- a whole pass as a program ------------------------------------------------------
+// What the records of a pass read, where their values are kept and in which order they come; hop_lower_sweep below writes
+// it down for sweep_kernel, which has no use for the runs and the added zeros.
 // The records of a pass in an order that respects their dependences, for gradients that need no sum over the columns
 // (none, synthetic, external): every column can then run the whole pass by itself.  Words of 32 bits:
 //   runs     count << 8 | kind for every run of records of one kind: the number of sources (possibly rounded up to an even
@@ -112,18 +114,41 @@ struct HopSweepPlan {
 // False if the pass needs more than kSweepMaxLocal values at a time.  Host only.
 bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_workers, HopSweepPlan* plan);
 
+// What sweep_kernel reads: the plan with its local slots as vector registers, in words of 32 bits.
+//   records  of kSweepRecord words: 0 where the record enters the kernel's chains of sources (kSweepStep for every source
+//            short of kSweepInline; kSweepLong unless it has the gradient of the pass, if there is any, and a result that
+//            just goes to a local slot; kSweepOdd for every other record), 1 local slot of the result | flags, 2..4 hash
+//            keys or 2..3 address of the external gradient that the next record with one takes, hop_sweep_source(k) and the
+//            word behind it: (local slot, weight) of the first source (k = 0), then of the others from the last to the second,
+//            15 local slot of the velocity, 30..31 address of the ring slot the result is stored to.  Short records of few
+//            sources need the first half only.  More than kSweepInline sources become several records, whose sums go
+//            through a local slot of their own.  Behind the last one: a record that enters nowhere, which ends the pass
+//   lists    (address, address, local slot, 0) of the vectors loaded at the start, then of those stored back at the end,
+//            both filled up to eights by zeros
+constexpr int kSweepRecord = 32;
+constexpr uint32_t kSweepStep = 8, kSweepLong = 256, kSweepOdd = 512;
+constexpr int kSweepRegisters = 168;    // most local slots that the kernel is built for
+enum : uint32_t { kSweepWithGrad = 0x200u, kSweepToLocal = 0x400u, kSweepToRing = 0x800u,
+                  kSweepNextWhole = 0x1000u };          // flags; the last: the next record needs both halves of its words
+constexpr int hop_sweep_source(int k) { return k < 5 ? 5 + 2 * k : 6 + 2 * k; }
+
 struct HopSweepArgs {
-    const uint32_t* program;            // device copy of HopSweepPlan::program
-    int32_t n_runs, n_local, n_loads, n_vel, first_record, first_load;
-    int32_t mode;                       // HOP_GRAD_ZERO, HOP_GRAD_SYNTH or HOP_GRAD_EXTERNAL
-    float* ring;
-    float* vel;                         // null: no velocities
-    const float* external;              // n_workers x d
-    int32_t first_external;             // worker of the first record with a gradient
-    int32_t zero;
-    int64_t stride, d;
-    float eta, mu, scale;
+    const uint32_t* program = nullptr;  // on the device
+    uint64_t first_external = 0;        // address of the external gradient of the first record with one
+    int32_t n_records = 0, n_local = 0, n_load_groups = 0, n_store_groups = 0, first_list = 0;
+    int32_t mode = 0;                   // HOP_GRAD_ZERO, HOP_GRAD_SYNTH or HOP_GRAD_EXTERNAL
+    int32_t velocities = 0;             // a context with velocities
+    float eta = 0.f, mu = 0.f, scale = 0.f;
+    int64_t d = 0;
 };
+
+// The vectors that a plan's numbers stand for.
+struct HopSweepVectors {
+    const float *ring = nullptr, *vel = nullptr, *external = nullptr;
+    int64_t stride = 0, d = 0;
+};
+// Writes the plan down for the kernel; sets the counts of `args`.  Host only.
+void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors& at, HopSweepArgs* args, std::vector<uint32_t>* words);
 
 // Packs the Reduce jobs of one wave for pair_mix_kernel (appends to `out`; see its definition for the rule); returns the
 // number of distinct vectors the jobs read.  Host only.
@@ -185,7 +210,7 @@ struct hop_schedule {
     HopMixJob* mix_dev = nullptr;       // n_records, in wave order
     HopPairJob* pair_dev = nullptr;     // the same records packed in pairs, wave by wave (null with a velocity)
     HopGradJob* grad_dev = nullptr;     // STEP records only, in wave order
-    HopSweepArgs sweep{};               // the whole pass as one launch (program null: not available for this schedule)
+    HopSweepArgs sweep;                 // the whole pass as one launch (program null: not available for this schedule)
     int32_t* rows_dev = nullptr;        // n_records x batch
     float* coef_dev = nullptr;          // n_records x batch
     bool dense_in_place = false;        // dense SVM: margins beside the Reduce, gradient applied in place

@@ -632,222 +632,320 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 // ------------------------------------------------------------- a whole pass, column by column ----
 // Reduce, Apply and the synthetic (external, absent) gradient act on every column by itself, so a wavefront can run ALL
 // records of a pass on its own 64 columns: no launch, no barrier and no trip to HBM between two waves of the schedule.
-// The values that later records still read live in LDS (the host hands out the local slots by live range: about 1.6
-// vectors per worker, whatever the ring depth), gradients in registers; a ring slot is read once if its old content is
-// used and written once if its content survives the pass.  Lanes never exchange data: one wavefront is a workgroup.
-// Bound by instruction issue: 20 integer instructions (4 of them half-rate multiplies) for a synthetic gradient and two
-// vector instructions per source, at nine tenths of the vector rate with 12 wavefronts per CU.  Measured on 32 workers x
-// 25 M columns x 3136 records (52 local slots): 242.1 ms wave by wave -> 83.1 ms; 16 workers x 2 M columns x 640 records with
-// momentum: 7.93 -> 1.58 ms.  On the way there: words unpacked from bytes 180 ms (scalar unit), flags tested per record
-// 110 ms, next words loaded where the compiler moves them 99 ms, a kind for every number of sources 88 ms; 2 and 4 columns
-// per lane (fewer wavefronts per CU: the local slots fill LDS either way) 115 and 190 ms; several wavefronts per workgroup
-// 109 to 130 ms.  Lanes past the end of the vectors end at once; with a loop over the sources for the last wavefront the
-// launch waited for it (16 workers x 2500 columns, 160 records: 78.5 us against 24.8).
-typedef const __attribute__((address_space(4))) uint32_t* sweep_words;     // scalar loads
+// The values that later records still read live in vector registers (the host hands out the local slots by live range:
+// about 1.6 vectors per worker, whatever the ring depth); a ring slot is read once if its old content is used and written
+// once if its content survives the pass.  Lanes never exchange data.
+// Bound by the vector unit's issue rate: per record one instruction per source, 18 for a synthetic gradient (4 of them
+// multiplies at about half rate) and one to apply it.  That is why the body is written out:
+//  - a record names its sources, and registers can only be named by number: the index mode of the vector unit (M0, set by
+//    the scalar unit beside the arithmetic) lets v_fmac read a local slot where it is.  With the local slots in LDS a source
+//    took an address, a load and the v_fmac;
+//  - the number of sources is a jump into a chain of twelve, so records of different kinds need no sorting and no tests;
+//  - the centred byte sum of a gradient times the scale is one of 3061 numbers, in LDS: three v_dot4 give the address, in
+//    place of three v_sad_u8, a conversion and a multiplication.  Four wavefronts share the table, and nothing else.
+// 32 workers x 25 M columns x 3136 records (52 local slots): 242 ms wave by wave, 83.7 with local slots in LDS, 60.5 with them
+// in registers, 57.0 with the table, 54.1 with a scalar unit that only sets indexes (records count themselves, the jump
+// is one s_or); 16 workers x 2 M columns x 640 records with momentum: 7.7, 1.57, 0.98, 0.94, 0.90 ms.  Without a gradient
+// the words of the records count (128 B each through the scalar cache): short records of up to five sources are one
+// load, 16 workers x 3 M columns, 240 records of three sources: 336 -> 290 us.
+// Index mode stays on all along and the instructions outside the chains have no relative operand: with the mode off between
+// them and on again a few scalar instructions later, a vector instruction now and then ran in the mode before.  The
+// instructions between the last v_dot4 and the ds_read of its result are needed too: inside an asm block no compiler fills
+// up wait states.
+#define HOP_REGS_2(x, t) x #t "0", x #t "1"
+#define HOP_REGS_4(x, t) HOP_REGS_2(x, t), x #t "2", x #t "3"
+#define HOP_REGS_6(x, t) HOP_REGS_4(x, t), x #t "4", x #t "5"
+#define HOP_REGS(x, t) HOP_REGS_6(x, t), x #t "6", x #t "7", x #t "8", x #t "9"
+#define HOP_SWEEP_V64                                                                                                    \
+    "v8", "v9", HOP_REGS("v", 1), HOP_REGS("v", 2), HOP_REGS("v", 3), HOP_REGS("v", 4), HOP_REGS("v", 5), HOP_REGS_4("v", 6)
+#define HOP_SWEEP_V96                                                                                                    \
+    HOP_SWEEP_V64, "v64", "v65", "v66", "v67", "v68", "v69", HOP_REGS("v", 7), HOP_REGS("v", 8), HOP_REGS_6("v", 9)
+#define HOP_SWEEP_V128                                                                                                   \
+    HOP_SWEEP_V96, "v96", "v97", "v98", "v99", HOP_REGS("v", 10), HOP_REGS("v", 11), HOP_REGS_6("v", 12), "v126", "v127"
+#define HOP_SWEEP_V184                                                                                                   \
+    HOP_SWEEP_V128, "v128", "v129", HOP_REGS("v", 13), HOP_REGS("v", 14), HOP_REGS("v", 15), HOP_REGS("v", 16),          \
+        HOP_REGS("v", 17), HOP_REGS_4("v", 18)
+#define HOP_SWEEP_S                                                                                                      \
+    "s16", "s17", "s18", "s19", HOP_REGS("s", 2), "s30", "s31", "s34", "s35", "s36", "s37", "s38", "s39", HOP_REGS("s", 4), \
+        HOP_REGS("s", 5), HOP_REGS("s", 6), HOP_REGS("s", 7), HOP_REGS("s", 8), HOP_REGS("s", 9)
 
-// N program words (a multiple of 4, at most 32) by as few scalar loads as there can be
-template <int N>
-struct SweepWords {
-    static constexpr int N0 = N >= 16 ? 16 : N >= 8 ? 8 : 4, N1 = N - N0 >= 16 ? 16 : N - N0 >= 8 ? 8 : 4;
-    static constexpr bool TWO = N > N0, THREE = N > N0 + N1;
-    template <int LEN> struct Part { typedef uint32_t type __attribute__((ext_vector_type(LEN), aligned(16))); };
-    typename Part<N0>::type a;
-    typename Part<N1>::type b;
-    typename Part<4>::type c;
-    static_assert(N % 4 == 0 && N <= N0 + N1 + 4, "records come in whole fours, up to 12 sources");
-    template <class T>
-    static __device__ __forceinline__ T part(sweep_words p) { return *(const __attribute__((address_space(4))) T*)p; }
-    __device__ __forceinline__ void load(sweep_words p) {
-        a = part<typename Part<N0>::type>(p);
-        if constexpr (TWO) b = part<typename Part<N1>::type>(p + N0);
-        if constexpr (THREE) c = part<typename Part<4>::type>(p + N0 + N1);
+// v8..v15 work, v16.. the local slots; s[36:67] and s[68:99] the words of the record at work and of the next one;
+//   s[16:17] records  s[18:19] list  s[20:21] byte offset of the workgroup's columns  s23 list groups left  s24 -eta  s25 mu
+//   s26 the chains' low address  s27 s28 the hash's factors  s29 four bytes of 4  s[30:31] an address  s[34:35] a jump
+#define HOP_SWEEP_TEXT                                                                                                \
+    /* eight vectors of the list at s[18:19] */                                                                       \
+    ".macro hop_list_words\n"                                                                                         \
+    "  s_load_dwordx16 s[36:51], s[18:19], 0\n"                                                                       \
+    "  s_load_dwordx16 s[52:67], s[18:19], 64\n"                                                                      \
+    "  s_add_u32 s18, s18, 128\n"                                                                                     \
+    "  s_addc_u32 s19, s19, 0\n"                                                                                      \
+    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
+    ".endm\n"                                                                                                         \
+    /* s[30:31]: the address at s[w:w+1] for the columns of this workgroup */                                         \
+    ".macro hop_columns w\n"                                                                                          \
+    "  s_add_u32 s30, s[\\w], s20\n"                                                                                  \
+    "  s_addc_u32 s31, s[\\w+1], s21\n"                                                                               \
+    ".endm\n"                                                                                                         \
+    ".macro hop_list_load q\n"                                                                                        \
+    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cbranch_scc1 .Lhop_wait_%=\n"                                                                                \
+    "  hop_columns 36+4*\\q\n"                                                                                        \
+    "  global_load_dword v[8+\\q], %[lane], s[30:31] nt\n"                                                            \
+    ".endm\n"                                                                                                         \
+    ".macro hop_list_put q\n"                                                                                         \
+    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cbranch_scc1 .Lhop_loaded_%=\n"                                                                              \
+    "  s_set_gpr_idx_on s[38+4*\\q], 8\n"                                                                             \
+    "  v_mov_b32_e32 v16, v[8+\\q]\n"                                                                                 \
+    ".endm\n"                                                                                                         \
+    ".macro hop_list_store q\n"                                                                                       \
+    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cbranch_scc1 .Lhop_out_%=\n"                                                                                 \
+    "  s_set_gpr_idx_on s[38+4*\\q], 1\n"                                                                             \
+    "  v_mov_b32_e32 v[8+\\q], v16\n"                                                                                 \
+    "  hop_columns 36+4*\\q\n"                                                                                        \
+    "  global_store_dword %[lane], v[8+\\q], s[30:31] nt\n"                                                           \
+    ".endm\n"                                                                                                         \
+    /* v11: where the synthetic gradient of the keys at s[w+2] is in the table */                                     \
+    ".macro hop_generate w\n"                                                                                         \
+    "  v_xor_b32_e32 v8, s[\\w+2], %[folded]\n"                                                                       \
+    "  v_xor_b32_e32 v9, s[\\w+3], %[folded]\n"                                                                       \
+    "  v_mul_lo_u32 v8, v8, s27\n"                                                                                    \
+    "  v_mul_lo_u32 v9, v9, s27\n"                                                                                    \
+    "  v_lshrrev_b32_e32 v10, 15, v8\n"                                                                               \
+    "  v_lshrrev_b32_e32 v11, 15, v9\n"                                                                               \
+    "  v_xor_b32_e32 v8, v8, v10\n"                                                                                   \
+    "  v_xor_b32_e32 v9, v9, v11\n"                                                                                   \
+    "  v_mul_lo_u32 v8, v8, s28\n"                                                                                    \
+    "  v_mul_lo_u32 v9, v9, s28\n"                                                                                    \
+    "  v_xor_b32_sdwa v8, v8, v8 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n"                \
+    "  v_xor_b32_sdwa v9, v9, v9 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1 src1_sel:DWORD\n"                \
+    "  v_alignbit_b32 v10, v9, v9, 16\n"                                                                              \
+    "  v_dot4_u32_u8 v11, v8, s29, %[table]\n"                                                                        \
+    "  v_add_u32_e32 v10, v8, v10\n"                                                                                  \
+    "  v_dot4_u32_u8 v11, v9, s29, v11\n"                                                                             \
+    "  v_xor_b32_e32 v10, s[\\w+4], v10\n"                                                                            \
+    "  v_dot4_u32_u8 v11, v10, s29, v11\n"                                                                            \
+    ".endm\n"                                                                                                         \
+    /* v13: the external gradient that the next record with one takes */                                              \
+    ".macro hop_external w\n"                                                                                         \
+    "  hop_columns \\w+2\n"                                                                                           \
+    "  global_load_dword v13, %[lane], s[30:31]\n"                                                                    \
+    ".endm\n"                                                                                                         \
+    /* the gradient (with a velocity the velocity, which stays in its local slot too) applied to the sum; */          \
+    /* dst 8: into the local slot, 0: left in v12 */                                                                  \
+    ".macro hop_apply w, dst\n"                                                                                       \
+    "  .if %[mode] == %[external]\n"                                                                                  \
+    "  s_waitcnt vmcnt(0)\n"                                                                                          \
+    "  .else\n"                                                                                                       \
+    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
+    "  .endif\n"                                                                                                      \
+    "  .if %[mom]\n"                                                                                                  \
+    "  s_set_gpr_idx_on s[\\w+15], 2\n"                                                                               \
+    "  v_fma_f32 v11, s25, v16, v[11+2*(%[mode]/%[external])]\n"                                                      \
+    "  s_set_gpr_idx_on s[\\w+15], 8\n"                                                                               \
+    "  v_mov_b32_e32 v16, v11\n"                                                                                      \
+    "  s_set_gpr_idx_on s[\\w+1], \\dst\n"                                                                            \
+    "  v_fma_f32 v[12+\\dst/2], s24, v11, v12\n"                                                                      \
+    "  .else\n"                                                                                                       \
+    "  s_set_gpr_idx_on s[\\w+1], \\dst\n"                                                                            \
+    "  v_fma_f32 v[12+\\dst/2], s24, v[11+2*(%[mode]/%[external])], v12\n"                                            \
+    "  .endif\n"                                                                                                      \
+    "  .if %[mode] == %[external]\n"                                                                                  \
+    "  hop_external \\w\n"                                                                                            \
+    "  .endif\n"                                                                                                      \
+    ".endm\n"                                                                                                         \
+    /* sources 2 to 12 of a record; a jump to the first entry ends the pass */                                        \
+    ".macro hop_chain w\n"                                                                                            \
+    "  .p2align 8\n"                                                                                                  \
+    "  s_branch .Lhop_end_%=\n"                                                                                       \
+    "  s_nop 0\n"                                                                                                     \
+    "  .irp k, 28, 26, 24, 22, 20, 18, 16, 13, 11, 9, 7\n"                                                            \
+    "  s_set_gpr_idx_idx s[\\w+\\k]\n"                                                                                \
+    "  v_fmac_f32_e32 v12, s[\\w+1+\\k], v16\n"                                                                       \
+    "  .endr\n"                                                                                                       \
+    ".endm\n"                                                                                                         \
+    /* a record as most are: with the gradient of the pass, if it has any, and its result to a local slot only */     \
+    ".macro hop_short w, n\n"                                                                                         \
+    "  hop_chain \\w\n"                                                                                               \
+    "  .if %[mode] == %[zero]\n"                                                                                      \
+    "  s_set_gpr_idx_on s[\\w+1], 8\n"                                                                                \
+    "  v_mov_b32_e32 v16, v12\n"                                                                                      \
+    "  .else\n"                                                                                                       \
+    "  hop_apply \\w, 8\n"                                                                                            \
+    "  .endif\n"                                                                                                      \
+    "  .if %[mode] == %[synth]\n"                                                                                     \
+    "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
+    "  .endif\n"                                                                                                      \
+    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
+    "  s_branch .Lhop_record\\n\\()_%=\n"                                                                             \
+    ".endm\n"                                                                                                         \
+    ".macro hop_long w\n"                                                                                             \
+    "  hop_chain \\w\n"                                                                                               \
+    "  s_branch .Lhop_rest\\w\\()_%=\n"                                                                               \
+    ".endm\n"                                                                                                         \
+    ".macro hop_rest w, n\n"                                                                                          \
+    ".Lhop_rest\\w\\()_%=:\n"                                                                                         \
+    "  .if %[mode] != %[zero]\n"                                                                                      \
+    "  s_bitcmp1_b32 s[\\w+1], 9\n"                                                                                   \
+    "  s_cbranch_scc0 .Lhop_plain\\w\\()_%=\n"                                                                        \
+    "  hop_apply \\w, 0\n"                                                                                            \
+    ".Lhop_plain\\w\\()_%=:\n"                                                                                        \
+    "  .endif\n"                                                                                                      \
+    "  s_bitcmp1_b32 s[\\w+1], 10\n"                                                                                  \
+    "  s_cbranch_scc0 .Lhop_store\\w\\()_%=\n"                                                                        \
+    "  s_set_gpr_idx_on s[\\w+1], 8\n"                                                                                \
+    "  v_mov_b32_e32 v16, v12\n"                                                                                      \
+    ".Lhop_store\\w\\()_%=:\n"                                                                                        \
+    "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
+    "  s_bitcmp1_b32 s[\\w+1], 11\n"                                                                                  \
+    "  s_cbranch_scc0 .Lhop_stored\\w\\()_%=\n"                                                                       \
+    "  hop_columns \\w+30\n"                                                                                          \
+    "  global_store_dword %[lane], v12, s[30:31] nt\n"                                                                \
+    ".Lhop_stored\\w\\()_%=:\n"                                                                                       \
+    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
+    "  s_branch .Lhop_record\\n\\()_%=\n"                                                                             \
+    ".endm\n"                                                                                                         \
+    /* the record whose words are at s[w..], while those of the next are loaded to s[n..] */                          \
+    ".macro hop_record w, n, at\n"                                                                                    \
+    ".Lhop_record\\w\\()_%=:\n"                                                                                       \
+    "  s_load_dwordx16 s[\\n:\\n+15], s[16:17], \\at\n"                                                               \
+    "  .if %[mode] != %[synth]\n"                                                                                     \
+    "  s_bitcmp1_b32 s[\\w+1], 12\n"                                                                                  \
+    "  s_cbranch_scc0 .Lhop_half\\w\\()_%=\n"                                                                         \
+    "  .endif\n"                                                                                                      \
+    "  s_load_dwordx16 s[\\n+16:\\n+31], s[16:17], \\at+64\n"                                                         \
+    ".Lhop_half\\w\\()_%=:\n"                                                                                         \
+    "  .if %[mode] == %[synth]\n"                                                                                     \
+    "  hop_generate \\w\n"                                                                                            \
+    "  .endif\n"                                                                                                      \
+    "  s_or_b32 s34, s26, s[\\w]\n"                                                                                   \
+    "  s_set_gpr_idx_on s[\\w+5], 2\n"                                                                                \
+    "  .if %[mom]\n"                                                                                                  \
+    "  v_mul_f32_e32 v12, s[\\w+6], v16\n"                                                                            \
+    "  .else\n"                                                                                                       \
+    "  v_fma_f32 v12, s[\\w+6], v16, 0\n"                                                                             \
+    "  .endif\n"                                                                                                      \
+    "  .if %[mode] == %[synth]\n"                                                                                     \
+    "  ds_read_b32 v11, v11\n"                                                                                        \
+    "  .endif\n"                                                                                                      \
+    ".endm\n"                                                                                                         \
+    "  s_mov_b64 s[16:17], %[records]\n"                                                                              \
+    "  s_mov_b64 s[18:19], %[lists]\n"                                                                                \
+    "  s_mov_b64 s[20:21], %[columns]\n"                                                                              \
+    "  s_mov_b32 s23, %[loads]\n"                                                                                     \
+    "  s_mov_b32 s24, %[neg_eta]\n"                                                                                   \
+    "  s_mov_b32 s25, %[mu]\n"                                                                                        \
+    "  s_mov_b32 s27, 0x7FEB352D\n"                                                                                   \
+    "  s_mov_b32 s28, 0x846CA68B\n"                                                                                   \
+    "  s_mov_b32 s29, 0x04040404\n"                                                                                   \
+    "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
+    "  s_nop 7\n"                                                                                                     \
+    ".Lhop_load_%=:\n"                                                                                                \
+    "  s_sub_u32 s23, s23, 1\n"                                                                                       \
+    "  s_cbranch_scc1 .Lhop_loaded_%=\n"                                                                              \
+    "  hop_list_words\n"                                                                                              \
+    "  .irp q, 0, 1, 2, 3, 4, 5, 6, 7\n"                                                                              \
+    "  hop_list_load \\q\n"                                                                                           \
+    "  .endr\n"                                                                                                       \
+    ".Lhop_wait_%=:\n"                                                                                                \
+    "  s_waitcnt vmcnt(0)\n"                                                                                          \
+    "  .irp q, 0, 1, 2, 3, 4, 5, 6, 7\n"                                                                              \
+    "  hop_list_put \\q\n"                                                                                            \
+    "  .endr\n"                                                                                                       \
+    "  s_branch .Lhop_load_%=\n"                                                                                      \
+    ".Lhop_loaded_%=:\n"                                                                                              \
+    "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
+    "  .if %[mode] == %[external]\n"                                                                                  \
+    "  s_mov_b64 s[38:39], %[first]\n"                                                                                \
+    "  hop_external 36\n"                                                                                             \
+    "  .endif\n"                                                                                                      \
+    "  s_load_dwordx16 s[36:51], s[16:17], 0\n"                                                                       \
+    "  s_load_dwordx16 s[52:67], s[16:17], 64\n"                                                                      \
+    "  s_getpc_b64 s[34:35]\n"                                                                                        \
+    ".Lhop_here_%=:\n"                                                                                                \
+    "  s_add_u32 s26, s34, .Lhop_chains_%=-.Lhop_here_%=\n"                                                           \
+    "  s_addc_u32 s35, s35, 0\n"                                                                                      \
+    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
+    "  hop_record 36, 68, 128\n"                                                                                      \
+    "  s_setpc_b64 s[34:35]\n"                                                                                        \
+    "  hop_record 68, 36, 256\n"                                                                                      \
+    "  s_add_u32 s16, s16, 256\n"                                                                                     \
+    "  s_addc_u32 s17, s17, 0\n"                                                                                      \
+    "  s_setpc_b64 s[34:35]\n"                                                                                        \
+    /* four chains, 256 bytes apart, in a block that no address crosses a carry in: a record names its own */         \
+    "  .p2align 10\n"                                                                                                 \
+    ".Lhop_chains_%=:\n"                                                                                              \
+    "  hop_short 36, 68\n"                                                                                            \
+    "  hop_long 36\n"                                                                                                 \
+    "  hop_short 68, 36\n"                                                                                            \
+    "  hop_long 68\n"                                                                                                 \
+    "  hop_rest 36, 68\n"                                                                                             \
+    "  hop_rest 68, 36\n"                                                                                             \
+    ".Lhop_end_%=:\n"                                                                                                 \
+    /* what the last record had loaded ahead is not used, but its registers are */                                    \
+    "  s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                                               \
+    "  .if %[mom]\n"                                                                                                  \
+    "  s_mov_b32 s23, %[velocities]\n"                                                                                \
+    ".Lhop_back_%=:\n"                                                                                                \
+    "  s_sub_u32 s23, s23, 1\n"                                                                                       \
+    "  s_cbranch_scc1 .Lhop_out_%=\n"                                                                                 \
+    "  hop_list_words\n"                                                                                              \
+    "  .irp q, 0, 1, 2, 3, 4, 5, 6, 7\n"                                                                              \
+    "  hop_list_store \\q\n"                                                                                          \
+    "  .endr\n"                                                                                                       \
+    "  s_branch .Lhop_back_%=\n"                                                                                      \
+    ".Lhop_out_%=:\n"                                                                                                 \
+    "  .endif\n"                                                                                                      \
+    "  s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                                               \
+    "  s_nop 7\n"                                                                                                     \
+    "  s_set_gpr_idx_off\n"                                                                                           \
+    "  s_nop 7\n"                                                                                                     \
+    ".purgem hop_list_words\n"                                                                                        \
+    ".purgem hop_columns\n"                                                                                           \
+    ".purgem hop_list_load\n"                                                                                         \
+    ".purgem hop_list_put\n"                                                                                          \
+    ".purgem hop_list_store\n"                                                                                        \
+    ".purgem hop_generate\n"                                                                                          \
+    ".purgem hop_external\n"                                                                                          \
+    ".purgem hop_apply\n"                                                                                             \
+    ".purgem hop_chain\n"                                                                                             \
+    ".purgem hop_short\n"                                                                                             \
+    ".purgem hop_long\n"                                                                                              \
+    ".purgem hop_rest\n"                                                                                              \
+    ".purgem hop_record\n"
+
+#define HOP_SWEEP_ASM(...)                                                                                            \
+    asm volatile(HOP_SWEEP_TEXT                                                                                       \
+                 :                                                                                                    \
+                 : [records] "s"(a.program), [lists] "s"(a.program + a.first_list), [columns] "s"(columns),           \
+                   [loads] "s"(a.n_load_groups), [velocities] "s"(a.n_store_groups),    \
+                   [neg_eta] "s"(-a.eta), [mu] "s"(a.mu), [first] "s"(a.first_external), [lane] "v"(lane),            \
+                   [folded] "v"(folded), [table] "v"(table), [mode] "n"(MODE), [mom] "n"((int)MOM),                   \
+                   [zero] "n"(HOP_GRAD_ZERO), [synth] "n"(HOP_GRAD_SYNTH), [external] "n"(HOP_GRAD_EXTERNAL)          \
+                 : "memory", "scc", "vcc", HOP_SWEEP_S, __VA_ARGS__)
+
+constexpr int kSweepThreads = 256;
+constexpr int kSynthSums = 12 * 255 + 1;               // values of a sum of 12 bytes
+
+// LOCAL: local slots there are registers for.  64, 96, 128 and 184 registers: 8, 5, 4 and 2 wavefronts per SIMD.
+template <int MODE, bool MOM, int LOCAL>
+__global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const HopSweepArgs a) {
+    __shared__ float tableS[MODE == HOP_GRAD_SYNTH ? kSynthSums : 1];
+    if (MODE == HOP_GRAD_SYNTH) {
+        for (int k = threadIdx.x; k < kSynthSums; k += kSweepThreads) tableS[k] = (float)(k - 1530) * a.scale;
+        __syncthreads();
     }
-    __device__ __forceinline__ uint32_t operator[](int k) const {          // k constant
-        return k < N0 ? a[k < N0 ? k : 0] : k < N0 + N1 ? b[k < N0 + N1 ? k - N0 : 0] : c[(k - N0 - N1) & 3];
-    }
-    // a use of all words: the loads stay in front of it
-    __device__ __forceinline__ void hold() const {
-        asm volatile("" ::"s"(a));
-        if constexpr (TWO) asm volatile("" ::"s"(b));
-        if constexpr (THREE) asm volatile("" ::"s"(c));
-    }
-};
-
-// what a wavefront works on: column c of every vector, its lane's part of LDS
-struct SweepLane {
-    char* lds;
-    int64_t c;
-    uint32_t folded;         // fold16(c)
-    float ahead;             // external gradients: that of the next record with one
-};
-__device__ __forceinline__ float& sweep_local(const SweepLane& l, uint32_t offset) { return *(float*)(l.lds + offset); }
-
-__device__ __forceinline__ float sweep_load(const float* p, const SweepLane& l) {
-    return __builtin_nontemporal_load((const HOP_GLOBAL float*)p + l.c);
-}
-__device__ __forceinline__ void sweep_store(float* p, const SweepLane& l, float v) {
-    __builtin_nontemporal_store(v, (HOP_GLOBAL float*)p + l.c);
-}
-
-// a worker's external gradient; its next record reads it again: ordinary loads
-__device__ __forceinline__ float sweep_external(const HopSweepArgs& a, uint32_t worker, const SweepLane& l) {
-    return ((const HOP_GLOBAL float*)(a.external + (int64_t)worker * a.d))[l.c];
-}
-
-template <int MODE, class Words>
-__device__ __forceinline__ float sweep_grad(const HopSweepArgs& a, const Words& h, SweepLane& l) {
-    if (MODE == HOP_GRAD_SYNTH) return synth_one(l.folded, h[4], h[5], h[6], a.scale);
-    if (MODE == HOP_GRAD_EXTERNAL) {
-        const float g = l.ahead;
-        l.ahead = sweep_external(a, h[5], l);
-        return g;
-    }
-    return 0.f;
-}
-
-// acc - eta g, through the velocity with MOM
-template <bool MOM, class Words>
-__device__ __forceinline__ float sweep_apply(const HopSweepArgs& a, const Words& h, const SweepLane& l, float g, float acc) {
-    if (MOM) {
-        float& v = sweep_local(l, h[3]);
-        g = fmaf(a.mu, v, g);
-        v = g;
-    }
-    return fmaf(-a.eta, g, acc);
-}
-
-// the first term of a sum, as mix_tile (MOM) and pair_tile begin theirs: all ways of running a record give the same bits
-template <bool MOM>
-__device__ __forceinline__ float sweep_first(uint32_t w, float x) {
-    return MOM ? __uint_as_float(w) * x : fmaf(__uint_as_float(w), x, 0.f);
-}
-
-// the result of a record to where it is read from or stays
-template <class Words>
-__device__ __forceinline__ void sweep_put(const HopSweepArgs& a, const Words& h, const SweepLane& l, float acc) {
-    if (h[0] & kSweepKeep) sweep_local(l, h[1]) = acc;
-    if (h[0] & kSweepStore) sweep_store(a.ring + (int64_t)h[2] * a.stride, l, acc);
-}
-
-// One record with A sources, while the words of the next are loaded; KEPT: the result goes to a local slot and nowhere
-// else.  All loads come first, then the gradient's arithmetic over their latency (scalar loads answer out of order, so
-// the first wait for a source is a wait for the next words too), then the sum.
-template <int A, bool GRAD, bool KEPT, int MODE, bool MOM>
-__device__ __forceinline__ void sweep_record(const HopSweepArgs& a, const SweepWords<hop_sweep_words(A)>& h,
-                                             SweepWords<hop_sweep_words(A)>& next, sweep_words ahead, SweepLane& l) {
-    float x[A], g = 0.f;
-    next.load(ahead);
-#pragma unroll
-    for (int t = 0; t < A; ++t) x[t] = sweep_local(l, h[kSweepHead + 2 * t]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (GRAD) g = sweep_grad<MODE>(a, h, l);
-    if (GRAD && MODE == HOP_GRAD_SYNTH) asm volatile("" : "+v"(g));        // computed here, not where it is used
-    __builtin_amdgcn_sched_barrier(0);
-    float acc = sweep_first<MOM>(h[kSweepHead + 1], x[0]);
-#pragma unroll
-    for (int t = 1; t < A; ++t) acc = fmaf(__uint_as_float(h[kSweepHead + 2 * t + 1]), x[t], acc);
-    if (GRAD) acc = sweep_apply<MOM>(a, h, l, g, acc);
-    next.hold();                                           // else the compiler loads them where they are first needed
-    if (KEPT) sweep_local(l, h[1]) = acc;
-    else sweep_put(a, h, l, acc);
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// a run of such records, two a turn so that their words need not be moved; returns the words behind it
-template <int A, bool GRAD, bool KEPT, int MODE, bool MOM>
-__device__ __forceinline__ sweep_words sweep_run(const HopSweepArgs& a, sweep_words rec, uint32_t count, SweepLane& l) {
-    constexpr int N = hop_sweep_words(A);
-    SweepWords<N> even, odd;
-    even.load(rec);
-    for (;;) {
-        rec += N;
-        sweep_record<A, GRAD, KEPT, MODE, MOM>(a, even, odd, rec, l);
-        if (--count == 0) break;
-        rec += N;
-        sweep_record<A, GRAD, KEPT, MODE, MOM>(a, odd, even, rec, l);
-        if (--count == 0) break;
-    }
-    return rec;                                            // the words loaded behind the last record were not used
-}
-
-// a run of any records
-template <int MODE, bool MOM>
-__device__ sweep_words sweep_run_any(const HopSweepArgs& a, sweep_words rec, uint32_t count, SweepLane& l) {
-    do {
-        SweepWords<kSweepHead> h;
-        h.load(rec);
-        const sweep_words term = rec + kSweepHead;
-        float acc = sweep_first<MOM>(term[1], sweep_local(l, term[0]));
-        for (uint32_t t = 1; t < h[7]; ++t) acc = fmaf(__uint_as_float(term[2 * t + 1]), sweep_local(l, term[2 * t]), acc);
-        if (MODE != HOP_GRAD_ZERO && (h[0] & kSweepGrad))
-            acc = sweep_apply<MOM>(a, h, l, sweep_grad<MODE>(a, h, l), acc);
-        sweep_put(a, h, l, acc);
-        rec += hop_sweep_words((int)h[7]);
-    } while (--count);
-    return rec;
-}
-
-// `n` vectors (rows of `base`) into their local slots, eight loads in flight
-__device__ __forceinline__ void sweep_fill(const uint32_t* __restrict__ list, int n, const float* base, int64_t stride,
-                                           const SweepLane& l) {
-    for (int k = 0; k < n; k += 8) {
-        float t[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (k + q < n) t[q] = sweep_load(base + (int64_t)list[2 * (k + q)] * stride, l);
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (k + q < n) sweep_local(l, list[2 * (k + q) + 1]) = t[q];
-    }
-}
-
-template <int MODE, bool MOM>
-__device__ __forceinline__ void sweep_columns(const HopSweepArgs& a, SweepLane& l) {
-    const uint32_t* lists = a.program + a.first_load;
-    sweep_fill(lists, a.n_loads, a.ring, a.stride, l);
-    lists += 2 * a.n_loads;
-    if (MOM) sweep_fill(lists, a.n_vel, a.vel, a.stride, l);
-    if (MODE == HOP_GRAD_EXTERNAL) l.ahead = sweep_external(a, (uint32_t)a.first_external, l);
-    if (a.zero >= 0) sweep_local(l, (uint32_t)a.zero) = 0.f;            // the missing source of an odd record
-    const sweep_words runs = (sweep_words)a.program;
-    sweep_words rec = runs + a.first_record;
-    uint32_t ahead = runs[0];
-    for (int k = 0; k < a.n_runs; ++k) {
-        const uint32_t run = ahead, count = run >> 8;
-        ahead = runs[k + 1];
-        static_assert(kSweepInline == 12, "the switches below unroll 1..12 sources");
-#define HOP_SWEEP_CASE(AA)                                                                     \
-    case AA: rec = sweep_run<AA, false, true, MODE, MOM>(a, rec, count, l); continue;          \
-    case AA + 32: rec = sweep_run<AA, false, false, MODE, MOM>(a, rec, count, l); continue;
-#define HOP_SWEEP_GRAD(AA)                                                                     \
-    case AA + 16: rec = sweep_run<AA, true, true, MODE, MOM>(a, rec, count, l); continue;      \
-    case AA + 48: rec = sweep_run<AA, true, false, MODE, MOM>(a, rec, count, l); continue;
-        switch (run & 0xFFu) {
-            HOP_SWEEP_CASE(1) HOP_SWEEP_CASE(2) HOP_SWEEP_CASE(3) HOP_SWEEP_CASE(4) HOP_SWEEP_CASE(5) HOP_SWEEP_CASE(6)
-            HOP_SWEEP_CASE(7) HOP_SWEEP_CASE(8) HOP_SWEEP_CASE(9) HOP_SWEEP_CASE(10) HOP_SWEEP_CASE(11) HOP_SWEEP_CASE(12)
-            default: break;
-        }
-        if (MODE != HOP_GRAD_ZERO) switch (run & 0xFFu) {
-            HOP_SWEEP_GRAD(1) HOP_SWEEP_GRAD(2) HOP_SWEEP_GRAD(3) HOP_SWEEP_GRAD(4) HOP_SWEEP_GRAD(5) HOP_SWEEP_GRAD(6)
-            HOP_SWEEP_GRAD(7) HOP_SWEEP_GRAD(8) HOP_SWEEP_GRAD(9) HOP_SWEEP_GRAD(10) HOP_SWEEP_GRAD(11) HOP_SWEEP_GRAD(12)
-            default: break;
-        }
-        rec = sweep_run_any<MODE, MOM>(a, rec, count, l);
-#undef HOP_SWEEP_CASE
-#undef HOP_SWEEP_GRAD
-    }
-    if (MOM)
-        for (int n = 0; n < a.n_vel; ++n)
-            sweep_store(a.vel + (int64_t)lists[2 * n] * a.stride, l, sweep_local(l, lists[2 * n + 1]));
-}
-
-template <int MODE, bool MOM>
-__global__ __launch_bounds__(64) void sweep_kernel(const HopSweepArgs a) {
-    extern __shared__ float sweep_lds[];
-    const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const uint32_t table = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)tableS;
+    const int64_t c = (int64_t)blockIdx.x * kSweepThreads + threadIdx.x;
     if (c >= a.d) return;                              // the wavefront at the end of the vectors: fewer lanes, the same way
-    SweepLane l{(char*)(sweep_lds + threadIdx.x), c, fold16((uint32_t)c), 0.f};
-    sweep_columns<MODE, MOM>(a, l);
+    const uint32_t lane = threadIdx.x * (uint32_t)sizeof(float), folded = fold16((uint32_t)c);
+    const uint64_t columns = (uint64_t)blockIdx.x * kSweepThreads * sizeof(float);
+    static_assert(LOCAL == 48 || LOCAL == 80 || LOCAL == 112 || LOCAL == kSweepRegisters, "16 registers beside the local slots");
+    if constexpr (LOCAL == 48) HOP_SWEEP_ASM(HOP_SWEEP_V64);
+    else if constexpr (LOCAL == 80) HOP_SWEEP_ASM(HOP_SWEEP_V96);
+    else if constexpr (LOCAL == 112) HOP_SWEEP_ASM(HOP_SWEEP_V128);
+    else HOP_SWEEP_ASM(HOP_SWEEP_V184);
 }
 
 // ------------------------------------------------------------------ wavefront reductions ----
@@ -1374,16 +1472,25 @@ int hopk_synth(const HopGradJob* jobs_dev, int n_jobs, int reverse, int64_t d, v
     return launch_status();
 }
 
+template <int MODE, bool MOM>
+static void launch_sweep(const HopSweepArgs& a, unsigned grid, void* stream) {
+    const dim3 blocks(grid), threads(kSweepThreads);
+    const hipStream_t st = (hipStream_t)stream;
+    if (a.n_local <= 48) hipLaunchKernelGGL((sweep_kernel<MODE, MOM, 48>), blocks, threads, 0, st, a);
+    else if (a.n_local <= 80) hipLaunchKernelGGL((sweep_kernel<MODE, MOM, 80>), blocks, threads, 0, st, a);
+    else if (a.n_local <= 112) hipLaunchKernelGGL((sweep_kernel<MODE, MOM, 112>), blocks, threads, 0, st, a);
+    else hipLaunchKernelGGL((sweep_kernel<MODE, MOM, kSweepRegisters>), blocks, threads, 0, st, a);
+}
 template <int MODE>
 static void launch_sweep(const HopSweepArgs& a, unsigned grid, void* stream) {
-    const size_t lds = (size_t)a.n_local * 64 * sizeof(float);
-    if (a.vel) hipLaunchKernelGGL((sweep_kernel<MODE, true>), dim3(grid), dim3(64), lds, (hipStream_t)stream, a);
-    else hipLaunchKernelGGL((sweep_kernel<MODE, false>), dim3(grid), dim3(64), lds, (hipStream_t)stream, a);
+    if (a.velocities) launch_sweep<MODE, true>(a, grid, stream);
+    else launch_sweep<MODE, false>(a, grid, stream);
 }
 
 int hopk_sweep(const HopSweepArgs& a, void* stream) {
-    if (a.n_runs <= 0) return 0;
-    const int64_t grid = (a.d + 63) / 64;
+    if (a.n_records <= 0) return 0;
+    if (a.n_local > kSweepRegisters) return (int)hipErrorInvalidValue;
+    const int64_t grid = (a.d + kSweepThreads - 1) / kSweepThreads;
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
     if (a.mode == HOP_GRAD_SYNTH) launch_sweep<HOP_GRAD_SYNTH>(a, (unsigned)grid, stream);
     else if (a.mode == HOP_GRAD_EXTERNAL) launch_sweep<HOP_GRAD_EXTERNAL>(a, (unsigned)grid, stream);

@@ -779,6 +779,7 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
                     if (!dd.X || !dd.y) return HOP_ERR_STATE;
                     gj.X = dd.X;
                     gj.y = dd.y;
+                    gj.k0 = (uint32_t)c->opts.loss;
                     gj.partial = c->partial + (int64_t)i * partial_floats(c->d, c->opts.batch);
                     // the gradient kernel applies -eta g (through the velocity, if any) itself, so no dense g is
                     // written and read back: in place on the vector the mix has reduced (small minibatches), or on

@@ -70,7 +70,7 @@ struct alignas(16) HopGradJob {
     const HopMixJob* reduce;   // dense with out set: if set, out = sum_a w'_a x_a - eta g (the gradient kernel does the
                                // record's Reduce too); if null, out already holds the reduced vector
     float eta, mu;             // dense with out set
-    uint32_t k0, k1, k2;       // synth: hash keys of (seed, worker, iteration)
+    uint32_t k0, k1, k2;       // synth: hash keys of (seed, worker, iteration); dense: k0 the loss, for the margins
     float scale;               // synth: fp32 factor
 };
 

@@ -1159,15 +1159,20 @@ constexpr int kSegVec = 16;
 constexpr int kSeg4 = kThreads * kSegVec;             // float4 per segment
 constexpr int64_t kSegCols = (int64_t)kSeg4 * 4;
 
-// ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t.
-// Each row is summed in the same order whatever ROWS is.
-template <int ROWS, bool STREAM>
+// ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t,
+// or, where a row has one segment only, its coefficient: the gradient kernel then has that to load and nothing to work out
+// (the label's load under the row's; see dense_grad_chunk).  Each row is summed in the same order whatever ROWS is.
+template <int ROWS, bool STREAM, bool ONE>
 __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, int seg,
                                                   int m0, float (*red)[kThreads / 64]) {
     const float* w = job->w;
     const float* x[ROWS];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) x[r] = job->X + (int64_t)job->rows[min(m0 + r, B - 1)] * d;
+    const int mine = m0 + (int)threadIdx.x;
+    const bool writes = threadIdx.x < ROWS && mine < B;
+    float y = 0.f;
+    if (ONE && writes) y = job->y[job->rows[mine]];
     const int64_t lo = (int64_t)seg * kSegCols;
     const int64_t hi = min(d, lo + kSegCols);
     float a[ROWS][4];
@@ -1205,20 +1210,21 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
         if (lane == 0) red[r][wv] = v;
     }
     __syncthreads();
-    if (threadIdx.x < ROWS && m0 + threadIdx.x < B) {
+    if (writes) {
         float t = 0.f;
 #pragma unroll
         for (int k = 0; k < kThreads / 64; ++k) t += red[threadIdx.x][k];
-        job->partial[(int64_t)(m0 + threadIdx.x) * nseg + seg] = t;
+        if (ONE) job->coef[mine] = loss_coef(y, t, 1.0f / (float)B, (int)job->k0);
+        else job->partial[(int64_t)mine * nseg + seg] = t;
     }
 }
 
 // one workgroup per (job, ROWS minibatch rows, column segment); b: its index
-template <int ROWS, bool STREAM>
+template <int ROWS, bool STREAM, bool ONE>
 __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
                                                    int64_t b, float (*red)[kThreads / 64]) {
     const int groups = (B + ROWS - 1) / ROWS;
-    dense_margin_rows<ROWS, STREAM>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
+    dense_margin_rows<ROWS, STREAM, ONE>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
                             (int)((b / nseg) % groups) * ROWS, red);
 }
 
@@ -1236,20 +1242,20 @@ constexpr int kMarginRows = 4;
 constexpr int64_t kMarginFew = 384;
 constexpr int64_t kMarginNear = 128ll << 20;           // bytes of rows in a launch up to which they are left in the caches
 
-template <int ROWS, bool STREAM>
+template <int ROWS, bool STREAM, bool ONE>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
                                                                 int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_block<ROWS, STREAM>(jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_block<ROWS, STREAM, ONE>(jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
 // allocated, copied or staged.  Per call: 128 x 65536 dense 42.5 -> 28.4 us, 64 x 1024 without allocation 10.4 -> 7.7 us
 // (one launch fewer), 256 samples of 64 non-zeros on 2^20 columns 33.0 -> 18.6 us (margins beside the dense part).
-template <int ROWS, bool STREAM>
+template <int ROWS, bool STREAM, bool ONE>
 __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob job, int B, int64_t d, int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_rows<ROWS, STREAM>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
+    dense_margin_rows<ROWS, STREAM, ONE>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
 }
 
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
@@ -1265,7 +1271,8 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
         mix_block<VEC, NT, MAP, kThreads>(mix_jobs, n_mix, d, n_chunks, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block<1, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    if (nseg == 1) dense_margin_block<1, false, true>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    else dense_margin_block<1, false, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
@@ -1301,12 +1308,14 @@ constexpr int kSegThread = 64;
 
 // (Loading a wavefront's 8 rows at once, active or not, while the coefficients are still being worked out - one chain of
 // loads instead of two, for minibatches of up to 8 SPLIT rows - was slower: 4 x 1024, B = 64: 364 -> 460 us per pass.)
-template <int SPLIT, int WIDE>
+// ONE: a row has one segment, and the margins have left the coefficients themselves: one round of loads less in the chain to
+// the rows (4 workers x 1024 columns, B = 64: 360 -> 338 us a pass).
+template <int SPLIT, int WIDE, bool ONE>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
     __shared__ float coefS[kMaxB];
     __shared__ int rowS[kMaxB + kRowUnroll];
-    __shared__ float allC[kMaxB];
+    __shared__ float allC[ONE ? 1 : kMaxB];
     __shared__ int nactS;
     constexpr int kCols = 64 * WIDE;                   // threads side by side
     __shared__ float4 joinS[SPLIT > 1 ? (SPLIT - 1) * kCols : 1];
@@ -1333,36 +1342,39 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
             o = ldu4(out, c, n);
         }
     }
-    auto put_coef = [&](int m, float dot) {
-        const float cm = loss_coef(job->y[job->rows[m]], dot, invB, loss);
-        allC[m] = cm;
-        if (chunk == 0) job->coef[m] = cm;
-    };
-    if (WIDE == 1 || nseg <= kSegThread) {
-        for (int m = threadIdx.x; m < B; m += kCols * SPLIT) {
-            float dot = 0.f;
-            for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
-            put_coef(m, dot);
+    if (!ONE) {
+        auto put_coef = [&](int m, float dot) {
+            const float cm = loss_coef(job->y[job->rows[m]], dot, invB, loss);
+            allC[m] = cm;
+            if (chunk == 0) job->coef[m] = cm;
+        };
+        if (WIDE == 1 || nseg <= kSegThread) {
+            for (int m = threadIdx.x; m < B; m += kCols * SPLIT) {
+                float dot = 0.f;
+                for (int sg = 0; sg < nseg; ++sg) dot += job->partial[(int64_t)m * nseg + sg];
+                put_coef(m, dot);
+            }
+        } else {                                           // a wavefront per row
+            for (int m = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64); m < B; m += WIDE * SPLIT) {
+                float dot = 0.f;
+                for (int sg = (int)threadIdx.x % 64; sg < nseg; sg += 64) dot += job->partial[(int64_t)m * nseg + sg];
+                dot = wave_sum(dot);
+                if (threadIdx.x % 64 == 0) put_coef(m, dot);
+            }
         }
-    } else {                                           // a wavefront per row
-        for (int m = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64); m < B; m += WIDE * SPLIT) {
-            float dot = 0.f;
-            for (int sg = (int)threadIdx.x % 64; sg < nseg; sg += 64) dot += job->partial[(int64_t)m * nseg + sg];
-            dot = wave_sum(dot);
-            if (threadIdx.x % 64 == 0) put_coef(m, dot);
-        }
+        __syncthreads();
     }
-    __syncthreads();
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (threadIdx.x < 64) {                        // first wavefront compacts the active rows, keeping order
         int count = 0, any = 0;
         for (int base = 0; base < B; base += 64) {
             const int m = base + threadIdx.x;
-            const float cm = m < B ? allC[m] : 0.f;
+            const float cm = m < B ? ONE ? job->coef[m] : allC[m] : 0.f;
+            const int id = ONE && m < B ? job->rows[m] : 0;
             const bool act = cm != 0.f;
             const unsigned long long mask = __ballot(act);
             const int pos = count + __popcll(mask & ((1ull << threadIdx.x) - 1ull));
-            const int row = act ? job->rows[m] : 0;
+            const int row = act ? ONE ? id : job->rows[m] : 0;
             if (act) {
                 coefS[pos] = cm;
                 rowS[pos] = row;
@@ -1418,20 +1430,20 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
     stu4(out, c, n, fma4(-job->eta, gv, o));
 }
 
-template <int SPLIT, int WIDE>
+template <int SPLIT, int WIDE, bool ONE>
 __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
                                                                 int64_t d, int nseg, float lambda, int loss,
                                                                 int64_t n_chunks) {
     int j;
     int64_t chunk;
     if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
-        dense_grad_chunk<SPLIT, WIDE>(jobs + j, B, d, nseg, lambda, loss, chunk);
+        dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + j, B, d, nseg, lambda, loss, chunk);
 }
 
-template <int SPLIT, int WIDE>
+template <int SPLIT, int WIDE, bool ONE>
 __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
                                                              int loss) {
-    dense_grad_chunk<SPLIT, WIDE>(&job, B, d, nseg, lambda, loss, blockIdx.x);
+    dense_grad_chunk<SPLIT, WIDE, ONE>(&job, B, d, nseg, lambda, loss, blockIdx.x);
 }
 
 // ------------------------------------------------------------------- CSR SVM: margins ----
@@ -1552,7 +1564,8 @@ __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPa
         pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
         return;
     }
-    dense_margin_block<1, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    if (nseg == 1) dense_margin_block<1, false, true>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    else dense_margin_block<1, false, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
 }
 
 template <int VEC, int NT, int MAP>
@@ -1748,15 +1761,17 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;      // few is used only where grid is small
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
-    if (grid < kMarginFew && near)
-        hipLaunchKernelGGL((dense_margin_kernel<1, false>), dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream,
-                           jobs_dev, B, d, nseg);
-    else if (grid < kMarginFew)
-        hipLaunchKernelGGL((dense_margin_kernel<1, true>), dim3((unsigned)few), dim3(kThreads), 0, (hipStream_t)stream,
-                           jobs_dev, B, d, nseg);
-    else
-        hipLaunchKernelGGL((dense_margin_kernel<kMarginRows, true>), dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream,
-                           jobs_dev, B, d, nseg);
+#define HOP_MARGINS(BLOCKS, ROWS, STREAM)                                                                                   \
+    do {                                                                                                                    \
+        if (nseg == 1) hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, true>), dim3((unsigned)(BLOCKS)), dim3(kThreads), \
+                                          0, (hipStream_t)stream, jobs_dev, B, d, nseg);                                    \
+        else hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, false>), dim3((unsigned)(BLOCKS)), dim3(kThreads), 0,    \
+                                (hipStream_t)stream, jobs_dev, B, d, nseg);                                                 \
+    } while (0)
+    if (grid < kMarginFew && near) HOP_MARGINS(few, 1, false);
+    else if (grid < kMarginFew) HOP_MARGINS(few, 1, true);
+    else HOP_MARGINS(grid, kMarginRows, true);
+#undef HOP_MARGINS
     return launch_status();
 }
 
@@ -1775,15 +1790,16 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
     const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;
     const int64_t grid = grid_for(n_jobs, n_chunks);
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    if (shape == GradShape::few)
-        hipLaunchKernelGGL((dense_grad_kernel<8, 1>), dim3((unsigned)grid), dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs,
-                           B, d, nseg, lambda, loss, n_chunks);
-    else if (shape == GradShape::some)
-        hipLaunchKernelGGL((dense_grad_kernel<4, 1>), dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs,
-                           B, d, nseg, lambda, loss, n_chunks);
-    else
-        hipLaunchKernelGGL((dense_grad_kernel<1, 4>), dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, jobs_dev, n_jobs,
-                           B, d, nseg, lambda, loss, n_chunks);
+#define HOP_GRADS(SPLIT, WIDE, ONE)                                                                                         \
+    hipLaunchKernelGGL((dense_grad_kernel<SPLIT, WIDE, ONE>), dim3((unsigned)grid), dim3(64 * SPLIT * WIDE), 0,              \
+                       (hipStream_t)stream, jobs_dev, n_jobs, B, d, nseg, lambda, loss, n_chunks)
+    if (shape == GradShape::few && nseg == 1) HOP_GRADS(8, 1, true);
+    else if (shape == GradShape::few) HOP_GRADS(8, 1, false);
+    else if (shape == GradShape::some && nseg == 1) HOP_GRADS(4, 1, true);
+    else if (shape == GradShape::some) HOP_GRADS(4, 1, false);
+    else if (nseg == 1) HOP_GRADS(1, 4, true);
+    else HOP_GRADS(1, 4, false);
+#undef HOP_GRADS
     return launch_status();
 }
 
@@ -1942,28 +1958,37 @@ int hopk_split_end(const HopSplit& p, const HopSweepArgs& a, void* stream) {
     return launch_status();
 }
 
-int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
+int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
     const hipStream_t st = (hipStream_t)stream;
+    HopGradJob job = given;
     if (mode == HOP_GRAD_SVM_DENSE) {
+        job.k0 = (uint32_t)loss;
         const int nseg = hopk_dense_nseg(d);
         const int64_t few = (int64_t)B * nseg, grid = (int64_t)((B + kMarginRows - 1) / kMarginRows) * nseg;
         if (B > kMaxB) return (int)hipErrorInvalidValue;
         if (grid > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-        if (grid < kMarginFew && (int64_t)B * d * 4 <= kMarginNear)
-            hipLaunchKernelGGL((dense_margin_one<1, false>), dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
+        const dim3 threads(kThreads), rows((unsigned)few), groups((unsigned)grid);
+        const bool near = (int64_t)B * d * 4 <= kMarginNear;
+        if (nseg == 1 && grid < kMarginFew)                          // a row of one segment is at most 64 KB: always near
+            hipLaunchKernelGGL((dense_margin_one<1, false, true>), rows, threads, 0, st, job, B, d, nseg);
+        else if (grid < kMarginFew && near)
+            hipLaunchKernelGGL((dense_margin_one<1, false, false>), rows, threads, 0, st, job, B, d, nseg);
         else if (grid < kMarginFew)
-            hipLaunchKernelGGL((dense_margin_one<1, true>), dim3((unsigned)few), dim3(kThreads), 0, st, job, B, d, nseg);
+            hipLaunchKernelGGL((dense_margin_one<1, true, false>), rows, threads, 0, st, job, B, d, nseg);
         else
-            hipLaunchKernelGGL((dense_margin_one<kMarginRows, true>), dim3((unsigned)grid), dim3(kThreads), 0, st, job, B, d, nseg);
+            hipLaunchKernelGGL((dense_margin_one<kMarginRows, true, false>), groups, threads, 0, st, job, B, d, nseg);
         if (const int rc = launch_status()) return rc;
         const GradShape shape = grad_shape(1, d, nseg);
         const unsigned chunks = (unsigned)((d + 255) / 256);
-        if (shape == GradShape::few)
-            hipLaunchKernelGGL((dense_grad_one<8, 1>), dim3(chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
+        static_assert((kMaxB + kMarginRows - 1) / kMarginRows < kMarginFew && kSegCols / 256 <= kGradFew, "one segment: few of both");
+        if (nseg == 1)
+            hipLaunchKernelGGL((dense_grad_one<8, 1, true>), dim3(chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
+        else if (shape == GradShape::few)
+            hipLaunchKernelGGL((dense_grad_one<8, 1, false>), dim3(chunks), dim3(512), 0, st, job, B, d, nseg, lambda, loss);
         else if (shape == GradShape::some)
-            hipLaunchKernelGGL((dense_grad_one<4, 1>), dim3(chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
+            hipLaunchKernelGGL((dense_grad_one<4, 1, false>), dim3(chunks), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
         else
-            hipLaunchKernelGGL((dense_grad_one<1, 4>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
+            hipLaunchKernelGGL((dense_grad_one<1, 4, false>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
         const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
         const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;

@@ -190,10 +190,8 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         }
         return runs;
     };
-    // A run starts with a load that nothing covers.  Where runs are short, records with an odd number of sources take a
-    // zero with weight -0 as one more: half as many kinds (32 workers x 25 M columns, 4.5 -> 8.5 records per run: 88.4 ->
-    // 82 ms; 16 x 2 M with momentum, 1.7 -> 2.3: 1.75 -> 1.63 ms).  Where they are long that only costs the source and a
-    // local slot (64 workers with 5 sources each in lock-step: 5.47 -> 6.74 ms).
+    // Where runs are short, records with an odd number of sources take a zero with weight -0 as one more: half as many
+    // kinds.  That is for whoever runs a plan kind by kind; hop_lower_sweep takes records one by one and leaves the zeros out.
     const bool even = arrange() * 8 > R;
     if (even) {
         for (int& k : kind)

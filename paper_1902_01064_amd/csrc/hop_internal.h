@@ -81,7 +81,7 @@ struct alignas(16) HopGradJob {
 // (none, synthetic, external): every column can then run the whole pass by itself.  Words of 32 bits:
 //   runs     count << 8 | kind for every run of records of one kind: the number of sources (possibly rounded up to an even
 //            one), + kSweepGrad << 4 with a gradient, + kSweepStore << 4 where a result is not just kept in a local slot
-//            (the flags of each record say); kSweepOther: more sources than are unrolled
+//            (the flags of each record say); kSweepOther: more sources than that
 //   records  0 flags, 1 local slot of the result, 2 ring slot it is stored to, 3 local slot of the velocity, 4..6 key[]
 //            (synthetic: hash keys, the first two folded; external: the worker, and the worker of
 //            the next record with a gradient, whose load is issued ahead), 7 number of sources, then (local slot,
@@ -90,9 +90,9 @@ struct alignas(16) HopGradJob {
 //   loads    (ring slot, local slot) of the values read from the rings, then (worker, local slot) of the velocities
 // A local slot is written as its byte offset.
 constexpr int kSweepHead = 8;
-constexpr int kSweepInline = 12;        // most sources that the kernel unrolls
+constexpr int kSweepInline = 12;        // most sources of the kernel's chain
 constexpr int kSweepOther = 255;
-constexpr int kSweepMaxLocal = 160;     // most local slots: 40 KB of LDS per wavefront, 4 wavefronts per CU
+constexpr int kSweepMaxLocal = 160;     // most local slots: 184 registers, 2 wavefronts per SIMD
 enum : uint32_t { kSweepGrad = 1u, kSweepStore = 2u, kSweepKeep = 4u };
 constexpr int hop_sweep_words(int A) { return kSweepHead + (2 * A + 3) / 4 * 4; }
 

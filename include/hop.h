@@ -136,10 +136,7 @@ typedef struct {
                                      front of the first of them (0 or 1: wave by wave; at most 16); every
                                      worker then has that many gradient buffers in the arena.  Same values either
                                      way; fewer switches between the arithmetic-bound generator and the
-                                     memory-bound Reduce + Apply, which runs slower right after one.
-                                     HOP_GRAD_SVM_CSR without momentum: the same memory lets whole passes keep the
-                                     columns that minibatch rows hold apart (see hop_step), where they are at most
-                                     about grad_ahead / depth of all */
+                                     memory-bound Reduce + Apply, which runs slower right after one */
 } hop_opts;
 
 typedef struct {
@@ -275,10 +272,7 @@ int hop_schedule_bind(hop_ctx* ctx, hop_schedule* s, void* workspace, size_t byt
  * whole schedule (wave_begin 0, wave_end -1 or n_waves) and is not being profiled runs as ONE launch when
  * gradients are absent, synthetic or external and an estimate of both ways has it ahead (it is not with very
  * many workers, nor with many or wide records per wave on a narrow model): every column then goes through all records by itself, no gradient is
- * written to memory, and the results are those of the waves bit for bit.  Such a call on CSR data without momentum
- * may find the columns that its rows hold (anew in every pass), run the waves on a copy of those only, kept in the
- * gradient buffers, and take all others through the records column by column, where an estimate has that ahead and
- * the buffers have room; a pass whose rows hold more columns than that runs on all of them.  The results are the same in every
+ * written to memory, and the results are those of the waves bit for bit.  The results are the same in every
  * arrangement up to the rounding of the sums.  The first call for a schedule (and the first after the gradient
  * source or a data set changed) copies the descriptors into the schedule's workspace with synchronous
  * host-to-device copies; after that the call only launches.  Records of one wave touch no

@@ -72,7 +72,6 @@ void free_device_side(hop_schedule* s) {
     s->rows_dev = nullptr;
     s->coef_dev = nullptr;
     s->sweep = HopSweepArgs{};
-    s->split = HopSplit{};
     s->built_mode = -1;
     if (s->graph_exec) (void)hipGraphExecDestroy((hipGraphExec_t)s->graph_exec);
     s->graph_exec = nullptr;
@@ -338,14 +337,6 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
     const uint32_t partial = (uint32_t)plan.n_local;         // the sum so far of a record in parts
     std::vector<std::pair<uint32_t, uint32_t>> terms;
     const uint32_t* p = plan.program.data() + plan.first_record;
-    std::vector<const float*> stored;                        // with touched columns apart: where those of each stored vector are
-    if (at.own)
-        for (int r = 0; r < n_ops; ++r, p += hop_sweep_words((int)p[7]))
-            if (p[0] & kSweepStore) stored.push_back(at.own + (int64_t)p[2] * at.own_stride);
-    const size_t n_stored = stored.size();
-    stored.resize(n_stored + kSweepAhead, at.own);           // behind the last: loaded and not used
-    size_t next_stored = 0;
-    p = plan.program.data() + plan.first_record;
     for (int r = 0; r < n_ops; ++r, p += hop_sweep_words((int)p[7])) {
         terms.clear();
         for (uint32_t t = 0; t < p[7]; ++t)
@@ -371,10 +362,6 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
             else if (grad) std::copy(p + 4, p + 7, out.begin() + (std::ptrdiff_t)w + 2);
             out[w + 15] = p[3] / kLane;
             if (store) put_address(w + 30, at.ring + (int64_t)p[2] * at.stride);
-            if (store && at.own) {
-                out[w + 4] = kSweepMerge * (uint32_t)(next_stored % kSweepAhead + (w / kSweepRecord % 2 ? kSweepAhead : 0));
-                put_address(w + 2, stored[kSweepAhead + next_stored++]);
-            }
             if (!last) terms[first + --n] = std::make_pair(partial, kOne);    // first source of the next part
         }
     }
@@ -398,11 +385,6 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
     list(loads, plan.n_loads, at.ring);
     list(velocities, plan.n_vel, at.vel);
     args->n_load_groups = groups((size_t)args->first_list);
-    if (at.own) {
-        const size_t firsts = out.size();
-        out.resize(firsts + 16, 0u);                         // loaded at once
-        for (int k = 0; k < kSweepAhead; ++k) put_address(firsts + 2 * (size_t)k, stored[(size_t)k]);
-    }
     const size_t stores = out.size();
     list(velocities, plan.n_vel, at.vel);
     args->n_store_groups = groups(stores);
@@ -577,115 +559,6 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     return HOP_OK;
 }
 
-// Sparse data: the gradient buffers, which such contexts have no other use for, hold a ring of the columns that a pass
-// touches, as wide as there is room for, and what says which they are.  Its stride, 0 where there is none.
-int64_t split_room(const hop_ctx* c, HopSplit* p) {
-    p->d = c->d;
-    const size_t have = (size_t)c->N * c->grad_ahead * c->stride * sizeof(float);
-    const size_t words = ws_round((size_t)((c->d + 63) / 64) * sizeof(HopSplitWord)), flags = ws_round((size_t)c->d + 16);
-    const size_t sums = ws_round((size_t)((c->d + 4095) / 4096) * sizeof(uint32_t)), tail = words + flags + sums + kWsAlign;
-    if (have <= tail) return 0;
-    int64_t stride = std::min<int64_t>((int64_t)((have - tail) / sizeof(float)) / ((int64_t)c->N * c->slots), c->stride) / 64;
-    stride = (stride - (stride % 2 == 0)) * 64;              // an odd number of 256 B, like the rings' own
-    if (stride < 4096 || stride >= 1 << 30) return 0;
-    char* at = (char*)c->gbuf + (have - tail) / kWsAlign * kWsAlign;
-    p->words = (HopSplitWord*)at;
-    p->flags = (uint8_t*)(at + words);
-    p->sums = (uint32_t*)(at + words + flags);
-    p->head = (HopSplitHead*)(at + words + flags + sums);
-    p->room = stride - 64;
-    return stride;
-}
-
-// Whether whole passes keep the touched columns apart, and what they need for it.  `room`: memory for the descriptors.
-int build_split(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, const std::vector<HopPairJob>& pairs, HopSplit p,
-                int64_t own_stride, int n_grad, char* room, size_t room_bytes) {
-    const int R = (int)mix.size(), slots = c->N * c->slots;
-    for (const HopPairJob& pj : pairs)
-        if (pj.U > HOP_PAIR_U) return HOP_OK;
-    if (n_grad == 0 || c->N > kSweepMaxLocal) return HOP_OK;
-    // What is saved: the part of the waves' vectors (at 5.6 TB/s) that holds untouched columns.  What it costs: the sweep, which
-    // takes twice the time of one without anything to put in, marking rows, places to look up in every wave.  Measured: 64
-    // workers x 2^24 columns, 37 % touched, mixes 71.9 -> 28.7 ms, sweep 27.3, the rest 2.6, a pass 76.3 -> 63.6 ms; 16 x 2^20, 57 %
-    // touched, 1600 records in 467 waves: mixes 5.2 -> 4.2, sweep 1.1, scatters and the rest 0.5, a pass 7.3 -> 7.9 ms.
-    double moved = 0;
-    for (int w = 0; w < s->n_waves; ++w)
-        moved += 4.0 * (double)c->d * (s->wave_sources[w] + (s->wave_begin[w + 1] - s->wave_begin[w])) / 5.6e6;
-    SweepCost cost = sweep_cost(c, s, mix);
-    cost.mode = HOP_GRAD_ZERO;
-    cost.gradients = 0;
-    const double fixed = 30.0 + 1.5 * s->n_waves + 0.0008 * (double)n_grad * s->batch + 4.0 * (double)c->d * c->N / 4e6;
-    if (moved < fixed + 2.0 * cost.sweep_us(c->N)) return HOP_OK;
-    HOP_LAUNCH(c, hopk_split_plan(p, s->grad_dev, n_grad, s->batch, c->stream));
-    HopSplitHead head;
-    HOP_HIP(c, hipMemcpyAsync(&head, p.head, sizeof(head), hipMemcpyDeviceToHost, (hipStream_t)c->stream));
-    HOP_HIP(c, hipStreamSynchronize((hipStream_t)c->stream));
-    if (!head.fits) return HOP_OK;
-    const double share = (double)head.touched / (double)c->d;
-    if (moved * (1.0 - share) < fixed + 2.0 * cost.sweep_us(c->N)) return HOP_OK;
-    auto slot_of = [c](const float* v) { return (int)((v - c->ring) / c->stride); };
-    auto own = [&](const float* v) { return c->gbuf + (int64_t)slot_of(v) * own_stride; };
-    std::vector<HopSweepOp> ops((size_t)R);
-    std::vector<HopPairArg> args(pairs.size());
-    std::vector<int> at((size_t)slots, -1);                      // position of the record that writes a slot, this wave
-    for (int w = 0; w < s->n_waves; ++w) {
-        for (int q = s->wave_begin[w]; q < s->wave_begin[w + 1]; ++q) {
-            ops[q].wave = w;
-            ops[q].out_slot = slot_of(mix[q].out);
-            ops[q].worker = s->worker[s->wave_order[q]];
-            at[ops[q].out_slot] = q;
-        }
-        for (int q = s->pair_begin[w]; q < s->pair_begin[w + 1]; ++q) {
-            const HopPairJob& pj = pairs[q];
-            HopPairArg& a = args[q];
-            std::memset(&a, 0, sizeof(a));
-            a.U = (uint8_t)pj.U;
-            a.G = (uint8_t)pj.G;
-            for (int u = 0; u < pj.U; ++u) a.src[u] = own(pj.src[u]);
-            for (int r = 0; r < pj.G; ++r) {
-                a.out[r] = const_cast<float*>(own(pj.out[r]));
-                a.mask[r] = pj.mask[r];
-                std::copy(pj.w[r], pj.w[r] + HOP_PAIR_U, a.w[r]);
-                HopSweepOp& op = ops[at[slot_of(pj.out[r])]];
-                for (int u = 0; u < pj.U; ++u)
-                    if ((pj.mask[r] >> u) & 1u) op.terms.emplace_back(slot_of(pj.src[u]), pj.w[r][u]);
-            }
-        }
-    }
-    HopSweepPlan plan;
-    if (!hop_plan_sweep(ops, slots, c->N, &plan)) return HOP_OK;
-    if (plan.n_local > kSplitLocal || moved * (1.0 - share) < fixed + 2.0 * cost.sweep_us(plan.n_local)) return HOP_OK;
-    HopSweepVectors vectors;
-    vectors.ring = c->ring;
-    vectors.stride = c->stride;
-    vectors.d = c->d;
-    vectors.own = c->gbuf;
-    vectors.own_stride = own_stride;
-    std::vector<uint32_t> words;
-    hop_lower_sweep(plan, R, vectors, &p.sweep, &words);
-    std::vector<uint64_t> copies;
-    const uint32_t* loads = plan.program.data() + plan.first_load;
-    for (int k = 0; k < plan.n_loads; ++k) {
-        const float* v = c->ring + (int64_t)loads[2 * k] * c->stride;
-        copies.push_back((uint64_t)(uintptr_t)v);
-        copies.push_back((uint64_t)(uintptr_t)own(v));
-    }
-    const size_t for_args = ws_round(args.size() * sizeof(HopPairArg)), for_copies = ws_round(copies.size() * sizeof(uint64_t));
-    if (plan.n_loads > 65535 || for_args + for_copies + words.size() * sizeof(uint32_t) > room_bytes) return HOP_OK;
-    HOP_HIP(c, hipMemcpy(room, args.data(), args.size() * sizeof(HopPairArg), hipMemcpyHostToDevice));
-    HOP_HIP(c, hipMemcpy(room + for_args, copies.data(), copies.size() * sizeof(uint64_t), hipMemcpyHostToDevice));
-    HOP_HIP(c, hipMemcpy(room + for_args + for_copies, words.data(), words.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-    p.own = (const HopPairArg*)room;
-    p.copies = (const uint64_t*)(room + for_args);
-    p.n_copies = plan.n_loads;
-    p.touched = head.touched;
-    p.sweep.program = (const uint32_t*)(room + for_args + for_copies);
-    p.sweep.d = c->d;
-    p.ready = true;
-    s->split = p;
-    return HOP_OK;
-}
-
 // Translate the schedule into device descriptors for the context's current gradient source.
 int build_jobs(hop_ctx* c, hop_schedule* s) {
     free_device_side(s);
@@ -729,9 +602,6 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
     s->wave_grad_bytes.assign(s->n_waves, 0.0);
     const float eta = c->opts.lr;
     std::vector<int> grad_seen((size_t)c->N, 0);
-    HopSplit split;
-    const int64_t own_stride = mode == HOP_GRAD_SVM_CSR && !c->vel ? split_room(c, &split) : 0;
-    auto own = [c, own_stride](const float* v) { return c->gbuf + (int64_t)((v - c->ring) / c->stride) * own_stride; };
     if (R > 0) s->mix_dev = (HopMixJob*)carve((size_t)R * sizeof(HopMixJob));
     auto has_gradient = [&](int e) {
         return (s->kind[e] == HOP_STEP || s->kind[e] == HOP_APPLY) && mode != HOP_GRAD_ZERO;
@@ -809,10 +679,6 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
                     } else {
                         // lambda w folds into the self term: sum_a w'_a x_a - eta lambda x_self - eta (sparse part)
                         mj.w[0] = mj.w[0] - eta * c->opts.lambda;
-                        if (own_stride) {
-                            gj.X = own(gj.w);
-                            gj.g = const_cast<float*>(own(gj.out));
-                        }
                     }
                 } else if (mode == HOP_GRAD_SYNTH) {
                     hoprng::synth_keys(c->opts.seed, i, s->iter[e], &gj.k0, &gj.k1, &gj.k2);
@@ -857,11 +723,6 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
     if (!grad.empty()) {
         s->grad_dev = (HopGradJob*)carve((size_t)R * sizeof(HopGradJob));
         HOP_HIP(c, hipMemcpy(s->grad_dev, grad.data(), grad.size() * sizeof(HopGradJob), hipMemcpyHostToDevice));
-    }
-    if (own_stride && R > 0) {
-        const int rc = build_split(c, s, mix, pairs, split, own_stride, (int)grad.size(), (char*)s->mix_dev,
-                                   (size_t)R * sizeof(HopMixJob));
-        if (rc != HOP_OK) return rc;
     }
     s->built_mode = mode;
     s->built_epoch = c->epoch;
@@ -1349,21 +1210,6 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
     return HOP_OK;
 }
 
-// A whole pass, never timed.
-static int launch_pass(hop_ctx* c, hop_schedule* s, void* stream) {
-    const HopSplit& p = s->split;
-    if (!p.ready) return launch_waves(c, s, 0, s->n_waves, stream, false);
-    HOP_LAUNCH(c, hopk_split_plan(p, s->grad_dev, s->grad_begin[s->n_waves], s->batch, stream));
-    HOP_LAUNCH(c, hopk_split_begin(p, stream));
-    for (int w = 0; w < s->n_waves; ++w) {
-        const int pb = s->pair_begin[w], gb = s->grad_begin[w];
-        HOP_LAUNCH(c, hopk_split_wave(p, p.own + pb, s->pair_dev + pb, s->pair_begin[w + 1] - pb, s->wave_sources[w], w & 1,
-                                      s->grad_dev + gb, s->grad_begin[w + 1] - gb, s->batch, c->opts.loss, c->opts.lr, stream));
-    }
-    HOP_LAUNCH(c, hopk_split_end(p, p.sweep, stream));
-    return HOP_OK;
-}
-
 // Record waves [0, n_waves) once into a HIP graph (captured on a stream of the library's own, default
 // priority; the caller's may be the null stream, which cannot be captured) and keep the executable.
 static int capture_graph(hop_ctx* c, hop_schedule* s) {
@@ -1378,7 +1224,7 @@ static int capture_graph(hop_ctx* c, hop_schedule* s) {
     }
     hipStream_t cs = (hipStream_t)c->capture_stream;
     HOP_HIP(c, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-    int rc = launch_pass(c, s, c->capture_stream);
+    int rc = launch_waves(c, s, 0, s->n_waves, c->capture_stream, false);
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(cs, &graph);
     if (rc != HOP_OK) {
@@ -1421,8 +1267,6 @@ int hop_step(hop_ctx* c, const hop_schedule* sched, int32_t wave_begin, int32_t 
         if (!s->graph_exec || s->graph_epoch != c->epoch || s->graph_mode != c->grad_mode)
             if ((rc = capture_graph(c, s)) != HOP_OK) return rc;
         HOP_HIP(c, hipGraphLaunch((hipGraphExec_t)s->graph_exec, (hipStream_t)c->stream));
-    } else if (!c->profiling && wave_begin == 0 && wave_end == s->n_waves) {
-        if ((rc = launch_pass(c, s, c->stream)) != HOP_OK) return rc;
     } else if ((rc = launch_waves(c, s, wave_begin, wave_end, c->stream, c->profiling)) != HOP_OK) {
         return rc;
     }

@@ -53,14 +53,14 @@ static_assert(sizeof(HopPairArg) * kPairArgs <= 4096 - 64, "kernel arguments");
 
 struct alignas(16) HopGradJob {
     // dense: X row-major rows x d; csr: rowptr/col/val
-    const float* X;            // csr, with the touched columns apart: w in their ring
+    const float* X;
     const int64_t* rowptr;
     const int32_t* col;
     const float* val;
     const float* y;
     const float* w;            // x_{k,i}: the version the gradient is taken at
     const int32_t* rows;       // B sample ids
-    float* g;                  // dense gradient buffer of the worker (dense / synth modes); csr, as X: out in that ring
+    float* g;                  // dense gradient buffer of the worker (dense / synth modes)
     float* coef;               // B hinge coefficients of this record
     float* partial;            // dense: B x nseg partial dot products
     float* out;                // csr: the vector the sparse part is scattered into; dense: if set, the gradient is
@@ -122,15 +122,11 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_
 //            word behind it: (local slot, weight) of the first source (k = 0), then of the others from the last to the second,
 //            15 local slot of the velocity, 30..31 address of the ring slot the result is stored to.  Short records of few
 //            sources need the first half only.  More than kSweepInline sources become several records, whose sums go
-//            through a local slot of their own.  Behind the last one: a record that enters nowhere, which ends the pass.
-//            With touched columns apart, in records whose result is stored: 2..3 address of the touched columns of the
-//            vector stored kSweepAhead such records later, 4 which of the kernel's registers they are in (kSweepMerge apart)
+//            through a local slot of their own.  Behind the last one: a record that enters nowhere, which ends the pass
 //   lists    (address, address, local slot, 0) of the vectors loaded at the start, then of those stored back at the end,
-//            both filled up to eights by zeros; with touched columns apart the addresses of the first kSweepAhead behind
+//            both filled up to eights by zeros
 constexpr int kSweepRecord = 32;
 constexpr uint32_t kSweepStep = 8, kSweepLong = 256, kSweepOdd = 512;
-constexpr int kSweepAhead = 7;
-constexpr uint32_t kSweepMerge = 64;
 constexpr int kSweepRegisters = 168;    // most local slots that the kernel is built for
 enum : uint32_t { kSweepWithGrad = 0x200u, kSweepToLocal = 0x400u, kSweepToRing = 0x800u,
                   kSweepNextWhole = 0x1000u };          // flags; the last: the next record needs both halves of its words
@@ -150,33 +146,9 @@ struct HopSweepArgs {
 struct HopSweepVectors {
     const float *ring = nullptr, *vel = nullptr, *external = nullptr;
     int64_t stride = 0, d = 0;
-    const float* own = nullptr;         // the ring of the touched columns, if they are apart, and its stride
-    int64_t own_stride = 0;
 };
 // Writes the plan down for the kernel; sets the counts of `args`.  Host only.
 void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors& at, HopSweepArgs* args, std::vector<uint32_t>* words);
-
-// ---- a pass over sparse data, the columns it touches apart --------------------------
-struct HopSplitWord {                   // 64 columns
-    uint64_t bits;                      // the touched ones
-    uint32_t base, reserved;            // touched columns in front of them
-};
-struct HopSplitHead {
-    int32_t touched, fits;              // touched columns, up to a multiple of four; they fit into the ring for them
-};
-constexpr int kSplitLocal = 112;        // most local slots of the sweep that puts touched columns in
-struct HopSplit {                       // host side of it; ready: the schedule's whole passes go this way
-    bool ready = false;
-    int64_t d = 0, room = 0, touched = 0;   // columns; most touched ones that fit, what was touched when this was planned
-    uint8_t* flags = nullptr;           // d
-    HopSplitWord* words = nullptr;      // one per 64 columns
-    uint32_t* sums = nullptr;           // one per 4096 columns
-    HopSplitHead* head = nullptr;
-    const HopPairArg* own = nullptr;    // the paired Reduce descriptors on the ring for the touched columns
-    const uint64_t* copies = nullptr;   // (vector of all columns, vector of the touched ones) read before they are written
-    int n_copies = 0;
-    HopSweepArgs sweep;
-};
 
 // Packs the Reduce jobs of one wave for pair_mix_kernel (appends to `out`; see its definition for the rule); returns the
 // number of distinct vectors the jobs read.  Host only.
@@ -207,13 +179,6 @@ int hopk_copy(void* dst, const void* src, size_t bytes, void* stream);
 __attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
 // one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out), the Reduce of up to kPairArgs jobs: descriptors on the host
 __attribute__((weak)) int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream);
-// marks and counts; copies; one wave; the sweep
-__attribute__((weak)) int hopk_split_plan(const HopSplit& split, const HopGradJob* jobs_dev, int n_jobs, int B, void* stream);
-__attribute__((weak)) int hopk_split_begin(const HopSplit& split, void* stream);
-__attribute__((weak)) int hopk_split_wave(const HopSplit& split, const HopPairArg* own, const HopPairJob* mix_dev, int n_mix,
-                                          int n_sources, int reverse, const HopGradJob* grad_dev, int n_grad, int B, int loss,
-                                          float lr, void* stream);
-__attribute__((weak)) int hopk_split_end(const HopSplit& split, const HopSweepArgs& args, void* stream);
 __attribute__((weak)) int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
@@ -246,7 +211,6 @@ struct hop_schedule {
     HopPairJob* pair_dev = nullptr;     // the same records packed in pairs, wave by wave (null with a velocity)
     HopGradJob* grad_dev = nullptr;     // STEP records only, in wave order
     HopSweepArgs sweep;                 // the whole pass as one launch (program null: not available for this schedule)
-    HopSplit split;                     // CSR: the whole pass with the touched columns apart
     int32_t* rows_dev = nullptr;        // n_records x batch
     float* coef_dev = nullptr;          // n_records x batch
     bool dense_in_place = false;        // dense SVM: margins beside the Reduce, gradient applied in place

@@ -538,7 +538,7 @@ inline int pair_vec(int n_jobs, int64_t d, bool margins) {
     return margins ? kPairMargin : blocks <= kPairTurn ? 4 : kPairPlain;
 }
 
-__host__ __device__ inline int64_t pair_chunks(int64_t d, int vec) {
+inline int64_t pair_chunks(int64_t d, int vec) {
     const int64_t per = (int64_t)kThreads * vec;
     const int64_t n = ((d >> 2) + per - 1) / per;
     return n < 1 ? 1 : n;
@@ -546,7 +546,7 @@ __host__ __device__ inline int64_t pair_chunks(int64_t d, int vec) {
 
 // chunks an XCD walks per job group: run x chunk x distinct sources near 3 MB of its 4 MB L2 (measured on 32
 // sources: runs of 5 to 7 equal, 4 and 8 1.3 % slower, 12 10 % slower), never more than the vector has
-__host__ __device__ inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
+inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
     int run = (192 * 4 / vec + n_sources / 2) / (n_sources < 1 ? 1 : n_sources);
     if (run > 8 * 4 / vec) run = 8 * 4 / vec;
     const int64_t room = n_chunks / kXcd;
@@ -554,7 +554,7 @@ __host__ __device__ inline int pair_run(int n_sources, int64_t n_chunks, int vec
     return run < 1 ? 1 : run;
 }
 
-__host__ __device__ inline int64_t pair_grid(int n_jobs, int64_t n_chunks, int run) {
+inline int64_t pair_grid(int n_jobs, int64_t n_chunks, int run) {
     const int64_t span = (int64_t)kXcd * run;
     return (n_chunks + span - 1) / span * span * n_jobs;
 }
@@ -800,30 +800,11 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
     "  s_bitcmp1_b32 s[\\w+1], 11\n"                                                                                  \
     "  s_cbranch_scc0 .Lhop_stored\\w\\()_%=\n"                                                                       \
-    "  .if %[merge]\n"                                                                                                \
-    "  s_add_u32 s30, s28, s[\\w+4]\n"                                                                                \
-    "  s_addc_u32 s31, s29, 0\n"                                                                                      \
-    "  s_setpc_b64 s[30:31]\n"                                                                                        \
-    "  .else\n"                                                                                                       \
     "  hop_columns \\w+30\n"                                                                                          \
     "  global_store_dword %[lane], v12, s[30:31] nt\n"                                                                \
-    "  .endif\n"                                                                                                      \
     ".Lhop_stored\\w\\()_%=:\n"                                                                                       \
     "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
     "  s_branch .Lhop_record\\n\\()_%=\n"                                                                             \
-    ".endm\n"                                                                                                         \
-    /* columns with a value of their own in the vector at s[w+2:w+3] take that: loaded seven such records ahead, to v[r] */\
-    ".macro hop_merge w, r\n"                                                                                         \
-    "  .p2align 6\n"                                                                                                  \
-    "  s_waitcnt vmcnt(12)\n"                                                                                         \
-    "  v_cndmask_b32_e32 v12, v12, v[\\r], vcc\n"                                                                     \
-    "  hop_columns \\w+30\n"                                                                                          \
-    "  global_store_dword %[lane], v12, s[30:31] nt\n"                                                                \
-    "  global_load_dword v[\\r], %[own], s[\\w+2:\\w+3]\n"                                                            \
-    "  s_branch .Lhop_stored\\w\\()_%=\n"                                                                             \
-    ".endm\n"                                                                                                         \
-    ".macro hop_merge_first q, r\n"                                                                                   \
-    "  global_load_dword v[\\r], %[own], s[36+2*\\q:37+2*\\q]\n"                                                      \
     ".endm\n"                                                                                                         \
     /* the record whose words are at s[w..], while those of the next are loaded to s[n..] */                          \
     ".macro hop_record w, n, at\n"                                                                                    \
@@ -879,26 +860,10 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  s_mov_b64 s[38:39], %[first]\n"                                                                                \
     "  hop_external 36\n"                                                                                             \
     "  .endif\n"                                                                                                      \
-    "  .if %[merge]\n"                                                                                                \
-    "  s_load_dwordx16 s[36:51], s[18:19], 0\n"                                                                       \
-    "  s_mov_b64 vcc, %[mask]\n"                                                                                      \
-    "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
-    "  .irp q, 0, 1, 2, 3\n"                                                                                          \
-    "  hop_merge_first \\q, 8+\\q\n"                                                                                  \
-    "  .endr\n"                                                                                                       \
-    "  .irp q, 4, 5, 6\n"                                                                                             \
-    "  hop_merge_first \\q, 9+\\q\n"                                                                                  \
-    "  .endr\n"                                                                                                       \
-    "  s_waitcnt vmcnt(0)\n"                                                                                          \
-    "  .endif\n"                                                                                                      \
     "  s_load_dwordx16 s[36:51], s[16:17], 0\n"                                                                       \
     "  s_load_dwordx16 s[52:67], s[16:17], 64\n"                                                                      \
     "  s_getpc_b64 s[34:35]\n"                                                                                        \
     ".Lhop_here_%=:\n"                                                                                                \
-    "  .if %[merge]\n"                                                                                                \
-    "  s_add_u32 s28, s34, .Lhop_merges_%=-.Lhop_here_%=\n"                                                           \
-    "  s_addc_u32 s29, s35, 0\n"                                                                                      \
-    "  .endif\n"                                                                                                      \
     "  s_add_u32 s26, s34, .Lhop_chains_%=-.Lhop_here_%=\n"                                                           \
     "  s_addc_u32 s35, s35, 0\n"                                                                                      \
     "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
@@ -917,22 +882,6 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  hop_long 68\n"                                                                                                 \
     "  hop_rest 36, 68\n"                                                                                             \
     "  hop_rest 68, 36\n"                                                                                             \
-    "  .if %[merge]\n"                                                                                                \
-    "  .p2align 6\n"                                                                                                  \
-    ".Lhop_merges_%=:\n"                                                                                              \
-    "  .irp q, 0, 1, 2, 3\n"                                                                                          \
-    "  hop_merge 36, 8+\\q\n"                                                                                         \
-    "  .endr\n"                                                                                                       \
-    "  .irp q, 4, 5, 6\n"                                                                                             \
-    "  hop_merge 36, 9+\\q\n"                                                                                         \
-    "  .endr\n"                                                                                                       \
-    "  .irp q, 0, 1, 2, 3\n"                                                                                          \
-    "  hop_merge 68, 8+\\q\n"                                                                                         \
-    "  .endr\n"                                                                                                       \
-    "  .irp q, 4, 5, 6\n"                                                                                             \
-    "  hop_merge 68, 9+\\q\n"                                                                                         \
-    "  .endr\n"                                                                                                       \
-    "  .endif\n"                                                                                                      \
     ".Lhop_end_%=:\n"                                                                                                 \
     /* what the last record had loaded ahead is not used, but its registers are */                                    \
     "  s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                                               \
@@ -964,8 +913,6 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     ".purgem hop_short\n"                                                                                             \
     ".purgem hop_long\n"                                                                                              \
     ".purgem hop_rest\n"                                                                                              \
-    ".purgem hop_merge\n"                                                                                             \
-    ".purgem hop_merge_first\n"                                                                                       \
     ".purgem hop_record\n"
 
 #define HOP_SWEEP_ASM(...)                                                                                            \
@@ -975,10 +922,8 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
                    [loads] "s"(a.n_load_groups), [velocities] "s"(a.n_store_groups),    \
                    [neg_eta] "s"(-a.eta), [mu] "s"(a.mu), [first] "s"(a.first_external), [lane] "v"(lane),            \
                    [folded] "v"(folded), [table] "v"(table), [mode] "n"(MODE), [mom] "n"((int)MOM),                   \
-                   [zero] "n"(HOP_GRAD_ZERO), [synth] "n"(HOP_GRAD_SYNTH), [external] "n"(HOP_GRAD_EXTERNAL), HOP_SWEEP_MERGE          \
+                   [zero] "n"(HOP_GRAD_ZERO), [synth] "n"(HOP_GRAD_SYNTH), [external] "n"(HOP_GRAD_EXTERNAL)          \
                  : "memory", "scc", "vcc", HOP_SWEEP_S, __VA_ARGS__)
-
-#define HOP_SWEEP_MERGE [merge] "n"(0), [mask] "n"(0), [own] "n"(0)
 
 constexpr int kSweepThreads = 256;
 constexpr int kSynthSums = 12 * 255 + 1;               // values of a sum of 12 bytes
@@ -1001,142 +946,6 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const HopSweepArgs
     else if constexpr (LOCAL == 80) HOP_SWEEP_ASM(HOP_SWEEP_V96);
     else if constexpr (LOCAL == 112) HOP_SWEEP_ASM(HOP_SWEEP_V128);
     else HOP_SWEEP_ASM(HOP_SWEEP_V184);
-}
-
-// ------------------------------------------- a pass over sparse data: which columns it touches ----
-// A sparse minibatch row couples the columns it holds: its margin reads them.  All others go through the pass column by
-// column, as above, and they are many: of 2^24 columns 63 % (64 workers, 1841 records of 512 rows x 128 non-zeros), of 2^20
-// 43 % (16 workers, 1600 records of 256 x 64).  So a whole pass marks the columns that its rows hold, keeps these side by
-// side in a ring of their own, runs the waves on that ring, and the sweep then runs over all columns and puts the touched
-// ones in from there as it stores its vectors.  Bytes instead of bits while marking: no atomics, and a row that is drawn
-// again writes the same.  Nothing is kept from one pass to the next; where the touched columns are more than the ring has
-// room for (HopSplitHead::fits), the same launches run the waves on all columns and the sweep does nothing.
-// 64 workers x 2^24 columns: 76.3 -> 61.6 ms a pass: mixes 71.9 -> 28.7, marking 0.74, copying 1.24 (one column a thread: 2.97),
-// sweep 27.3, scatters 4.5 -> 5.0.
-__device__ __forceinline__ bool split_fits(const HopSplitHead* head) {
-    return *(const __attribute__((address_space(4))) int32_t*)&head->fits != 0;
-}
-// where a column is in the ring of the touched ones
-__device__ __forceinline__ uint32_t split_place(const HopSplitWord* words, uint32_t col) {
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    const u4 e = ((const HOP_GLOBAL u4*)words)[col >> 6];
-    const uint64_t bits = ((uint64_t)e.y << 32 | e.x) & ((1ull << (col & 63)) - 1);
-    return e.z + (uint32_t)__popcll(bits);
-}
-
-__global__ __launch_bounds__(kThreads) void split_clear_kernel(float4* flags, int64_t n16) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n16) flags[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
-// one wavefront per (record, row), as in the margins
-__global__ __launch_bounds__(kThreads) void split_mark_kernel(const HopGradJob* __restrict__ jobs, int B, int per, uint8_t* flags) {
-    const int lane = threadIdx.x & 63, m = (int)(blockIdx.x % per) * (kThreads / 64) + (threadIdx.x >> 6);
-    const HopGradJob* job = jobs + blockIdx.x / per;
-    if (m >= B) return;
-    const int r = job->rows[m];
-    const int64_t hi = job->rowptr[r + 1];
-    for (int64_t p = job->rowptr[r] + lane; p < hi; p += 64) flags[job->col[p]] = 1;
-}
-
-// 4096 columns per workgroup: a word and the number of touched columns in front of it, inside the workgroup
-__global__ __launch_bounds__(kThreads) void split_words_kernel(const uint8_t* __restrict__ flags, int64_t d, HopSplitWord* words,
-                                                               uint32_t* sums) {
-    __shared__ uint32_t totalS[kThreads / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int64_t first = (int64_t)blockIdx.x * 64 + wv * 16;                   // this wavefront's first word
-    uint64_t mine = 0;
-    uint32_t before = 0, count = 0;
-#pragma unroll 4
-    for (int k = 0; k < 16; ++k) {
-        const int64_t c = (first + k) * 64 + lane;
-        const uint64_t bits = __ballot(c < d && flags[c] != 0);
-        if (lane == k) {
-            mine = bits;
-            before = count;
-        }
-        count += (uint32_t)__popcll(bits);
-    }
-    if (lane == 0) totalS[wv] = count;
-    __syncthreads();
-    uint32_t base = 0, all = 0;
-    for (int k = 0; k < kThreads / 64; ++k) {
-        base += k < wv ? totalS[k] : 0;
-        all += totalS[k];
-    }
-    if (lane < 16 && (first + lane) * 64 < d) words[first + lane] = HopSplitWord{mine, base + before, 0};
-    if (threadIdx.x == 0) sums[blockIdx.x] = all;
-}
-
-// the same counted from the first column on
-__global__ __launch_bounds__(kThreads) void split_scan_kernel(const uint32_t* __restrict__ sums, int64_t d, HopSplitWord* words,
-                                                              HopSplitHead* head, int64_t room) {
-    __shared__ uint32_t partS[kThreads / 64];
-    const int lane = threadIdx.x & 63;
-    uint32_t t = 0;
-    for (unsigned k = threadIdx.x; k < blockIdx.x; k += kThreads) t += sums[k];
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_down(t, off, 64);
-    if (lane == 0) partS[threadIdx.x >> 6] = t;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < kThreads / 64; ++k) before += partS[k];
-    const int64_t word = (int64_t)blockIdx.x * 64 + lane;
-    if (threadIdx.x < 64 && word * 64 < d) words[word].base += before;
-    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) {
-        const uint32_t n = before + sums[blockIdx.x];
-        head->touched = (int32_t)((n + 3) & ~3u);
-        head->fits = n <= room;
-    }
-}
-
-// the touched columns of the vectors that the pass reads before it writes them
-constexpr int kSplitCopy = 8;
-__global__ __launch_bounds__(kThreads) void split_copy_kernel(const HopSplitHead* head, const HopSplitWord* __restrict__ words,
-                                                              const uint64_t* __restrict__ list, int64_t d) {
-    if (!split_fits(head)) return;
-    const float* from = (const float*)list[2 * blockIdx.y];
-    float* to = (float*)list[2 * blockIdx.y + 1];
-    const int64_t c0 = (int64_t)blockIdx.x * (kThreads * kSplitCopy) + threadIdx.x;
-    float v[kSplitCopy];
-    HopSplitWord e[kSplitCopy];
-#pragma unroll
-    for (int k = 0; k < kSplitCopy; ++k) {
-        const int64_t c = min(c0 + k * kThreads, d - 1);
-        e[k] = words[c >> 6];
-        v[k] = __builtin_nontemporal_load((const HOP_GLOBAL float*)from + c);
-    }
-#pragma unroll
-    for (int k = 0; k < kSplitCopy; ++k) {
-        const int64_t c = c0 + k * kThreads;
-        if (c < d && (e[k].bits >> (c & 63) & 1))
-            ((HOP_GLOBAL float*)to)[e[k].base + (uint32_t)__popcll(e[k].bits & ((1ull << (c & 63)) - 1))] = v[k];
-    }
-}
-
-#undef HOP_SWEEP_MERGE
-#define HOP_SWEEP_MERGE [merge] "n"(1), [mask] "s"(touched), [own] "v"(own)
-// The sweep without gradients over all columns, the touched ones put in as vectors are stored.  Without them it takes 14.2 ms
-// (64 workers x 2^24 columns, 1841 records, 576 vectors stored); bound by their loads, 95 B a wavefront and vector: loaded 32
-// vectors ahead instead of seven (fewer wavefronts) 37 ms, side by side and then permuted 36, workgroups of 1024 in step 29;
-// each XCD on a part of its own 29.1 -> 27.3.  Stores of the untouched columns alone, and of the touched ones later, would be
-// read-modify-writes: dword stores of 63 % of the columns of every line run at 2.1 TB/s of whole lines, against 5.
-constexpr int kSplitThreads = 256;
-template <int LOCAL>
-__global__ __launch_bounds__(kSplitThreads) void split_sweep_kernel(const HopSweepArgs a, const HopSplitHead* head,
-                                                                    const HopSplitWord* words) {
-    constexpr int MODE = HOP_GRAD_ZERO;
-    constexpr bool MOM = false;
-    if (!split_fits(head)) return;
-    const int64_t per = (gridDim.x + kXcd - 1) / kXcd, block = (int64_t)(blockIdx.x % kXcd) * per + blockIdx.x / kXcd;
-    const int64_t c = block * kSplitThreads + threadIdx.x;
-    if (c >= a.d) return;
-    const uint32_t lane = threadIdx.x * (uint32_t)sizeof(float), folded = 0, table = 0;
-    const uint64_t columns = (uint64_t)block * kSplitThreads * sizeof(float);
-    const uint64_t touched = __ballot(words[c >> 6].bits >> (c & 63) & 1);
-    const uint32_t own = split_place(words, (uint32_t)c) * (uint32_t)sizeof(float);
-    if constexpr (LOCAL == 48) HOP_SWEEP_ASM(HOP_SWEEP_V64);
-    else if constexpr (LOCAL == 80) HOP_SWEEP_ASM(HOP_SWEEP_V96);
-    else HOP_SWEEP_ASM(HOP_SWEEP_V128);
 }
 
 // ------------------------------------------------------------------ wavefront reductions ----
@@ -1448,21 +1257,15 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGra
 
 // ------------------------------------------------------------------- CSR SVM: margins ----
 // One wavefront per (job, minibatch row): gather w[col], reduce across the 64 lanes.
-// words: the columns are those of the ring of touched ones, job->X is w there
-__device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int block,
-                                                const HopSplitWord* words = nullptr) {
+__device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int block) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = block * (kThreads / 64) + wv;
     if (m >= B) return;
     const int r = job->rows[m];
     const int64_t lo = job->rowptr[r], hi = job->rowptr[r + 1];
-    const float* w = words ? job->X : job->w;
+    const float* w = job->w;
     float acc = 0.f;
-    if (words) {
-        for (int64_t p = lo + lane; p < hi; p += 64) acc = fmaf(job->val[p], w[split_place(words, (uint32_t)job->col[p])], acc);
-    } else {
-        for (int64_t p = lo + lane; p < hi; p += 64) acc = fmaf(job->val[p], w[job->col[p]], acc);
-    }
+    for (int64_t p = lo + lane; p < hi; p += 64) acc = fmaf(job->val[p], w[job->col[p]], acc);
     acc = wave_sum(acc);
     if (lane == 0) job->coef[m] = loss_coef(job->y[r], acc, 1.0f / (float)B, loss);
 }
@@ -1522,38 +1325,6 @@ __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPair
     pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
 }
 
-// The same on the ring of the touched columns, `own` naming its vectors, or on all columns where that ring is too small.
-// n_chunks and run are those of `touched` columns, as many as when the pass was planned; the grid was chosen for them.
-// (Two instances of the Reduce in one kernel: without a bound on the registers each wavefront takes more of them and half
-// as many run.)
-template <int VEC>
-__global__ __launch_bounds__(kThreads, 8 / VEC) void split_mix_kernel(const HopSplitHead* head, const HopSplitWord* words,
-                                                             const HopPairArg* __restrict__ own, const HopPairJob* __restrict__ jobs,
-                                                             int n_mix, int64_t touched, int64_t n_chunks, int run, int reverse,
-                                                             const HopGradJob* __restrict__ grad_jobs, int B,
-                                                             int rows_per_job_blocks, int loss, int margin_blocks, int n_sources,
-                                                             int64_t d) {
-    const bool fits = split_fits(head);
-    if ((int)blockIdx.x < margin_blocks) {
-        csr_margin_rows(grad_jobs + blockIdx.x / rows_per_job_blocks, B, loss, (int)(blockIdx.x % rows_per_job_blocks),
-                        fits ? words : nullptr);
-        return;
-    }
-    const int64_t now = *(const __attribute__((address_space(4))) int32_t*)&head->touched, bid = (int64_t)blockIdx.x - margin_blocks;
-    if (fits && now == touched) {
-        pair_block<VEC>((pair_args_in)own, n_mix, touched, n_chunks, run, reverse, bid);
-        return;
-    }
-    if (fits) d = now;
-    n_chunks = pair_chunks(d, VEC);
-    run = pair_run(n_sources, n_chunks, VEC);
-    const int64_t blocks = pair_grid(n_mix, n_chunks, run), step = (int64_t)gridDim.x - margin_blocks;
-    for (int64_t b = bid; b < blocks; b += step) {
-        if (fits) pair_block<VEC>((pair_args_in)own, n_mix, d, n_chunks, run, reverse, b);
-        else pair_block<VEC>(jobs, n_mix, d, n_chunks, run, reverse, b);
-    }
-}
-
 template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int n_mix,
                                                                      int64_t d, int64_t n_chunks, int run, int reverse,
@@ -1597,14 +1368,12 @@ constexpr int kHotCols = 1024;
 // 512 and 256 threads per workgroup, which sum fewer rows' hot columns before they leave: 7.17 -> 7.20, 7.66 ms per run of
 // 16 x 2^20; 256 hot columns 7.39 ms.
 template <bool BOTH>
-__device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ job, int B, float factor, int block,
-                                                 const HopSplitWord* words = nullptr) {
+__device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ job, int B, float factor, int block) {
     __shared__ float hot[BOTH ? 2 : 1][kHotCols];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = block * kScatterRows + wv;
-    float* out = words ? job->g : job->out;
+    float* out = job->out;
     float* vel = BOTH ? job->vel : nullptr;
-    auto place = [&](int col) { return words ? split_place(words, (uint32_t)col) : (uint32_t)col; };
     float c = 0.f, val = 0.f;
     int col = 0;
     int64_t p = 0, hi = 0;
@@ -1631,7 +1400,7 @@ __device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ 
                 atomicAdd(&hot[0][col], v);
                 if (BOTH) atomicAdd(&hot[BOTH ? 1 : 0][col], g);
             } else {
-                unsafeAtomicAdd(out + place(col), v);
+                unsafeAtomicAdd(out + col, v);
                 if (BOTH) unsafeAtomicAdd(vel + col, g);
             }
             p += 64;
@@ -1644,7 +1413,7 @@ __device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ 
     __syncthreads();
     for (int i = threadIdx.x; i < kHotCols; i += kScatterThreads) {
         const float v = hot[0][i];
-        if (v != 0.f) unsafeAtomicAdd(out + place(i), v);
+        if (v != 0.f) unsafeAtomicAdd(out + i, v);
         if (BOTH) {
             const float g = hot[BOTH ? 1 : 0][i];
             if (g != 0.f) unsafeAtomicAdd(vel + i, g);
@@ -1656,13 +1425,6 @@ template <bool BOTH>
 __global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopGradJob* __restrict__ jobs, int B,
                                                                       int blocks_per_job, float factor) {
     csr_scatter_rows<BOTH>(jobs + blockIdx.x / blocks_per_job, B, factor, blockIdx.x % blocks_per_job);
-}
-
-__global__ __launch_bounds__(kScatterThreads) void split_scatter_kernel(const HopSplitHead* head, const HopSplitWord* words,
-                                                                        const HopGradJob* __restrict__ jobs, int B,
-                                                                        int blocks_per_job, float factor) {
-    csr_scatter_rows<false>(jobs + blockIdx.x / blocks_per_job, B, factor, blockIdx.x % blocks_per_job,
-                            split_fits(head) ? words : nullptr);
 }
 
 __global__ __launch_bounds__(kScatterThreads) void csr_scatter_one(const HopGradJob job, int B, float factor) {
@@ -1898,63 +1660,6 @@ int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor
     else
         hipLaunchKernelGGL(csr_scatter_kernel<false>, dim3((unsigned)grid), dim3(kScatterThreads), 0, (hipStream_t)stream,
                            jobs_dev, B, per, factor);
-    return launch_status();
-}
-
-int hopk_split_plan(const HopSplit& p, const HopGradJob* jobs_dev, int n_jobs, int B, void* stream) {
-    const hipStream_t st = (hipStream_t)stream;
-    const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
-    const int64_t marks = (int64_t)n_jobs * per, blocks = (p.d + 4095) / 4096, n16 = (p.d + 15) / 16;
-    if (marks > 0x7FFFFFFFll || blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(split_clear_kernel, dim3((unsigned)((n16 + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
-                       (float4*)p.flags, n16);
-    hipLaunchKernelGGL(split_mark_kernel, dim3((unsigned)marks), dim3(kThreads), 0, st, jobs_dev, B, per, p.flags);
-    hipLaunchKernelGGL(split_words_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, p.flags, p.d, p.words, p.sums);
-    hipLaunchKernelGGL(split_scan_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, p.sums, p.d, p.words, p.head, p.room);
-    return launch_status();
-}
-
-int hopk_split_begin(const HopSplit& p, void* stream) {
-    hipLaunchKernelGGL(split_copy_kernel, dim3((unsigned)((p.d + kThreads * kSplitCopy - 1) / (kThreads * kSplitCopy)),
-                       (unsigned)p.n_copies), dim3(kThreads), 0, (hipStream_t)stream, p.head, p.words, p.copies, p.d);
-    return launch_status();
-}
-
-int hopk_split_wave(const HopSplit& p, const HopPairArg* own, const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse,
-                    const HopGradJob* grad_dev, int n_grad, int B, int loss, float lr, void* stream) {
-    const hipStream_t st = (hipStream_t)stream;
-    const int vec = pair_vec(n_mix, p.touched, n_grad > 0);
-    const int64_t n_chunks = pair_chunks(p.touched, vec);
-    const int run = pair_run(n_sources, n_chunks, vec);
-    const int64_t grid = pair_grid(n_mix, n_chunks, run);
-    const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
-    const int64_t margin_blocks = (int64_t)n_grad * per, all = grid + margin_blocks;
-    if (all > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    const dim3 blocks((unsigned)all), threads(kThreads);
-#define HOP_SPLIT_MIX(V)                                                                                                  \
-    hipLaunchKernelGGL(split_mix_kernel<V>, blocks, threads, 0, st, p.head, p.words, own, mix_dev, n_mix, p.touched, n_chunks, \
-                       run, reverse, grad_dev, B, per, loss, (int)margin_blocks, n_sources, p.d)
-    if (vec == 4) HOP_SPLIT_MIX(4);
-    else if (vec == 2) HOP_SPLIT_MIX(2);
-    else HOP_SPLIT_MIX(1);
-#undef HOP_SPLIT_MIX
-    if (n_grad > 0) {
-        const int rows = (B + kScatterRows - 1) / kScatterRows;
-        hipLaunchKernelGGL(split_scatter_kernel, dim3((unsigned)(n_grad * rows)), dim3(kScatterThreads), 0, st, p.head, p.words,
-                           grad_dev, B, rows, lr);
-    }
-    return launch_status();
-}
-
-int hopk_split_end(const HopSplit& p, const HopSweepArgs& a, void* stream) {
-    if (a.n_local > kSplitLocal) return (int)hipErrorInvalidValue;
-    const int64_t grid = ((a.d + kSplitThreads - 1) / kSplitThreads + kXcd - 1) / kXcd * kXcd;
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    const dim3 blocks((unsigned)grid), threads(kSplitThreads);
-    const hipStream_t st = (hipStream_t)stream;
-    if (a.n_local <= 48) hipLaunchKernelGGL(split_sweep_kernel<48>, blocks, threads, 0, st, a, p.head, p.words);
-    else if (a.n_local <= 80) hipLaunchKernelGGL(split_sweep_kernel<80>, blocks, threads, 0, st, a, p.head, p.words);
-    else hipLaunchKernelGGL(split_sweep_kernel<kSplitLocal>, blocks, threads, 0, st, a, p.head, p.words);
     return launch_status();
 }
 

@@ -18,11 +18,6 @@ class Session:
         # mix runs slower right behind the arithmetic-bound generator), one buffer per worker and wave, as far as a
         # quarter of the free memory (at most 64 GiB) holds them; grad_ahead=1 keeps one buffer per worker
         ahead = c.get("grad_ahead", 16 if c["model"] == "synth" else 1)
-        if "grad_ahead" not in c and c["model"] == "csr" and c["d"] >= 1 << 18 and not c.get("momentum", 0.0):
-            # whole passes over wide sparse data keep the columns that the minibatches touch apart, in this memory: room
-            # for three fifths of all columns of every version
-            ahead = min(16, -(-3 * hop.hop_layout(c["d"], c["s"], hop.make_opts(
-                max_ig=c["max_ig"], max_latency=c.get("max_latency", 0), serial=c.get("serial", False)))[0] // 5))
         if "grad_ahead" not in c and ahead > 1:
             room = min(torch.cuda.mem_get_info(self.dev)[0] // 4, 64 << 30)
             while ahead > 1 and c["N"] * ahead * (c["d"] + 128) * 4 > room:

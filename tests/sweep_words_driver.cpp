@@ -36,7 +36,7 @@ static float grad_of(const uint32_t* key) { return (float)((key[0] * 2654435761u
 int main() {
     std::mt19937 gen(11);
     auto below = [&](int n) { return (int)(gen() % (unsigned)n); };
-    int run = 0, parts = 0, shorts = 0, rest = 0, most = 0, merged = 0;
+    int run = 0, parts = 0, shorts = 0, rest = 0, most = 0;
     for (; run < 300; ++run) {
         const int N = 1 + below(run % 9 == 0 ? 60 : 12), depth = 1 + below(4), slots = N * depth;
         const int mode = run % 3 == 0 ? HOP_GRAD_ZERO : run % 3 == 1 ? HOP_GRAD_SYNTH : HOP_GRAD_EXTERNAL;
@@ -84,25 +84,18 @@ int main() {
         HopSweepVectors at;
         at.ring = ring.data(); at.vel = vel.data(); at.external = ext.data();
         at.stride = at.d = 1;
-        // touched columns apart: every stored vector's are loaded kSweepAhead such records ahead
-        std::vector<float> own((size_t)slots);
-        for (int q = 0; q < slots; ++q) own[q] = (float)(1000 + q);
-        const bool apart = mode == HOP_GRAD_ZERO && !mom && run % 2;
-        if (apart) { at.own = own.data(); at.own_stride = 1; }
         std::vector<uint32_t> P;
         hop_lower_sweep(plan, (int)ops.size(), at, &a, &P);
         // as the kernel reads it: a record is loaded while the one before is at work, so the words behind the end are read too
         EXPECT(a.n_local <= kSweepRegisters && a.first_list == (a.n_records + 1) * kSweepRecord);
         EXPECT(P[(size_t)a.n_records * kSweepRecord] == (a.n_records % 2 ? kSweepOdd : 0u));
-        EXPECT(P.size() == (size_t)a.first_list + 32 * (size_t)(a.n_load_groups + a.n_store_groups) + (apart ? 16 : 0) && a.n_load_groups >= 1);
+        EXPECT(P.size() == (size_t)a.first_list + 32 * (size_t)(a.n_load_groups + a.n_store_groups) && a.n_load_groups >= 1);
         most = std::max(most, a.n_local);
         std::vector<float> local((size_t)a.n_local, NAN);
         for (int k = 0; k < 8 * a.n_load_groups && address(&P.at(a.first_list + 4 * k)); ++k)
             local.at(P.at(a.first_list + 4 * k + 2)) = *address(&P.at(a.first_list + 4 * k));
         const float* ahead = (const float*)(uintptr_t)a.first_external;
-        int finished = 0, stored = 0;
-        float early[kSweepAhead] = {};
-        for (int k = 0; apart && k < kSweepAhead; ++k) early[k] = *address(&P.at((size_t)a.first_list + 32 * a.n_load_groups + 2 * k));
+        int finished = 0;
         for (int r = 0; r < a.n_records; ++r) {
             const uint32_t *w = &P.at((size_t)r * kSweepRecord), flags = w[1] & ~255u, whole = r == 0 || (w[1 - kSweepRecord] & kSweepNextWhole);
             const uint32_t entry = w[0] % kSweepLong;
@@ -127,23 +120,16 @@ int main() {
             }
             if (flags & kSweepToLocal) local.at(w[1] & 255u) = acc;
             if (flags & kSweepToRing) *address(w + 30) = acc;
-            if (apart && (flags & kSweepToRing)) {
-                const uint32_t place = w[4] / kSweepMerge;
-                EXPECT(w[4] % kSweepMerge == 0 && place == (uint32_t)(stored % kSweepAhead + (r & 1 ? kSweepAhead : 0)));
-                EXPECT(early[stored % kSweepAhead] == own[address(w + 30) - ring.data()]);
-                early[stored++ % kSweepAhead] = *address(w + 2);
-            }
             finished += (flags & kSweepToLocal) == 0 || (w[1] & 255u) != (uint32_t)plan.n_local;
         }
         EXPECT(finished == (int)ops.size());
         parts += a.n_records - finished;
-        merged += stored;
         for (int k = 8 * a.n_load_groups; k < 8 * (a.n_load_groups + a.n_store_groups) && address(&P.at(a.first_list + 4 * k)); ++k)
             *address(&P.at(a.first_list + 4 * k)) = local.at(P.at(a.first_list + 4 * k + 2));
         for (int q = 0; q < slots; ++q) EXPECT(ring[q] == want[q]);
         for (int q = 0; q < N; ++q) EXPECT(vel[q] == wvel[q]);
     }
-    EXPECT(parts > 50 && shorts > 500 && rest > 500 && most > 112 && merged > 300);
+    EXPECT(parts > 50 && shorts > 500 && rest > 500 && most > 112);
     std::printf("ok parts=%d short=%d rest=%d locals=%d\n", parts, shorts, rest, most);
     return 0;
 }

@@ -87,6 +87,14 @@ class hop_mix_job(C.Structure):
 _lib = None
 
 
+class _mix_jobs:
+    """Argument type of hop_mix: structures as their pointer type takes them, or the bytes of packed ones."""
+
+    @classmethod
+    def from_param(cls, jobs):
+        return jobs if type(jobs) is bytes else C.POINTER(hop_mix_job).from_param(jobs)
+
+
 def load():
     """Loads libhop.so (after torch, so that both share one HIP runtime)."""
     global _lib
@@ -129,7 +137,7 @@ def load():
         "hop_use_graph": (C.c_int, [vp, C.c_int]),
         "hop_profile_read": (C.c_int, [vp, C.c_int, C.POINTER(C.c_double), C.POINTER(i64),
                                        C.POINTER(C.c_double)]),
-        "hop_mix": (C.c_int, [vp, i32, i64, vp]),
+        "hop_mix": (C.c_int, [_mix_jobs, i32, i64, vp]),
         "hop_grad_scratch_floats": (i64, [i64, i32]),
         "hop_svm_grad_dense": (C.c_int, [vp, vp, vp, vp, i32, i64, f32, i32, vp, vp, vp, vp]),
         "hop_svm_grad_dense_static": (C.c_int, [vp, vp, vp, vp, i32, i64, f32, i32, vp, vp, vp]),

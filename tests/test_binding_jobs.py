@@ -1,4 +1,6 @@
 """The binding's two ways of writing a hop_mix job down give the same bytes; what only ctypes takes or refuses goes there."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -21,3 +23,14 @@ def test_packed_jobs_equal_the_structures(n):
 def test_other_jobs_are_not_packed(job):
     with pytest.raises(Exception):
         hop._pack_jobs([dict(dict(out=64, src=[64], w=[1.0]), **job)])
+
+
+def test_the_library_call_takes_structures_and_packed_jobs_only():
+    """One structure, an array of them, a pointer to them or nothing, as for every structure that a call takes; no bare addresses."""
+    call, job = hop.load().hop_mix, hop.hop_mix_job()
+    for jobs in (job, (hop.hop_mix_job * 2)(), C.pointer(job), C.byref(job), bytes(job)):
+        assert call(jobs, 0, 1, None) == 0
+    assert call(None, 0, 1, None) == call(None, 1, 1, None) == -1
+    for jobs in (4096, "jobs", hop.hop_opts()):
+        with pytest.raises(C.ArgumentError):
+            call(jobs, 0, 1, None)

@@ -160,51 +160,16 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
 // Hands every value of the pass (the content a ring slot has between two writes) a local slot from its production, or
 // its load at the start, to its last reader, reusing slots greedily.  A result may take over the slot of a source that
 // this record reads for the last time: a lane reads all its sources before it writes.
-bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int n_workers, HopSweepPlan* plan) {
-    const int R = (int)given.size();
-    if (R >= 1 << 24) return false;                  // a run's length has 24 bits
-    std::vector<int> last_writer((size_t)n_ring_slots, -1), reader_after((size_t)n_ring_slots, 0);
-    std::vector<int> kind((size_t)R);                // what the record's run is written down as
-    for (int r = 0; r < R; ++r) last_writer[given[r].out_slot] = r;
-    for (int r = R - 1; r >= 0; --r) {
-        const HopSweepOp& op = given[r];
-        const bool only_kept = reader_after[op.out_slot] && last_writer[op.out_slot] != r;
-        kind[r] = op.terms.size() > (size_t)kSweepInline ? kSweepOther
-                  : (int)(op.terms.size() + (op.grad ? kSweepGrad << 4 : 0) + (only_kept ? 0 : kSweepStore << 4));
-        reader_after[op.out_slot] = 0;
-        for (const auto& t : op.terms) reader_after[t.first] = 1;
-    }
-    // by kind inside a wave, beginning with the kind that the wave before ended on: long runs; returns their number
-    std::vector<int> order((size_t)R);
-    auto arrange = [&] {
-        int runs = 0;
-        for (int b = 0; b < R;) {
-            int e = b;
-            for (; e < R && given[e].wave == given[b].wave; ++e) order[e] = e;
-            const int open = b ? kind[order[b - 1]] : 0;
-            std::stable_sort(order.begin() + b, order.begin() + e, [&](int x, int y) {
-                return std::make_pair(kind[x] != open, kind[x]) < std::make_pair(kind[y] != open, kind[y]);
-            });
-            for (; b < e; ++b) runs += b == 0 || kind[order[b]] != kind[order[b - 1]];
-        }
-        return runs;
-    };
-    // Where runs are short, records with an odd number of sources take a zero with weight -0 as one more: half as many
-    // kinds.  That is for whoever runs a plan kind by kind; hop_lower_sweep takes records one by one and leaves the zeros out.
-    const bool even = arrange() * 8 > R;
-    if (even) {
-        for (int& k : kind)
-            if (k != kSweepOther) k += k & 1;
-        arrange();
-    }
-    auto op_at = [&](int r) -> const HopSweepOp& { return given[order[r]]; };
-    std::vector<int> holds((size_t)n_ring_slots, -1);
+bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_workers, HopSweepPlan* plan) {
+    const int R = (int)ops.size();
+    std::vector<int> last_writer((size_t)n_ring_slots, -1), holds((size_t)n_ring_slots, -1);
     std::vector<int> last_use;                       // by value
     std::vector<std::pair<int, int>> initial;        // (ring slot, value) read before it is written
     std::vector<std::vector<int>> reads((size_t)R);
     std::vector<int> result((size_t)R);
     for (int r = 0; r < R; ++r) {
-        const HopSweepOp& op = op_at(r);
+        const HopSweepOp& op = ops[r];
+        last_writer[op.out_slot] = r;
         for (const auto& t : op.terms) {
             int& v = holds[t.first];
             if (v < 0) {
@@ -229,39 +194,23 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
     for (const auto& i : initial) local[i.second] = take();
     std::vector<int> vel((size_t)n_workers, -1);
     int n_vel = 0;
-    for (const HopSweepOp& op : given)
+    for (const HopSweepOp& op : ops)
         if (op.vel && vel[op.worker] < 0) {
             vel[op.worker] = take();
             ++n_vel;
         }
-    if (n_local >= kSweepMaxLocal) return false;
-    auto bits = [](float f) {
-        uint32_t u;
-        std::memcpy(&u, &f, sizeof(u));
-        return u;
-    };
-    constexpr uint32_t kLane = 64 * sizeof(float);   // bytes of a local slot at one column per lane
+    if (n_local > kSweepMaxLocal) return false;
     std::vector<uint32_t>& prog = plan->program;
     prog.clear();
     for (int r = 0; r < R; ++r) {
-        const int k = kind[order[r]];
-        if (r == 0 || k != kind[order[r - 1]]) prog.push_back((uint32_t)k);
-        prog.back() += 256u;
-    }
-    plan->n_runs = (int)prog.size();
-    prog.resize((prog.size() + 4) / 4 * 4, 0u);      // at least one word of padding: the next run is read ahead
-    plan->first_record = (int)prog.size();
-    std::vector<size_t> padded;                      // where a source is missing to an even number: the zero, weight -0
-    for (int r = 0; r < R; ++r) {
-        const HopSweepOp& op = op_at(r);
+        const HopSweepOp& op = ops[r];
         const size_t A = op.terms.size(), at = prog.size();
         prog.resize(at + hop_sweep_words((int)A), 0u);
         uint32_t* p = prog.data() + at;
         p[7] = (uint32_t)A;
-        if (even && A % 2 && A <= (size_t)kSweepInline) padded.push_back(at + kSweepHead + 2 * A);
         for (size_t t = 0; t < A; ++t) {
-            p[kSweepHead + 2 * t] = (uint32_t)local[reads[r][t]] * kLane;
-            p[kSweepHead + 2 * t + 1] = bits(op.terms[t].second);
+            p[kSweepHead + 2 * t] = (uint32_t)local[reads[r][t]];
+            std::memcpy(&p[kSweepHead + 2 * t + 1], &op.terms[t].second, sizeof(float));
         }
         for (int v : reads[r])
             if (last_use[v] == r && local[v] >= 0) {
@@ -271,11 +220,11 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
         const int v = result[r];
         if (last_use[v] >= 0) {
             local[v] = take();
-            if (n_local >= kSweepMaxLocal) return false;
+            if (n_local > kSweepMaxLocal) return false;
             p[0] |= kSweepKeep;
-            p[1] = (uint32_t)local[v] * kLane;
+            p[1] = (uint32_t)local[v];
         }
-        if (last_writer[op.out_slot] == order[r]) {
+        if (last_writer[op.out_slot] == r) {
             p[0] |= kSweepStore;
             p[2] = (uint32_t)op.out_slot;
         }
@@ -283,36 +232,29 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
             p[0] |= kSweepGrad;
             for (int k = 0; k < 3; ++k) p[4 + k] = op.key[k];
         }
-        if (op.vel) p[3] = (uint32_t)vel[op.worker] * kLane;
-    }
-    prog.resize(prog.size() + hop_sweep_words(kSweepInline), 0u);
-    int following = -1;                              // from the last record with an external gradient to the first
-    size_t at_word = plan->n_runs ? prog.size() - hop_sweep_words(kSweepInline) : 0;
-    for (int r = R - 1; r >= 0; --r) {
-        const HopSweepOp& op = op_at(r);
-        at_word -= hop_sweep_words((int)op.terms.size());
-        if (!op.external) continue;
-        prog[at_word + 5] = (uint32_t)(following < 0 ? op.worker : following);
-        following = op.worker;
-    }
-    plan->first_external = std::max(following, 0);
-    for (size_t q : padded) {
-        prog[q] = (uint32_t)n_local * kLane;
-        prog[q + 1] = bits(-0.f);                    // -0 * 0 = -0, which changes no sum: not even one of -0
+        if (op.vel) p[3] = (uint32_t)vel[op.worker];
     }
     plan->first_load = (int)prog.size();
+    int following = -1;                              // from the last record with an external gradient to the first
+    size_t at_word = prog.size();
+    for (int r = R - 1; r >= 0; --r) {
+        at_word -= hop_sweep_words((int)ops[r].terms.size());
+        if (!ops[r].external) continue;
+        prog[at_word + 5] = (uint32_t)(following < 0 ? ops[r].worker : following);
+        following = ops[r].worker;
+    }
+    plan->first_external = std::max(following, 0);
     // the initial values were given the first local slots, in this order
     for (size_t i = 0; i < initial.size(); ++i) {
         prog.push_back((uint32_t)initial[i].first);
-        prog.push_back((uint32_t)i * kLane);
+        prog.push_back((uint32_t)i);
     }
     for (int w = 0; w < n_workers; ++w)
         if (vel[w] >= 0) {
             prog.push_back((uint32_t)w);
-            prog.push_back((uint32_t)vel[w] * kLane);
+            prog.push_back((uint32_t)vel[w]);
         }
-    plan->n_local = std::max(n_local + (even ? 1 : 0), 1);
-    plan->zero = even ? n_local * (int)kLane : -1;
+    plan->n_local = std::max(n_local, 1);
     plan->n_loads = (int)initial.size();
     plan->n_vel = n_vel;
     return true;
@@ -320,7 +262,6 @@ bool hop_plan_sweep(const std::vector<HopSweepOp>& given, int n_ring_slots, int 
 
 void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors& at, HopSweepArgs* args,
                      std::vector<uint32_t>* words) {
-    constexpr uint32_t kLane = 64 * sizeof(float);
     constexpr uint32_t kOne = 0x3F800000u;
     std::vector<uint32_t>& out = *words;
     out.clear();
@@ -336,11 +277,11 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
     const bool external = args->mode == HOP_GRAD_EXTERNAL, none = args->mode == HOP_GRAD_ZERO;
     const uint32_t partial = (uint32_t)plan.n_local;         // the sum so far of a record in parts
     std::vector<std::pair<uint32_t, uint32_t>> terms;
-    const uint32_t* p = plan.program.data() + plan.first_record;
+    const uint32_t* p = plan.program.data();
     for (int r = 0; r < n_ops; ++r, p += hop_sweep_words((int)p[7])) {
         terms.clear();
         for (uint32_t t = 0; t < p[7]; ++t)
-            terms.emplace_back(p[kSweepHead + 2 * t] / kLane, p[kSweepHead + 2 * t + 1]);
+            terms.emplace_back(p[kSweepHead + 2 * t], p[kSweepHead + 2 * t + 1]);
         for (size_t first = 0, n = 0; first < terms.size(); first += n) {
             n = std::min(terms.size() - first, (size_t)kSweepInline);
             const bool last = first + n == terms.size();
@@ -355,12 +296,12 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
             const bool on_its_way = keep && !store && (grad || none);
             out[w] = (uint32_t)(kSweepInline + 1 - n) * kSweepStep + (on_its_way ? 0u : kSweepLong) +
                      (w / kSweepRecord % 2 ? kSweepOdd : 0u);
-            out[w + 1] = (grad ? kSweepWithGrad : 0u) | (keep ? kSweepToLocal | local(last ? p[1] / kLane : partial) : 0u) |
+            out[w + 1] = (grad ? kSweepWithGrad : 0u) | (keep ? kSweepToLocal | local(last ? p[1] : partial) : 0u) |
                          (store ? kSweepToRing : 0u);
             if (w && (n > 5 || !on_its_way)) out[w - kSweepRecord + 1] |= kSweepNextWhole;
             if (grad && external) put_address(w + 2, at.external + (int64_t)p[5] * at.d);
             else if (grad) std::copy(p + 4, p + 7, out.begin() + (std::ptrdiff_t)w + 2);
-            out[w + 15] = p[3] / kLane;
+            out[w + 15] = p[3];
             if (store) put_address(w + 30, at.ring + (int64_t)p[2] * at.stride);
             if (!last) terms[first + --n] = std::make_pair(partial, kOne);    // first source of the next part
         }
@@ -374,7 +315,7 @@ void hop_lower_sweep(const HopSweepPlan& plan, int n_ops, const HopSweepVectors&
             const size_t w = out.size();
             out.resize(w + 4, 0u);
             put_address(w, base + (int64_t)pairs[2 * k] * at.stride);
-            out[w + 2] = local(pairs[2 * k + 1] / kLane);
+            out[w + 2] = local(pairs[2 * k + 1]);
         }
     };
     auto groups = [&](size_t from) {                         // filled up to eights
@@ -535,7 +476,6 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     }
     HopSweepPlan plan;
     if (!hop_plan_sweep(ops, c->N * c->slots, c->N, &plan)) return HOP_OK;
-    if (cost.sweep_us(plan.n_local) > waves_us) return HOP_OK;
     HopSweepArgs a;
     a.mode = mode;
     HopSweepVectors vectors;
@@ -547,7 +487,7 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
     std::vector<uint32_t> words;
     hop_lower_sweep(plan, R, vectors, &a, &words);
     const size_t bytes = words.size() * sizeof(uint32_t);
-    if (bytes > room_bytes) return HOP_OK;
+    if (cost.sweep_us(a.n_local) > waves_us || bytes > room_bytes) return HOP_OK;
     HOP_HIP(c, hipMemcpy(room, words.data(), bytes, hipMemcpyHostToDevice));
     a.program = (const uint32_t*)room;
     a.velocities = c->vel != nullptr;

@@ -75,26 +75,19 @@ struct alignas(16) HopGradJob {
 };
 
 // ---- a whole pass as a program ------------------------------------------------------
-// What the records of a pass read, where their values are kept and in which order they come; hop_lower_sweep below writes
-// it down for sweep_kernel, which has no use for the runs and the added zeros.
-// The records of a pass in an order that respects their dependences, for gradients that need no sum over the columns
-// (none, synthetic, external): every column can then run the whole pass by itself.  Words of 32 bits:
-//   runs     count << 8 | kind for every run of records of one kind: the number of sources (possibly rounded up to an even
-//            one), + kSweepGrad << 4 with a gradient, + kSweepStore << 4 where a result is not just kept in a local slot
-//            (the flags of each record say); kSweepOther: more sources than that
+// The records of a pass, for gradients that need no sum over the columns (none, synthetic, external): every column can then
+// run the whole pass by itself.  What they read and where their values are kept, in words of 32 bits; hop_lower_sweep below
+// writes it down for the kernel:
 //   records  0 flags, 1 local slot of the result, 2 ring slot it is stored to, 3 local slot of the velocity, 4..6 key[]
 //            (synthetic: hash keys, the first two folded; external: the worker, and the worker of
 //            the next record with a gradient, whose load is issued ahead), 7 number of sources, then (local slot,
-//            weight) of every source, padded to whole fours; one empty record behind the last.  Where the
-//            number is rounded up, the local slot `zero`, which holds zero, follows with weight -0
+//            weight) of every source
 //   loads    (ring slot, local slot) of the values read from the rings, then (worker, local slot) of the velocities
-// A local slot is written as its byte offset.
 constexpr int kSweepHead = 8;
 constexpr int kSweepInline = 12;        // most sources of the kernel's chain
-constexpr int kSweepOther = 255;
 constexpr int kSweepMaxLocal = 160;     // most local slots: 184 registers, 2 wavefronts per SIMD
 enum : uint32_t { kSweepGrad = 1u, kSweepStore = 2u, kSweepKeep = 4u };
-constexpr int hop_sweep_words(int A) { return kSweepHead + (2 * A + 3) / 4 * 4; }
+constexpr int hop_sweep_words(int A) { return kSweepHead + 2 * A; }
 
 struct HopSweepOp {                     // one record, in ring-slot terms (host only)
     int wave = 0, out_slot = 0, worker = 0;
@@ -104,13 +97,13 @@ struct HopSweepOp {                     // one record, in ring-slot terms (host 
 };
 
 struct HopSweepPlan {
-    int n_runs = 0, n_local = 0, n_loads = 0, n_vel = 0;
-    int first_record = 0, first_load = 0;       // words
-    int first_external = 0, zero = -1;          // zero: -1 if no record uses it
+    int n_local = 0, n_loads = 0, n_vel = 0;
+    int first_load = 0;                         // word
+    int first_external = 0;                     // worker of the first record with one
     std::vector<uint32_t> program;
 };
 
-// Ops come wave by wave; records of one wave are independent of each other and may change places.
+// Ops come in an order that respects their dependences.
 // False if the pass needs more than kSweepMaxLocal values at a time.  Host only.
 bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_workers, HopSweepPlan* plan);
 

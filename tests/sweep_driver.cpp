@@ -1,6 +1,7 @@
 // The program of a whole pass (hop_plan_sweep) run on the CPU against its records run one by one on the rings:
 // random schedules of waves, ring depths, source counts past the unrolled ones, vectors listed twice, jumps into
 // their own slot, velocities, every kind of gradient.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -38,7 +39,7 @@ static float grad_of(const uint32_t* key) { return (float)((key[0] * 2654435761u
 int main() {
     std::mt19937 gen(3);
     auto below = [&](int n) { return (int)(gen() % (unsigned)n); };
-    int wide = 0, refused = 0, evens = 0, planned = 0, kinds[4] = {0, 0, 0, 0};
+    int wide = 0, refused = 0, kinds[4] = {0, 0, 0, 0};
     for (int run = 0; run < 400; ++run) {
         const int N = 1 + below(run % 7 == 0 ? 90 : 12), depth = 1 + below(5), slots = N * depth, waves = 1 + below(12);
         const int mode = below(3);                                   // 0 none, 1 keys, 2 external
@@ -97,65 +98,66 @@ int main() {
         HopSweepPlan plan;
         if (!hop_plan_sweep(ops, slots, N, &plan)) { ++refused; continue; }
         EXPECT(plan.n_local <= kSweepMaxLocal);
-        ++planned;
         std::vector<float> got = ring0, gvel = vel0, local((size_t)plan.n_local, NAN);
         const std::vector<uint32_t>& P = plan.program;
-        auto at = [&](uint32_t off) -> float& { return local.at(off / 256); };
+        std::vector<char> used((size_t)plan.n_local, 0);
+        auto at = [&](uint32_t slot) -> float& { used.at(slot) = 1; return local[slot]; };
         size_t list = (size_t)plan.first_load;
         for (int k = 0; k < plan.n_loads; ++k, list += 2) at(P.at(list + 1)) = ring0.at(P.at(list));
         const size_t vels = list;
         for (int k = 0; k < plan.n_vel; ++k, list += 2) at(P.at(list + 1)) = vel0.at(P.at(list));
         EXPECT(list == P.size());
-        const bool even = plan.zero >= 0;                            // odd records read a zero more
-        if (even) at((uint32_t)plan.zero) = 0.f;
-        evens += even;
         std::vector<char> stored((size_t)slots, 0);
-        size_t rec = (size_t)plan.first_record;
+        size_t rec = 0;
         int done = 0;
         float ahead = ext.at(plan.first_external);
-        for (int k = 0; k < plan.n_runs; ++k) {
-            const uint32_t kind = P.at(k) & 0xFF;
-            for (uint32_t n = P.at(k) >> 8; n > 0; --n, ++done) {
-                const uint32_t* h = &P.at(rec);
-                const int A = (int)h[7];
-                EXPECT(rec % 4 == 0 && rec + hop_sweep_words(A) + hop_sweep_words(kSweepInline) <= (size_t)plan.first_load);
-                const bool kept = (h[0] & kSweepKeep) && !(h[0] & kSweepStore);
-                if (kind == (uint32_t)kSweepOther) EXPECT(A > kSweepInline);
-                else EXPECT(kind == (even ? (A + 1) / 2 * 2 : A) + ((h[0] & kSweepGrad) << 4) + (kept ? 0u : kSweepStore << 4));
-                if (kind != (uint32_t)kSweepOther) kinds[kind >> 4]++;
-                float acc = 0.f;
-                for (int t = 0; t < (even && A <= kSweepInline ? (A + 1) / 2 * 2 : A); ++t) {
-                    EXPECT(!std::isnan(at(h[kSweepHead + 2 * t])));
-                    if (t >= A) EXPECT(h[kSweepHead + 2 * t + 1] == 0x80000000u);     // -0 * 0: no change to a sum of -0
-                    acc = std::fmaf(as_float(h[kSweepHead + 2 * t + 1]), at(h[kSweepHead + 2 * t]), acc);
-                }
-                if (h[0] & kSweepGrad) {
-                    float g;
-                    if (mode == 2) {
-                        g = ahead;
-                        EXPECT(g == ext.at(h[4]));
-                        ahead = ext.at(h[5]);
-                    } else {
-                        g = grad_of(h + 4);
-                    }
-                    if (mom) g = at(h[3]) = std::fmaf(mu, at(h[3]), g);
-                    acc = std::fmaf(-eta, g, acc);
-                }
-                if (h[0] & kSweepKeep) at(h[1]) = acc;
-                if (h[0] & kSweepStore) {
-                    EXPECT(!stored.at(h[2]));                        // once per ring slot
-                    stored[h[2]] = 1;
-                    got[h[2]] = acc;
-                }
-                rec += hop_sweep_words(A);
+        for (; rec < (size_t)plan.first_load; ++done) {
+            const uint32_t* h = &P.at(rec);
+            const int A = (int)h[7];
+            EXPECT(rec + hop_sweep_words(A) <= (size_t)plan.first_load);
+            kinds[(h[0] & kSweepGrad) + ((h[0] & kSweepKeep) && !(h[0] & kSweepStore) ? 0 : 2)]++;
+            float acc = 0.f;
+            for (int t = 0; t < A; ++t) {
+                EXPECT(!std::isnan(at(h[kSweepHead + 2 * t])));
+                acc = std::fmaf(as_float(h[kSweepHead + 2 * t + 1]), at(h[kSweepHead + 2 * t]), acc);
             }
+            if (h[0] & kSweepGrad) {
+                float g;
+                if (mode == 2) {
+                    g = ahead;
+                    EXPECT(g == ext.at(h[4]));
+                    ahead = ext.at(h[5]);
+                } else {
+                    g = grad_of(h + 4);
+                }
+                if (mom) g = at(h[3]) = std::fmaf(mu, at(h[3]), g);
+                acc = std::fmaf(-eta, g, acc);
+            }
+            if (h[0] & kSweepKeep) at(h[1]) = acc;
+            if (h[0] & kSweepStore) {
+                EXPECT(!stored.at(h[2]));                        // once per ring slot
+                stored[h[2]] = 1;
+                got[h[2]] = acc;
+            }
+            rec += hop_sweep_words(A);
         }
         EXPECT(done == (int)ops.size());
+        EXPECT(ops.empty() || std::find(used.begin(), used.end(), 0) == used.end());    // no local slot is counted in vain
         for (int k = 0; k < plan.n_vel; ++k) gvel.at(P.at(vels + 2 * k)) = at(P.at(vels + 2 * k + 1));
         for (int q = 0; q < slots; ++q) EXPECT(got[q] == ring[q]);
         for (int q = 0; q < N; ++q) EXPECT(gvel[q] == vel[q]);
     }
-    EXPECT(wide > 50 && refused > 0 && evens > 20 && planned - evens > 20 && kinds[0] && kinds[1] && kinds[2] && kinds[3]);
+    EXPECT(wide > 50 && refused > 0 && kinds[0] && kinds[1] && kinds[2] && kinds[3]);
+    // as many values at a time as there are local slots, and one more
+    for (int n = kSweepMaxLocal; n <= kSweepMaxLocal + 1; ++n) {
+        std::vector<HopSweepOp> ops((size_t)n);
+        for (int q = 0; q < n; ++q) {
+            ops[q].out_slot = ops[q].worker = q;
+            ops[q].terms.emplace_back(q, 1.f);
+        }
+        HopSweepPlan plan;
+        EXPECT(hop_plan_sweep(ops, n, n, &plan) == (n == kSweepMaxLocal) && (n > kSweepMaxLocal || plan.n_local == n));
+    }
     std::printf("ok wide=%d refused=%d\n", wide, refused);
     return 0;
 }

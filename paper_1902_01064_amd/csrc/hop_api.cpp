@@ -340,14 +340,18 @@ float* slot_ptr(const hop_ctx* c, int worker, int slot) {
 
 // A pass in microseconds as one sweep and wave by wave, to choose between the two.  The waves' side is fitted to 5082 passes
 // on MI355X (rings, tori, rings with chords and complete graphs of 4 to 100 workers, 64 to 4 M columns, each gradient, with
-// and without a velocity, in lock-step, with Exp(1) delays and with a straggler), the sweep's to 1300 like them: half of
-// them within 10 %, nine in ten within 30 %.
+// and without a velocity, in lock-step, with Exp(1) delays and with a straggler), the sweep's to 1344 like them: half of
+// them within 10 %, nine in ten within 30 %.  Of those 1344, 13 go the way that is slower by more than 4 %, at most by 30 %
+// (32 workers of 7 sources x 64 columns, synthetic gradients and a velocity, lock-step: 80 us in waves, 62 in the sweep); three
+// of them go into the sweep, at most 9 % slower there (64 workers x 20 000 columns, external gradients and a velocity, lock-step:
+// 130 us in waves, 142).
 struct SweepCost {
     int64_t d = 0;
     int waves = 0, records = 0, gradients = 0, mode = 0, workers = 0;
+    int parts = 0;                       // what the sweep makes of the records: more than one of a wide one
     bool vel = false;                    // the context has velocities
     int wide = 0;                        // records with more sources than the sweep's chain has
-    double terms = 0, wide_terms = 0;    // sources of the other records and of these
+    double sources = 0;
     double wide_chain = 0;               // over the waves: the most sources a wide record of the wave has
     double bytes = 0;                    // that reach the CUs wave by wave
     double distinct = 0;                 // over the waves: vectors read, each once per wave
@@ -356,19 +360,19 @@ struct SweepCost {
     // `one`: a wavefront takes its records one after the other, 0.14 us each with five sources and a synthetic gradient.
     // Alone on its SIMD it waits most of that time (the words of the next record, jumps); what it issues is a fifth to a
     // half, and the wavefronts there are registers for fill the rest.  A pass is the larger of the two, or what it reads and
-    // writes.  External gradients are read while the record before is at work, which is too short where wavefronts take turns.
-    // Wide records count about 1.7 times what their parts take (complete graphs of 13 to 32 workers in lock-step: 0.016 to
-    // 0.022 us a source): there the waves' estimate is at its weakest, and a refusal costs at most as much (24 workers x
-    // 65 540 columns: 285 us in waves, 179 in the sweep, which is refused).
+    // writes.  Synthetic gradients are worked out beside every part, whether it takes one or not.  External gradients are read
+    // while the record before is at work, which is too short where wavefronts take turns.
+    // The parts of wide records count like any record.  (Counted 1.7 times, 112 of the 1344 passes went the slower way, up to
+    // 2.2 times slower: 24 workers x 65 540 columns, complete and in lock-step, 285 us in waves, 177 in the sweep.)
     double sweep_us(int n_local) const {
         const double per_simd = std::max(1.0, (double)((d + 255) / 256) / 256.0);
         const int at_a_time = n_local <= 48 ? 8 : n_local <= 80 ? 5 : n_local <= 112 ? 4 : 2;
         const double turns = std::ceil(per_simd / at_a_time);
         const bool synth = mode == HOP_GRAD_SYNTH, external = mode == HOP_GRAD_EXTERNAL;
-        double one = 0.069 * (records - wide) + 0.0043 * terms + 0.036 * wide_terms + 0.94 * ((n_local + 7) / 8);
-        one += gradients * (synth ? 0.047 : external ? turns > 1 ? 0.17 : 0.011 : 0.0);
-        double issue = 0.017 * (records - wide) + 0.002 * terms + 0.01 * wide_terms;
-        issue += gradients * ((synth ? 0.021 : 0.0) + (vel ? 0.0094 : 0.0));
+        double one = 0.069 * parts + 0.0043 * sources + 0.94 * ((n_local + 7) / 8);
+        one += synth ? 0.047 * parts : external ? (turns > 1 ? 0.17 : 0.011) * gradients : 0.0;
+        double issue = 0.017 * parts + 0.002 * sources;
+        issue += (synth ? 0.021 * parts : 0.0) + (vel ? 0.0094 * gradients : 0.0);
         double vectors = 4.0 * workers;                          // read at the start and stored, about
         if (vel && gradients) vectors += 2.0 * workers;
         if (external) vectors += gradients;
@@ -380,8 +384,8 @@ struct SweepCost {
     // each 1024 of up to 4096 columns.
     double waves_us() const {
         const bool mostly_wide = 2 * wide > records, cached = ring_bytes < 30e6 && !mostly_wide, moved = vel && gradients > 0;
-        const double sources = terms + wide_terms, mean = std::min(sources / records, 8.0);
-        double launch = waves * (vel ? 2.9 : 2.1 + 0.31 * mean);
+        const double mean = std::min(sources / records, 8.0);
+        double launch = waves * (vel ? 2.9 : 2.1 + (wide ? 0.2 : 0.31) * mean);      // sources of wide records: in the chain
         if (d >= 4096) launch += records * (moved ? 0.062 : 0.012);
         if (d >= 16384 && !vel) launch += 1.3 * waves;
         const double chain = 0.13 * (double)std::min<int64_t>(4, (d + 1023) / 1024) * wide_chain;
@@ -414,7 +418,8 @@ SweepCost sweep_cost(const hop_ctx* c, const hop_schedule* s, const std::vector<
             const bool wide = j.A > kSweepInline;
             k.gradients += j.g != nullptr;
             k.wide += wide;
-            (wide ? k.wide_terms : k.terms) += j.A;
+            k.parts += wide ? 1 + (j.A - 2) / (kSweepInline - 1) : 1;      // a part takes 12, one of them the sum so far
+            k.sources += j.A;
             if (wide) widest = std::max(widest, j.A);
             seen.insert(seen.end(), j.src, j.src + j.A);
         }

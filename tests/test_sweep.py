@@ -102,13 +102,15 @@ def test_pass_keeps_the_sign_of_zero():
         sess.close()
 
 
-# records with more sources than are unrolled, and many records per wave of a narrow model, are faster in waves
+# many records per wave of a narrow model are faster in waves, and so are synthetic gradients where records of many sources take
+# several parts; without them such records are faster in one launch (15 iterations in lock-step, waves and one launch: 14 workers x
+# 1024 columns 56.5 and 42.2 us, 24 x 65 536 267 and 110 us)
 @pytest.mark.gpu
 @pytest.mark.parametrize("nb,d,delay,mode,one", [
     (inputs.ring(4), 1024, "none", "zero", True), (inputs.torus(4, 4), 1000, "none", "zero", True),
     (inputs.torus(9, 9), 1024, "none", "zero", False), (inputs.torus(9, 9), 1 << 20, "none", "synth", True),
-    (inputs.complete(14), 1024, "none", "zero", False), (inputs.complete(14), 1024, "exp1", "zero", True),
-    (inputs.complete(24), 1024, "none", "synth", False), (inputs.complete(24), 65536, "none", "zero", False),
+    (inputs.complete(14), 1024, "none", "zero", True), (inputs.complete(14), 1024, "exp1", "zero", True),
+    (inputs.complete(24), 1024, "none", "synth", False), (inputs.complete(24), 65536, "none", "zero", True),
     (inputs.complete(14), 1 << 20, "none", "synth", True), (inputs.ring_with_chords(32, 2, 7), 300007, "exp1", "synth", True),
 ])
 def test_which_way_a_pass_goes(nb, d, delay, mode, one):

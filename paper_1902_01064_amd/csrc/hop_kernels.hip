@@ -675,8 +675,8 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 #define HOP_SWEEP_TEXT                                                                                                \
     /* eight vectors of the list at s[18:19] */                                                                       \
     ".macro hop_list_words\n"                                                                                         \
-    "  s_load_dwordx16 s[36:51], s[18:19], 0\n"                                                                       \
-    "  s_load_dwordx16 s[52:67], s[18:19], 64\n"                                                                      \
+    "  s_load_dwordx16 s[68:83], s[18:19], 0\n"                                                                       \
+    "  s_load_dwordx16 s[84:99], s[18:19], 64\n"                                                                      \
     "  s_add_u32 s18, s18, 128\n"                                                                                     \
     "  s_addc_u32 s19, s19, 0\n"                                                                                      \
     "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
@@ -687,23 +687,23 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  s_addc_u32 s31, s[\\w+1], s21\n"                                                                               \
     ".endm\n"                                                                                                         \
     ".macro hop_list_load q\n"                                                                                        \
-    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cmp_eq_u64 s[68+4*\\q:69+4*\\q], 0\n"                                                                        \
     "  s_cbranch_scc1 .Lhop_wait_%=\n"                                                                                \
-    "  hop_columns 36+4*\\q\n"                                                                                        \
+    "  hop_columns 68+4*\\q\n"                                                                                        \
     "  global_load_dword v[8+\\q], %[lane], s[30:31] nt\n"                                                            \
     ".endm\n"                                                                                                         \
     ".macro hop_list_put q\n"                                                                                         \
-    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cmp_eq_u64 s[68+4*\\q:69+4*\\q], 0\n"                                                                        \
     "  s_cbranch_scc1 .Lhop_loaded_%=\n"                                                                              \
-    "  s_set_gpr_idx_on s[38+4*\\q], 8\n"                                                                             \
+    "  s_set_gpr_idx_on s[70+4*\\q], 8\n"                                                                             \
     "  v_mov_b32_e32 v16, v[8+\\q]\n"                                                                                 \
     ".endm\n"                                                                                                         \
     ".macro hop_list_store q\n"                                                                                       \
-    "  s_cmp_eq_u64 s[36+4*\\q:37+4*\\q], 0\n"                                                                        \
+    "  s_cmp_eq_u64 s[68+4*\\q:69+4*\\q], 0\n"                                                                        \
     "  s_cbranch_scc1 .Lhop_out_%=\n"                                                                                 \
-    "  s_set_gpr_idx_on s[38+4*\\q], 1\n"                                                                             \
+    "  s_set_gpr_idx_on s[70+4*\\q], 1\n"                                                                             \
     "  v_mov_b32_e32 v[8+\\q], v16\n"                                                                                 \
-    "  hop_columns 36+4*\\q\n"                                                                                        \
+    "  hop_columns 68+4*\\q\n"                                                                                        \
     "  global_store_dword %[lane], v[8+\\q], s[30:31] nt\n"                                                           \
     ".endm\n"                                                                                                         \
     /* v11: where the synthetic gradient of the keys at s[w+2] is in the table */                                     \
@@ -831,6 +831,9 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  .endif\n"                                                                                                      \
     ".endm\n"                                                                                                         \
     "  s_mov_b64 s[16:17], %[records]\n"                                                                              \
+    /* the first record's words, under the lists */                                                                   \
+    "  s_load_dwordx16 s[36:51], s[16:17], 0\n"                                                                       \
+    "  s_load_dwordx16 s[52:67], s[16:17], 64\n"                                                                      \
     "  s_mov_b64 s[18:19], %[lists]\n"                                                                                \
     "  s_mov_b64 s[20:21], %[columns]\n"                                                                              \
     "  s_mov_b32 s23, %[loads]\n"                                                                                     \
@@ -857,11 +860,9 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     ".Lhop_loaded_%=:\n"                                                                                              \
     "  s_set_gpr_idx_on s29, 0\n"                                                                                     \
     "  .if %[mode] == %[external]\n"                                                                                  \
-    "  s_mov_b64 s[38:39], %[first]\n"                                                                                \
-    "  hop_external 36\n"                                                                                             \
+    "  s_mov_b64 s[70:71], %[first]\n"                                                                                \
+    "  hop_external 68\n"                                                                                             \
     "  .endif\n"                                                                                                      \
-    "  s_load_dwordx16 s[36:51], s[16:17], 0\n"                                                                       \
-    "  s_load_dwordx16 s[52:67], s[16:17], 64\n"                                                                      \
     "  s_getpc_b64 s[34:35]\n"                                                                                        \
     ".Lhop_here_%=:\n"                                                                                                \
     "  s_add_u32 s26, s34, .Lhop_chains_%=-.Lhop_here_%=\n"                                                           \
@@ -927,13 +928,18 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 
 constexpr int kSweepThreads = 256;
 constexpr int kSynthSums = 12 * 255 + 1;               // values of a sum of 12 bytes
+// Of each thread, the table filled up: written out it is three instructions an entry.  As a loop up to the last sum it was a
+// tenth of a short pass (2 workers x 3 M columns, 30 records: 65.9 -> 60.6 us; 16 workers, 240 records: 497 -> 492).
+constexpr int kSynthEach = (kSynthSums + kSweepThreads - 1) / kSweepThreads;
 
 // LOCAL: local slots there are registers for.  64, 96, 128 and 184 registers: 8, 5, 4 and 2 wavefronts per SIMD.
 template <int MODE, bool MOM, int LOCAL>
 __global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const HopSweepArgs a) {
-    __shared__ float tableS[MODE == HOP_GRAD_SYNTH ? kSynthSums : 1];
+    __shared__ float tableS[MODE == HOP_GRAD_SYNTH ? kSynthEach * kSweepThreads : 1];
     if (MODE == HOP_GRAD_SYNTH) {
-        for (int k = threadIdx.x; k < kSynthSums; k += kSweepThreads) tableS[k] = (float)(k - 1530) * a.scale;
+        const float sum = (float)((int)threadIdx.x - 1530);
+#pragma unroll
+        for (int k = 0; k < kSynthEach; ++k) tableS[threadIdx.x + k * kSweepThreads] = (sum + (float)(k * kSweepThreads)) * a.scale;
         __syncthreads();
     }
     const uint32_t table = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)tableS;

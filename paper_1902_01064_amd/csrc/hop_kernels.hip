@@ -635,8 +635,10 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 // The values that later records still read live in vector registers (the host hands out the local slots by live range:
 // about 1.6 vectors per worker, whatever the ring depth); a ring slot is read once if its old content is used and written
 // once if its content survives the pass.  Lanes never exchange data.
-// Bound by the vector unit's issue rate: per record one instruction per source, 18 for a synthetic gradient (4 of them
-// multiplies at about half rate) and one to apply it.  That is why the body is written out:
+// Bound by the vector unit's issue rate: per record one instruction per source, 18 for a synthetic gradient (worked out beside
+// every record) and one to apply it, each 4.1 to 4.4 cycles.  In index mode every vector instruction takes that, the multiplies
+// among the 18 no more than a v_xor; outside it v_xor, shifts, adds and v_fma take 2.2 to 2.4 on a full SIMD, v_mul_lo, v_dot4,
+// v_alignbit and sdwa forms 4.1.  That is why the body is written out:
 //  - a record names its sources, and registers can only be named by number: the index mode of the vector unit (M0, set by
 //    the scalar unit beside the arithmetic) lets v_fmac read a local slot where it is.  With the local slots in LDS a source
 //    took an address, a load and the v_fmac;
@@ -645,12 +647,16 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
 //    place of three v_sad_u8, a conversion and a multiplication.  Four wavefronts share the table, and nothing else.
 // 32 workers x 25 M columns x 3136 records (52 local slots): 242 ms wave by wave, 83.7 with local slots in LDS, 60.5 with them
 // in registers, 57.0 with the table, 54.1 with a scalar unit that only sets indexes (records count themselves, the jump
-// is one s_or); 16 workers x 2 M columns x 640 records with momentum: 7.7, 1.57, 0.98, 0.94, 0.90 ms.  Without a gradient
+// is one s_or): 25.7 vector instructions a record, 95 % of the launch at 4 cycles; 16 workers x 2 M columns x 640 records with
+// momentum: 7.7, 1.57, 0.98, 0.94, 0.90 ms.  Without a gradient
 // the words of the records count (128 B each through the scalar cache): short records of up to five sources are one
 // load, 16 workers x 3 M columns, 240 records of three sources: 336 -> 290 us.
-// Index mode stays on all along and the instructions outside the chains have no relative operand: with the mode off between
-// them and on again a few scalar instructions later, a vector instruction now and then ran in the mode before.  The
-// instructions between the last v_dot4 and the ds_read of its result are needed too: inside an asm block no compiler fills
+// Index mode stays on all along; which operand is relative, if any, is said anew by s_set_gpr_idx_on, which writes M0 as any
+// scalar instruction writes its result and holds for the next vector instruction.  (A first form that turned the mode off
+// between the chains gave wrong velocities now and then, and its cause is not known: on a full GPU, 6e9 rounds of three changes
+// each by off and on, with 0 to 8 scalar instructions between, ran no vector instruction in a wrong mode, nor did as many
+// rounds of the changes made here.)  M0 is reserved, so no clobber: the compiler sets it before each use of its own.
+// The instructions between the last v_dot4 and the ds_read of its result are needed: inside an asm block no compiler fills
 // up wait states.
 #define HOP_REGS_2(x, t) x #t "0", x #t "1"
 #define HOP_REGS_4(x, t) HOP_REGS_2(x, t), x #t "2", x #t "3"
@@ -806,8 +812,10 @@ __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob jo
     "  s_waitcnt lgkmcnt(0)\n"                                                                                        \
     "  s_branch .Lhop_record\\n\\()_%=\n"                                                                             \
     ".endm\n"                                                                                                         \
-    /* the record whose words are at s[w..], while those of the next are loaded to s[n..] */                          \
+    /* the record whose words are at s[w..], while those of the next are loaded to s[n..]; from the start of a line of the */ \
+    /* instruction cache on: 25 M columns 54.3 -> 54.0 ms against 4 lines touched instead of 3 */                     \
     ".macro hop_record w, n, at\n"                                                                                    \
+    "  .p2align 6\n"                                                                                                  \
     ".Lhop_record\\w\\()_%=:\n"                                                                                       \
     "  s_load_dwordx16 s[\\n:\\n+15], s[16:17], \\at\n"                                                               \
     "  .if %[mode] != %[synth]\n"                                                                                     \

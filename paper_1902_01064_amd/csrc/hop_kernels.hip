@@ -1537,16 +1537,15 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
     if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;      // few is used only where grid is small
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
-#define HOP_MARGINS(BLOCKS, ROWS, STREAM)                                                                                   \
-    do {                                                                                                                    \
-        if (nseg == 1) hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, true>), dim3((unsigned)(BLOCKS)), dim3(kThreads), \
-                                          0, (hipStream_t)stream, jobs_dev, B, d, nseg);                                    \
-        else hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, false>), dim3((unsigned)(BLOCKS)), dim3(kThreads), 0,    \
-                                (hipStream_t)stream, jobs_dev, B, d, nseg);                                                 \
-    } while (0)
-    if (grid < kMarginFew && near) HOP_MARGINS(few, 1, false);
-    else if (grid < kMarginFew) HOP_MARGINS(few, 1, true);
-    else HOP_MARGINS(grid, kMarginRows, true);
+#define HOP_MARGINS(BLOCKS, ROWS, STREAM, ONE)                                                                              \
+    hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, ONE>), dim3((unsigned)(BLOCKS)), dim3(kThreads), 0,               \
+                       (hipStream_t)stream, jobs_dev, B, d, nseg)
+    static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "few workgroups of one segment: near");
+    if (grid < kMarginFew && nseg == 1) HOP_MARGINS(few, 1, false, true);
+    else if (grid < kMarginFew && near) HOP_MARGINS(few, 1, false, false);
+    else if (grid < kMarginFew) HOP_MARGINS(few, 1, true, false);
+    else if (nseg == 1) HOP_MARGINS(grid, kMarginRows, true, true);
+    else HOP_MARGINS(grid, kMarginRows, true, false);
 #undef HOP_MARGINS
     return launch_status();
 }

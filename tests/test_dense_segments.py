@@ -44,7 +44,7 @@ def test_gradient_and_coefficients(d, B, loss):
 @pytest.mark.parametrize("d", [16384, 16385])
 @pytest.mark.parametrize("momentum", [0.0, 0.9])
 def test_coefficients_of_a_run(d, momentum):
-    """Both ways a wave runs its gradients: margins beside the Reduce (32 rows) and ahead of it (64 rows)."""
+    """Both ways a wave runs its gradients: margins beside the Reduce (8 rows) and ahead of it (64 rows)."""
     nb = inputs.ring(4)
     for B in (8, 64):
         c = dict(inputs.config(1, d=d, rows=96, K=3), in_nbrs=nb, W=inputs.uniform_weights(nb), N=4, batch=B, loss=1, momentum=momentum)
@@ -66,3 +66,44 @@ def test_coefficients_of_a_run(d, momentum):
                     assert float((got - want).abs().max()) <= 1e-5 / B
         finally:
             sess.close()
+
+
+# one wave of all workers.  752, 1024 and 2304 chunks of 256 columns: 8 or 4 wavefronts share a chunk's rows, or chunks of 1024
+# columns with the rows whole; 208, 512 and 900 workgroups of four rows: one row each in the first, four in the others
+@pytest.mark.parametrize("side,d,B", [(4, 12001, 50), (4, 16384, 128), (6, 16383, 100)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_large_waves_of_one_segment(side, d, B, momentum):
+    """Coefficients and results of a wave against 64 bits, from them the gradient (log loss: no sample leaves the sum)."""
+    N, nb = side * side, inputs.torus(side, side)
+    c = dict(inputs.config(1, d=d, rows=160, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
+             lr=0.5, momentum=momentum, skip_on=False, mult=None, delay_kind=inputs.DELAY_NONE)
+    ws = inputs.hidden_w(6, d, "cuda")
+    data = [inputs.dense_svm_data(6, i, 160, d, ws, "cuda") for i in range(N)]
+    p0 = torch.randn(N, d, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda") / d ** 0.5
+    sess = Session(c)
+    try:
+        sess.set_dense([x for x, _ in data], [y for _, y in data])
+        sess.set_params(p0)
+        s = sess.simulate()
+        assert s.n_waves == 1 and s.n_records == N
+        sess.step()
+        sess.sync()
+        for e in range(N):
+            i, ids = int(s.worker[e]), torch.from_numpy(s.batch_rows[e].copy()).cuda().long()
+            X, y = data[i][0][ids].double(), data[i][1][ids].double()
+            coef = torch.from_numpy(sess.coef(e)).cuda().double()
+            # the slope of a coefficient in its margin is at most 1 / 4 B; a sum of d products is off by (d + 1) 2^-24 of their magnitudes
+            off = (d + 1) * 2.0 ** -24 * (X.abs() @ p0[i].double().abs())
+            want = y / (B * (1 + torch.exp(y * (X @ p0[i].double()))))
+            assert bool(((coef - want).abs() <= (0.25 * off + 1e-6) / B).all())
+            g = 0.25 * p0[i].double() - coef @ X
+            mag = 0.25 * p0[i].double().abs() + coef.abs() @ X.abs()
+            acc, size = torch.zeros_like(g), torch.zeros_like(g)
+            for a in range(int(s.src_begin[e]), int(s.src_begin[e + 1])):
+                x = float(s.src_weight[a]) * p0[int(s.src_worker[a])].double()
+                acc, size = acc + x, size + x.abs()
+            got = sess.slot(i, int(s.out_slot[e])).double()
+            room = 2.0 ** -24 * (0.5 * (B + 4) * mag + 8 * size)        # B + 1 products, five sources and the step
+            assert bool(((got - (acc - 0.5 * g)).abs() <= room).all())
+    finally:
+        sess.close()

@@ -1,5 +1,5 @@
 // The program of a whole pass (hop_plan_sweep) run on the CPU against its records run one by one on the rings:
-// random schedules of waves, ring depths, source counts past the unrolled ones, vectors listed twice, jumps into
+// random schedules of waves, ring depths, source counts past what the kernel takes in one part, vectors listed twice, jumps into
 // their own slot, velocities, every kind of gradient.
 #include <algorithm>
 #include <cmath>

@@ -29,7 +29,8 @@ def test_program_gives_what_the_records_give(tmp_path):
 
 
 # 1 column, one short of / exactly / one past a wavefront's 64, a ragged tail past the narrow-model limit; records of
-# 1 to 14 sources (12 are unrolled); velocities; jumps; both approaches; a graph that leaves too many values for LDS
+# 1 to 14 sources (12 go through the kernel's chain); velocities; jumps; both approaches; a graph with too many values for the
+# registers
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", ["zero", "synth", "external"])
 @pytest.mark.parametrize("graph,over", [
@@ -81,8 +82,8 @@ def test_pass_equals_the_waves_bit_for_bit(mode, graph, over):
 
 @pytest.mark.gpu
 def test_pass_keeps_the_sign_of_zero():
-    """Parameters of -0: with a velocity a sum starts with a product, so every average is -0 again, also where a record
-    with an odd number of sources is filled up with a zero."""
+    """Parameters of -0: with a velocity a sum starts with a product, so every average is -0 again, whether the number of
+    sources is odd or even."""
     nb = inputs.ring_with_chords(32, 2, 7)
     c = dict(inputs.config(4, d=130, K=8), in_nbrs=nb, W=inputs.uniform_weights(nb), N=32, s=2, b=1, skip_on=False, mult=None,
              delay_kind=inputs.DELAY_EXP1, momentum=0.9)

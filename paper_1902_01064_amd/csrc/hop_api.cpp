@@ -162,6 +162,8 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out) {
 // this record reads for the last time: a lane reads all its sources before it writes.
 bool hop_plan_sweep(const std::vector<HopSweepOp>& ops, int n_ring_slots, int n_workers, HopSweepPlan* plan) {
     const int R = (int)ops.size();
+    static_assert(((HOP_MAX_A - 2) / (kSweepInline - 1) + 1) * kSweepRecord < 1 << 7, "words of a record");
+    if (R >= 1 << 24) return false;                  // the words of a pass are counted in 31 bits
     std::vector<int> last_writer((size_t)n_ring_slots, -1), holds((size_t)n_ring_slots, -1);
     std::vector<int> last_use;                       // by value
     std::vector<std::pair<int, int>> initial;        // (ring slot, value) read before it is written
@@ -452,7 +454,6 @@ int build_sweep(hop_ctx* c, hop_schedule* s, const std::vector<HopMixJob>& mix, 
         for (int p = s->wave_begin[w]; p < s->wave_begin[w + 1]; ++p) {
             const int e = s->wave_order[p];
             HopSweepOp& op = ops[p];
-            op.wave = w;
             op.out_slot = slot_of(mix[p].out);
             op.worker = s->worker[e];
             op.grad = mix[p].g != nullptr;

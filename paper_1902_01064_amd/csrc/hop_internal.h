@@ -90,7 +90,7 @@ enum : uint32_t { kSweepGrad = 1u, kSweepStore = 2u, kSweepKeep = 4u };
 constexpr int hop_sweep_words(int A) { return kSweepHead + 2 * A; }
 
 struct HopSweepOp {                     // one record, in ring-slot terms (host only)
-    int wave = 0, out_slot = 0, worker = 0;
+    int out_slot = 0, worker = 0;
     bool grad = false, vel = false, external = false;
     uint32_t key[3] = {0, 0, 0};
     std::vector<std::pair<int, float>> terms;   // (ring slot, weight), in the order the sum is taken

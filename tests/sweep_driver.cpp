@@ -49,14 +49,14 @@ int main() {
         std::vector<HopSweepOp> ops;
         for (int w = 0; w < waves; ++w) {
             // no record of a wave writes a slot that another one of it reads or writes
+            const size_t wave_begin = ops.size();
             std::vector<int> read_by((size_t)slots, -1), written_by((size_t)slots, -1);
             for (int n = 1 + below(2 * N); n > 0; --n) {
                 HopSweepOp op;
-                op.wave = w;
                 op.worker = below(N);
                 op.out_slot = op.worker * depth + below(depth);
                 bool seen = false;
-                for (const HopSweepOp& o : ops) seen = seen || (o.wave == w && o.worker == op.worker);
+                for (size_t o = wave_begin; o < ops.size(); ++o) seen = seen || ops[o].worker == op.worker;
                 const int me = (int)ops.size();
                 if (seen || written_by[op.out_slot] >= 0 || read_by[op.out_slot] >= 0) continue;
                 const int A = uniform ? uniform : 1 + below(below(6) == 0 ? 20 : 8);

@@ -47,7 +47,6 @@ int main() {
             std::vector<char> read((size_t)slots, 0), written((size_t)slots, 0), used((size_t)N, 0);
             for (int n = 1 + below(2 * N); n > 0; --n) {
                 HopSweepOp op;
-                op.wave = w;
                 op.worker = below(N);
                 op.out_slot = op.worker * depth + below(depth);
                 if (used[op.worker] || written[op.out_slot] || read[op.out_slot]) continue;

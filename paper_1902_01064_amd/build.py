@@ -15,8 +15,11 @@ OBJ = os.path.join(HERE, "_build")
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+# The last flag has a kernel's first 14 words of arguments in scalar registers when a wavefront starts, instead of a load from the
+# argument segment in front of everything else (4 workers x 1024 columns, two launches a wave: 339 -> 316 us per pass; 16 x 2^20
+# sparse columns: 7.16 -> 6.89 ms).
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          "-munsafe-fp-atomics"]
+          "-munsafe-fp-atomics", "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def _run(cmd):

@@ -5,6 +5,7 @@
 // tables; the generator of synthetic gradients and the whole pass in one launch are bound by instruction issue.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -74,21 +75,59 @@ __device__ __forceinline__ void st4_stream(float* p, int64_t i4, float4 v) {
     __builtin_nontemporal_store(t, (gvec_out)p + i4);
 }
 
-// blockIdx -> (job, chunk) so that the 8 workgroups dealt to the 8 XCDs at the same moment work on
-// 8 different column chunks, and one XCD sees the same chunk for all jobs of a wave back to back:
-// a source vector read by several jobs (a worker and its neighbours all average it) is then
+// A launch's grid over jobs and column chunks is (chunks of one round, jobs, rounds), so a workgroup's job and chunk are its
+// block index: worked out from one number they took up to four divisions, 100 to 200 scalar instructions in front of the first
+// load of every workgroup (us per pass: 4 workers x 1024 columns, dense, 316 -> 308; 8 x 30 011 2085 -> 2022; 16 x 65536
+// 3544 -> 3480; external gradients 16 x 4 M 2983 -> 2933; 16 x 2^20 sparse 6921 -> 6870).  Workgroups are dealt out in the order x, y, z, one to each of the 8 XCDs in turn, and a round is a
+// multiple of 8 chunks: those dealt out at the same moment work on 8 different chunks, and one XCD sees the same chunk for
+// all jobs of a wave back to back, so a source vector read by several jobs (a worker and its neighbours all average it) is
 // fetched from HBM once per XCD-local L2 instead of once per job.
-__device__ __forceinline__ bool map_block(int64_t b, int n_jobs, int64_t n_chunks, int* job, int64_t* chunk) {
-    int xcd = (int)(b % kXcd);
-    int64_t local = b / kXcd;
-    *job = (int)(local % n_jobs);
-    *chunk = (local / n_jobs) * kXcd + xcd;
-    return *chunk < n_chunks;
-}
+constexpr int64_t kMaxGridYZ = 65535;
 
-inline int64_t grid_for(int n_jobs, int64_t n_chunks) {
-    int64_t padded = (n_chunks + kXcd - 1) / kXcd * kXcd;
-    return padded * n_jobs;
+// (8, jobs, chunks / 8), wider rounds where a grid has no room for as many; false: too many workgroups
+inline bool chunk_grid(int n_jobs, int64_t n_chunks, dim3* grid) {
+    int64_t width = kXcd;
+    while ((n_chunks + width - 1) / width > kMaxGridYZ) width *= 2;
+    const int64_t rounds = (n_chunks + width - 1) / width;
+    if (width * n_jobs * rounds > 0x7FFFFFFFll) return false;
+    *grid = dim3((unsigned)width, (unsigned)n_jobs, (unsigned)rounds);
+    return true;
+}
+// chunk of this workgroup of such a grid (`width`: its x); it may lie past the last one
+__device__ __forceinline__ int64_t grid_chunk(int width) { return (int64_t)blockIdx.z * width + blockIdx.x; }
+
+// Rounds in which every XCD takes a run of consecutive chunks: longer contiguous pieces of every stream are in flight at a
+// time.  The last, partly filled round is dealt out evenly (shorter runs on all XCDs, not full runs on the first few).
+struct Runs {
+    int n_chunks, run, whole, tail;         // chunks, length of a run, whole rounds, length of a run in the round behind them
+    int front;                              // rounds of other workgroups in front
+};
+// its members as arguments of a kernel: one by one, so that they are in scalar registers when a wavefront starts
+#define HOP_RUNS_IN int n_chunks, int run, int whole, int tail
+#define HOP_RUNS Runs{n_chunks, run, whole, tail, 0}
+#define HOP_RUNS_OF(r) r.n_chunks, r.run, r.whole, r.tail
+// grid.z: `front` workgroups for something else, filled up to whole rounds, then the rounds; false: too many workgroups
+inline bool run_grid(int n_jobs, int64_t n_chunks, int run, int64_t front, Runs* r, dim3* grid) {
+    for (;; run *= 2) {
+        const int64_t span = (int64_t)kXcd * run, round = span * n_jobs;
+        const int64_t ahead = (front + round - 1) / round, z = ahead + (n_chunks + span - 1) / span;
+        if (z * round > 0x7FFFFFFFll) return false;
+        if (z > kMaxGridYZ) continue;
+        *r = Runs{(int)n_chunks, run, (int)(n_chunks / span), (int)((n_chunks % span + kXcd - 1) / kXcd), (int)ahead};
+        *grid = dim3((unsigned)span, (unsigned)n_jobs, (unsigned)z);
+        return true;
+    }
+}
+// index of this workgroup in the order in which they are dealt out
+__device__ __forceinline__ unsigned grid_index(const Runs& r, int n_jobs) {
+    return (blockIdx.z * n_jobs + blockIdx.y) * (unsigned)(kXcd * r.run) + blockIdx.x;
+}
+// chunk of this workgroup in round `round`; -1: none
+__device__ __forceinline__ int run_chunk(const Runs& r, int round) {
+    const int xcd = blockIdx.x % kXcd, sub = blockIdx.x / kXcd;
+    if (round < r.whole) return (round * kXcd + xcd) * r.run + sub;
+    const int chunk = r.whole * kXcd * r.run + xcd * r.tail + sub;
+    return sub < r.tail && chunk < r.n_chunks ? chunk : -1;
 }
 
 // ------------------------------------------------------------------------ Reduce + Apply ----
@@ -96,10 +135,9 @@ inline int64_t grid_for(int n_jobs, int64_t n_chunks) {
 // weights from Eq. 2 times the mixing matrix, already normalised on the host).
 //
 // Template knobs: VEC float4 per thread per source; NT 0 = ordinary accesses, 1 = g and the result
-// non-temporal (each touched once), 2 = sources too; MAP 1 = the XCD-aware map above, 10 + G = the same
-// with runs of G consecutive chunks per XCD; T threads per workgroup.
+// non-temporal (each touched once), 2 = sources too; T threads per workgroup.
 // Measured on 32 jobs x 25 M columns with ~7.6 shared sources each: job-major workgroups are 2.3x slower than
-// MAP 1 and chunk-major ones that ignore the XCDs 1.45x slower; vector width (1-8), block size (128-1024) and
+// the grid above and chunk-major ones that ignore the XCDs 1.45x slower; vector width (1-8), block size (128-1024) and
 // cache hints move the time by under 5 %.
 template <int NT>
 __device__ __forceinline__ float4 ld_src(const float* p, int64_t i) {
@@ -229,31 +267,14 @@ __device__ __forceinline__ void mix_tile_any(const HopMixJob* __restrict__ job, 
     }
 }
 
-// Work of one workgroup of the mix; `bid` is its index among the mix's workgroups (the launch may
-// hold other workgroups in front of them, which only rotates the assignment of XCDs).
-template <int VEC, int NT, int MAP, int T>
-__device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, int n_jobs, int64_t d,
-                                          int64_t n_chunks, int64_t bid) {
-    int j;
-    int64_t chunk;
-    if (MAP == 1) {
-        if (!map_block(bid, n_jobs, n_chunks, &j, &chunk)) return;
-    } else {
-        // XCD-aware like MAP 1, but every XCD owns runs of G = MAP - 10 consecutive chunks, and visits
-        // them job by job: longer contiguous pieces of every stream are in flight at a time
-        static_assert(MAP == 1 || MAP > 10, "MAP is 1 or 10 + run length");
-        constexpr int G = MAP > 10 ? MAP - 10 : 1;
-        int xcd = (int)(bid % kXcd);
-        int64_t local = bid / kXcd;
-        int sub = (int)(local % G);
-        j = (int)((local / G) % n_jobs);
-        int64_t group = local / ((int64_t)G * n_jobs);
-        chunk = (group * kXcd + xcd) * G + sub;
-        if (chunk >= n_chunks) return;
-    }
-    const HopMixJob* job = jobs + j;
+// Work of one workgroup of the mix in round `round` of the chunks (the launch may hold other workgroups in front of them).
+template <int VEC, int NT, int T>
+__device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, int64_t d, const Runs& runs, int round) {
+    const int chunk = run_chunk(runs, round);
+    if (chunk < 0) return;
+    const HopMixJob* job = jobs + blockIdx.y;
     const int64_t n4 = d >> 2;
-    const int64_t first4 = chunk * (int64_t)(T * VEC);
+    const int64_t first4 = (int64_t)chunk * (T * VEC);
     if (job->vel != nullptr) {
         switch (job->A) {
             case 1: mix_tile<1, VEC, NT, T, true>(job, first4, n4); break;
@@ -288,7 +309,7 @@ __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, in
         }
     }
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
-    if (chunk == n_chunks - 1) {
+    if (chunk == runs.n_chunks - 1) {
         int64_t c = (n4 << 2) + threadIdx.x;
         if (threadIdx.x < 4 && c < d) {
             float acc = job->w[0] * job->src[0][c];
@@ -306,35 +327,18 @@ __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, in
     }
 }
 
-template <int VEC, int NT, int MAP, int T>
-__global__ __launch_bounds__(T) void mix_kernel(const HopMixJob* __restrict__ jobs, int n_jobs, int64_t d,
-                                                int64_t n_chunks) {
-    mix_block<VEC, NT, MAP, T>(jobs, n_jobs, d, n_chunks, blockIdx.x);
+template <int VEC, int NT, int T>
+__global__ __launch_bounds__(T) void mix_kernel(const HopMixJob* __restrict__ jobs, int64_t d, HOP_RUNS_IN) {
+    mix_block<VEC, NT, T>(jobs, d, HOP_RUNS, (int)blockIdx.z);
 }
 
-template <int VEC, int MAP, int T>
-int64_t mix_grid(int n_jobs, int64_t d, int64_t* n_chunks_out) {
-    int64_t n4 = d >> 2;
-    int64_t per = (int64_t)T * VEC;
-    int64_t n_chunks = (n4 + per - 1) / per;
-    if (n_chunks < 1) n_chunks = 1;
-    int64_t grid = grid_for(n_jobs, n_chunks);
-    if (MAP > 10) {
-        int64_t span = (int64_t)kXcd * (MAP - 10);
-        grid = (n_chunks + span - 1) / span * span * n_jobs;
-    }
-    *n_chunks_out = n_chunks;
-    return grid;
-}
-
-template <int VEC, int NT, int MAP, int T>
-int launch_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
-    int64_t n_chunks;
-    int64_t grid = mix_grid<VEC, MAP, T>(n_jobs, d, &n_chunks);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((mix_kernel<VEC, NT, MAP, T>), dim3((unsigned)grid), dim3(T), 0, (hipStream_t)stream,
-                       jobs_dev, n_jobs, d, n_chunks);
-    return (int)hipGetLastError();
+// float4 per thread and vector of a mix, and the runs of its chunks.  Long vectors: every XCD takes runs of 4 consecutive 16 KB
+// chunks (3-4 % faster on 64-100 MB vectors); short ones: single chunks, less padding
+constexpr int kMixVec = 4;
+inline bool mix_grid(int n_jobs, int64_t d, int64_t front, Runs* runs, dim3* grid) {
+    constexpr int64_t per = (int64_t)kThreads * kMixVec;
+    const int64_t n4 = d >> 2, n_chunks = n4 > per ? (n4 + per - 1) / per : 1;
+    return run_grid(n_jobs, n_chunks, n4 >= 1024 * per ? 4 : 1, front, runs, grid);
 }
 
 // ---------------------------------------------------------- Reduce + Apply, records in pairs ----
@@ -449,33 +453,19 @@ __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t 
     }
 }
 
-// Work of one workgroup; `bid` is its index among the launch's mix workgroups.
+// Work of one workgroup in round `round` of the chunks.
 // Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
 template <int VEC, class Job>
-__device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int64_t n_chunks,
-                                           int run, int reverse, int64_t bid) {
-    const int xcd = (int)(bid % kXcd);
-    const int64_t local = bid / kXcd;
-    const int sub = (int)(local % run);
-    const int j = (int)((local / run) % n_jobs);
-    const int64_t round = local / ((int64_t)run * n_jobs);
-    int64_t ahead = (round * kXcd + xcd) * run + sub;
-    // the last, partly filled round is dealt out evenly (shorter runs on all XCDs, not full runs on the first few)
-    const int64_t span = (int64_t)kXcd * run;
-    const int64_t done = n_chunks / span * span;
-    if (round * span >= done) {
-        const int tail_run = (int)((n_chunks - done + kXcd - 1) / kXcd);
-        if (sub >= tail_run) return;
-        ahead = done + (int64_t)xcd * tail_run + sub;
-    }
-    if (ahead >= n_chunks) return;
+__device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs, int reverse, int round) {
+    const int ahead = run_chunk(runs, round);
+    if (ahead < 0) return;
     // consecutive launches walk the vectors in opposite directions: what the previous kernels wrote or read last
     // is still in the memory-side cache when the next launch begins there (1453 -> 1430 us per launch with the
     // gradient generator in between, 386 -> 381 us between launches of small waves)
-    const int64_t chunk = reverse ? n_chunks - 1 - ahead : ahead;
-    const Job job = jobs + j;
+    const int chunk = reverse ? runs.n_chunks - 1 - ahead : ahead;
+    const Job job = jobs + blockIdx.y;
     const int64_t n4 = d >> 2;
-    const int64_t first4 = chunk * (int64_t)(kThreads * VEC);
+    const int64_t first4 = (int64_t)chunk * (kThreads * VEC);
     const bool full = first4 + kThreads * VEC <= n4;
     static_assert(kPairU == 12, "the switch below unrolls unions of 1..12 vectors");
 #define HOP_PAIR_CASE(UU)                                      \
@@ -490,7 +480,7 @@ __device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int6
     }
 #undef HOP_PAIR_CASE
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
-    if (chunk == n_chunks - 1) {
+    if (chunk == runs.n_chunks - 1) {
         const int64_t c = (n4 << 2) + (threadIdx.x & 3);
         const int r = threadIdx.x >> 2;
         if (threadIdx.x < 8 && r < job->G && c < d) {
@@ -504,9 +494,9 @@ __device__ __forceinline__ void pair_block(Job jobs, int n_jobs, int64_t d, int6
 }
 
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void pair_mix_kernel(const HopPairJob* __restrict__ jobs, int n_jobs, int64_t d,
-                                                            int64_t n_chunks, int run, int reverse) {
-    pair_block<VEC>(jobs, n_jobs, d, n_chunks, run, reverse, blockIdx.x);
+__global__ __launch_bounds__(kThreads) void pair_mix_kernel(const HopPairJob* __restrict__ jobs, int64_t d, int reverse,
+                                                            HOP_RUNS_IN) {
+    pair_block<VEC>(jobs, d, HOP_RUNS, reverse, (int)blockIdx.z);
 }
 
 // The same for a stand-alone call: its descriptors travel as the kernel's argument, so the call allocates and copies
@@ -518,10 +508,9 @@ struct HopPairArgs {
 typedef const __attribute__((address_space(4))) HopPairArg* pair_args_in;
 
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, int n_jobs, int64_t d, int64_t n_chunks,
-                                                                 int run) {
+__global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, int64_t d, HOP_RUNS_IN) {
     // the first argument where it lies: a copy indexed by job would go through scratch memory
-    pair_block<VEC>((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), n_jobs, d, n_chunks, run, 0, blockIdx.x);
+    pair_block<VEC>((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), d, HOP_RUNS, 0, (int)blockIdx.z);
 }
 
 // float4 per thread and vector, and with it the columns of a chunk.  Long launches: 4, 16 KB of every vector per workgroup
@@ -554,9 +543,11 @@ inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
     return run < 1 ? 1 : run;
 }
 
-inline int64_t pair_grid(int n_jobs, int64_t n_chunks, int run) {
-    const int64_t span = (int64_t)kXcd * run;
-    return (n_chunks + span - 1) / span * span * n_jobs;
+// width, runs and grid of a launch over pairs, `front` other workgroups in front
+inline bool pair_grid(int n_jobs, int n_sources, int64_t d, bool margins, int64_t front, int* vec, Runs* runs, dim3* grid) {
+    *vec = pair_vec(n_jobs, d, margins);
+    const int64_t n_chunks = pair_chunks(d, *vec);
+    return run_grid(n_jobs, n_chunks, pair_run(n_sources, n_chunks, *vec), front, runs, grid);
 }
 
 // ------------------------------------------------------------------- synthetic gradient ----
@@ -617,12 +608,10 @@ __device__ __forceinline__ void synth_chunk(const HopGradJob* __restrict__ job, 
     }
 }
 
-__global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __restrict__ jobs, int n_jobs,
-                                                         int64_t d, int64_t n_chunks, int reverse) {
-    int j;
-    int64_t chunk;
-    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
-        synth_chunk(jobs + j, d, n_chunks, reverse ? n_chunks - 1 - chunk : chunk);
+__global__ __launch_bounds__(kThreads) void synth_kernel(const HopGradJob* __restrict__ jobs, int width, int reverse, int64_t d,
+                                                         int64_t n_chunks) {
+    const int64_t chunk = grid_chunk(width);
+    if (chunk < n_chunks) synth_chunk(jobs + blockIdx.y, d, n_chunks, reverse ? n_chunks - 1 - chunk : chunk);
 }
 
 __global__ __launch_bounds__(kThreads) void synth_one_kernel(const HopGradJob job, int64_t d, int64_t n_chunks) {
@@ -1042,13 +1031,15 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
     }
 }
 
-// one workgroup per (job, ROWS minibatch rows, column segment); b: its index
-template <int ROWS, bool STREAM, bool ONE>
+// one workgroup per (job, minibatch row, column segment), b its index, in launches with other workgroups
 __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
-                                                   int64_t b, float (*red)[kThreads / 64]) {
-    const int groups = (B + ROWS - 1) / ROWS;
-    dense_margin_rows<ROWS, STREAM, ONE>(jobs + b / ((int64_t)nseg * groups), B, d, nseg, (int)(b % nseg),
-                            (int)((b / nseg) % groups) * ROWS, red);
+                                                   unsigned b, float (*red)[kThreads / 64]) {
+    if (nseg == 1) {
+        dense_margin_rows<1, false, true>(jobs + b / (unsigned)B, B, d, nseg, 0, (int)(b % (unsigned)B), red);
+        return;
+    }
+    const unsigned row = b / (unsigned)nseg;
+    dense_margin_rows<1, false, false>(jobs + row / (unsigned)B, B, d, nseg, (int)(b % (unsigned)nseg), (int)(row % (unsigned)B), red);
 }
 
 // The margin pass as a launch of its own: four minibatch rows per workgroup share every load of w (the L2 sees
@@ -1069,7 +1060,7 @@ template <int ROWS, bool STREAM, bool ONE>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
                                                                 int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_block<ROWS, STREAM, ONE>(jobs, B, d, nseg, blockIdx.x, red);
+    dense_margin_rows<ROWS, STREAM, ONE>(jobs + blockIdx.z, B, d, nseg, (int)blockIdx.x, (int)blockIdx.y * ROWS, red);
 }
 
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
@@ -1084,18 +1075,17 @@ __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob jo
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
 // (the parallel approach of Section 3.2 runs Compute beside Reduce).  The Reduce leaves sum_a w'_a x_a
 // in the result slot; dense_grad_kernel then applies -eta g to it.
-template <int VEC, int NT, int MAP>
-__global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int n_mix,
-                                                                    int64_t d, int64_t n_chunks,
-                                                                    const HopGradJob* __restrict__ grad_jobs, int B,
-                                                                    int nseg, int64_t margin_blocks) {
+template <int VEC, int NT>
+__global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
+                                                                    HOP_RUNS_IN, unsigned margins, int n_mix,
+                                                                    const HopGradJob* __restrict__ grad_jobs, int B, int nseg) {
     __shared__ float red[1][kThreads / 64];
-    if ((int64_t)blockIdx.x >= margin_blocks) {
-        mix_block<VEC, NT, MAP, kThreads>(mix_jobs, n_mix, d, n_chunks, (int64_t)blockIdx.x - margin_blocks);
+    if ((int)blockIdx.z >= front) {
+        mix_block<VEC, NT, kThreads>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
-    if (nseg == 1) dense_margin_block<1, false, true>(grad_jobs, B, d, nseg, blockIdx.x, red);
-    else dense_margin_block<1, false, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
+    const unsigned b = grid_index(HOP_RUNS, n_mix);
+    if (b < margins) dense_margin_block(grad_jobs, B, d, nseg, b, red);
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
@@ -1254,13 +1244,11 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
 }
 
 template <int SPLIT, int WIDE, bool ONE>
-__global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B,
+__global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const HopGradJob* __restrict__ jobs, int width, int B,
                                                                 int64_t d, int nseg, float lambda, int loss,
                                                                 int64_t n_chunks) {
-    int j;
-    int64_t chunk;
-    if (map_block(blockIdx.x, n_jobs, n_chunks, &j, &chunk))
-        dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + j, B, d, nseg, lambda, loss, chunk);
+    const int64_t chunk = grid_chunk(width);
+    if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
 }
 
 template <int SPLIT, int WIDE, bool ONE>
@@ -1284,11 +1272,6 @@ __device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ j
     if (lane == 0) job->coef[m] = loss_coef(job->y[r], acc, 1.0f / (float)B, loss);
 }
 
-__device__ __forceinline__ void csr_margin_block(const HopGradJob* __restrict__ jobs, int B,
-                                                 int rows_per_job_blocks, int loss, int bid) {
-    csr_margin_rows(jobs + bid / rows_per_job_blocks, B, loss, bid % rows_per_job_blocks);
-}
-
 // Margins and the dense part lambda w of a gradient that is wanted as a dense vector, side by side (the sparse part is
 // scattered into g afterwards).
 __global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJob job, int B, int64_t d, float lambda,
@@ -1305,65 +1288,52 @@ __global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJo
     }
 }
 
-__global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* __restrict__ jobs, int B,
-                                                              int rows_per_job_blocks, int loss) {
-    csr_margin_block(jobs, B, rows_per_job_blocks, loss, (int)blockIdx.x);
+__global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int loss) {
+    csr_margin_rows(jobs + blockIdx.y, B, loss, (int)blockIdx.x);
 }
 
 // The margins of a wave's STEP records and the wave's Reduce + Apply in one launch: both only read
 // x_k, and nothing a wave writes is read inside it, so they need no order between them.  The few
 // latency-bound margin workgroups come first and run under the streaming ones.
-template <int VEC, int NT, int MAP>
-__global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int n_mix,
-                                                                  int64_t d, int64_t n_chunks,
-                                                                  const HopGradJob* __restrict__ grad_jobs, int B,
-                                                                  int rows_per_job_blocks, int loss,
-                                                                  int margin_blocks) {
-    if ((int)blockIdx.x < margin_blocks) {
-        csr_margin_block(grad_jobs, B, rows_per_job_blocks, loss, (int)blockIdx.x);
+// (`per`: margin workgroups of a record)
+template <int VEC, int NT>
+__global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
+                                                                  HOP_RUNS_IN, unsigned margins, int n_mix,
+                                                                  const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
+                                                                  int loss) {
+    if ((int)blockIdx.z >= front) {
+        mix_block<VEC, NT, kThreads>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
-    mix_block<VEC, NT, MAP, kThreads>(mix_jobs, n_mix, d, n_chunks, (int64_t)blockIdx.x - margin_blocks);
+    const unsigned b = grid_index(HOP_RUNS, n_mix);
+    if (b < margins) csr_margin_rows(grad_jobs + b / per, B, loss, (int)(b % per));
 }
 
 // the same two fusions for the paired Reduce + Apply
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int n_mix,
-                                                                   int64_t d, int64_t n_chunks, int run, int reverse,
-                                                                   const HopGradJob* __restrict__ grad_jobs, int B,
-                                                                   int rows_per_job_blocks, int loss, int margin_blocks) {
-    if ((int)blockIdx.x < margin_blocks) {
-        csr_margin_block(grad_jobs, B, rows_per_job_blocks, loss, (int)blockIdx.x);
+__global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
+                                                                   HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
+                                                                   const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
+                                                                   int loss) {
+    if ((int)blockIdx.z >= front) {
+        pair_block<VEC>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
-    pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
+    const unsigned b = grid_index(HOP_RUNS, n_mix);
+    if (b < margins) csr_margin_rows(grad_jobs + b / per, B, loss, (int)(b % per));
 }
 
 template <int VEC>
-__global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int n_mix,
-                                                                     int64_t d, int64_t n_chunks, int run, int reverse,
-                                                                     const HopGradJob* __restrict__ grad_jobs, int B,
-                                                                     int nseg, int64_t margin_blocks) {
+__global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
+                                                                     HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
+                                                                     const HopGradJob* __restrict__ grad_jobs, int B, int nseg) {
     __shared__ float red[1][kThreads / 64];
-    if ((int64_t)blockIdx.x >= margin_blocks) {
-        pair_block<VEC>(mix_jobs, n_mix, d, n_chunks, run, reverse, (int64_t)blockIdx.x - margin_blocks);
+    if ((int)blockIdx.z >= front) {
+        pair_block<VEC>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
-    if (nseg == 1) dense_margin_block<1, false, true>(grad_jobs, B, d, nseg, blockIdx.x, red);
-    else dense_margin_block<1, false, false>(grad_jobs, B, d, nseg, blockIdx.x, red);
-}
-
-template <int VEC, int NT, int MAP>
-int launch_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
-                          int loss, void* stream) {
-    int64_t n_chunks;
-    const int64_t grid = mix_grid<VEC, MAP, kThreads>(n_mix, d, &n_chunks);
-    const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
-    const int64_t margin_blocks = (int64_t)n_grad * per;
-    if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((mix_csr_margin_kernel<VEC, NT, MAP>), dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                       (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, grad_dev, B, per, loss, (int)margin_blocks);
-    return (int)hipGetLastError();
+    const unsigned b = grid_index(HOP_RUNS, n_mix);
+    if (b < margins) dense_margin_block(grad_jobs, B, d, nseg, b, red);
 }
 
 // target[col] += factor * c_m * val for the active rows (the sparse part of -eta g, or of g).
@@ -1436,9 +1406,8 @@ __device__ __forceinline__ void csr_scatter_rows(const HopGradJob* __restrict__ 
 }
 
 template <bool BOTH>
-__global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopGradJob* __restrict__ jobs, int B,
-                                                                      int blocks_per_job, float factor) {
-    csr_scatter_rows<BOTH>(jobs + blockIdx.x / blocks_per_job, B, factor, blockIdx.x % blocks_per_job);
+__global__ __launch_bounds__(kScatterThreads) void csr_scatter_kernel(const HopGradJob* __restrict__ jobs, int B, float factor) {
+    csr_scatter_rows<BOTH>(jobs + blockIdx.y, B, factor, (int)blockIdx.x);
 }
 
 __global__ __launch_bounds__(kScatterThreads) void csr_scatter_one(const HopGradJob job, int B, float factor) {
@@ -1477,26 +1446,38 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float4* __restrict__ dst
 
 inline int launch_status() { return (int)hipGetLastError(); }
 
+// workgroups of the margins of a sparse minibatch
+inline int csr_margin_blocks(int B) { return (B + kThreads / 64 - 1) / (kThreads / 64); }
+
 }  // namespace
 
+// More jobs than a grid has rows (kMaxGridYZ) go in several launches: the records of a launch need no order between them.
+template <class Job, class F>
+static int in_parts(const Job* jobs, int n_jobs, F launch) {
+    for (int64_t at = 0; at < n_jobs; at += kMaxGridYZ)
+        if (const int rc = launch(jobs + at, (int)std::min<int64_t>(n_jobs - at, kMaxGridYZ))) return rc;
+    return 0;
+}
+
 int hopk_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
-    if (n_jobs <= 0) return 0;
-    // long vectors: every XCD takes runs of 4 consecutive 16 KB chunks (3-4 % faster on 64-100 MB
-    // vectors: longer contiguous pieces per stream); short ones: single chunks, less padding
-    if ((d >> 2) >= (int64_t)1024 * kThreads * 4) return launch_mix<4, 1, 14, 256>(jobs_dev, n_jobs, d, stream);
-    return launch_mix<4, 1, 1, 256>(jobs_dev, n_jobs, d, stream);
+    return in_parts(jobs_dev, n_jobs, [&](const HopMixJob* jobs, int n) {
+        Runs runs;
+        dim3 grid;
+        if (!mix_grid(n, d, 0, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL((mix_kernel<kMixVec, 1, kThreads>), grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d,
+                           HOP_RUNS_OF(runs));
+        return launch_status();
+    });
 }
 
 int hopk_synth(const HopGradJob* jobs_dev, int n_jobs, int reverse, int64_t d, void* stream) {
-    if (n_jobs <= 0) return 0;
-    int64_t n4 = d >> 2;
-    int64_t n_chunks = (n4 + kSynthChunk4 - 1) / kSynthChunk4;
-    if (n_chunks < 1) n_chunks = 1;
-    int64_t grid = grid_for(n_jobs, n_chunks);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(synth_kernel, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev,
-                       n_jobs, d, n_chunks, reverse);
-    return launch_status();
+    const int64_t n = ((d >> 2) + kSynthChunk4 - 1) / kSynthChunk4, n_chunks = n < 1 ? 1 : n;
+    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n_part) {
+        dim3 grid;
+        if (!chunk_grid(n_part, n_chunks, &grid)) return (int)hipErrorInvalidConfiguration;
+        hipLaunchKernelGGL(synth_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, (int)grid.x, reverse, d, n_chunks);
+        return launch_status();
+    });
 }
 
 template <int MODE, bool MOM>
@@ -1532,22 +1513,23 @@ int hopk_dense_nseg(int64_t d) {
 
 int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
-    const int nseg = hopk_dense_nseg(d);
-    const int64_t few = (int64_t)n_jobs * B * nseg;
-    const int64_t grid = (int64_t)n_jobs * ((B + kMarginRows - 1) / kMarginRows) * nseg;
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;      // few is used only where grid is small
+    const int nseg = hopk_dense_nseg(d), groups = (B + kMarginRows - 1) / kMarginRows;
+    const int64_t blocks = (int64_t)n_jobs * groups * nseg;
+    if (blocks > 0x7FFFFFFFll || B > kMaxB) return (int)hipErrorInvalidConfiguration;
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
-#define HOP_MARGINS(BLOCKS, ROWS, STREAM, ONE)                                                                              \
-    hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, ONE>), dim3((unsigned)(BLOCKS)), dim3(kThreads), 0,               \
-                       (hipStream_t)stream, jobs_dev, B, d, nseg)
-    static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "few workgroups of one segment: near");
-    if (grid < kMarginFew && nseg == 1) HOP_MARGINS(few, 1, false, true);
-    else if (grid < kMarginFew && near) HOP_MARGINS(few, 1, false, false);
-    else if (grid < kMarginFew) HOP_MARGINS(few, 1, true, false);
-    else if (nseg == 1) HOP_MARGINS(grid, kMarginRows, true, true);
-    else HOP_MARGINS(grid, kMarginRows, true, false);
+    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+        const dim3 rows((unsigned)nseg, (unsigned)B, (unsigned)n), fours((unsigned)nseg, (unsigned)groups, (unsigned)n);
+#define HOP_MARGINS(GRID, ROWS, STREAM, ONE)                                                                                \
+    hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, ONE>), GRID, dim3(kThreads), 0, (hipStream_t)stream, jobs, B, d, nseg)
+        static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "few workgroups of one segment: near");
+        if (blocks < kMarginFew && nseg == 1) HOP_MARGINS(rows, 1, false, true);
+        else if (blocks < kMarginFew && near) HOP_MARGINS(rows, 1, false, false);
+        else if (blocks < kMarginFew) HOP_MARGINS(rows, 1, true, false);
+        else if (nseg == 1) HOP_MARGINS(fours, kMarginRows, true, true);
+        else HOP_MARGINS(fours, kMarginRows, true, false);
 #undef HOP_MARGINS
-    return launch_status();
+        return launch_status();
+    });
 }
 
 enum class GradShape { few, some, many };
@@ -1563,117 +1545,119 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
     const int nseg = hopk_dense_nseg(d);
     const GradShape shape = grad_shape(n_jobs, d, nseg);
     const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;
-    const int64_t grid = grid_for(n_jobs, n_chunks);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+        dim3 grid;
+        if (!chunk_grid(n, n_chunks, &grid)) return (int)hipErrorInvalidConfiguration;
 #define HOP_GRADS(SPLIT, WIDE, ONE)                                                                                         \
-    hipLaunchKernelGGL((dense_grad_kernel<SPLIT, WIDE, ONE>), dim3((unsigned)grid), dim3(64 * SPLIT * WIDE), 0,              \
-                       (hipStream_t)stream, jobs_dev, n_jobs, B, d, nseg, lambda, loss, n_chunks)
-    if (shape == GradShape::few && nseg == 1) HOP_GRADS(8, 1, true);
-    else if (shape == GradShape::few) HOP_GRADS(8, 1, false);
-    else if (shape == GradShape::some && nseg == 1) HOP_GRADS(4, 1, true);
-    else if (shape == GradShape::some) HOP_GRADS(4, 1, false);
-    else if (nseg == 1) HOP_GRADS(1, 4, true);
-    else HOP_GRADS(1, 4, false);
+    hipLaunchKernelGGL((dense_grad_kernel<SPLIT, WIDE, ONE>), grid, dim3(64 * SPLIT * WIDE), 0, (hipStream_t)stream, jobs,   \
+                       (int)grid.x, B, d, nseg, lambda, loss, n_chunks)
+        if (shape == GradShape::few && nseg == 1) HOP_GRADS(8, 1, true);
+        else if (shape == GradShape::few) HOP_GRADS(8, 1, false);
+        else if (shape == GradShape::some && nseg == 1) HOP_GRADS(4, 1, true);
+        else if (shape == GradShape::some) HOP_GRADS(4, 1, false);
+        else if (nseg == 1) HOP_GRADS(1, 4, true);
+        else HOP_GRADS(1, 4, false);
 #undef HOP_GRADS
-    return launch_status();
+        return launch_status();
+    });
 }
 
 int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
-    int per = (B + kThreads / 64 - 1) / (kThreads / 64);
-    hipLaunchKernelGGL(csr_margin_kernel, dim3((unsigned)(n_jobs * per)), dim3(kThreads), 0, (hipStream_t)stream,
-                       jobs_dev, B, per, loss);
-    return launch_status();
+    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+        hipLaunchKernelGGL(csr_margin_kernel, dim3((unsigned)csr_margin_blocks(B), (unsigned)n), dim3(kThreads), 0, (hipStream_t)stream,
+                           jobs, B, loss);
+        return launch_status();
+    });
 }
 
-template <int VEC, int NT, int MAP>
-int launch_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
-                            void* stream) {
-    int64_t n_chunks;
-    const int64_t grid = mix_grid<VEC, MAP, kThreads>(n_mix, d, &n_chunks);
-    const int nseg = hopk_dense_nseg(d);
-    const int64_t margin_blocks = (int64_t)n_grad * B * nseg;
-    if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((mix_dense_margin_kernel<VEC, NT, MAP>), dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                       (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, grad_dev, B, nseg, margin_blocks);
-    return (int)hipGetLastError();
-}
-
+// Margins in front of a Reduce over at most kMaxGridYZ jobs; the rest of a longer one behind it, by itself.
 int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
                           void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
-    if ((d >> 2) >= (int64_t)1024 * kThreads * 4)
-        return launch_mix_dense_margin<4, 1, 14>(mix_dev, n_mix, d, grad_dev, n_grad, B, stream);
-    return launch_mix_dense_margin<4, 1, 1>(mix_dev, n_mix, d, grad_dev, n_grad, B, stream);
+    const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = (int64_t)n_grad * B * nseg;
+    Runs runs;
+    dim3 grid;
+    if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((mix_dense_margin_kernel<kMixVec, 1>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+                       runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, nseg);
+    if (const int rc = launch_status()) return rc;
+    return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
 
 int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
                         int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
-    if ((d >> 2) >= (int64_t)1024 * kThreads * 4)
-        return launch_mix_csr_margin<4, 1, 14>(mix_dev, n_mix, d, grad_dev, n_grad, B, loss, stream);
-    return launch_mix_csr_margin<4, 1, 1>(mix_dev, n_mix, d, grad_dev, n_grad, B, loss, stream);
+    const int per = csr_margin_blocks(B), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = (int64_t)n_grad * per;
+    Runs runs;
+    dim3 grid;
+    if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((mix_csr_margin_kernel<kMixVec, 1>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+                       runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
+    if (const int rc = launch_status()) return rc;
+    return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
 
 int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream) {
-    if (n_jobs <= 0) return 0;
-    const int vec = pair_vec(n_jobs, d, false);
-    const int64_t n_chunks = pair_chunks(d, vec);
-    const int run = pair_run(n_sources, n_chunks, vec);
-    const int64_t grid = pair_grid(n_jobs, n_chunks, run);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_mix_kernel, kPairPlain, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs,
-                    d, n_chunks, run, reverse);
-    return launch_status();
+    return in_parts(jobs_dev, n_jobs, [&](const HopPairJob* jobs, int n) {
+        int vec;
+        Runs runs;
+        dim3 grid;
+        if (!pair_grid(n, n_sources, d, false, 0, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+        HOP_PAIR_LAUNCH(pair_mix_kernel, kPairPlain, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, reverse,
+                        HOP_RUNS_OF(runs));
+        return launch_status();
+    });
 }
 
 int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
                          const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
-    const int vec = pair_vec(n_mix, d, true);
-    const int64_t n_chunks = pair_chunks(d, vec);
-    const int run = pair_run(n_sources, n_chunks, vec);
-    const int64_t grid = pair_grid(n_mix, n_chunks, run);
-    const int per = (B + kThreads / 64 - 1) / (kThreads / 64);
-    const int64_t margin_blocks = (int64_t)n_grad * per;
-    if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, kPairMargin, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                    (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, per, loss,
-                    (int)margin_blocks);
-    return launch_status();
+    const int per = csr_margin_blocks(B), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = (int64_t)n_grad * per;
+    int vec;
+    Runs runs;
+    dim3 grid;
+    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, kPairMargin, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front,
+                    HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
+    if (const int rc = launch_status()) return rc;
+    return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
 
 int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
-    const int vec = pair_vec(n_mix, d, true);
-    const int64_t n_chunks = pair_chunks(d, vec);
-    const int run = pair_run(n_sources, n_chunks, vec);
-    const int64_t grid = pair_grid(n_mix, n_chunks, run);
-    const int nseg = hopk_dense_nseg(d);
-    const int64_t margin_blocks = (int64_t)n_grad * B * nseg;
-    if (grid + margin_blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, kPairMargin, dim3((unsigned)(grid + margin_blocks)), dim3(kThreads), 0,
-                    (hipStream_t)stream, mix_dev, n_mix, d, n_chunks, run, reverse, grad_dev, B, nseg, margin_blocks);
-    return launch_status();
+    const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = (int64_t)n_grad * B * nseg;
+    int vec;
+    Runs runs;
+    dim3 grid;
+    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, kPairMargin, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front,
+                    HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, nseg);
+    if (const int rc = launch_status()) return rc;
+    return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
 
 int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor, int into_velocity, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     const int per = (B + kScatterRows - 1) / kScatterRows;
-    const int64_t grid = (int64_t)n_jobs * per;
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    if (into_velocity)
-        hipLaunchKernelGGL(csr_scatter_kernel<true>, dim3((unsigned)grid), dim3(kScatterThreads), 0, (hipStream_t)stream,
-                           jobs_dev, B, per, factor);
-    else
-        hipLaunchKernelGGL(csr_scatter_kernel<false>, dim3((unsigned)grid), dim3(kScatterThreads), 0, (hipStream_t)stream,
-                           jobs_dev, B, per, factor);
-    return launch_status();
+    if ((int64_t)n_jobs * per > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+        const dim3 grid((unsigned)per, (unsigned)n), threads(kScatterThreads);
+        if (into_velocity)
+            hipLaunchKernelGGL(csr_scatter_kernel<true>, grid, threads, 0, (hipStream_t)stream, jobs, B, factor);
+        else
+            hipLaunchKernelGGL(csr_scatter_kernel<false>, grid, threads, 0, (hipStream_t)stream, jobs, B, factor);
+        return launch_status();
+    });
 }
 
 int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lambda, int loss, void* stream) {
@@ -1708,7 +1692,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
         else
             hipLaunchKernelGGL((dense_grad_one<1, 4, false>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
-        const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
+        const int margin_blocks = csr_margin_blocks(B);
         const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;
         if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         const uintptr_t w0 = (uintptr_t)job.w, g0 = (uintptr_t)job.out, bytes = (uintptr_t)d * sizeof(float);
@@ -1737,13 +1721,11 @@ int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d,
     if (n_jobs > kPairArgs) return (int)hipErrorInvalidValue;
     HopPairArgs args;
     memcpy(args.job, jobs, (size_t)n_jobs * sizeof(HopPairArg));
-    const int vec = pair_vec(n_jobs, d, false);
-    const int64_t n_chunks = pair_chunks(d, vec);
-    const int run = pair_run(n_sources, n_chunks, vec);
-    const int64_t grid = pair_grid(n_jobs, n_chunks, run);
-    if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_mix_args_kernel, kPairPlain, dim3((unsigned)grid), dim3(kThreads), 0, (hipStream_t)stream, args,
-                    n_jobs, d, n_chunks, run);
+    int vec;
+    Runs runs;
+    dim3 grid;
+    if (!pair_grid(n_jobs, n_sources, d, false, 0, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    HOP_PAIR_LAUNCH(pair_mix_args_kernel, kPairPlain, grid, dim3(kThreads), 0, (hipStream_t)stream, args, d, HOP_RUNS_OF(runs));
     return launch_status();
 }
 

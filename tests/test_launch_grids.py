@@ -1,0 +1,65 @@
+"""Launches at the edges of a grid: more jobs than it has rows, and vectors of more rounds of chunks than it has layers."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1902_01064_amd import hop, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+# rows of a grid: 65535; pairs are not formed where every vector is read once
+@pytest.mark.parametrize("n", [65535, 65536, 70001])
+@pytest.mark.parametrize("momentum", [False, True])
+def test_mix_of_many_jobs(n, momentum):
+    d, stride, eta, mu = 5, 8, 0.5, 0.75
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    src, g, vel = (torch.randn(n, stride, generator=gen, device="cuda") for _ in range(3))
+    out, before = torch.zeros(n, stride, device="cuda"), vel.double()
+    at = [t.data_ptr() for t in (out, g, src, vel)]
+    jobs = [dict(out=at[0] + 4 * stride * i, g=at[1] + 4 * stride * i, eta=eta, src=[at[2] + 4 * stride * i], w=[1.0 / (1 + i % 7)])
+            for i in range(n)]
+    if momentum:
+        for i, j in enumerate(jobs):
+            j.update(vel=at[3] + 4 * stride * i, mu=mu)
+    print("mix of", n, "jobs, momentum", momentum, flush=True)
+    hop.hop_mix(jobs, d, torch.cuda.current_stream().cuda_stream)
+    w = torch.tensor([float(np.float32(1.0 / (1 + k))) for k in range(7)], dtype=torch.float64, device="cuda")
+    v = mu * before + g.double() if momentum else g.double()
+    want = w[torch.arange(n, device="cuda") % 7][:, None] * src.double() - eta * v
+    room = 4 * 2.0 ** -24 * (src.double().abs() + eta * (mu * before.abs() + g.double().abs()))    # three roundings of the terms
+    assert bool(((out.double() - want).abs() <= room)[:, :d].all()) and bool((out[:, d:] == 0).all())
+    if momentum:
+        assert bool(((vel.double() - v).abs() <= room / eta)[:, :d].all()) and torch.equal(vel[:, d:].double(), before[:, d:])
+
+
+# 65535 layers of 8 chunks of 2048 columns are not enough for the generator of a wave: the same bits as the pass in one launch
+@pytest.mark.parametrize("d", [65535 * 8 * 2048, 65535 * 8 * 2048 + 5])
+def test_generator_of_very_long_vectors(d):
+    from paper_1902_01064_amd.session import Session
+    nb = inputs.ring(2)
+    c = dict(inputs.config(4, d=d, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=2, s=1, b=0, skip_on=False, mult=None,
+             delay_kind=inputs.DELAY_NONE, grad_ahead=1)
+    some = torch.cat([torch.arange(0, 4096), torch.randint(0, d, (1 << 16,), generator=torch.Generator().manual_seed(d % 97)),
+                      torch.arange(d - 4096, d)]).cuda()
+    p0 = torch.zeros(d, device="cuda")
+    got = []
+    print("generator of", d, "columns", flush=True)
+    for whole in (True, False):
+        sess = Session(c)
+        try:
+            hop.hop_set_grad_source(sess.ctx, hop.HOP_GRAD_SYNTH, 1e-3)
+            sess.set_params(p0)
+            n = sess.simulate().n_waves
+            for at in [(0, n)] if whole else [(w, w + 1) for w in range(n)]:
+                hop.hop_profile(sess.ctx, int(not whole))            # a profiled pass goes wave by wave
+                sess.step(*at)
+            sess.sync()
+            got.append([p[some].clone() for p in sess.params()[0]])
+            assert all(bool((p != 0).any()) for p in got[-1])
+        finally:
+            sess.close()
+            del sess
+            torch.cuda.empty_cache()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)

@@ -134,179 +134,74 @@ __device__ __forceinline__ int run_chunk(const Runs& r, int round) {
 // out[c] = sum_a w_a src_a[c] - eta g[c]   (Figure "Standard Decentralized Training", steps 2-3;
 // weights from Eq. 2 times the mixing matrix, already normalised on the host).
 //
-// Template knobs: VEC float4 per thread per source; NT 0 = ordinary accesses, 1 = g and the result
-// non-temporal (each touched once), 2 = sources too; T threads per workgroup.
-// Measured on 32 jobs x 25 M columns with ~7.6 shared sources each: job-major workgroups are 2.3x slower than
-// the grid above and chunk-major ones that ignore the XCDs 1.45x slower; vector width (1-8), block size (128-1024) and
-// cache hints move the time by under 5 %.
-template <int NT>
-__device__ __forceinline__ float4 ld_src(const float* p, int64_t i) {
-    return NT >= 2 ? ld4_stream(p, i) : ld4(p, i);
-}
-template <int NT>
-__device__ __forceinline__ float4 ld_once(const float* p, int64_t i) {
-    return NT >= 1 ? ld4_stream(p, i) : ld4(p, i);
-}
-template <int NT>
-__device__ __forceinline__ void st_once(float* p, int64_t i, float4 v) {
-    if (NT >= 1) st4_stream(p, i, v); else st4(p, i, v);
-}
-
-template <int A, int VEC, int NT, int T, bool MOM>
-__device__ __forceinline__ void mix_tile(const HopMixJob* __restrict__ job, int64_t first4, int64_t n4) {
+// A thread takes one float4 of every vector, a workgroup 4 KB: few registers, so many workgroups at a time, is what counts
+// (records with a velocity, us per pass with 4, 2 and 1: 64 workers x 50 000 columns, external gradients, 290 / 242 / 215;
+// 16 x 300 000 256 / 229 / 215; 32 x 4 M 5160 / 5020 / 4970; 16 x 2^20, sparse, 935 / 858 / 813).  g, velocity and result
+// non-temporal (each touched once).  Measured on 32 jobs x 25 M columns with ~7.6 shared sources each: job-major workgroups
+// are 2.3x slower than the grid above and chunk-major ones that ignore the XCDs 1.45x slower.
+template <int A, bool MOM>
+__device__ __forceinline__ void mix_tile(const HopMixJob* __restrict__ job, int64_t i) {
     const float* g = job->g;
     const float neg_eta = -job->eta;
     float* vel = job->vel;
-    const float mu = job->mu;
-    const float lam_fold = job->lam_fold;
-    float* out = job->out;
-    float4 acc[VEC];
-    int64_t idx[VEC];
-    bool ok[VEC];
+    const float4 x0 = ld4(job->src[0], i);
+    const float w0 = job->w[0];
+    float4 acc = make_float4(w0 * x0.x, w0 * x0.y, w0 * x0.z, w0 * x0.w);
 #pragma unroll
-    for (int u = 0; u < VEC; ++u) {
-        idx[u] = first4 + (int64_t)u * T + threadIdx.x;
-        ok[u] = idx[u] < n4;
-    }
-    {
-        const float* s0 = job->src[0];
-        const float w0 = job->w[0];
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            float4 v = ok[u] ? ld_src<NT>(s0, idx[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            acc[u] = make_float4(w0 * v.x, w0 * v.y, w0 * v.z, w0 * v.w);
-        }
-    }
-#pragma unroll
-    for (int a = 1; a < A; ++a) {
-        const float* sa = job->src[a];
-        const float wa = job->w[a];
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            float4 v = ok[u] ? ld_src<NT>(sa, idx[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            acc[u].x = fmaf(wa, v.x, acc[u].x);
-            acc[u].y = fmaf(wa, v.y, acc[u].y);
-            acc[u].z = fmaf(wa, v.z, acc[u].z);
-            acc[u].w = fmaf(wa, v.w, acc[u].w);
-        }
-    }
+    for (int a = 1; a < A; ++a) acc = fma4(job->w[a], ld4(job->src[a], i), acc);
     if (MOM) {
         // v <- mu v + g (a missing g counts as zero), Apply with the new velocity
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            float4 v = ok[u] ? ld_once<NT>(vel, idx[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            float4 gg = (ok[u] && g != nullptr) ? ld_once<NT>(g, idx[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (lam_fold != 0.f && ok[u]) {      // dense part lambda w of a gradient whose sparse part is scattered later
-                const float4 x0 = ld_src<NT>(job->src[0], idx[u]);
-                gg = make_float4(fmaf(lam_fold, x0.x, gg.x), fmaf(lam_fold, x0.y, gg.y), fmaf(lam_fold, x0.z, gg.z),
-                                 fmaf(lam_fold, x0.w, gg.w));
-            }
-            v = make_float4(fmaf(mu, v.x, gg.x), fmaf(mu, v.y, gg.y), fmaf(mu, v.z, gg.z), fmaf(mu, v.w, gg.w));
-            if (ok[u]) st_once<NT>(vel, idx[u], v);
-            acc[u].x = fmaf(neg_eta, v.x, acc[u].x);
-            acc[u].y = fmaf(neg_eta, v.y, acc[u].y);
-            acc[u].z = fmaf(neg_eta, v.z, acc[u].z);
-            acc[u].w = fmaf(neg_eta, v.w, acc[u].w);
-        }
+        float4 v = ld4_stream(vel, i);
+        float4 gg = g != nullptr ? ld4_stream(g, i) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (job->lam_fold != 0.f) gg = fma4(job->lam_fold, x0, gg);    // lambda w of a gradient whose sparse part is scattered later
+        v = fma4(job->mu, v, gg);
+        st4_stream(vel, i, v);
+        acc = fma4(neg_eta, v, acc);
     } else if (g != nullptr) {
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-            float4 v = ok[u] ? ld_once<NT>(g, idx[u]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            acc[u].x = fmaf(neg_eta, v.x, acc[u].x);
-            acc[u].y = fmaf(neg_eta, v.y, acc[u].y);
-            acc[u].z = fmaf(neg_eta, v.z, acc[u].z);
-            acc[u].w = fmaf(neg_eta, v.w, acc[u].w);
-        }
+        acc = fma4(neg_eta, ld4_stream(g, i), acc);
     }
-#pragma unroll
-    for (int u = 0; u < VEC; ++u)
-        if (ok[u]) st_once<NT>(out, idx[u], acc[u]);
+    st4_stream(job->out, i, acc);
 }
 
 // more than 12 sources: a loop over the sources instead of an unrolled chain
-template <int VEC, int NT, int T>
-__device__ __forceinline__ void mix_tile_any(const HopMixJob* __restrict__ job, int64_t first4, int64_t n4) {
+__device__ __forceinline__ void mix_tile_any(const HopMixJob* __restrict__ job, int64_t i) {
     const int A = job->A;
     const float* g = job->g;
     const float neg_eta = -job->eta;
-    for (int u = 0; u < VEC; ++u) {
-        int64_t i = first4 + (int64_t)u * T + threadIdx.x;
-        if (i >= n4) continue;
-        float4 v = ld_src<NT>(job->src[0], i);
-        float w = job->w[0];
-        float4 acc = make_float4(w * v.x, w * v.y, w * v.z, w * v.w);
-        for (int a = 1; a < A; ++a) {
-            v = ld_src<NT>(job->src[a], i);
-            w = job->w[a];
-            acc.x = fmaf(w, v.x, acc.x);
-            acc.y = fmaf(w, v.y, acc.y);
-            acc.z = fmaf(w, v.z, acc.z);
-            acc.w = fmaf(w, v.w, acc.w);
-        }
-        if (job->vel != nullptr) {
-            float4 gg = g != nullptr ? ld_once<NT>(g, i) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (job->lam_fold != 0.f) {
-                const float4 x0 = ld_src<NT>(job->src[0], i);
-                const float lf = job->lam_fold;
-                gg = make_float4(fmaf(lf, x0.x, gg.x), fmaf(lf, x0.y, gg.y), fmaf(lf, x0.z, gg.z), fmaf(lf, x0.w, gg.w));
-            }
-            v = ld_once<NT>(job->vel, i);
-            const float mu = job->mu;
-            v = make_float4(fmaf(mu, v.x, gg.x), fmaf(mu, v.y, gg.y), fmaf(mu, v.z, gg.z), fmaf(mu, v.w, gg.w));
-            st_once<NT>(job->vel, i, v);
-        } else if (g != nullptr) {
-            v = ld_once<NT>(g, i);
-        }
-        if (job->vel != nullptr || g != nullptr) {
-            acc.x = fmaf(neg_eta, v.x, acc.x);
-            acc.y = fmaf(neg_eta, v.y, acc.y);
-            acc.z = fmaf(neg_eta, v.z, acc.z);
-            acc.w = fmaf(neg_eta, v.w, acc.w);
-        }
-        st_once<NT>(job->out, i, acc);
+    const float4 x0 = ld4(job->src[0], i);
+    const float w0 = job->w[0];
+    float4 acc = make_float4(w0 * x0.x, w0 * x0.y, w0 * x0.z, w0 * x0.w);
+    for (int a = 1; a < A; ++a) acc = fma4(job->w[a], ld4(job->src[a], i), acc);
+    if (job->vel != nullptr) {
+        float4 gg = g != nullptr ? ld4_stream(g, i) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (job->lam_fold != 0.f) gg = fma4(job->lam_fold, x0, gg);
+        const float4 v = fma4(job->mu, ld4_stream(job->vel, i), gg);
+        st4_stream(job->vel, i, v);
+        acc = fma4(neg_eta, v, acc);
+    } else if (g != nullptr) {
+        acc = fma4(neg_eta, ld4_stream(g, i), acc);
     }
+    st4_stream(job->out, i, acc);
 }
 
 // Work of one workgroup of the mix in round `round` of the chunks (the launch may hold other workgroups in front of them).
-template <int VEC, int NT, int T>
 __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, int64_t d, const Runs& runs, int round) {
     const int chunk = run_chunk(runs, round);
     if (chunk < 0) return;
     const HopMixJob* job = jobs + blockIdx.y;
-    const int64_t n4 = d >> 2;
-    const int64_t first4 = (int64_t)chunk * (T * VEC);
-    if (job->vel != nullptr) {
+    const int64_t n4 = d >> 2, i = (int64_t)chunk * kThreads + threadIdx.x;
+    if (i < n4) {
+#define HOP_MIX_CASE(AA)                                    \
+    case AA:                                                \
+        if (job->vel != nullptr) mix_tile<AA, true>(job, i); \
+        else mix_tile<AA, false>(job, i);                   \
+        break;
         switch (job->A) {
-            case 1: mix_tile<1, VEC, NT, T, true>(job, first4, n4); break;
-            case 2: mix_tile<2, VEC, NT, T, true>(job, first4, n4); break;
-            case 3: mix_tile<3, VEC, NT, T, true>(job, first4, n4); break;
-            case 4: mix_tile<4, VEC, NT, T, true>(job, first4, n4); break;
-            case 5: mix_tile<5, VEC, NT, T, true>(job, first4, n4); break;
-            case 6: mix_tile<6, VEC, NT, T, true>(job, first4, n4); break;
-            case 7: mix_tile<7, VEC, NT, T, true>(job, first4, n4); break;
-            case 8: mix_tile<8, VEC, NT, T, true>(job, first4, n4); break;
-            case 9: mix_tile<9, VEC, NT, T, true>(job, first4, n4); break;
-            case 10: mix_tile<10, VEC, NT, T, true>(job, first4, n4); break;
-            case 11: mix_tile<11, VEC, NT, T, true>(job, first4, n4); break;
-            case 12: mix_tile<12, VEC, NT, T, true>(job, first4, n4); break;
-            default: mix_tile_any<VEC, NT, T>(job, first4, n4); break;
+            HOP_MIX_CASE(1) HOP_MIX_CASE(2) HOP_MIX_CASE(3) HOP_MIX_CASE(4) HOP_MIX_CASE(5) HOP_MIX_CASE(6)
+            HOP_MIX_CASE(7) HOP_MIX_CASE(8) HOP_MIX_CASE(9) HOP_MIX_CASE(10) HOP_MIX_CASE(11) HOP_MIX_CASE(12)
+            default: mix_tile_any(job, i); break;
         }
-    } else {
-        switch (job->A) {
-            case 1: mix_tile<1, VEC, NT, T, false>(job, first4, n4); break;
-            case 2: mix_tile<2, VEC, NT, T, false>(job, first4, n4); break;
-            case 3: mix_tile<3, VEC, NT, T, false>(job, first4, n4); break;
-            case 4: mix_tile<4, VEC, NT, T, false>(job, first4, n4); break;
-            case 5: mix_tile<5, VEC, NT, T, false>(job, first4, n4); break;
-            case 6: mix_tile<6, VEC, NT, T, false>(job, first4, n4); break;
-            case 7: mix_tile<7, VEC, NT, T, false>(job, first4, n4); break;
-            case 8: mix_tile<8, VEC, NT, T, false>(job, first4, n4); break;
-            case 9: mix_tile<9, VEC, NT, T, false>(job, first4, n4); break;
-            case 10: mix_tile<10, VEC, NT, T, false>(job, first4, n4); break;
-            case 11: mix_tile<11, VEC, NT, T, false>(job, first4, n4); break;
-            case 12: mix_tile<12, VEC, NT, T, false>(job, first4, n4); break;
-            default: mix_tile_any<VEC, NT, T>(job, first4, n4); break;
-        }
+#undef HOP_MIX_CASE
     }
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
     if (chunk == runs.n_chunks - 1) {
@@ -327,18 +222,15 @@ __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, in
     }
 }
 
-template <int VEC, int NT, int T>
-__global__ __launch_bounds__(T) void mix_kernel(const HopMixJob* __restrict__ jobs, int64_t d, HOP_RUNS_IN) {
-    mix_block<VEC, NT, T>(jobs, d, HOP_RUNS, (int)blockIdx.z);
+// Runs of its 4 KB chunks: 32 on vectors of 16 MB and more (against 16: 32 workers x 8 M columns 7714 -> 7645 us per pass, 16 x
+// 12 M 4912 -> 4868), 4 on shorter ones (8: 32 x 50 000 columns 170.5 -> 171.9)
+inline bool mix_grid(int n_jobs, int64_t d, int64_t front, Runs* runs, dim3* grid) {
+    const int64_t n4 = d >> 2, n_chunks = n4 > kThreads ? (n4 + kThreads - 1) / kThreads : 1;
+    return run_grid(n_jobs, n_chunks, n4 >= (1 << 20) ? 32 : 4, front, runs, grid);
 }
 
-// float4 per thread and vector of a mix, and the runs of its chunks.  Long vectors: every XCD takes runs of 4 consecutive 16 KB
-// chunks (3-4 % faster on 64-100 MB vectors); short ones: single chunks, less padding
-constexpr int kMixVec = 4;
-inline bool mix_grid(int n_jobs, int64_t d, int64_t front, Runs* runs, dim3* grid) {
-    constexpr int64_t per = (int64_t)kThreads * kMixVec;
-    const int64_t n4 = d >> 2, n_chunks = n4 > per ? (n4 + per - 1) / per : 1;
-    return run_grid(n_jobs, n_chunks, n4 >= 1024 * per ? 4 : 1, front, runs, grid);
+__global__ __launch_bounds__(kThreads) void mix_kernel(const HopMixJob* __restrict__ jobs, int64_t d, HOP_RUNS_IN) {
+    mix_block(jobs, d, HOP_RUNS, (int)blockIdx.z);
 }
 
 // ---------------------------------------------------------- Reduce + Apply, records in pairs ----
@@ -1075,13 +967,12 @@ __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob jo
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
 // (the parallel approach of Section 3.2 runs Compute beside Reduce).  The Reduce leaves sum_a w'_a x_a
 // in the result slot; dense_grad_kernel then applies -eta g to it.
-template <int VEC, int NT>
 __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                     HOP_RUNS_IN, unsigned margins, int n_mix,
                                                                     const HopGradJob* __restrict__ grad_jobs, int B, int nseg) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
-        mix_block<VEC, NT, kThreads>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
+        mix_block(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1296,13 +1187,12 @@ __global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* 
 // x_k, and nothing a wave writes is read inside it, so they need no order between them.  The few
 // latency-bound margin workgroups come first and run under the streaming ones.
 // (`per`: margin workgroups of a record)
-template <int VEC, int NT>
 __global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                   HOP_RUNS_IN, unsigned margins, int n_mix,
                                                                   const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
                                                                   int loss) {
     if ((int)blockIdx.z >= front) {
-        mix_block<VEC, NT, kThreads>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
+        mix_block(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1464,8 +1354,7 @@ int hopk_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
         Runs runs;
         dim3 grid;
         if (!mix_grid(n, d, 0, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL((mix_kernel<kMixVec, 1, kThreads>), grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d,
-                           HOP_RUNS_OF(runs));
+        hipLaunchKernelGGL(mix_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, HOP_RUNS_OF(runs));
         return launch_status();
     });
 }
@@ -1581,7 +1470,7 @@ int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const 
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((mix_dense_margin_kernel<kMixVec, 1>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+    hipLaunchKernelGGL(mix_dense_margin_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
                        runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, nseg);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
@@ -1596,7 +1485,7 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((mix_csr_margin_kernel<kMixVec, 1>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+    hipLaunchKernelGGL(mix_csr_margin_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
                        runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);

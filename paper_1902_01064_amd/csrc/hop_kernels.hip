@@ -923,6 +923,21 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
     }
 }
 
+// Small minibatches keep to one XCD: all margins of a record run on XCD (record mod 8) and so does its gradient, which finds
+// rows and coefficients in that XCD's L2.  Up to kOneXcdBytes of rows of kOneXcdCols columns; us per pass of 4 / 16 / 64 workers,
+// all XCDs -> one: B = 64, d = 1024 108 / 326 / 543 -> 101 / 301 / 485; B = 200, d = 1024 151 / 435 / 892 -> 145 / 401 / 781;
+// B = 128, d = 4096 (2 MB, half of an L2) 142 / 436 / 1039 -> 141 / 427 / 999; but B = 32, d = 8000 150 / 455 / 916 -> 152 / 469 /
+// 879, d = 15 000 159 / 525 / 1156 -> 165 / 535 / 1154: an XCD is busy with some 16 chunks of 256 columns of a record.
+constexpr int64_t kOneXcdBytes = 2 << 20, kOneXcdCols = 4096;
+static_assert(kOneXcdCols <= kSegCols, "rows of one segment");
+
+// one workgroup per (job, minibatch row), the job on one XCD; b: its index, in launches with other workgroups
+__device__ __forceinline__ void dense_margin_near(const HopGradJob* __restrict__ jobs, unsigned n_jobs, int B, int64_t d, unsigned b,
+                                                  float (*red)[kThreads / 64]) {
+    const unsigned rest = b / kXcd, job = rest / (unsigned)B * kXcd + b % kXcd;
+    if (job < n_jobs) dense_margin_rows<1, false, true>(jobs + job, B, d, 1, 0, (int)(rest % (unsigned)B), red);
+}
+
 // one workgroup per (job, minibatch row, column segment), b its index, in launches with other workgroups
 __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
                                                    unsigned b, float (*red)[kThreads / 64]) {
@@ -958,6 +973,12 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
 // allocated, copied or staged.  Per call: 128 x 65536 dense 42.5 -> 28.4 us, 64 x 1024 without allocation 10.4 -> 7.7 us
 // (one launch fewer), 256 samples of 64 non-zeros on 2^20 columns 33.0 -> 18.6 us (margins beside the dense part).
+// every eighth workgroup: the call keeps to one XCD (kOneXcdBytes)
+__global__ __launch_bounds__(kThreads) void dense_margin_near_one(const HopGradJob job, int B, int64_t d) {
+    __shared__ float red[1][kThreads / 64];
+    if (blockIdx.x == 0) dense_margin_rows<1, false, true>(&job, B, d, 1, 0, (int)blockIdx.y, red);
+}
+
 template <int ROWS, bool STREAM, bool ONE>
 __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob job, int B, int64_t d, int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
@@ -967,16 +988,21 @@ __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob jo
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
 // (the parallel approach of Section 3.2 runs Compute beside Reduce).  The Reduce leaves sum_a w'_a x_a
 // in the result slot; dense_grad_kernel then applies -eta g to it.
+// (NEAR: each record on one XCD, n their number; else n the segments of a row)
+template <bool NEAR>
 __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                     HOP_RUNS_IN, unsigned margins, int n_mix,
-                                                                    const HopGradJob* __restrict__ grad_jobs, int B, int nseg) {
+                                                                    const HopGradJob* __restrict__ grad_jobs, int B,
+                                                                    int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
         mix_block(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
-    if (b < margins) dense_margin_block(grad_jobs, B, d, nseg, b, red);
+    if (b >= margins) return;
+    if (NEAR) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
+    else dense_margin_block(grad_jobs, B, d, n, b, red);
 }
 
 // ----------------------------------------------------- dense SVM: g = lambda w - sum_m c_m x_m ----
@@ -1142,6 +1168,17 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const Hop
     if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
 }
 
+// each job on one XCD: a grid of (8, chunks, jobs / 8)
+__global__ __launch_bounds__(512) void dense_grad_near_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B, int64_t d,
+                                                              float lambda, int loss) {
+    const int job = (int)(blockIdx.z * kXcd + blockIdx.x);
+    if (job < n_jobs) dense_grad_chunk<8, 1, true>(jobs + job, B, d, 1, lambda, loss, blockIdx.y);
+}
+
+__global__ __launch_bounds__(512) void dense_grad_near_one(const HopGradJob job, int B, int64_t d, float lambda, int loss) {
+    if (blockIdx.x == 0) dense_grad_chunk<8, 1, true>(&job, B, d, 1, lambda, loss, blockIdx.y);
+}
+
 template <int SPLIT, int WIDE, bool ONE>
 __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
                                                              int loss) {
@@ -1217,17 +1254,20 @@ __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPair
     if (b < margins) csr_margin_rows(grad_jobs + b / per, B, loss, (int)(b % per));
 }
 
-template <int VEC>
+template <int VEC, bool NEAR>
 __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                      HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
-                                                                     const HopGradJob* __restrict__ grad_jobs, int B, int nseg) {
+                                                                     const HopGradJob* __restrict__ grad_jobs, int B,
+                                                                    int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
         pair_block<VEC>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
-    if (b < margins) dense_margin_block(grad_jobs, B, d, nseg, b, red);
+    if (b >= margins) return;
+    if (NEAR) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
+    else dense_margin_block(grad_jobs, B, d, n, b, red);
 }
 
 // target[col] += factor * c_m * val for the active rows (the sparse part of -eta g, or of g).
@@ -1433,12 +1473,22 @@ static GradShape grad_shape(int n_jobs, int64_t d, int nseg) {
     return chunks > kGradMany || nseg >= kGradSegs ? GradShape::many : chunks > kGradFew ? GradShape::some : GradShape::few;
 }
 
+// see kOneXcdBytes; with few column chunks, as a wave of so small minibatches has
+static bool one_xcd(int n_jobs, int B, int64_t d) {
+    return d <= kOneXcdCols && (int64_t)B * d * 4 <= kOneXcdBytes && grad_shape(n_jobs, d, 1) == GradShape::few;
+}
+
 int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss,
                     void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
     const int nseg = hopk_dense_nseg(d);
     const GradShape shape = grad_shape(n_jobs, d, nseg);
+    if (one_xcd(n_jobs, B, d)) {
+        const dim3 grid(kXcd, (unsigned)((d + 255) / 256), (unsigned)((n_jobs + kXcd - 1) / kXcd));
+        hipLaunchKernelGGL(dense_grad_near_kernel, grid, dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B, d, lambda, loss);
+        return launch_status();
+    }
     const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;
     return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
         dim3 grid;
@@ -1466,18 +1516,26 @@ int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, voi
     });
 }
 
+// workgroups of margins that keep to one XCD a record
+static int64_t near_margins(int n_grad, int B) { return (int64_t)(n_grad + kXcd - 1) / kXcd * kXcd * B; }
+
 // Margins in front of a Reduce over at most kMaxGridYZ jobs; the rest of a longer one behind it, by itself.
 int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
                           void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const int64_t margins = (int64_t)n_grad * B * nseg;
+    const bool near = one_xcd(n_grad, B, d);
+    const int64_t margins = near ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(mix_dense_margin_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
-                       runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, nseg);
+    if (near)
+        hipLaunchKernelGGL(mix_dense_margin_kernel<true>, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+                           runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, n_grad);
+    else
+        hipLaunchKernelGGL(mix_dense_margin_kernel<false>, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+                           runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, nseg);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
@@ -1530,13 +1588,19 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const int64_t margins = (int64_t)n_grad * B * nseg;
+    const bool near = one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
+    const int64_t margins = near ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     int vec;
     Runs runs;
     dim3 grid;
     if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_dense_margin_kernel, kPairMargin, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front,
-                    HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, nseg);
+#define HOP_DENSE_PAIRS(VEC, NEAR, ARG)                                                                                     \
+    hipLaunchKernelGGL((pair_dense_margin_kernel<VEC, NEAR>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,      \
+                       runs.front, HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, ARG)
+    if (vec == 4) HOP_DENSE_PAIRS(4, false, nseg);
+    else if (near) HOP_DENSE_PAIRS(kPairMargin, true, n_grad);
+    else HOP_DENSE_PAIRS(kPairMargin, false, nseg);
+#undef HOP_DENSE_PAIRS
     if (const int rc = launch_status()) return rc;
     return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
@@ -1565,6 +1629,12 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
         if (B > kMaxB) return (int)hipErrorInvalidValue;
         if (grid > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         const dim3 threads(kThreads), rows((unsigned)few), groups((unsigned)grid);
+        if (one_xcd(1, B, d)) {
+            hipLaunchKernelGGL(dense_margin_near_one, dim3(kXcd, (unsigned)B), threads, 0, st, job, B, d);
+            if (const int rc = launch_status()) return rc;
+            hipLaunchKernelGGL(dense_grad_near_one, dim3(kXcd, (unsigned)((d + 255) / 256)), dim3(512), 0, st, job, B, d, lambda, loss);
+            return launch_status();
+        }
         const bool near = (int64_t)B * d * 4 <= kMarginNear;
         if (nseg == 1 && grid < kMarginFew)                          // a row of one segment is at most 64 KB: always near
             hipLaunchKernelGGL((dense_margin_one<1, false, true>), rows, threads, 0, st, job, B, d, nseg);

@@ -1,0 +1,49 @@
+"""Waves of small dense minibatches, each record on one XCD, and just beyond that rule: coefficients and results against 64 bits."""
+import pytest
+import torch
+
+from paper_1902_01064_amd import hop, inputs
+from paper_1902_01064_amd.session import Session
+
+pytestmark = pytest.mark.gpu
+
+
+# one wave of all workers: 1, 7, 8, 9 and 17 records; 2 MB of rows (B = 128 x 4096) and one row or column more; 48 and 49 records of
+# 16 column chunks (768 and more)
+@pytest.mark.parametrize("N,d,B", [(1, 1, 1), (7, 257, 3), (8, 1024, 64), (9, 4096, 128), (9, 4096, 129), (9, 4097, 100), (17, 1000, 200),
+                                   (3, 512, 1024), (3, 512, 1000), (48, 4096, 5), (49, 4096, 5)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_wave_of_small_minibatches(N, d, B, momentum):
+    nb = [[]] if N == 1 else inputs.ring(N)
+    c = dict(inputs.config(1, d=d, rows=70, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
+             lr=0.5, momentum=momentum, skip_on=False, mult=None, delay_kind=inputs.DELAY_NONE)
+    ws = inputs.hidden_w(6, d, "cuda")
+    data = [inputs.dense_svm_data(6, i, 70, d, ws, "cuda") for i in range(N)]
+    p0 = torch.randn(N, d, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda") / d ** 0.5
+    print("one XCD", N, d, B, momentum, flush=True)
+    sess = Session(c)
+    try:
+        sess.set_dense([x for x, _ in data], [y for _, y in data])
+        sess.set_params(p0)
+        s = sess.simulate()
+        assert s.n_waves == 1 and s.n_records == N
+        sess.step()
+        sess.sync()
+        for e in range(N):
+            i, ids = int(s.worker[e]), torch.from_numpy(s.batch_rows[e].copy()).cuda().long()
+            X, y, w = data[i][0][ids].double(), data[i][1][ids].double(), p0[i].double()
+            coef = torch.from_numpy(sess.coef(e)).cuda().double()
+            # the slope of a coefficient in its margin is at most 1 / 4 B; a sum of d products is off by (d + 1) 2^-24 of their magnitudes
+            off = (d + 1) * 2.0 ** -24 * (X.abs() @ w.abs())
+            want = y / (B * (1 + torch.exp(y * (X @ w))))
+            assert bool(((coef - want).abs() <= (0.25 * off + 1e-6) / B).all())
+            g, mag = 0.25 * w - coef @ X, 0.25 * w.abs() + coef.abs() @ X.abs()
+            acc, size = torch.zeros_like(g), torch.zeros_like(g)
+            for a in range(int(s.src_begin[e]), int(s.src_begin[e + 1])):
+                x = float(s.src_weight[a]) * p0[int(s.src_worker[a])].double()
+                acc, size = acc + x, size + x.abs()
+            got = sess.slot(i, int(s.out_slot[e])).double()
+            room = 2.0 ** -24 * (0.5 * (B + 4) * mag + 8 * size)        # B + 1 products, up to three sources and the step
+            assert bool(((got - (acc - 0.5 * g)).abs() <= room).all())
+    finally:
+        sess.close()

@@ -17,7 +17,6 @@ namespace {
 constexpr int64_t kAlignFloats = 64;       // 256 bytes
 constexpr int kMaxBatch = 1024;
 constexpr size_t kMaxPendingEvents = 1 << 15;
-constexpr int64_t kDenseInPlaceBytes = 2 << 20;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
@@ -534,7 +533,7 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
     }
     // dense minibatches of up to 2 MB per record take the margins-beside-the-Reduce path of launch_waves (measured:
     // 0.65 -> 0.51 ms per pass at 256 KB per record; at 32 MB the margin pass wants a launch of its own for occupancy)
-    s->dense_in_place = mode == HOP_GRAD_SVM_DENSE && (int64_t)B * c->d * 4 <= kDenseInPlaceBytes;
+    s->dense_in_place = mode == HOP_GRAD_SVM_DENSE && !hop_dense_slices(B, c->d) && (int64_t)B * c->d * 4 <= kDenseInPlaceBytes;
     // Larger dense minibatches: margins, then a gradient kernel that also does the Reduce + Apply of its record
     // (the time is the rows'; a separate mix launch of a few hundred KB per record would only add its start-up,
     // measured 4 us + gap per wave at 16 workers x 65536 columns).  The wave's mix then only holds the records
@@ -594,7 +593,8 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
                     gj.X = dd.X;
                     gj.y = dd.y;
                     gj.k0 = (uint32_t)c->opts.loss;
-                    gj.partial = c->partial + (int64_t)i * partial_floats(c->d, c->opts.batch);
+                    gj.partial = hop_dense_slices(B, c->d) ? c->gbuf + (int64_t)i * c->grad_ahead * c->stride
+                                                           : c->partial + (int64_t)i * partial_floats(c->d, c->opts.batch);
                     // the gradient kernel applies -eta g (through the velocity, if any) itself, so no dense g is
                     // written and read back: in place on the vector the mix has reduced (small minibatches), or on
                     // its own Reduce of the record's sources (large ones)

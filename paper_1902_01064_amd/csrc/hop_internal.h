@@ -175,6 +175,17 @@ __attribute__((weak)) int hopk_one_grad(const HopGradJob& job, int mode, int B, 
 __attribute__((weak)) int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
+constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce
+// Whether the columns of a wave's dense minibatches are dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in
+// the worker's gradient buffer, which dense passes have no other use for.  us per pass of 4 / 16 / 64 workers without and with:
+// B = 64, d = 12 000 211 / 699 / 1863 -> 179 / 585 / 1630; B = 64, d = 20 000 260 / 979 / 3132 -> 216 / 746 / 2421; B = 128, d = 65 536
+// 556 / 2130 / 9528 -> 495 / 1964 / 9350.  Below, against margins beside the Reduce: B = 32, d = 10 000 143 / 412 / 938 -> 149 / 417 / 964,
+// d = 7000 138 / 368 / 776 -> 140 / 384 / 862; against margins by themselves (over 2 MB): B = 100, d = 8000 193 / 574 / 1491 -> 162 / 510 /
+// 1384, B = 128, d = 5000 163 / 484 / 1253 -> 161 / 498 / 1384.  Above, a slice would be more than a segment.
+inline bool hop_dense_slices(int B, int64_t d) {
+    return d <= 8 * 16384 && 8 * (int64_t)B <= d && d > ((int64_t)B * d * 4 > kDenseInPlaceBytes ? 7168 : 11264);
+}
+
 // ---- host-side random numbers (hop_sim.cpp) ---------------------------------------
 namespace hoprng {
 enum : uint64_t { STREAM_DELAY = 1, STREAM_BATCH = 2, STREAM_SYNTHGRAD = 6, STREAM_LATENCY = 7 };

@@ -866,9 +866,16 @@ constexpr int64_t kSegCols = (int64_t)kSeg4 * 4;
 // ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t,
 // or, where a row has one segment only, its coefficient: the gradient kernel then has that to load and nothing to work out
 // (the label's load under the row's; see dense_grad_chunk).  Each row is summed in the same order whatever ROWS is.
-template <int ROWS, bool STREAM, bool ONE>
+// How a row is cut up: segments of kSegCols columns, one such segment, or a slice for each XCD (hop_dense_slices), whose margins
+// and gradient run there: the gradient finds in that XCD's L2 what the margins have read, as much as fits.
+enum class Cut { segments, one, slices };
+// first of n_chunks chunks that belong to slice s
+__device__ __forceinline__ int slice_begin(int n_chunks, int s) { return n_chunks * s / kXcd; }
+
+template <int ROWS, bool STREAM, Cut CUT>
 __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, int seg,
                                                   int m0, float (*red)[kThreads / 64]) {
+    constexpr bool ONE = CUT == Cut::one;
     const float* w = job->w;
     const float* x[ROWS];
 #pragma unroll
@@ -877,8 +884,9 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
     const bool writes = threadIdx.x < ROWS && mine < B;
     float y = 0.f;
     if (ONE && writes) y = job->y[job->rows[mine]];
-    const int64_t lo = (int64_t)seg * kSegCols;
-    const int64_t hi = min(d, lo + kSegCols);
+    const int chunks = (int)((d + 255) / 256);
+    const int64_t lo = CUT == Cut::slices ? slice_begin(chunks, seg) * 256 : (int64_t)seg * kSegCols;
+    const int64_t hi = min(d, CUT == Cut::slices ? slice_begin(chunks, seg + 1) * (int64_t)256 : lo + kSegCols);
     float a[ROWS][4];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) a[r][0] = a[r][1] = a[r][2] = a[r][3] = 0.f;
@@ -926,27 +934,28 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
 // Small minibatches keep to one XCD: all margins of a record run on XCD (record mod 8) and so does its gradient, which finds
 // rows and coefficients in that XCD's L2.  Up to kOneXcdBytes of rows of kOneXcdCols columns; us per pass of 4 / 16 / 64 workers,
 // all XCDs -> one: B = 64, d = 1024 108 / 326 / 543 -> 101 / 301 / 485; B = 200, d = 1024 151 / 435 / 892 -> 145 / 401 / 781;
-// B = 128, d = 4096 (2 MB, half of an L2) 142 / 436 / 1039 -> 141 / 427 / 999; but B = 32, d = 8000 150 / 455 / 916 -> 152 / 469 /
-// 879, d = 15 000 159 / 525 / 1156 -> 165 / 535 / 1154: an XCD is busy with some 16 chunks of 256 columns of a record.
-constexpr int64_t kOneXcdBytes = 2 << 20, kOneXcdCols = 4096;
+// B = 128, d = 4096 (2 MB, half of an L2) 142 / 436 / 1039 -> 141 / 427 / 999; B = 32, d = 8000 150 / 410 / 898 -> 153 / 402 / 863;
+// but B = 32, d = 10 000 143 / 412 / 938 -> 147 / 423 / 914, d = 16 000 167 / 549 / 1231 -> 182 / 593 / 1236: an XCD is busy with
+// some 32 chunks of 256 columns of a record.
+constexpr int64_t kOneXcdBytes = 2 << 20, kOneXcdCols = 8192;
 static_assert(kOneXcdCols <= kSegCols, "rows of one segment");
 
 // one workgroup per (job, minibatch row), the job on one XCD; b: its index, in launches with other workgroups
 __device__ __forceinline__ void dense_margin_near(const HopGradJob* __restrict__ jobs, unsigned n_jobs, int B, int64_t d, unsigned b,
                                                   float (*red)[kThreads / 64]) {
     const unsigned rest = b / kXcd, job = rest / (unsigned)B * kXcd + b % kXcd;
-    if (job < n_jobs) dense_margin_rows<1, false, true>(jobs + job, B, d, 1, 0, (int)(rest % (unsigned)B), red);
+    if (job < n_jobs) dense_margin_rows<1, false, Cut::one>(jobs + job, B, d, 1, 0, (int)(rest % (unsigned)B), red);
 }
 
 // one workgroup per (job, minibatch row, column segment), b its index, in launches with other workgroups
 __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict__ jobs, int B, int64_t d, int nseg,
                                                    unsigned b, float (*red)[kThreads / 64]) {
     if (nseg == 1) {
-        dense_margin_rows<1, false, true>(jobs + b / (unsigned)B, B, d, nseg, 0, (int)(b % (unsigned)B), red);
+        dense_margin_rows<1, false, Cut::one>(jobs + b / (unsigned)B, B, d, nseg, 0, (int)(b % (unsigned)B), red);
         return;
     }
     const unsigned row = b / (unsigned)nseg;
-    dense_margin_rows<1, false, false>(jobs + row / (unsigned)B, B, d, nseg, (int)(b % (unsigned)nseg), (int)(row % (unsigned)B), red);
+    dense_margin_rows<1, false, Cut::segments>(jobs + row / (unsigned)B, B, d, nseg, (int)(b % (unsigned)nseg), (int)(row % (unsigned)B), red);
 }
 
 // The margin pass as a launch of its own: four minibatch rows per workgroup share every load of w (the L2 sees
@@ -960,14 +969,16 @@ __device__ __forceinline__ void dense_margin_block(const HopGradJob* __restrict_
 // margins 37.4 -> 42.5 us, gradient 23.8 -> 21.5 us per wave, nothing gained; where a launch of few workgroups reads no
 // more than half of that cache (kMarginNear) ordinary loads pay: 3 to 4 records of 100 x 30 011 2.20 -> 2.12 ms per pass.
 constexpr int kMarginRows = 4;
+// Slices are an eighth of a row, at most a segment: two rows per workgroup (geometric mean over 33 sizes 3.6 % ahead of four).
+constexpr int kSliceRows = 2;
 constexpr int64_t kMarginFew = 384;
 constexpr int64_t kMarginNear = 128ll << 20;           // bytes of rows in a launch up to which they are left in the caches
 
-template <int ROWS, bool STREAM, bool ONE>
+template <int ROWS, bool STREAM, Cut CUT>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
                                                                 int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_rows<ROWS, STREAM, ONE>(jobs + blockIdx.z, B, d, nseg, (int)blockIdx.x, (int)blockIdx.y * ROWS, red);
+    dense_margin_rows<ROWS, STREAM, CUT>(jobs + blockIdx.z, B, d, nseg, (int)blockIdx.x, (int)blockIdx.y * ROWS, red);
 }
 
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
@@ -976,13 +987,13 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob
 // every eighth workgroup: the call keeps to one XCD (kOneXcdBytes)
 __global__ __launch_bounds__(kThreads) void dense_margin_near_one(const HopGradJob job, int B, int64_t d) {
     __shared__ float red[1][kThreads / 64];
-    if (blockIdx.x == 0) dense_margin_rows<1, false, true>(&job, B, d, 1, 0, (int)blockIdx.y, red);
+    if (blockIdx.x == 0) dense_margin_rows<1, false, Cut::one>(&job, B, d, 1, 0, (int)blockIdx.y, red);
 }
 
 template <int ROWS, bool STREAM, bool ONE>
 __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob job, int B, int64_t d, int nseg) {
     __shared__ float red[ROWS][kThreads / 64];
-    dense_margin_rows<ROWS, STREAM, ONE>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
+    dense_margin_rows<ROWS, STREAM, ONE ? Cut::one : Cut::segments>(&job, B, d, nseg, (int)(blockIdx.x % nseg), (int)(blockIdx.x / nseg) * ROWS, red);
 }
 
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
@@ -1166,6 +1177,15 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const Hop
                                                                 int64_t n_chunks) {
     const int64_t chunk = grid_chunk(width);
     if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
+}
+
+// each XCD a slice of the columns: a grid of (8, jobs, chunks of the longest slice)
+template <int SPLIT, int WIDE>
+__global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_slice_kernel(const HopGradJob* __restrict__ jobs, int n_chunks, int B,
+                                                                             int64_t d, float lambda, int loss) {
+    const int chunk = slice_begin(n_chunks, (int)blockIdx.x) + (int)blockIdx.z;
+    if (chunk < slice_begin(n_chunks, (int)blockIdx.x + 1))
+        dense_grad_chunk<SPLIT, WIDE, false>(jobs + blockIdx.y, B, d, kXcd, lambda, loss, chunk);
 }
 
 // each job on one XCD: a grid of (8, chunks, jobs / 8)
@@ -1452,16 +1472,28 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int64_t blocks = (int64_t)n_jobs * groups * nseg;
     if (blocks > 0x7FFFFFFFll || B > kMaxB) return (int)hipErrorInvalidConfiguration;
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
+    if (hop_dense_slices(B, d))
+        return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+            const dim3 rows(kXcd, (unsigned)B, (unsigned)n), pairs(kXcd, (unsigned)((B + kSliceRows - 1) / kSliceRows), (unsigned)n);
+#define HOP_SLICES(GRID, ROWS, STREAM)                                                                                      \
+    hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, Cut::slices>), GRID, dim3(kThreads), 0, (hipStream_t)stream, jobs, \
+                       B, d, kXcd)
+            if ((int64_t)n * groups * kXcd < kMarginFew) HOP_SLICES(rows, 1, false);
+            else if (near) HOP_SLICES(pairs, kSliceRows, false);
+            else HOP_SLICES(pairs, kSliceRows, true);
+#undef HOP_SLICES
+            return launch_status();
+        });
     return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
         const dim3 rows((unsigned)nseg, (unsigned)B, (unsigned)n), fours((unsigned)nseg, (unsigned)groups, (unsigned)n);
 #define HOP_MARGINS(GRID, ROWS, STREAM, ONE)                                                                                \
     hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, ONE>), GRID, dim3(kThreads), 0, (hipStream_t)stream, jobs, B, d, nseg)
         static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "few workgroups of one segment: near");
-        if (blocks < kMarginFew && nseg == 1) HOP_MARGINS(rows, 1, false, true);
-        else if (blocks < kMarginFew && near) HOP_MARGINS(rows, 1, false, false);
-        else if (blocks < kMarginFew) HOP_MARGINS(rows, 1, true, false);
-        else if (nseg == 1) HOP_MARGINS(fours, kMarginRows, true, true);
-        else HOP_MARGINS(fours, kMarginRows, true, false);
+        if (blocks < kMarginFew && nseg == 1) HOP_MARGINS(rows, 1, false, Cut::one);
+        else if (blocks < kMarginFew && near) HOP_MARGINS(rows, 1, false, Cut::segments);
+        else if (blocks < kMarginFew) HOP_MARGINS(rows, 1, true, Cut::segments);
+        else if (nseg == 1) HOP_MARGINS(fours, kMarginRows, true, Cut::one);
+        else HOP_MARGINS(fours, kMarginRows, true, Cut::segments);
 #undef HOP_MARGINS
         return launch_status();
     });
@@ -1489,6 +1521,19 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
         hipLaunchKernelGGL(dense_grad_near_kernel, grid, dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B, d, lambda, loss);
         return launch_status();
     }
+    if (hop_dense_slices(B, d))
+        return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
+            const int cols = shape == GradShape::many ? 1024 : 256, n_chunks = (int)((d + cols - 1) / cols);
+            const dim3 grid(kXcd, (unsigned)n, (unsigned)((n_chunks + kXcd - 1) / kXcd));
+#define HOP_SLICES(SPLIT, WIDE)                                                                                             \
+    hipLaunchKernelGGL((dense_grad_slice_kernel<SPLIT, WIDE>), grid, dim3(64 * SPLIT * WIDE), 0, (hipStream_t)stream, jobs,  \
+                       n_chunks, B, d, lambda, loss)
+            if (shape == GradShape::few) HOP_SLICES(8, 1);
+            else if (shape == GradShape::some) HOP_SLICES(4, 1);
+            else HOP_SLICES(1, 4);
+#undef HOP_SLICES
+            return launch_status();
+        });
     const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;
     return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
         dim3 grid;

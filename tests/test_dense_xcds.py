@@ -1,4 +1,5 @@
-"""Waves of small dense minibatches, each record on one XCD, and just beyond that rule: coefficients and results against 64 bits."""
+"""Waves of dense minibatches with each record on one XCD, or a slice of the columns on each, and just beyond those rules:
+coefficients and results against 64 bits."""
 import pytest
 import torch
 
@@ -8,19 +9,23 @@ from paper_1902_01064_amd.session import Session
 pytestmark = pytest.mark.gpu
 
 
-# one wave of all workers: 1, 7, 8, 9 and 17 records; 2 MB of rows (B = 128 x 4096) and one row or column more; 48 and 49 records of
-# 16 column chunks (768 and more)
+# one wave of all workers.  One XCD a record: 1, 7, 8, 9 and 17 records; 2 MB of rows (B = 128 x 4096, 64 x 8192) and one row or
+# column more; 48 and 49 records of 16 column chunks (768 and more).
+# Slices: from 7169 columns on where rows are over 2 MB (B = 73, 74), else from 11 265; up to 131 072; at least 8 columns a row;
+# slices of 5 and 6 chunks, of one less where the last chunk has one column; 940 and 2256 chunks
 @pytest.mark.parametrize("N,d,B", [(1, 1, 1), (7, 257, 3), (8, 1024, 64), (9, 4096, 128), (9, 4096, 129), (9, 4097, 100), (17, 1000, 200),
-                                   (3, 512, 1024), (3, 512, 1000), (48, 4096, 5), (49, 4096, 5)])
+                                   (3, 512, 1024), (3, 512, 1000), (48, 4096, 5), (49, 4096, 5), (3, 8192, 64), (3, 8193, 64),
+                                   (2, 7168, 74), (2, 7169, 73), (2, 7169, 74), (3, 11264, 40), (3, 11265, 40), (2, 131072, 16),
+                                   (2, 131073, 16), (2, 8192, 1024), (2, 8191, 1024), (1, 11521, 3), (20, 12001, 50), (48, 12001, 17)])
 @pytest.mark.parametrize("momentum", [0.0, 0.9])
-def test_wave_of_small_minibatches(N, d, B, momentum):
+def test_wave(N, d, B, momentum):
     nb = [[]] if N == 1 else inputs.ring(N)
     c = dict(inputs.config(1, d=d, rows=70, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
              lr=0.5, momentum=momentum, skip_on=False, mult=None, delay_kind=inputs.DELAY_NONE)
     ws = inputs.hidden_w(6, d, "cuda")
     data = [inputs.dense_svm_data(6, i, 70, d, ws, "cuda") for i in range(N)]
     p0 = torch.randn(N, d, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda") / d ** 0.5
-    print("one XCD", N, d, B, momentum, flush=True)
+    print("XCDs", N, d, B, momentum, flush=True)
     sess = Session(c)
     try:
         sess.set_dense([x for x, _ in data], [y for _, y in data])

@@ -413,9 +413,12 @@ __global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, in
 // Plain launches that fit one turn stay (64 records in 32 pairs, 32768 columns: 6.9 us per wave against 7.5 with 2).
 constexpr int64_t kPairShort = 8192, kPairTurn = 512;  // workgroups of 16 KB chunks
 constexpr int kPairPlain = 2, kPairMargin = 1;         // the short width alone, and with margins beside
-inline int pair_vec(int n_jobs, int64_t d, bool margins) {
+// Long launches with sparse margins beside single records: 1 too, in runs twice as long (64 workers x 2^24 columns 75.1 ->
+// 73.9 ms, 64 x 2^23 10.18 -> 9.96); in pairs a source shared in registers is what counts (32 workers x 3 M columns, lock-step,
+// 1.88 -> 2.24).
+inline int pair_vec(int n_jobs, int64_t d, bool margins, bool single = false) {
     const int64_t blocks = n_jobs * ((d + 4095) / 4096);
-    if (blocks >= kPairShort) return 4;
+    if (blocks >= kPairShort) return single ? kPairMargin : 4;
     return margins ? kPairMargin : blocks <= kPairTurn ? 4 : kPairPlain;
 }
 
@@ -436,10 +439,12 @@ inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
 }
 
 // width, runs and grid of a launch over pairs, `front` other workgroups in front
-inline bool pair_grid(int n_jobs, int n_sources, int64_t d, bool margins, int64_t front, int* vec, Runs* runs, dim3* grid) {
-    *vec = pair_vec(n_jobs, d, margins);
+inline bool pair_grid(int n_jobs, int n_sources, int64_t d, bool margins, int64_t front, int* vec, Runs* runs, dim3* grid,
+                      bool single = false) {
+    *vec = pair_vec(n_jobs, d, margins, single);
     const int64_t n_chunks = pair_chunks(d, *vec);
-    return run_grid(n_jobs, n_chunks, pair_run(n_sources, n_chunks, *vec), front, runs, grid);
+    const int run = pair_run(n_sources, n_chunks, *vec);
+    return run_grid(n_jobs, n_chunks, single && *vec != pair_vec(n_jobs, d, margins) ? 2 * run : run, front, runs, grid);
 }
 
 // ------------------------------------------------------------------- synthetic gradient ----
@@ -1621,7 +1626,8 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
     int vec;
     Runs runs;
     dim3 grid;
-    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
+    // fewer jobs than gradients: some hold two records
+    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid, n_mix >= n_grad)) return (int)hipErrorInvalidConfiguration;
     HOP_PAIR_LAUNCH(pair_csr_margin_kernel, kPairMargin, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front,
                     HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
     if (const int rc = launch_status()) return rc;

@@ -74,6 +74,12 @@ __device__ __forceinline__ void st4_stream(float* p, int64_t i4, float4 v) {
     vf4 t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, (gvec_out)p + i4);
 }
+// NEAR: see kNearBytes (a template argument: of a run-time choice the compiler makes one store, without the hint)
+template <bool NEAR>
+__device__ __forceinline__ void st4_once(float* p, int64_t i4, float4 v) {
+    if (NEAR) st4(p, i4, v);
+    else st4_stream(p, i4, v);
+}
 
 // A launch's grid over jobs and column chunks is (chunks of one round, jobs, rounds), so a workgroup's job and chunk are its
 // block index: worked out from one number they took up to four divisions, 100 to 200 scalar instructions in front of the first
@@ -95,6 +101,16 @@ inline bool chunk_grid(int n_jobs, int64_t n_chunks, dim3* grid) {
 }
 // chunk of this workgroup of such a grid (`width`: its x); it may lie past the last one
 __device__ __forceinline__ int64_t grid_chunk(int width) { return (int64_t)blockIdx.z * width + blockIdx.x; }
+
+// Vectors that the next launches find in the L2s: where a launch writes no more than the 32 MB of all of them, results are
+// stored like any other data (else non-temporally, so that they push nothing out), and a chunk of columns goes to the same XCD in
+// every launch: runs of one chunk, always from the front.  us, without and with: a pass of 16 workers x 300 000 columns, sparse,
+// 373 / 312; 16 x 2^20 (18 MB a wave) 2733 / 2500; wave by wave with external gradients 16 x 300 000 253 / 204, 32 x 150 000 322 / 257.
+// Beyond: 16 x 4 M 1370 / 1440, 32 x 2 M (72 MB a wave) 1613 / 1665.
+constexpr int64_t kNearBytes = 32ll << 20;
+// `vectors` that a job writes: with a velocity its own share is written and read between, which counts as three (16 x 300 000,
+// sparse, 419 / 402; 64 x 500 000 1357 / 1375).
+inline bool stays_near(int n_jobs, int64_t d, int vectors = 1) { return vectors * n_jobs * d * (int64_t)sizeof(float) <= kNearBytes; }
 
 // Rounds in which every XCD takes a run of consecutive chunks: longer contiguous pieces of every stream are in flight at a
 // time.  The last, partly filled round is dealt out evenly (shorter runs on all XCDs, not full runs on the first few).
@@ -139,7 +155,7 @@ __device__ __forceinline__ int run_chunk(const Runs& r, int round) {
 // 16 x 300 000 256 / 229 / 215; 32 x 4 M 5160 / 5020 / 4970; 16 x 2^20, sparse, 935 / 858 / 813).  g, velocity and result
 // non-temporal (each touched once).  Measured on 32 jobs x 25 M columns with ~7.6 shared sources each: job-major workgroups
 // are 2.3x slower than the grid above and chunk-major ones that ignore the XCDs 1.45x slower.
-template <int A, bool MOM>
+template <int A, bool MOM, bool NEAR>
 __device__ __forceinline__ void mix_tile(const HopMixJob* __restrict__ job, int64_t i) {
     const float* g = job->g;
     const float neg_eta = -job->eta;
@@ -160,10 +176,11 @@ __device__ __forceinline__ void mix_tile(const HopMixJob* __restrict__ job, int6
     } else if (g != nullptr) {
         acc = fma4(neg_eta, ld4_stream(g, i), acc);
     }
-    st4_stream(job->out, i, acc);
+    st4_once<NEAR>(job->out, i, acc);
 }
 
 // more than 12 sources: a loop over the sources instead of an unrolled chain
+template <bool NEAR>
 __device__ __forceinline__ void mix_tile_any(const HopMixJob* __restrict__ job, int64_t i) {
     const int A = job->A;
     const float* g = job->g;
@@ -181,25 +198,26 @@ __device__ __forceinline__ void mix_tile_any(const HopMixJob* __restrict__ job, 
     } else if (g != nullptr) {
         acc = fma4(neg_eta, ld4_stream(g, i), acc);
     }
-    st4_stream(job->out, i, acc);
+    st4_once<NEAR>(job->out, i, acc);
 }
 
 // Work of one workgroup of the mix in round `round` of the chunks (the launch may hold other workgroups in front of them).
+template <bool NEAR>
 __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, int64_t d, const Runs& runs, int round) {
     const int chunk = run_chunk(runs, round);
     if (chunk < 0) return;
     const HopMixJob* job = jobs + blockIdx.y;
     const int64_t n4 = d >> 2, i = (int64_t)chunk * kThreads + threadIdx.x;
     if (i < n4) {
-#define HOP_MIX_CASE(AA)                                    \
-    case AA:                                                \
-        if (job->vel != nullptr) mix_tile<AA, true>(job, i); \
-        else mix_tile<AA, false>(job, i);                   \
+#define HOP_MIX_CASE(AA)                                           \
+    case AA:                                                       \
+        if (job->vel != nullptr) mix_tile<AA, true, NEAR>(job, i); \
+        else mix_tile<AA, false, NEAR>(job, i);                    \
         break;
         switch (job->A) {
             HOP_MIX_CASE(1) HOP_MIX_CASE(2) HOP_MIX_CASE(3) HOP_MIX_CASE(4) HOP_MIX_CASE(5) HOP_MIX_CASE(6)
             HOP_MIX_CASE(7) HOP_MIX_CASE(8) HOP_MIX_CASE(9) HOP_MIX_CASE(10) HOP_MIX_CASE(11) HOP_MIX_CASE(12)
-            default: mix_tile_any(job, i); break;
+            default: mix_tile_any<NEAR>(job, i); break;
         }
 #undef HOP_MIX_CASE
     }
@@ -226,11 +244,12 @@ __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, in
 // 12 M 4912 -> 4868), 4 on shorter ones (8: 32 x 50 000 columns 170.5 -> 171.9)
 inline bool mix_grid(int n_jobs, int64_t d, int64_t front, Runs* runs, dim3* grid) {
     const int64_t n4 = d >> 2, n_chunks = n4 > kThreads ? (n4 + kThreads - 1) / kThreads : 1;
-    return run_grid(n_jobs, n_chunks, n4 >= (1 << 20) ? 32 : 4, front, runs, grid);
+    return run_grid(n_jobs, n_chunks, stays_near(n_jobs, d, 3) ? 1 : n4 >= (1 << 20) ? 32 : 4, front, runs, grid);
 }
 
+template <bool NEAR>
 __global__ __launch_bounds__(kThreads) void mix_kernel(const HopMixJob* __restrict__ jobs, int64_t d, HOP_RUNS_IN) {
-    mix_block(jobs, d, HOP_RUNS, (int)blockIdx.z);
+    mix_block<NEAR>(jobs, d, HOP_RUNS, (int)blockIdx.z);
 }
 
 // ---------------------------------------------------------- Reduce + Apply, records in pairs ----
@@ -250,7 +269,7 @@ __global__ __launch_bounds__(kThreads) void mix_kernel(const HopMixJob* __restri
 // where the union has them), in fp32 FMAs starting from zero.
 constexpr int kPairU = HOP_PAIR_U;
 
-template <int VEC, int U, bool FULL, class Job>
+template <int VEC, int U, bool FULL, bool NEAR, class Job>
 __device__ __forceinline__ void pair_tile(Job job, int64_t first4, int64_t n4) {
     const int G = job->G;
     const float* src[U];
@@ -311,13 +330,13 @@ __device__ __forceinline__ void pair_tile(Job job, int64_t first4, int64_t n4) {
             }
 #pragma unroll
             for (int v = 0; v < VEC; ++v)
-                if (FULL || i0 + v * kThreads < n4) st4_stream(op[r], i0 + v * kThreads, acc[v]);
+                if (FULL || i0 + v * kThreads < n4) st4_once<NEAR>(op[r], i0 + v * kThreads, acc[v]);
         }
     }
 }
 
 // a single record with more than kPairU sources: a loop over the sources
-template <int VEC, class Job>
+template <int VEC, bool NEAR, class Job>
 __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t n4) {
     const int U = job->U;
     const float* g = job->g[0];
@@ -341,13 +360,13 @@ __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t 
             acc.z = fmaf(neg_eta, gv.z, acc.z);
             acc.w = fmaf(neg_eta, gv.w, acc.w);
         }
-        st4_stream(job->out[0], i, acc);
+        st4_once<NEAR>(job->out[0], i, acc);
     }
 }
 
 // Work of one workgroup in round `round` of the chunks.
 // Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
-template <int VEC, class Job>
+template <int VEC, bool NEAR, class Job>
 __device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs, int reverse, int round) {
     const int ahead = run_chunk(runs, round);
     if (ahead < 0) return;
@@ -360,15 +379,15 @@ __device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs
     const int64_t first4 = (int64_t)chunk * (kThreads * VEC);
     const bool full = first4 + kThreads * VEC <= n4;
     static_assert(kPairU == 12, "the switch below unrolls unions of 1..12 vectors");
-#define HOP_PAIR_CASE(UU)                                      \
-    case UU:                                                   \
-        if (full) pair_tile<VEC, UU, true>(job, first4, n4);   \
-        else pair_tile<VEC, UU, false>(job, first4, n4);       \
+#define HOP_PAIR_CASE(UU)                                            \
+    case UU:                                                         \
+        if (full) pair_tile<VEC, UU, true, NEAR>(job, first4, n4);   \
+        else pair_tile<VEC, UU, false, NEAR>(job, first4, n4);       \
         break;
     switch (job->U) {
         HOP_PAIR_CASE(1) HOP_PAIR_CASE(2) HOP_PAIR_CASE(3) HOP_PAIR_CASE(4) HOP_PAIR_CASE(5) HOP_PAIR_CASE(6)
         HOP_PAIR_CASE(7) HOP_PAIR_CASE(8) HOP_PAIR_CASE(9) HOP_PAIR_CASE(10) HOP_PAIR_CASE(11) HOP_PAIR_CASE(12)
-        default: pair_tile_wide<VEC>(job, first4, n4); break;
+        default: pair_tile_wide<VEC, NEAR>(job, first4, n4); break;
     }
 #undef HOP_PAIR_CASE
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
@@ -385,10 +404,10 @@ __device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs
     }
 }
 
-template <int VEC>
+template <int VEC, bool NEAR>
 __global__ __launch_bounds__(kThreads) void pair_mix_kernel(const HopPairJob* __restrict__ jobs, int64_t d, int reverse,
                                                             HOP_RUNS_IN) {
-    pair_block<VEC>(jobs, d, HOP_RUNS, reverse, (int)blockIdx.z);
+    pair_block<VEC, NEAR>(jobs, d, HOP_RUNS, reverse, (int)blockIdx.z);
 }
 
 // The same for a stand-alone call: its descriptors travel as the kernel's argument, so the call allocates and copies
@@ -402,7 +421,7 @@ typedef const __attribute__((address_space(4))) HopPairArg* pair_args_in;
 template <int VEC>
 __global__ __launch_bounds__(kThreads) void pair_mix_args_kernel(HopPairArgs, int64_t d, HOP_RUNS_IN) {
     // the first argument where it lies: a copy indexed by job would go through scratch memory
-    pair_block<VEC>((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), d, HOP_RUNS, 0, (int)blockIdx.z);
+    pair_block<VEC, false>((pair_args_in)__builtin_amdgcn_kernarg_segment_ptr(), d, HOP_RUNS, 0, (int)blockIdx.z);
 }
 
 // float4 per thread and vector, and with it the columns of a chunk.  Long launches: 4, 16 KB of every vector per workgroup
@@ -438,13 +457,23 @@ inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
     return run < 1 ? 1 : run;
 }
 
-// width, runs and grid of a launch over pairs, `front` other workgroups in front
-inline bool pair_grid(int n_jobs, int n_sources, int64_t d, bool margins, int64_t front, int* vec, Runs* runs, dim3* grid,
-                      bool single = false) {
-    *vec = pair_vec(n_jobs, d, margins, single);
-    const int64_t n_chunks = pair_chunks(d, *vec);
-    const int run = pair_run(n_sources, n_chunks, *vec);
-    return run_grid(n_jobs, n_chunks, single && *vec != pair_vec(n_jobs, d, margins) ? 2 * run : run, front, runs, grid);
+// A launch over pairs.  `may_near`: whether the next launches read the results (a stand-alone call waits for them to get out of
+// the L2s instead: 16 jobs x 400 000 columns 34.0 -> 34.9 us); margins: `front` workgroups of them in front; single: sparse margins
+// beside single records.
+struct PairShape {
+    int vec;
+    bool near;
+    Runs runs;
+    dim3 grid;
+};
+inline bool pair_shape(PairShape* p, int n_jobs, int n_sources, int64_t d, bool may_near, bool margins = false, int64_t front = 0,
+                       bool single = false) {
+    p->vec = pair_vec(n_jobs, d, margins, single);
+    p->near = may_near && stays_near(n_jobs, d);
+    const int64_t n_chunks = pair_chunks(d, p->vec);
+    int run = p->near ? 1 : pair_run(n_sources, n_chunks, p->vec);
+    if (!p->near && p->vec != pair_vec(n_jobs, d, margins)) run *= 2;
+    return run_grid(n_jobs, n_chunks, run, front, &p->runs, &p->grid);
 }
 
 // ------------------------------------------------------------------- synthetic gradient ----
@@ -1012,7 +1041,7 @@ __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMix
                                                                     int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
-        mix_block(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
+        mix_block<true>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1253,12 +1282,13 @@ __global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* 
 // x_k, and nothing a wave writes is read inside it, so they need no order between them.  The few
 // latency-bound margin workgroups come first and run under the streaming ones.
 // (`per`: margin workgroups of a record)
+template <bool NEAR>
 __global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                   HOP_RUNS_IN, unsigned margins, int n_mix,
                                                                   const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
                                                                   int loss) {
     if ((int)blockIdx.z >= front) {
-        mix_block(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
+        mix_block<NEAR>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1266,13 +1296,13 @@ __global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJo
 }
 
 // the same two fusions for the paired Reduce + Apply
-template <int VEC>
+template <int VEC, bool NEAR>
 __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                    HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
                                                                    const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
                                                                    int loss) {
     if ((int)blockIdx.z >= front) {
-        pair_block<VEC>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
+        pair_block<VEC, NEAR>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1286,7 +1316,7 @@ __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPa
                                                                     int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
-        pair_block<VEC>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
+        pair_block<VEC, true>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
@@ -1396,13 +1426,6 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float4* __restrict__ dst
         if (i < n16) dst[i] = src[i];
 }
 
-// the widths that pair_vec chooses from: 4, or SHORT
-#define HOP_PAIR_LAUNCH(KERNEL, SHORT, ...)                              \
-    do {                                                                 \
-        if (vec == 4) hipLaunchKernelGGL(KERNEL<4>, __VA_ARGS__);        \
-        else hipLaunchKernelGGL(KERNEL<SHORT>, __VA_ARGS__);             \
-    } while (0)
-
 inline int launch_status() { return (int)hipGetLastError(); }
 
 // workgroups of the scatter of a sparse minibatch, and of its margins
@@ -1425,7 +1448,8 @@ int hopk_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
         Runs runs;
         dim3 grid;
         if (!mix_grid(n, d, 0, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-        hipLaunchKernelGGL(mix_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, HOP_RUNS_OF(runs));
+        const auto kernel = stays_near(n, d, 3) ? mix_kernel<true> : mix_kernel<false>;
+        hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, HOP_RUNS_OF(runs));
         return launch_status();
     });
 }
@@ -1575,17 +1599,14 @@ int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const 
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const bool near = one_xcd(n_grad, B, d);
-    const int64_t margins = near ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
+    const bool one = one_xcd(n_grad, B, d);
+    const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    if (near)
-        hipLaunchKernelGGL(mix_dense_margin_kernel<true>, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
-                           runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, n_grad);
-    else
-        hipLaunchKernelGGL(mix_dense_margin_kernel<false>, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
-                           runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, nseg);
+    const auto kernel = one ? mix_dense_margin_kernel<true> : mix_dense_margin_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front, HOP_RUNS_OF(runs),
+                       (unsigned)margins, n, grad_dev, B, one ? n_grad : nseg);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
@@ -1599,7 +1620,8 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(mix_csr_margin_kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
+    const auto kernel = stays_near(n, d, 3) ? mix_csr_margin_kernel<true> : mix_csr_margin_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
                        runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
@@ -1607,12 +1629,11 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
 
 int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream) {
     return in_parts(jobs_dev, n_jobs, [&](const HopPairJob* jobs, int n) {
-        int vec;
-        Runs runs;
-        dim3 grid;
-        if (!pair_grid(n, n_sources, d, false, 0, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-        HOP_PAIR_LAUNCH(pair_mix_kernel, kPairPlain, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, reverse,
-                        HOP_RUNS_OF(runs));
+        PairShape p;
+        if (!pair_shape(&p, n, n_sources, d, true)) return (int)hipErrorInvalidConfiguration;
+        const auto kernel = p.vec == 4 ? p.near ? pair_mix_kernel<4, true> : pair_mix_kernel<4, false>
+                                       : p.near ? pair_mix_kernel<kPairPlain, true> : pair_mix_kernel<kPairPlain, false>;
+        hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, p.near ? 0 : reverse, HOP_RUNS_OF(p.runs));
         return launch_status();
     });
 }
@@ -1623,13 +1644,14 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
     const int per = csr_margin_blocks(B), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
     const int64_t margins = (int64_t)n_grad * per;
-    int vec;
-    Runs runs;
-    dim3 grid;
+    PairShape p;
     // fewer jobs than gradients: some hold two records
-    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid, n_mix >= n_grad)) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_csr_margin_kernel, kPairMargin, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front,
-                    HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
+    if (!pair_shape(&p, n, n_sources, d, true, true, margins, n_mix >= n_grad)) return (int)hipErrorInvalidConfiguration;
+    const auto kernel = p.vec == 4 ? pair_csr_margin_kernel<4, false>
+                        : p.near   ? pair_csr_margin_kernel<kPairMargin, true>
+                                   : pair_csr_margin_kernel<kPairMargin, false>;
+    hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, p.runs.front, HOP_RUNS_OF(p.runs),
+                       p.near ? 0 : reverse, (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
     if (const int rc = launch_status()) return rc;
     return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
@@ -1639,19 +1661,15 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const bool near = one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
-    const int64_t margins = near ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
-    int vec;
-    Runs runs;
-    dim3 grid;
-    if (!pair_grid(n, n_sources, d, true, margins, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-#define HOP_DENSE_PAIRS(VEC, NEAR, ARG)                                                                                     \
-    hipLaunchKernelGGL((pair_dense_margin_kernel<VEC, NEAR>), grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,      \
-                       runs.front, HOP_RUNS_OF(runs), reverse, (unsigned)margins, n, grad_dev, B, ARG)
-    if (vec == 4) HOP_DENSE_PAIRS(4, false, nseg);
-    else if (near) HOP_DENSE_PAIRS(kPairMargin, true, n_grad);
-    else HOP_DENSE_PAIRS(kPairMargin, false, nseg);
-#undef HOP_DENSE_PAIRS
+    const bool one = one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
+    const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
+    PairShape p;
+    if (!pair_shape(&p, n, n_sources, d, true, true, margins)) return (int)hipErrorInvalidConfiguration;
+    const auto kernel = p.vec == 4 ? pair_dense_margin_kernel<4, false>
+                        : one      ? pair_dense_margin_kernel<kPairMargin, true>
+                                   : pair_dense_margin_kernel<kPairMargin, false>;
+    hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, p.runs.front, HOP_RUNS_OF(p.runs),
+                       p.near ? 0 : reverse, (unsigned)margins, n, grad_dev, B, one ? n_grad : nseg);
     if (const int rc = launch_status()) return rc;
     return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
@@ -1737,11 +1755,10 @@ int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d,
     if (n_jobs > kPairArgs) return (int)hipErrorInvalidValue;
     HopPairArgs args;
     memcpy(args.job, jobs, (size_t)n_jobs * sizeof(HopPairArg));
-    int vec;
-    Runs runs;
-    dim3 grid;
-    if (!pair_grid(n_jobs, n_sources, d, false, 0, &vec, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    HOP_PAIR_LAUNCH(pair_mix_args_kernel, kPairPlain, grid, dim3(kThreads), 0, (hipStream_t)stream, args, d, HOP_RUNS_OF(runs));
+    PairShape p;
+    if (!pair_shape(&p, n_jobs, n_sources, d, false)) return (int)hipErrorInvalidConfiguration;
+    const auto kernel = p.vec == 4 ? pair_mix_args_kernel<4> : pair_mix_args_kernel<kPairPlain>;
+    hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, args, d, HOP_RUNS_OF(p.runs));
     return launch_status();
 }
 

@@ -63,3 +63,31 @@ def test_generator_of_very_long_vectors(d):
             torch.cuda.empty_cache()
     for a, b in zip(*got):
         assert torch.equal(a, b)
+
+
+# Waves that write 32 MB (three times a velocity's share) and a little more, with 1, 2 and 3 columns over a multiple of four:
+# results stored for the L2s or past them, wave by wave, against the pass in one launch, bit for bit
+@pytest.mark.parametrize("d,momentum", [(2097152, 0.0), (2097153, 0.0), (699050, 0.9), (699051, 0.9), (4099, 0.0), (4098, 0.9)])
+@pytest.mark.parametrize("gradient", [hop.HOP_GRAD_ZERO, hop.HOP_GRAD_SYNTH])
+def test_waves_that_stay_near(d, momentum, gradient):
+    from paper_1902_01064_amd.session import Session
+    nb = inputs.ring(4)
+    c = dict(inputs.config(4, d=d, K=6), in_nbrs=nb, W=inputs.uniform_weights(nb), N=4, s=1, b=0, skip_on=False, mult=None,
+             delay_kind=inputs.DELAY_NONE, grad_ahead=1, momentum=momentum)
+    p0 = torch.randn(4, d, generator=torch.Generator(device="cuda").manual_seed(d % 89), device="cuda")
+    got = []
+    print("near", d, momentum, gradient, flush=True)
+    for whole in (True, False):
+        sess = Session(c)
+        try:
+            hop.hop_set_grad_source(sess.ctx, gradient, 1e-3 if gradient == hop.HOP_GRAD_SYNTH else 0.0)
+            sess.set_params(p0)
+            n = sess.simulate().n_waves
+            for _ in range(2):
+                for at in [(0, n)] if whole else [(w, w + 1) for w in range(n)]:
+                    sess.step(*at)
+            sess.sync()
+            got.append(sess.arena[:4 * sess.D * sess.stride].clone())
+        finally:
+            sess.close()
+    assert torch.equal(*got)

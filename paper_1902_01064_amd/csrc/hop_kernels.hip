@@ -1085,7 +1085,10 @@ constexpr int kSegThread = 64;
 // loads instead of two, for minibatches of up to 8 SPLIT rows - was slower: 4 x 1024, B = 64: 364 -> 460 us per pass.)
 // ONE: a row has one segment, and the margins have left the coefficients themselves: one round of loads less in the chain to
 // the rows (4 workers x 1024 columns, B = 64: 360 -> 338 us a pass).
-template <int SPLIT, int WIDE, bool ONE>
+// LAST: rows by non-temporal loads, so that of what the margins left in the L2s what is yet to be read stays longest.  In a run the
+// next wave has other rows (8 workers x 30 011 columns, log loss, 1769 -> 1700 us per pass, 64 x 12 000 1680 -> 1590; hinge, half of
+// the rows, the same); a stand-alone call may be followed by one on the same (128 x 65536 26.0 -> 27.1 with it).
+template <int SPLIT, int WIDE, bool ONE, bool LAST>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
     __shared__ float coefS[kMaxB];
@@ -1178,7 +1181,7 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
             }
         }
     };
-    if (n == 4) add_rows([&](const float* x) { return ldu4(x, c); });
+    if (n == 4) add_rows([&](const float* x) { return LAST ? ldu4_stream(x, c) : ldu4(x, c); });
     else if (n > 0) add_rows([&](const float* x) { return ldu4(x, c, n); });     // the end of a vector, d mod 4 columns left
     if constexpr (SPLIT > 1) {                     // join the shares: ((part 0 + part 1) + part 2) + ...
         if (part > 0) joinS[(part - 1) * kCols + col] = acc;
@@ -1210,7 +1213,7 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const Hop
                                                                 int64_t d, int nseg, float lambda, int loss,
                                                                 int64_t n_chunks) {
     const int64_t chunk = grid_chunk(width);
-    if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
+    if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE, true>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
 }
 
 // each XCD a slice of the columns: a grid of (8, jobs, chunks of the longest slice)
@@ -1219,24 +1222,24 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_slice_kernel(con
                                                                              int64_t d, float lambda, int loss) {
     const int chunk = slice_begin(n_chunks, (int)blockIdx.x) + (int)blockIdx.z;
     if (chunk < slice_begin(n_chunks, (int)blockIdx.x + 1))
-        dense_grad_chunk<SPLIT, WIDE, false>(jobs + blockIdx.y, B, d, kXcd, lambda, loss, chunk);
+        dense_grad_chunk<SPLIT, WIDE, false, true>(jobs + blockIdx.y, B, d, kXcd, lambda, loss, chunk);
 }
 
 // each job on one XCD: a grid of (8, chunks, jobs / 8)
 __global__ __launch_bounds__(512) void dense_grad_near_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B, int64_t d,
                                                               float lambda, int loss) {
     const int job = (int)(blockIdx.z * kXcd + blockIdx.x);
-    if (job < n_jobs) dense_grad_chunk<8, 1, true>(jobs + job, B, d, 1, lambda, loss, blockIdx.y);
+    if (job < n_jobs) dense_grad_chunk<8, 1, true, false>(jobs + job, B, d, 1, lambda, loss, blockIdx.y);
 }
 
 __global__ __launch_bounds__(512) void dense_grad_near_one(const HopGradJob job, int B, int64_t d, float lambda, int loss) {
-    if (blockIdx.x == 0) dense_grad_chunk<8, 1, true>(&job, B, d, 1, lambda, loss, blockIdx.y);
+    if (blockIdx.x == 0) dense_grad_chunk<8, 1, true, false>(&job, B, d, 1, lambda, loss, blockIdx.y);
 }
 
 template <int SPLIT, int WIDE, bool ONE>
 __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGradJob job, int B, int64_t d, int nseg, float lambda,
                                                              int loss) {
-    dense_grad_chunk<SPLIT, WIDE, ONE>(&job, B, d, nseg, lambda, loss, blockIdx.x);
+    dense_grad_chunk<SPLIT, WIDE, ONE, false>(&job, B, d, nseg, lambda, loss, blockIdx.x);
 }
 
 // ------------------------------------------------------------------- CSR SVM: margins ----

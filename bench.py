@@ -335,7 +335,7 @@ def main():
         us = grad["ms"] * 1e3 / n_g
         out["roofline"] = r = {
             "bound": "hbm",
-            "kernel": ("dense_margin_kernel + dense_grad_kernel (one group per wave)" if c["batch"] * c["d"] * 4 > (2 << 20)
+            "kernel": ("dense_margin_kernel + dense_grad_kernel (one group per wave)" if c["batch"] * c["d"] * 4 > (2 << 20) or c["d"] > 11264
                        else "pair_dense_margin_kernel + dense_grad_kernel (one group per wave; bound by launches)"),
             "achieved": grad["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": grad["GBps"] / HBM_PEAK_GBS,
             "traffic": None, "launches": grad["launches"], "avg_launch_us": us,

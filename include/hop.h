@@ -264,8 +264,8 @@ int hop_schedule_bind(hop_ctx* ctx, hop_schedule* s, void* workspace, size_t byt
 
 /* Enqueues waves [wave_begin, wave_end) of the schedule: per wave the gradient kernels of its STEP
  * records (Compute on x_k, Section 3.2), then one fused Reduce + Apply launch over all its records.
- * Variations by gradient source: with CSR data, and with dense minibatches of up to 2 MB per record, the
- * margins ride in the Reduce launch and the gradient is applied to the results right after it (scattered,
+ * Variations by gradient source: with CSR data, and with dense minibatches of up to 2 MB and 11264
+ * columns, the margins ride in the Reduce launch and the gradient is applied to the results right after it (scattered,
  * or in place); with larger dense minibatches the gradient kernel itself reduces and applies its record,
  * and the Reduce launch only holds the records without a gradient; synthetic gradients of up to
  * hop_opts.grad_ahead consecutive waves are generated in front of the first of them.  A call that covers the

@@ -531,7 +531,7 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
                              hipMemcpyHostToDevice));
         HOP_HIP(c, hipMemset(s->coef_dev, 0, (size_t)R * B * sizeof(float)));
     }
-    // dense minibatches of up to 2 MB per record take the margins-beside-the-Reduce path of launch_waves (measured:
+    // dense minibatches of up to 2 MB per record, and not in slices, take the margins-beside-the-Reduce path of launch_waves (measured:
     // 0.65 -> 0.51 ms per pass at 256 KB per record; at 32 MB the margin pass wants a launch of its own for occupancy)
     s->dense_in_place = mode == HOP_GRAD_SVM_DENSE && !hop_dense_slices(B, c->d) && (int64_t)B * c->d * 4 <= kDenseInPlaceBytes;
     // Larger dense minibatches: margins, then a gradient kernel that also does the Reduce + Apply of its record

@@ -1129,11 +1129,17 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
             if (timed && (rc = prof_end(c))) return rc;
             continue;
         } else if (ng > 0 && mode == HOP_GRAD_SVM_DENSE) {
-            // Large minibatches: margins, then gradient + Reduce + Apply of the same records in one kernel.
+            // Large minibatches: margins, then gradient + Reduce + Apply of the same records in one kernel.  In slices the
+            // Reduce of the wave's jumps rides in the margins' launch, unless it is to be timed by itself.
+            const bool jumps = pj && nj > 0 && !timed && hop_dense_slices(B, c->d);
             if (timed && (rc = prof_begin(c, HOP_KERNEL_GRAD, s->wave_grad_bytes[w]))) return rc;
-            HOP_LAUNCH(c, hopk_dense_margin(gj, ng, B, c->d, stream));
+            if (jumps)
+                HOP_LAUNCH(c, hopk_pair_dense_margin(pj, np, s->wave_sources[w], w & 1, c->d, gj, ng, B, stream));
+            else
+                HOP_LAUNCH(c, hopk_dense_margin(gj, ng, B, c->d, stream));
             HOP_LAUNCH(c, hopk_dense_grad(gj, ng, B, c->d, c->opts.lambda, c->opts.loss, stream));
             if (timed && (rc = prof_end(c))) return rc;
+            if (jumps) continue;
         }
         if (nj == 0) continue;                         // every record of the wave was finished by its gradient kernel
         const bool csr = ng > 0 && mode == HOP_GRAD_SVM_CSR;

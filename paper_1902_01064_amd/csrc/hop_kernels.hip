@@ -364,17 +364,9 @@ __device__ __forceinline__ void pair_tile_wide(Job job, int64_t first4, int64_t 
     }
 }
 
-// Work of one workgroup in round `round` of the chunks.
-// Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
+// One chunk of a job.  Job: const HopPairJob*, or HopPairArg in the kernel's argument segment.
 template <int VEC, bool NEAR, class Job>
-__device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs, int reverse, int round) {
-    const int ahead = run_chunk(runs, round);
-    if (ahead < 0) return;
-    // consecutive launches walk the vectors in opposite directions: what the previous kernels wrote or read last
-    // is still in the memory-side cache when the next launch begins there (1453 -> 1430 us per launch with the
-    // gradient generator in between, 386 -> 381 us between launches of small waves)
-    const int chunk = reverse ? runs.n_chunks - 1 - ahead : ahead;
-    const Job job = jobs + blockIdx.y;
+__device__ __forceinline__ void pair_chunk(Job job, int64_t d, int n_chunks, int chunk) {
     const int64_t n4 = d >> 2;
     const int64_t first4 = (int64_t)chunk * (kThreads * VEC);
     const bool full = first4 + kThreads * VEC <= n4;
@@ -391,7 +383,7 @@ __device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs
     }
 #undef HOP_PAIR_CASE
     // the d mod 4 trailing columns, one thread each, by the workgroup of the last chunk
-    if (chunk == runs.n_chunks - 1) {
+    if (chunk == n_chunks - 1) {
         const int64_t c = (n4 << 2) + (threadIdx.x & 3);
         const int r = threadIdx.x >> 2;
         if (threadIdx.x < 8 && r < job->G && c < d) {
@@ -402,6 +394,17 @@ __device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs
             job->out[r][c] = acc;
         }
     }
+}
+
+// Work of one workgroup in round `round` of the chunks.
+template <int VEC, bool NEAR, class Job>
+__device__ __forceinline__ void pair_block(Job jobs, int64_t d, const Runs& runs, int reverse, int round) {
+    const int ahead = run_chunk(runs, round);
+    if (ahead < 0) return;
+    // consecutive launches walk the vectors in opposite directions: what the previous kernels wrote or read last
+    // is still in the memory-side cache when the next launch begins there (1453 -> 1430 us per launch with the
+    // gradient generator in between, 386 -> 381 us between launches of small waves)
+    pair_chunk<VEC, NEAR>(jobs + blockIdx.y, d, runs.n_chunks, reverse ? runs.n_chunks - 1 - ahead : ahead);
 }
 
 template <int VEC, bool NEAR>
@@ -1328,6 +1331,22 @@ __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPa
     else dense_margin_block(grad_jobs, B, d, n, b, red);
 }
 
+// Margins in slices and the Reduce of the wave's records without a gradient (jumps) behind them in one launch (us per pass
+// with skipping, jumps in a launch of their own before: 16 workers x 12 000 columns, B = 32, 621 -> 566, 16 x 65536, B = 128, 3331 ->
+// 3288).  grid: (8, groups of rows, records, then what the chunks need).
+template <int ROWS, bool STREAM>
+__global__ __launch_bounds__(kThreads) void pair_dense_slice_kernel(const HopGradJob* __restrict__ grad_jobs, int64_t d, int B, int n_grad,
+                                                                    int groups, int n_chunks, int n_mix,
+                                                                    const HopPairJob* __restrict__ mix_jobs) {
+    __shared__ float red[ROWS][kThreads / 64];
+    if ((int)blockIdx.z < n_grad) {
+        dense_margin_rows<ROWS, STREAM, Cut::slices>(grad_jobs + blockIdx.z, B, d, kXcd, (int)blockIdx.x, (int)blockIdx.y * ROWS, red);
+        return;
+    }
+    const unsigned b = ((blockIdx.z - n_grad) * groups + blockIdx.y) * kXcd + blockIdx.x, job = b / (unsigned)n_chunks;
+    if (job < (unsigned)n_mix) pair_chunk<kPairMargin, false>(mix_jobs + job, d, n_chunks, (int)(b % (unsigned)n_chunks));
+}
+
 // target[col] += factor * c_m * val for the active rows (the sparse part of -eta g, or of g).
 // One wavefront per minibatch row, 16 rows per workgroup, all in flight together.  Sparse features
 // are heavy-tailed (a few columns occur in almost every row) and fp32 atomics on one address
@@ -1663,6 +1682,23 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
+    if (hop_dense_slices(B, d)) {                      // large minibatches: the records without a gradient
+        const bool few = (int64_t)n_grad * ((B + kMarginRows - 1) / kMarginRows) * kXcd < kMarginFew;
+        const int groups = few ? B : (B + kSliceRows - 1) / kSliceRows;
+        const int64_t n_chunks = pair_chunks(d, kPairMargin), round = (int64_t)groups * kXcd;
+        const int64_t z = n_grad + (n_mix * n_chunks + round - 1) / round;
+        if (z > kMaxGridYZ || z * round > 0x7FFFFFFFll) {
+            const int rc = hopk_dense_margin(grad_dev, n_grad, B, d, stream);
+            return rc ? rc : hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
+        }
+        const bool near = (int64_t)n_grad * B * d * 4 <= kMarginNear;
+        const auto kernel = few    ? pair_dense_slice_kernel<1, false>
+                            : near ? pair_dense_slice_kernel<kSliceRows, false>
+                                   : pair_dense_slice_kernel<kSliceRows, true>;
+        hipLaunchKernelGGL(kernel, dim3(kXcd, (unsigned)groups, (unsigned)z), dim3(kThreads), 0, (hipStream_t)stream, grad_dev, d, B, n_grad,
+                           groups, (int)n_chunks, n_mix, mix_dev);
+        return launch_status();
+    }
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
     const bool one = one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
     const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;

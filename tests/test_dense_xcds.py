@@ -52,3 +52,35 @@ def test_wave(N, d, B, momentum):
             assert bool(((got - (acc - 0.5 * g)).abs() <= room).all())
     finally:
         sess.close()
+
+
+# Jumps: their Reduce in the margins' launch (one row a workgroup, two, and two past the caches) against a launch of its own, which
+# a profiled pass makes; the chunks of 1024 columns of a jump end with 1, 2 and 0 columns over a multiple of four
+@pytest.mark.parametrize("d,B", [(12001, 8), (30002, 100), (131072, 128)])
+def test_jumps_beside_the_margins(d, B):
+    nb = inputs.ring(16)
+    mult = [1.0] * 16
+    mult[3] = 4.0
+    c = dict(inputs.config(1, d=d, rows=130, K=10), in_nbrs=nb, W=inputs.uniform_weights(nb), N=16, s=2, b=0, batch=B, loss=1, lam=0.25,
+             skip_on=True, mult=mult, delay_kind=inputs.DELAY_NONE)
+    ws = inputs.hidden_w(6, d, "cuda")
+    data = [inputs.dense_svm_data(6, i, 130, d, ws, "cuda") for i in range(16)]
+    p0 = torch.randn(16, d, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda") / d ** 0.5
+    got = []
+    print("jumps", d, B, flush=True)
+    for timed in (False, True):
+        sess = Session(c)
+        try:
+            sess.set_dense([x for x, _ in data], [y for _, y in data])
+            sess.set_params(p0)
+            s = sess.simulate()
+            with_both = {int(s.wave[e]) for e in range(s.n_records) if int(s.kind[e]) == hop.HOP_JUMP} & {
+                int(s.wave[e]) for e in range(s.n_records) if int(s.kind[e]) == hop.HOP_STEP}
+            assert with_both
+            hop.hop_profile(sess.ctx, int(timed))
+            sess.step()
+            sess.sync()
+            got.append(sess.arena[:16 * sess.D * sess.stride].clone())
+        finally:
+            sess.close()
+    assert torch.equal(*got)

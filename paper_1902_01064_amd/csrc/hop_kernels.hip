@@ -1246,14 +1246,21 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGra
 }
 
 // ------------------------------------------------------------------- CSR SVM: margins ----
-// One wavefront per (job, minibatch row): gather w[col], reduce across the 64 lanes.  Blocks of a job come in multiples of 32,
-// dealt out to the XCDs one by one: the four blocks of rows that one workgroup of the scatter takes run on the XCD where it will
-// run, so it finds their row pointers, columns and values in that XCD's L2, or some of them (16 workers x 2^20 columns, B = 256:
-// 6870 -> 6761 us per pass).
-__device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int block) {
+// One wavefront per (job, minibatch row): gather w[col], reduce across the 64 lanes.  Workgroups are dealt out to the XCDs one
+// by one: the four blocks of rows that one workgroup of the scatter takes run on the XCD where it will run, so it finds their
+// row pointers, columns and values in that XCD's L2, or some of them (16 workers x 2^20 columns, B = 256: 6870 -> 6761 us per
+// pass).  Workgroup b of the margins belongs to workgroup csr_margin_group(b) of the scatter, counted over all records.  In waves of
+// few records each has whole turns of the XCDs (its first rows on the XCD whose L2 holds what the last wave wrote of the first
+// columns, which nearly every row reads); filled up like that beyond kCsrTurns workgroups, idle ones cost more than it brings.  us
+// per pass, filled up and not, 20 000 columns: 16 workers, Exp(1), B = 1 176 / 191, with a velocity 173 / 189; lock-step, B = 8, 16
+// workers 57.6 / 58.2, 32 (256 workgroups) 64.3 / 62.3, 40 71.6 / 64.0, 64 95.5 / 73.2, 64 with B = 64 110 / 86.
+constexpr int64_t kCsrTurns = 256;      // workgroups of the scatter
+__device__ __forceinline__ unsigned csr_margin_group(unsigned b) { return b / (4 * kXcd) * kXcd + b % kXcd; }
+
+// its rows: of the scatter's workgroup `group` of this record
+__device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int group, unsigned b) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int group = block / (4 * kXcd) * kXcd + block % kXcd;        // of the scatter's 16 rows
-    const int m = (group * 4 + block / kXcd % 4) * (kThreads / 64) + wv;
+    const int m = (group * 4 + (int)(b / kXcd % 4)) * (kThreads / 64) + wv;
     if (m >= B) return;
     const int r = job->rows[m];
     const int64_t lo = job->rowptr[r], hi = job->rowptr[r + 1];
@@ -1269,7 +1276,7 @@ __device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ j
 __global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJob job, int B, int64_t d, float lambda,
                                                                  int loss, int margin_blocks) {
     if ((int)blockIdx.x < margin_blocks) {
-        csr_margin_rows(&job, B, loss, (int)blockIdx.x);
+        csr_margin_rows(&job, B, loss, (int)csr_margin_group(blockIdx.x), blockIdx.x);
         return;
     }
     const int64_t c = ((int64_t)(blockIdx.x - margin_blocks) * kThreads + threadIdx.x) * 4;
@@ -1280,39 +1287,47 @@ __global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJo
     }
 }
 
-__global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int loss) {
-    csr_margin_rows(jobs + blockIdx.y, B, loss, (int)blockIdx.x);
+// workgroup b of the margins of n_jobs records, `per` workgroups of the scatter each
+__device__ __forceinline__ void csr_margin_block(const HopGradJob* __restrict__ jobs, unsigned n_jobs, int B, unsigned per, int loss,
+                                                 unsigned b) {
+    const unsigned at = csr_margin_group(b), job = at / per;
+    if (job < n_jobs) csr_margin_rows(jobs + job, B, loss, (int)(at % per), b);
+}
+
+__global__ __launch_bounds__(kThreads) void csr_margin_kernel(const HopGradJob* __restrict__ jobs, int n_jobs, int B, unsigned per,
+                                                              int loss) {
+    csr_margin_block(jobs, (unsigned)n_jobs, B, per, loss, blockIdx.x);
 }
 
 // The margins of a wave's STEP records and the wave's Reduce + Apply in one launch: both only read
 // x_k, and nothing a wave writes is read inside it, so they need no order between them.  The few
 // latency-bound margin workgroups come first and run under the streaming ones.
-// (`per`: margin workgroups of a record)
+// (n_grad records of `per` workgroups of the scatter)
 template <bool NEAR>
 __global__ __launch_bounds__(kThreads) void mix_csr_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                   HOP_RUNS_IN, unsigned margins, int n_mix,
-                                                                  const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
-                                                                  int loss) {
+                                                                  const HopGradJob* __restrict__ grad_jobs, int n_grad, int B,
+                                                                  unsigned per, int loss) {
     if ((int)blockIdx.z >= front) {
         mix_block<NEAR>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
-    if (b < margins) csr_margin_rows(grad_jobs + b / per, B, loss, (int)(b % per));
+    if (b < margins) csr_margin_block(grad_jobs, (unsigned)n_grad, B, per, loss, b);
 }
 
 // the same two fusions for the paired Reduce + Apply
 template <int VEC, bool NEAR>
 __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                    HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
-                                                                   const HopGradJob* __restrict__ grad_jobs, int B, unsigned per,
-                                                                   int loss) {
+                                                                   const HopGradJob* __restrict__ grad_jobs, int n_grad, int B,
+                                                                   unsigned per, int loss) {
     if ((int)blockIdx.z >= front) {
         pair_block<VEC, NEAR>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
-    if (b < margins) csr_margin_rows(grad_jobs + b / per, B, loss, (int)(b % per));
+    if (b < margins) csr_margin_block(grad_jobs, (unsigned)n_grad, B, per, loss, b);
 }
 
 template <int VEC, bool NEAR>
@@ -1450,10 +1465,15 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(float4* __restrict__ dst
 
 inline int launch_status() { return (int)hipGetLastError(); }
 
-// workgroups of the scatter of a sparse minibatch, and of its margins
+// workgroups of the scatter of a sparse minibatch, and of the margins of n of them
 static_assert(kScatterRows == 4 * (kThreads / 64), "four blocks of margins are one of the scatter");
-inline int csr_scatter_blocks(int B) { return (B + kScatterRows * kXcd - 1) / (kScatterRows * kXcd) * kXcd; }
-inline int csr_margin_blocks(int B) { return 4 * csr_scatter_blocks(B); }
+inline int csr_scatter_blocks(int n_jobs, int B) {
+    const int rows = (B + kScatterRows - 1) / kScatterRows, turns = (rows + kXcd - 1) / kXcd * kXcd;
+    return (int64_t)n_jobs * turns <= kCsrTurns ? turns : rows;
+}
+inline int64_t csr_margin_blocks(int n_jobs, int B) {
+    return 4 * (((int64_t)n_jobs * csr_scatter_blocks(n_jobs, B) + kXcd - 1) / kXcd * kXcd);
+}
 
 }  // namespace
 
@@ -1605,11 +1625,11 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
 
 int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
-    return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
-        hipLaunchKernelGGL(csr_margin_kernel, dim3((unsigned)csr_margin_blocks(B), (unsigned)n), dim3(kThreads), 0, (hipStream_t)stream,
-                           jobs, B, loss);
-        return launch_status();
-    });
+    const int64_t blocks = csr_margin_blocks(n_jobs, B);
+    if (blocks > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(csr_margin_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, (hipStream_t)stream, jobs_dev, n_jobs, B,
+                       (unsigned)csr_scatter_blocks(n_jobs, B), loss);
+    return launch_status();
 }
 
 // workgroups of margins that keep to one XCD a record
@@ -1637,14 +1657,14 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
                         int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
-    const int per = csr_margin_blocks(B), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const int64_t margins = (int64_t)n_grad * per;
+    const int n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = csr_margin_blocks(n_grad, B);
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
     const auto kernel = stays_near(n, d, 3) ? mix_csr_margin_kernel<true> : mix_csr_margin_kernel<false>;
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
-                       runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
+                       runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, n_grad, B, (unsigned)csr_scatter_blocks(n_grad, B), loss);
     if (const int rc = launch_status()) return rc;
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
@@ -1664,8 +1684,8 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
                          const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
-    const int per = csr_margin_blocks(B), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const int64_t margins = (int64_t)n_grad * per;
+    const int n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
+    const int64_t margins = csr_margin_blocks(n_grad, B);
     PairShape p;
     // fewer jobs than gradients: some hold two records
     if (!pair_shape(&p, n, n_sources, d, true, true, margins, n_mix >= n_grad)) return (int)hipErrorInvalidConfiguration;
@@ -1673,7 +1693,7 @@ int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, in
                         : p.near   ? pair_csr_margin_kernel<kPairMargin, true>
                                    : pair_csr_margin_kernel<kPairMargin, false>;
     hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, p.runs.front, HOP_RUNS_OF(p.runs),
-                       p.near ? 0 : reverse, (unsigned)margins, n, grad_dev, B, (unsigned)per, loss);
+                       p.near ? 0 : reverse, (unsigned)margins, n, grad_dev, n_grad, B, (unsigned)csr_scatter_blocks(n_grad, B), loss);
     if (const int rc = launch_status()) return rc;
     return hopk_pair(mix_dev + n, n_mix - n, n_sources, reverse, d, stream);
 }
@@ -1715,7 +1735,7 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
 
 int hopk_csr_scatter(const HopGradJob* jobs_dev, int n_jobs, int B, float factor, int into_velocity, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
-    const int per = csr_scatter_blocks(B);
+    const int per = csr_scatter_blocks(n_jobs, B);
     if ((int64_t)n_jobs * per > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
     return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
         const dim3 grid((unsigned)per, (unsigned)n), threads(kScatterThreads);
@@ -1765,7 +1785,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
         else
             hipLaunchKernelGGL((dense_grad_one<1, 4, false>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
-        const int margin_blocks = csr_margin_blocks(B);
+        const int margin_blocks = (int)csr_margin_blocks(1, B);
         const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;
         if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         const uintptr_t w0 = (uintptr_t)job.w, g0 = (uintptr_t)job.out, bytes = (uintptr_t)d * sizeof(float);
@@ -1779,7 +1799,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
                                margin_blocks);
         }
         if (const int rc = launch_status()) return rc;
-        hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)csr_scatter_blocks(B)), dim3(kScatterThreads), 0,
+        hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)csr_scatter_blocks(1, B)), dim3(kScatterThreads), 0,
                            st, job, B, -1.0f);
     } else {
         const int64_t n = ((d >> 2) + kSynthChunk4 - 1) / kSynthChunk4, n_chunks = n < 1 ? 1 : n;

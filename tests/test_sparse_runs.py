@@ -73,3 +73,48 @@ def test_whole_pass_as_in_parts(graphed, ahead):
     finally:
         for sess in both:
             sess.close()
+
+
+# Rows of a workgroup of the scatter (16), its four blocks of margins (4 rows), and their number over a wave's records around the
+# multiples of the XCDs: every coefficient is that of its own row, and the results are the records' sums
+@pytest.mark.parametrize("N,B", [(1, 1), (1, 129), (3, 5), (7, 16), (8, 17), (9, 32), (16, 4), (16, 33), (64, 1), (64, 8), (64, 15)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_margins_of_small_minibatches(N, B, momentum):
+    d = 3001
+    nb = [[]] if N == 1 else inputs.ring(N)
+    c = dict(inputs.config(3, d=d, rows=300, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
+             lr=0.5, momentum=momentum, skip_on=False, mult=None, delay_kind=inputs.DELAY_NONE)
+    data = [_data(100 + i, 300, d) for i in range(N)]
+    p0 = torch.randn(N, d, generator=torch.Generator(device="cuda").manual_seed(8), device="cuda") / 8
+    print("small minibatches", N, B, momentum, flush=True)
+    sess = Session(c)
+    try:
+        sess.set_csr(data)
+        sess.set_params(p0)
+        s = sess.simulate()
+        assert s.n_waves == 1 and s.n_records == N
+        sess.step()
+        sess.sync()
+        for e in range(N):
+            i, ids = int(s.worker[e]), s.batch_rows[e]
+            rowptr, col, val, y = data[i]
+            w, X = p0[i].double(), torch.zeros(B, d, dtype=torch.float64, device="cuda")
+            ends = rowptr.cpu().numpy()
+            for m, r in enumerate(ids):
+                X[m, col[ends[r]:ends[r + 1]].long()] = val[ends[r]:ends[r + 1]].double()
+            t = y[torch.from_numpy(ids.copy()).cuda().long()].double()
+            coef = torch.from_numpy(sess.coef(e)).cuda().double()
+            # the slope of a coefficient in its margin is at most 1 / 4 B; a sum of up to 130 products is off by 131 * 2^-24 of them
+            off = 131 * 2.0 ** -24 * (X.abs() @ w.abs())
+            want = t / (B * (1 + torch.exp(t * (X @ w))))
+            assert bool(((coef - want).abs() <= (0.25 * off + 1e-6) / B).all())
+            mag = 0.25 * w.abs() + coef.abs() @ X.abs()
+            acc = -0.5 * (0.25 * w - coef @ X)
+            size = torch.zeros_like(acc)
+            for a in range(int(s.src_begin[e]), int(s.src_begin[e + 1])):
+                x = float(s.src_weight[a]) * p0[int(s.src_worker[a])].double()
+                acc, size = acc + x, size + x.abs()
+            got = sess.slot(i, int(s.out_slot[e])).double()
+            assert bool(((got - acc).abs() <= 2.0 ** -24 * (0.5 * (B + 4) * mag + 8 * size)).all())
+    finally:
+        sess.close()

@@ -534,6 +534,14 @@ int build_jobs(hop_ctx* c, hop_schedule* s) {
     // dense minibatches of up to 2 MB per record, and not in slices, take the margins-beside-the-Reduce path of launch_waves (measured:
     // 0.65 -> 0.51 ms per pass at 256 KB per record; at 32 MB the margin pass wants a launch of its own for occupancy)
     s->dense_in_place = mode == HOP_GRAD_SVM_DENSE && !hop_dense_slices(B, c->d) && (int64_t)B * c->d * 4 <= kDenseInPlaceBytes;
+    if (mode == HOP_GRAD_SVM_DENSE) {
+        int64_t least = INT64_MAX, all = 0;
+        for (const HopData& dd : c->data) {
+            least = std::min(least, dd.rows);
+            all += dd.rows;
+        }
+        s->dense_rows_again = hop_rows_again(B, least, all * c->d * (int64_t)sizeof(float));
+    }
     // Larger dense minibatches: margins, then a gradient kernel that also does the Reduce + Apply of its record
     // (the time is the rows'; a separate mix launch of a few hundred KB per record would only add its start-up,
     // measured 4 us + gap per wave at 16 workers x 65536 columns).  The wave's mix then only holds the records
@@ -1125,7 +1133,7 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
                 HOP_LAUNCH(c, hopk_pair_dense_margin(pj, np, s->wave_sources[w], w & 1, c->d, gj, ng, B, stream));
             else
                 HOP_LAUNCH(c, hopk_mix_dense_margin(s->mix_dev + jb, nj, c->d, gj, ng, B, stream));
-            HOP_LAUNCH(c, hopk_dense_grad(gj, ng, B, c->d, c->opts.lambda, c->opts.loss, stream));
+            HOP_LAUNCH(c, hopk_dense_grad(gj, ng, B, c->d, c->opts.lambda, c->opts.loss, s->dense_rows_again, stream));
             if (timed && (rc = prof_end(c))) return rc;
             continue;
         } else if (ng > 0 && mode == HOP_GRAD_SVM_DENSE) {
@@ -1137,7 +1145,7 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
                 HOP_LAUNCH(c, hopk_pair_dense_margin(pj, np, s->wave_sources[w], w & 1, c->d, gj, ng, B, stream));
             else
                 HOP_LAUNCH(c, hopk_dense_margin(gj, ng, B, c->d, stream));
-            HOP_LAUNCH(c, hopk_dense_grad(gj, ng, B, c->d, c->opts.lambda, c->opts.loss, stream));
+            HOP_LAUNCH(c, hopk_dense_grad(gj, ng, B, c->d, c->opts.lambda, c->opts.loss, s->dense_rows_again, stream));
             if (timed && (rc = prof_end(c))) return rc;
             if (jumps) continue;
         }

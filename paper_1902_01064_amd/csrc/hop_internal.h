@@ -151,7 +151,6 @@ int hop_pack_pairs(const HopMixJob* jobs, int n, std::vector<HopPairJob>& out);
 int hopk_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream);
 int hopk_synth(const HopGradJob* jobs_dev, int n_jobs, int reverse, int64_t d, void* stream);
 int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, void* stream);
-int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, void* stream);
 int hopk_csr_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int loss, void* stream);
 int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const HopGradJob* grad_dev, int n_grad, int B,
                           void* stream);
@@ -173,8 +172,12 @@ __attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
 // one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out), the Reduce of up to kPairArgs jobs: descriptors on the host
 __attribute__((weak)) int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream);
 __attribute__((weak)) int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream);
+// rows_again: later waves read the same rows while a cache may still hold them (hop_rows_again)
+__attribute__((weak)) int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, bool rows_again,
+                                          void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
+constexpr int64_t kMemorySideCache = 256ll << 20;
 constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce
 // Whether the columns of a wave's dense minibatches are dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in
 // the worker's gradient buffer, which dense passes have no other use for.  us per pass of 4 / 16 / 64 workers without and with:
@@ -184,6 +187,17 @@ constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to whi
 // 1384, B = 128, d = 5000 163 / 484 / 1253 -> 161 / 498 / 1384.  Above, a slice would be more than a segment.
 inline bool hop_dense_slices(int B, int64_t d) {
     return d <= 8 * 16384 && 8 * (int64_t)B <= d && d > ((int64_t)B * d * 4 > kDenseInPlaceBytes ? 7168 : 11264);
+}
+
+// Whether the second and last reading of a record's rows, by its gradient kernel in slices, leaves them in the caches.  Non-temporal
+// loads there keep more of what is yet to be read in the L2s (us per pass, log loss, 32 minibatches of data: 8 workers x 20 000 columns,
+// B = 128, 262 -> 236; 16 x 65536, B = 64, 790 -> 745), but the next waves then find less of rows that come again: where all data sets
+// fit the memory-side cache (160 rows: 8 x 20 000, B = 128, 176 -> 188; 16 x 12 000 294 -> 307), or each holds at most two minibatches
+// (128 rows: 16 x 65536, B = 64, 628 -> 680).  With four: 16 x 65536, B = 64, 685 -> 702, 8 x 30 011, B = 100, 406 -> 389.
+// Not in slices rows are always read by ordinary loads: 2 x 131 073, B = 64, 128 and 2048 rows 255 -> 220, 278 -> 278; 1 x 600,
+// B = 1024, 32 768 rows 257 -> 201; 7 x 6283, B = 194, 1552 rows 238 -> 222.
+inline bool hop_rows_again(int B, int64_t least_rows, int64_t all_bytes) {
+    return least_rows <= 2 * (int64_t)B || all_bytes <= kMemorySideCache;
 }
 
 // ---- host-side random numbers (hop_sim.cpp) ---------------------------------------
@@ -218,6 +232,7 @@ struct hop_schedule {
     int32_t* rows_dev = nullptr;        // n_records x batch
     float* coef_dev = nullptr;          // n_records x batch
     bool dense_in_place = false;        // dense SVM: margins beside the Reduce, gradient applied in place
+    bool dense_rows_again = false;      // dense SVM: its minibatches come from few or small data, see hop_rows_again
     std::vector<int32_t> grad_begin;    // n_waves + 1 offsets into grad_dev
     std::vector<int32_t> pair_begin;    // n_waves + 1 offsets into pair_dev
     std::vector<int32_t> wave_sources;  // distinct vectors each wave reads

@@ -1088,9 +1088,7 @@ constexpr int kSegThread = 64;
 // loads instead of two, for minibatches of up to 8 SPLIT rows - was slower: 4 x 1024, B = 64: 364 -> 460 us per pass.)
 // ONE: a row has one segment, and the margins have left the coefficients themselves: one round of loads less in the chain to
 // the rows (4 workers x 1024 columns, B = 64: 360 -> 338 us a pass).
-// LAST: rows by non-temporal loads, so that of what the margins left in the L2s what is yet to be read stays longest.  In a run the
-// next wave has other rows (8 workers x 30 011 columns, log loss, 1769 -> 1700 us per pass, 64 x 12 000 1680 -> 1590; hinge, half of
-// the rows, the same); a stand-alone call may be followed by one on the same (128 x 65536 26.0 -> 27.1 with it).
+// LAST: rows by non-temporal loads, so that of what the margins left in the L2s what is yet to be read stays longest (hop_rows_again).
 template <int SPLIT, int WIDE, bool ONE, bool LAST>
 __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ job, int B, int64_t d, int nseg, float lambda,
                                                  int loss, int64_t chunk) {
@@ -1216,16 +1214,16 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_kernel(const Hop
                                                                 int64_t d, int nseg, float lambda, int loss,
                                                                 int64_t n_chunks) {
     const int64_t chunk = grid_chunk(width);
-    if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE, true>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
+    if (chunk < n_chunks) dense_grad_chunk<SPLIT, WIDE, ONE, false>(jobs + blockIdx.y, B, d, nseg, lambda, loss, chunk);
 }
 
 // each XCD a slice of the columns: a grid of (8, jobs, chunks of the longest slice)
-template <int SPLIT, int WIDE>
+template <int SPLIT, int WIDE, bool LAST>
 __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_slice_kernel(const HopGradJob* __restrict__ jobs, int n_chunks, int B,
                                                                              int64_t d, float lambda, int loss) {
     const int chunk = slice_begin(n_chunks, (int)blockIdx.x) + (int)blockIdx.z;
     if (chunk < slice_begin(n_chunks, (int)blockIdx.x + 1))
-        dense_grad_chunk<SPLIT, WIDE, false, true>(jobs + blockIdx.y, B, d, kXcd, lambda, loss, chunk);
+        dense_grad_chunk<SPLIT, WIDE, false, LAST>(jobs + blockIdx.y, B, d, kXcd, lambda, loss, chunk);
 }
 
 // each job on one XCD: a grid of (8, chunks, jobs / 8)
@@ -1581,8 +1579,7 @@ static bool one_xcd(int n_jobs, int B, int64_t d) {
     return d <= kOneXcdCols && (int64_t)B * d * 4 <= kOneXcdBytes && grad_shape(n_jobs, d, 1) == GradShape::few;
 }
 
-int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss,
-                    void* stream) {
+int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, bool rows_again, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
     const int nseg = hopk_dense_nseg(d);
@@ -1596,13 +1593,11 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
         return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
             const int cols = shape == GradShape::many ? 1024 : 256, n_chunks = (int)((d + cols - 1) / cols);
             const dim3 grid(kXcd, (unsigned)n, (unsigned)((n_chunks + kXcd - 1) / kXcd));
-#define HOP_SLICES(SPLIT, WIDE)                                                                                             \
-    hipLaunchKernelGGL((dense_grad_slice_kernel<SPLIT, WIDE>), grid, dim3(64 * SPLIT * WIDE), 0, (hipStream_t)stream, jobs,  \
-                       n_chunks, B, d, lambda, loss)
-            if (shape == GradShape::few) HOP_SLICES(8, 1);
-            else if (shape == GradShape::some) HOP_SLICES(4, 1);
-            else HOP_SLICES(1, 4);
-#undef HOP_SLICES
+            const auto kernel = shape == GradShape::few    ? rows_again ? dense_grad_slice_kernel<8, 1, false> : dense_grad_slice_kernel<8, 1, true>
+                                : shape == GradShape::some ? rows_again ? dense_grad_slice_kernel<4, 1, false> : dense_grad_slice_kernel<4, 1, true>
+                                                           : rows_again ? dense_grad_slice_kernel<1, 4, false> : dense_grad_slice_kernel<1, 4, true>;
+            hipLaunchKernelGGL(kernel, grid, dim3(shape == GradShape::few ? 512 : 256), 0, (hipStream_t)stream, jobs, n_chunks, B, d, lambda,
+                               loss);
             return launch_status();
         });
     const int64_t cols = shape == GradShape::many ? 1024 : 256, n_chunks = (d + cols - 1) / cols;

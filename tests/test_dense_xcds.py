@@ -19,13 +19,26 @@ pytestmark = pytest.mark.gpu
                                    (2, 131073, 16), (2, 8192, 1024), (2, 8191, 1024), (1, 11521, 3), (20, 12001, 50), (48, 12001, 17)])
 @pytest.mark.parametrize("momentum", [0.0, 0.9])
 def test_wave(N, d, B, momentum):
+    _check_wave(N, d, B, momentum, 70)
+
+
+# Data sets that do not fit the memory-side cache and hold more than two minibatches: rows of slices read past the caches, with 8 and
+# 4 wavefronts a chunk and with chunks of 1024 columns; ends of rows of 1, 2 and 0 columns over a multiple of four
+@pytest.mark.parametrize("N,d,B,rows", [(1, 131072, 16, 520), (2, 100001, 16, 340), (5, 131070, 20, 110)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_wave_of_large_data(N, d, B, rows, momentum):
+    assert rows > 2 * B and N * d * rows * 4 > 256 << 20
+    _check_wave(N, d, B, momentum, rows)
+
+
+def _check_wave(N, d, B, momentum, rows):
     nb = [[]] if N == 1 else inputs.ring(N)
-    c = dict(inputs.config(1, d=d, rows=70, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
+    c = dict(inputs.config(1, d=d, rows=rows, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
              lr=0.5, momentum=momentum, skip_on=False, mult=None, delay_kind=inputs.DELAY_NONE)
     ws = inputs.hidden_w(6, d, "cuda")
-    data = [inputs.dense_svm_data(6, i, 70, d, ws, "cuda") for i in range(N)]
+    data = [inputs.dense_svm_data(6, i, rows, d, ws, "cuda") for i in range(N)]
     p0 = torch.randn(N, d, generator=torch.Generator(device="cuda").manual_seed(4), device="cuda") / d ** 0.5
-    print("XCDs", N, d, B, momentum, flush=True)
+    print("XCDs", N, d, B, momentum, rows, flush=True)
     sess = Session(c)
     try:
         sess.set_dense([x for x, _ in data], [y for _, y in data])

@@ -1,0 +1,37 @@
+"""What a pass launches and the rules behind it, on the CPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"), reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("launches") / "launch_driver")
+    csrc = os.path.join(ROOT, "paper_1902_01064_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
+                    "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                    os.path.join(ROOT, "tests", "launch_driver.cpp"), os.path.join(csrc, "hop_api.cpp"),
+                    os.path.join(csrc, "hop_sim.cpp"), "-o", exe], check=True)
+
+    def run(*what):
+        env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0:verify_asan_link_order=0")
+        out = subprocess.run([exe] + [str(w) for w in what], capture_output=True, text=True, env=env, timeout=120)
+        assert out.returncode == 0, out.stdout[-2000:] + out.stderr[-4000:]
+        lines = [line.split() for line in out.stdout.splitlines()]
+        return [(name, dict(a.split("=") for a in rest)) for name, *rest in lines]
+    return run
+
+
+# 4 workers x 16384 columns are 256 KB a row of each data set: 1024 rows of all of them are the memory-side cache's 256 MB; two
+# minibatches of 600 rows are more than that
+@pytest.mark.parametrize("rows,batch,again", [(1024, 64, 1), (1025, 64, 0), (1200, 600, 1), (1201, 600, 0)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_rows_that_come_again(launches, rows, batch, again, momentum):
+    got = [a["rows_again"] for name, a in launches("dense", 4, 16384, batch, rows, momentum) if name == "dense_grad"]
+    assert got == [str(again)] * 2

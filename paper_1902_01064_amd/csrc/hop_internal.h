@@ -189,6 +189,26 @@ inline bool hop_dense_slices(int B, int64_t d) {
     return d <= 8 * 16384 && 8 * (int64_t)B <= d && d > ((int64_t)B * d * 4 > kDenseInPlaceBytes ? 7168 : 11264);
 }
 
+// Whether a wave's dense minibatches keep to one XCD each: up to kOneXcdBytes of rows of kOneXcdCols columns in launches of few column
+// chunks.  us per pass of 4 / 16 / 64 workers, all XCDs -> one: B = 64, d = 1024 108 / 326 / 543 -> 101 / 301 / 485; B = 200,
+// d = 1024 151 / 435 / 892 -> 145 / 401 / 781; B = 128, d = 4096 (2 MB, half of an L2) 142 / 436 / 1039 -> 141 / 427 / 999; B = 32, d = 8000
+// 150 / 410 / 898 -> 153 / 402 / 863; but B = 32, d = 10 000 143 / 412 / 938 -> 147 / 423 / 914, d = 16 000 167 / 549 / 1231 -> 182 /
+// 593 / 1236: an XCD is busy with some 32 chunks of 256 columns of a record.  Waves of up to five records at 7500 to 8192 columns: hinge
+// loss 4 % slower on one, log loss 1 to 20 % faster.
+// With one or two records most XCDs idle while one reads all rows.  12 iterations of 1 worker, hinge / log loss, 1000 columns: B = 100
+// 78 / 87 -> 73 / 82, B = 200 89 / 107 -> 90 / 106, B = 240 94 / 115 -> 101 / 120, B = 400 119 / 154 -> 133 / 160; of 2 workers: B = 200 100 /
+// 121 -> 99 / 112, B = 240, 2048 columns 112 / 133 -> 121 / 137, B = 400 136 / 166 -> 142 / 165; of 3: B = 400 142 / 171 -> 146 / 168, of 4:
+// 157 / 184 -> 150 / 170.
+constexpr int64_t kOneXcdBytes = 2 << 20, kOneXcdCols = 8192, kGradFew = 768;
+constexpr int kOneXcdRows = 200;
+inline bool hop_one_xcd(int n_jobs, int B, int64_t d) {
+    return d <= kOneXcdCols && (int64_t)B * d * 4 <= kOneXcdBytes && n_jobs * ((d + 255) / 256) <= kGradFew && (n_jobs > 2 || B <= kOneXcdRows);
+}
+// A stand-alone call, whose margins have a launch of their own, takes one XCD with any number of rows.  us, all XCDs -> one, rows warm / cold:
+// B = 64, d = 1024 8.6 / 7.7 -> 7.9 / 7.0, B = 128, d = 4096 8.5 / 7.6 -> 8.1 / 7.5, B = 64, d = 8192 8.6 / 7.4 -> 8.0 / 7.3, with synchronisation
+// (B = 32, d = 8000) 18.1 / 19.3 -> 16.8 / 18.2; up to 512 columns B = 300 to 500 4 to 6 % faster, 600 to 1000 the same within 2 %.
+inline bool hop_one_xcd_alone(int B, int64_t d) { return d <= kOneXcdCols && (int64_t)B * d * 4 <= kOneXcdBytes; }
+
 // Whether the second and last reading of a record's rows, by its gradient kernel in slices, leaves them in the caches.  Non-temporal
 // loads there keep more of what is yet to be read in the L2s (us per pass, log loss, 32 minibatches of data: 8 workers x 20 000 columns,
 // B = 128, 262 -> 236; 16 x 65536, B = 64, 790 -> 745), but the next waves then find less of rows that come again: where all data sets

@@ -968,13 +968,8 @@ __device__ __forceinline__ void dense_margin_rows(const HopGradJob* __restrict__
     }
 }
 
-// Small minibatches keep to one XCD: all margins of a record run on XCD (record mod 8) and so does its gradient, which finds
-// rows and coefficients in that XCD's L2.  Up to kOneXcdBytes of rows of kOneXcdCols columns; us per pass of 4 / 16 / 64 workers,
-// all XCDs -> one: B = 64, d = 1024 108 / 326 / 543 -> 101 / 301 / 485; B = 200, d = 1024 151 / 435 / 892 -> 145 / 401 / 781;
-// B = 128, d = 4096 (2 MB, half of an L2) 142 / 436 / 1039 -> 141 / 427 / 999; B = 32, d = 8000 150 / 410 / 898 -> 153 / 402 / 863;
-// but B = 32, d = 10 000 143 / 412 / 938 -> 147 / 423 / 914, d = 16 000 167 / 549 / 1231 -> 182 / 593 / 1236: an XCD is busy with
-// some 32 chunks of 256 columns of a record.
-constexpr int64_t kOneXcdBytes = 2 << 20, kOneXcdCols = 8192;
+// Small minibatches keep to one XCD (hop_one_xcd): all margins of a record run on XCD (record mod 8) and so does its gradient, which
+// finds rows and coefficients in that XCD's L2.
 static_assert(kOneXcdCols <= kSegCols, "rows of one segment");
 
 // one workgroup per (job, minibatch row), the job on one XCD; b: its index, in launches with other workgroups
@@ -1021,7 +1016,7 @@ __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob
 // The kernels whose name ends in _one are for stand-alone calls: the descriptor is the kernel's argument, nothing is
 // allocated, copied or staged.  Per call: 128 x 65536 dense 42.5 -> 28.4 us, 64 x 1024 without allocation 10.4 -> 7.7 us
 // (one launch fewer), 256 samples of 64 non-zeros on 2^20 columns 33.0 -> 18.6 us (margins beside the dense part).
-// every eighth workgroup: the call keeps to one XCD (kOneXcdBytes)
+// every eighth workgroup: the call keeps to one XCD (hop_one_xcd_alone)
 __global__ __launch_bounds__(kThreads) void dense_margin_near_one(const HopGradJob job, int B, int64_t d) {
     __shared__ float red[1][kThreads / 64];
     if (blockIdx.x == 0) dense_margin_rows<1, false, Cut::one>(&job, B, d, 1, 0, (int)blockIdx.y, red);
@@ -1076,7 +1071,7 @@ constexpr int kRowUnroll = 8;
 // the split gives.  SPLIT = WIDE = 4, 1 against 1, 4: one gradient of 2^20 columns, B = 128: 238 / 210 us, 4 M columns
 // 1564 / 962, 2^24 columns and B = 64 10.8 / 3.2 ms; a pass of 16 workers x 400 000 columns, B = 16: 1943 / 1487 us; of
 // 64 x 65536, B = 128, 13 records a wave: 3973 / 3813 us; the other way round 64 x 16384, B = 128: 1461 / 1543 us.
-constexpr int64_t kGradFew = 768;                      // chunks of 256 columns up to which a launch takes 8 wavefronts for each
+// kGradFew: chunks of 256 columns up to which a launch takes 8 wavefronts for each
 constexpr int64_t kGradMany = 2048;                    // over that many, or
 constexpr int kGradSegs = 16;                          // from that many partial products per row on: 1024 columns, rows whole
 // From 65 partial products per row on a wavefront sums them up, not a thread: 4 M columns, B = 1 and 128: 54 -> 20,
@@ -1574,17 +1569,12 @@ static GradShape grad_shape(int n_jobs, int64_t d, int nseg) {
     return chunks > kGradMany || nseg >= kGradSegs ? GradShape::many : chunks > kGradFew ? GradShape::some : GradShape::few;
 }
 
-// see kOneXcdBytes; with few column chunks, as a wave of so small minibatches has
-static bool one_xcd(int n_jobs, int B, int64_t d) {
-    return d <= kOneXcdCols && (int64_t)B * d * 4 <= kOneXcdBytes && grad_shape(n_jobs, d, 1) == GradShape::few;
-}
-
 int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, bool rows_again, void* stream) {
     if (n_jobs <= 0 || B <= 0) return 0;
     if (B > kMaxB) return (int)hipErrorInvalidValue;
     const int nseg = hopk_dense_nseg(d);
     const GradShape shape = grad_shape(n_jobs, d, nseg);
-    if (one_xcd(n_jobs, B, d)) {
+    if (hop_one_xcd(n_jobs, B, d)) {
         const dim3 grid(kXcd, (unsigned)((d + 255) / 256), (unsigned)((n_jobs + kXcd - 1) / kXcd));
         hipLaunchKernelGGL(dense_grad_near_kernel, grid, dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B, d, lambda, loss);
         return launch_status();
@@ -1636,7 +1626,7 @@ int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const 
     if (n_grad <= 0 || B <= 0) return hopk_mix(mix_dev, n_mix, d, stream);
     if (n_mix <= 0) return hopk_dense_margin(grad_dev, n_grad, B, d, stream);
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const bool one = one_xcd(n_grad, B, d);
+    const bool one = hop_one_xcd(n_grad, B, d);
     const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     Runs runs;
     dim3 grid;
@@ -1715,7 +1705,7 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
         return launch_status();
     }
     const int nseg = hopk_dense_nseg(d), n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
-    const bool one = one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
+    const bool one = hop_one_xcd(n_grad, B, d) && pair_vec(n, d, true) == kPairMargin;
     const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     PairShape p;
     if (!pair_shape(&p, n, n_sources, d, true, true, margins)) return (int)hipErrorInvalidConfiguration;
@@ -1752,7 +1742,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
         if (B > kMaxB) return (int)hipErrorInvalidValue;
         if (grid > 0x7FFFFFFFll || (d + 255) / 256 > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         const dim3 threads(kThreads), rows((unsigned)few), groups((unsigned)grid);
-        if (one_xcd(1, B, d)) {
+        if (hop_one_xcd_alone(B, d)) {
             hipLaunchKernelGGL(dense_margin_near_one, dim3(kXcd, (unsigned)B), threads, 0, st, job, B, d);
             if (const int rc = launch_status()) return rc;
             hipLaunchKernelGGL(dense_grad_near_one, dim3(kXcd, (unsigned)((d + 255) / 256)), dim3(512), 0, st, job, B, d, lambda, loss);

@@ -1,5 +1,6 @@
 // What a pass launches, on the CPU: hop_api.cpp with a HIP runtime of plain memory and launchers that print their arguments.
 //   launch_driver dense|csr|external WORKERS COLUMNS BATCH ROWS MOMENTUM
+//   launch_driver rules RECORDS COLUMNS BATCH
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -70,6 +71,12 @@ static void* aligned(std::vector<char>& m, size_t n) {
 }
 
 int main(int argc, char** argv) {
+    if (argc == 5) {
+        const int n = std::atoi(argv[2]), B = std::atoi(argv[4]);
+        const int64_t d = std::atoll(argv[3]);
+        std::printf("rules one_xcd=%d one_xcd_alone=%d\n", hop_one_xcd(n, B, d), hop_one_xcd_alone(B, d));
+        return 0;
+    }
     if (argc != 7) return 2;
     const std::string model = argv[1];
     const int N = std::atoi(argv[2]), B = std::atoi(argv[4]);

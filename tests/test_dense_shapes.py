@@ -92,3 +92,10 @@ def test_samples_that_are_not_finite(d, B, loss):
     mag = 1e-3 * np.abs(w.numpy()) + np.abs(cg[part]) @ np.abs(X.numpy()[part].astype(np.float64))
     # an fp32 sum of B + 1 products is within (B + 3) 2^-24 of the sum of magnitudes
     assert np.all(np.abs(got[1:] - ref[1:]) <= (B + 3) * 2.0 ** -24 * mag[1:])
+
+
+# a call of up to 2 MB keeps to one XCD
+@pytest.mark.parametrize("loss", ["hinge", "log"])
+@pytest.mark.parametrize("d,B", [(511, 1024), (513, 1024), (61, 769), (1024, 512), (1024, 513)])
+def test_dense_gradient_of_many_rows(d, B, loss):
+    test_dense_gradient_at_the_edges(d, B, 0, loss)

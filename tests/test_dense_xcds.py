@@ -31,6 +31,13 @@ def test_wave_of_large_data(N, d, B, rows, momentum):
     _check_wave(N, d, B, momentum, rows)
 
 
+# Many rows: one or two records on all XCDs, three on one each
+@pytest.mark.parametrize("N,d,B", [(1, 1000, 200), (1, 1000, 201), (2, 513, 200), (2, 513, 201), (2, 512, 1024), (3, 510, 201)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_wave_of_many_rows(N, d, B, momentum):
+    _check_wave(N, d, B, momentum, 70)
+
+
 def _check_wave(N, d, B, momentum, rows):
     nb = [[]] if N == 1 else inputs.ring(N)
     c = dict(inputs.config(1, d=d, rows=rows, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,

@@ -35,3 +35,11 @@ def launches(tmp_path_factory):
 def test_rows_that_come_again(launches, rows, batch, again, momentum):
     got = [a["rows_again"] for name, a in launches("dense", 4, 16384, batch, rows, momentum) if name == "dense_grad"]
     assert got == [str(again)] * 2
+
+
+# One XCD a record: 2 MB, 8192 columns, 768 chunks; one or two records of a wave only with up to 200 rows
+@pytest.mark.parametrize("n,d,B,one,alone", [
+    (1, 1024, 64, 1, 1), (1, 1024, 200, 1, 1), (2, 1024, 201, 0, 1), (1, 512, 1024, 0, 1), (3, 512, 1024, 1, 1),
+    (4, 8192, 64, 1, 1), (4, 8193, 63, 0, 0), (4, 4096, 129, 0, 0), (48, 4096, 5, 1, 1), (49, 4096, 5, 0, 1)])
+def test_one_xcd(launches, n, d, B, one, alone):
+    assert launches("rules", n, d, B) == [("rules", dict(one_xcd=str(one), one_xcd_alone=str(alone)))]

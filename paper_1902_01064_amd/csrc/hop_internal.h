@@ -179,7 +179,7 @@ int hopk_dense_nseg(int64_t d);                 // column segments per row in th
 
 constexpr int64_t kMemorySideCache = 256ll << 20;
 constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce
-// Whether the columns of a wave's dense minibatches are dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in
+// Whether the columns of a pass's dense minibatches may be dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in
 // the worker's gradient buffer, which dense passes have no other use for.  us per pass of 4 / 16 / 64 workers without and with:
 // B = 64, d = 12 000 211 / 699 / 1863 -> 179 / 585 / 1630; B = 64, d = 20 000 260 / 979 / 3132 -> 216 / 746 / 2421; B = 128, d = 65 536
 // 556 / 2130 / 9528 -> 495 / 1964 / 9350.  Below, against margins beside the Reduce: B = 32, d = 10 000 143 / 412 / 938 -> 149 / 417 / 964,
@@ -187,6 +187,17 @@ constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to whi
 // 1384, B = 128, d = 5000 163 / 484 / 1253 -> 161 / 498 / 1384.  Above, a slice would be more than a segment.
 inline bool hop_dense_slices(int B, int64_t d) {
     return d <= 8 * 16384 && 8 * (int64_t)B <= d && d > ((int64_t)B * d * 4 > kDenseInPlaceBytes ? 7168 : 11264);
+}
+
+// Whether a wave of such minibatches is.  The more rows it has, the less of them the L2s hold until the gradient reads them again, and
+// every workgroup of the gradient adds up 8 partial products a row, where rows of one segment have their coefficients worked out.
+// us per pass, in slices -> in segments, log loss, rows of a wave = records x B: 7200 columns: 32 x 100 221 -> 239, 32 x 160 364 -> 339,
+// 16 x 400 390 -> 337 (with a velocity); 8700: 8 x 400 391 -> 422, 64 x 64 383 -> 358, 32 x 800 2847 -> 2423; 10 000: 32 x 100 281 -> 304, 64 x 64
+// 420 -> 405, 8 x 600 632 -> 601; 12 000: 16 x 300 388 -> 391, 32 x 300 1269 -> 1217; 13 000: 64 x 64 488 -> 496, 100 x 100 1154 -> 1124; 16 000: 64 x
+// 100 807 -> 846, 32 x 200 1082 -> 1141, 32 x 600 3203 -> 3111; 24 000 (two segments): 32 x 600 4652 -> 4915.
+inline bool hop_wave_slices(int n_jobs, int B, int64_t d) {
+    const int64_t rows = (int64_t)n_jobs * B;
+    return hop_dense_slices(B, d) && rows <= (d <= 11264 ? 3500 : d <= 14336 ? 6000 : INT64_MAX);
 }
 
 // Whether a wave's dense minibatches keep to one XCD each: up to kOneXcdBytes of rows of kOneXcdCols columns in launches of few column

@@ -903,7 +903,7 @@ constexpr int64_t kSegCols = (int64_t)kSeg4 * 4;
 // ROWS minibatch rows from m0 on against one load of w; thread t < ROWS of the workgroup writes the partial of row m0 + t,
 // or, where a row has one segment only, its coefficient: the gradient kernel then has that to load and nothing to work out
 // (the label's load under the row's; see dense_grad_chunk).  Each row is summed in the same order whatever ROWS is.
-// How a row is cut up: segments of kSegCols columns, one such segment, or a slice for each XCD (hop_dense_slices), whose margins
+// How a row is cut up: segments of kSegCols columns, one such segment, or a slice for each XCD (hop_wave_slices), whose margins
 // and gradient run there: the gradient finds in that XCD's L2 what the margins have read, as much as fits.
 enum class Cut { segments, one, slices };
 // first of n_chunks chunks that belong to slice s
@@ -1536,7 +1536,7 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
     const int64_t blocks = (int64_t)n_jobs * groups * nseg;
     if (blocks > 0x7FFFFFFFll || B > kMaxB) return (int)hipErrorInvalidConfiguration;
     const bool near = (int64_t)n_jobs * B * d * 4 <= kMarginNear;
-    if (hop_dense_slices(B, d))
+    if (hop_wave_slices(n_jobs, B, d))
         return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
             const dim3 rows(kXcd, (unsigned)B, (unsigned)n), pairs(kXcd, (unsigned)((B + kSliceRows - 1) / kSliceRows), (unsigned)n);
 #define HOP_SLICES(GRID, ROWS, STREAM)                                                                                      \
@@ -1579,7 +1579,7 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
         hipLaunchKernelGGL(dense_grad_near_kernel, grid, dim3(512), 0, (hipStream_t)stream, jobs_dev, n_jobs, B, d, lambda, loss);
         return launch_status();
     }
-    if (hop_dense_slices(B, d))
+    if (hop_wave_slices(n_jobs, B, d))
         return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
             const int cols = shape == GradShape::many ? 1024 : 256, n_chunks = (int)((d + cols - 1) / cols);
             const dim3 grid(kXcd, (unsigned)n, (unsigned)((n_chunks + kXcd - 1) / kXcd));
@@ -1692,7 +1692,7 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
         const int groups = few ? B : (B + kSliceRows - 1) / kSliceRows;
         const int64_t n_chunks = pair_chunks(d, kPairMargin), round = (int64_t)groups * kXcd;
         const int64_t z = n_grad + (n_mix * n_chunks + round - 1) / round;
-        if (z > kMaxGridYZ || z * round > 0x7FFFFFFFll) {
+        if (!hop_wave_slices(n_grad, B, d) || z > kMaxGridYZ || z * round > 0x7FFFFFFFll) {
             const int rc = hopk_dense_margin(grad_dev, n_grad, B, d, stream);
             return rc ? rc : hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
         }

@@ -38,6 +38,13 @@ def test_wave_of_many_rows(N, d, B, momentum):
     _check_wave(N, d, B, momentum, 70)
 
 
+# Waves at the number of rows up to which they go in slices, and beyond it
+@pytest.mark.parametrize("N,d,B", [(4, 8001, 875), (4, 8001, 876), (35, 7170, 100), (36, 7171, 100), (12, 11266, 501)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_wave_of_many_rows_in_slices(N, d, B, momentum):
+    _check_wave(N, d, B, momentum, 70)
+
+
 def _check_wave(N, d, B, momentum, rows):
     nb = [[]] if N == 1 else inputs.ring(N)
     c = dict(inputs.config(1, d=d, rows=rows, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,
@@ -76,7 +83,7 @@ def _check_wave(N, d, B, momentum, rows):
 
 # Jumps: their Reduce in the margins' launch (one row a workgroup, two, and two past the caches) against a launch of its own, which
 # a profiled pass makes; the chunks of 1024 columns of a jump end with 1, 2 and 0 columns over a multiple of four
-@pytest.mark.parametrize("d,B", [(12001, 8), (30002, 100), (131072, 128)])
+@pytest.mark.parametrize("d,B", [(12001, 8), (30002, 100), (131072, 128), (8001, 500)])
 def test_jumps_beside_the_margins(d, B):
     nb = inputs.ring(16)
     mult = [1.0] * 16

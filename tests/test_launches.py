@@ -42,4 +42,14 @@ def test_rows_that_come_again(launches, rows, batch, again, momentum):
     (1, 1024, 64, 1, 1), (1, 1024, 200, 1, 1), (2, 1024, 201, 0, 1), (1, 512, 1024, 0, 1), (3, 512, 1024, 1, 1),
     (4, 8192, 64, 1, 1), (4, 8193, 63, 0, 0), (4, 4096, 129, 0, 0), (48, 4096, 5, 1, 1), (49, 4096, 5, 0, 1)])
 def test_one_xcd(launches, n, d, B, one, alone):
-    assert launches("rules", n, d, B) == [("rules", dict(one_xcd=str(one), one_xcd_alone=str(alone)))]
+    (_, got), = launches("rules", n, d, B)
+    assert (got["one_xcd"], got["one_xcd_alone"]) == (str(one), str(alone))
+
+
+# Slices: of a pass by its rows, of a wave by how many of them it has, where a row is one segment of the other form
+@pytest.mark.parametrize("n,d,B,of_pass,of_wave", [
+    (35, 7169, 100, 1, 1), (36, 11264, 100, 1, 0), (4, 11264, 875, 1, 1), (4, 11264, 876, 1, 0), (60, 11265, 100, 1, 1), (61, 14336, 100, 1, 0),
+    (61, 14337, 100, 1, 1), (1000, 131072, 1024, 1, 1), (1, 131073, 64, 0, 0), (1, 7168, 100, 0, 0), (2, 8191, 1024, 0, 0)])
+def test_slices(launches, n, d, B, of_pass, of_wave):
+    (_, got), = launches("rules", n, d, B)
+    assert (got["slices"], got["wave_slices"]) == (str(of_pass), str(of_wave))

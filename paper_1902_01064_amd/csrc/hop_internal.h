@@ -224,7 +224,10 @@ inline bool hop_one_xcd_alone(int B, int64_t d) { return d <= kOneXcdCols && (in
 // loads there keep more of what is yet to be read in the L2s (us per pass, log loss, 32 minibatches of data: 8 workers x 20 000 columns,
 // B = 128, 262 -> 236; 16 x 65536, B = 64, 790 -> 745), but the next waves then find less of rows that come again: where all data sets
 // fit the memory-side cache (160 rows: 8 x 20 000, B = 128, 176 -> 188; 16 x 12 000 294 -> 307), or each holds at most two minibatches
-// (128 rows: 16 x 65536, B = 64, 628 -> 680).  With four: 16 x 65536, B = 64, 685 -> 702, 8 x 30 011, B = 100, 406 -> 389.
+// (128 rows: 16 x 65536, B = 64, 628 -> 680).  With four: 16 x 65536, B = 64, 685 -> 702, 8 x 30 011, B = 100, 406 -> 389.  Waves whose rows
+// the L2s hold find them there anyway (8 x 11 500, two and six minibatches: 18 MB 98 -> 97 and 108 -> 105, 22 MB 112 -> 110 and 121 -> 117, 30 MB
+// 128 -> 133 and 140 -> 142; 76 sizes of 6 to 22 MB 0.3 % faster past the caches, 16 of 30 MB 1.6 % slower, 36 MB 4 %).
+constexpr int64_t kRowsNear = 24ll << 20;       // bytes of rows of a wave
 // Not in slices rows are always read by ordinary loads: 2 x 131 073, B = 64, 128 and 2048 rows 255 -> 220, 278 -> 278; 1 x 600,
 // B = 1024, 32 768 rows 257 -> 201; 7 x 6283, B = 194, 1552 rows 238 -> 222.
 inline bool hop_rows_again(int B, int64_t least_rows, int64_t all_bytes) {

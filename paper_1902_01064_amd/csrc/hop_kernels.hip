@@ -1583,9 +1583,10 @@ int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, fl
         return in_parts(jobs_dev, n_jobs, [&](const HopGradJob* jobs, int n) {
             const int cols = shape == GradShape::many ? 1024 : 256, n_chunks = (int)((d + cols - 1) / cols);
             const dim3 grid(kXcd, (unsigned)n, (unsigned)((n_chunks + kXcd - 1) / kXcd));
-            const auto kernel = shape == GradShape::few    ? rows_again ? dense_grad_slice_kernel<8, 1, false> : dense_grad_slice_kernel<8, 1, true>
-                                : shape == GradShape::some ? rows_again ? dense_grad_slice_kernel<4, 1, false> : dense_grad_slice_kernel<4, 1, true>
-                                                           : rows_again ? dense_grad_slice_kernel<1, 4, false> : dense_grad_slice_kernel<1, 4, true>;
+            const bool cached = rows_again && (int64_t)n_jobs * B * d * 4 > kRowsNear;
+            const auto kernel = shape == GradShape::few    ? cached ? dense_grad_slice_kernel<8, 1, false> : dense_grad_slice_kernel<8, 1, true>
+                                : shape == GradShape::some ? cached ? dense_grad_slice_kernel<4, 1, false> : dense_grad_slice_kernel<4, 1, true>
+                                                           : cached ? dense_grad_slice_kernel<1, 4, false> : dense_grad_slice_kernel<1, 4, true>;
             hipLaunchKernelGGL(kernel, grid, dim3(shape == GradShape::few ? 512 : 256), 0, (hipStream_t)stream, jobs, n_chunks, B, d, lambda,
                                loss);
             return launch_status();

@@ -177,6 +177,19 @@ __attribute__((weak)) int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs
                                           void* stream);
 int hopk_dense_nseg(int64_t d);                 // column segments per row in the margin pass
 
+// ---- rules of a launch ---------------------------------------------------------------
+// Vectors that the next launches find in the L2s: where the jobs of a launch come to no more than the 32 MB of all of them, results are
+// stored like any other data (else non-temporally, so that they push nothing out), and a chunk of columns goes to the same XCD in
+// every launch: runs of one chunk, always from the front.  us, without and with: a pass of 16 workers x 300 000 columns, sparse,
+// 373 / 312; 16 x 2^20 (18 MB a wave) 2733 / 2500; wave by wave with external gradients 16 x 300 000 253 / 204, 32 x 150 000 322 / 257.
+// Beyond, records that run singly: 16 x 4 M 1370 / 1440, 32 x 2 M (72 MB a wave) 1613 / 1665.  A pair counts once, so waves of pairs stay
+// up to 64 MB: lock-step rings, tori and rings with chords of 4 to 64 workers that write 34 to 63 MB, 24 sizes each: external gradients
+// 404 / 368 (4 workers, 34 MB) to 739 / 668 (64, 63 MB), sparse 404 / 309 (16, 34 MB) to 747 / 542 (64, 63 MB).
+constexpr int64_t kNearBytes = 32ll << 20;
+// `vectors` that go with a job: with a velocity its own share is written and read between, which counts as three (16 x 300 000,
+// sparse, 419 / 402; 64 x 500 000 1357 / 1375).
+inline bool hop_stays_near(int n_jobs, int64_t d, int vectors = 1) { return vectors * n_jobs * d * (int64_t)sizeof(float) <= kNearBytes; }
+
 constexpr int64_t kMemorySideCache = 256ll << 20;
 constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce
 // Whether the columns of a pass's dense minibatches may be dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in

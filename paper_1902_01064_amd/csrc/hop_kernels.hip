@@ -74,7 +74,7 @@ __device__ __forceinline__ void st4_stream(float* p, int64_t i4, float4 v) {
     vf4 t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, (gvec_out)p + i4);
 }
-// NEAR: see kNearBytes (a template argument: of a run-time choice the compiler makes one store, without the hint)
+// NEAR: see hop_stays_near (a template argument: of a run-time choice the compiler makes one store, without the hint)
 template <bool NEAR>
 __device__ __forceinline__ void st4_once(float* p, int64_t i4, float4 v) {
     if (NEAR) st4(p, i4, v);
@@ -101,16 +101,6 @@ inline bool chunk_grid(int n_jobs, int64_t n_chunks, dim3* grid) {
 }
 // chunk of this workgroup of such a grid (`width`: its x); it may lie past the last one
 __device__ __forceinline__ int64_t grid_chunk(int width) { return (int64_t)blockIdx.z * width + blockIdx.x; }
-
-// Vectors that the next launches find in the L2s: where a launch writes no more than the 32 MB of all of them, results are
-// stored like any other data (else non-temporally, so that they push nothing out), and a chunk of columns goes to the same XCD in
-// every launch: runs of one chunk, always from the front.  us, without and with: a pass of 16 workers x 300 000 columns, sparse,
-// 373 / 312; 16 x 2^20 (18 MB a wave) 2733 / 2500; wave by wave with external gradients 16 x 300 000 253 / 204, 32 x 150 000 322 / 257.
-// Beyond: 16 x 4 M 1370 / 1440, 32 x 2 M (72 MB a wave) 1613 / 1665.
-constexpr int64_t kNearBytes = 32ll << 20;
-// `vectors` that a job writes: with a velocity its own share is written and read between, which counts as three (16 x 300 000,
-// sparse, 419 / 402; 64 x 500 000 1357 / 1375).
-inline bool stays_near(int n_jobs, int64_t d, int vectors = 1) { return vectors * n_jobs * d * (int64_t)sizeof(float) <= kNearBytes; }
 
 // Rounds in which every XCD takes a run of consecutive chunks: longer contiguous pieces of every stream are in flight at a
 // time.  The last, partly filled round is dealt out evenly (shorter runs on all XCDs, not full runs on the first few).
@@ -244,7 +234,7 @@ __device__ __forceinline__ void mix_block(const HopMixJob* __restrict__ jobs, in
 // 12 M 4912 -> 4868), 4 on shorter ones (8: 32 x 50 000 columns 170.5 -> 171.9)
 inline bool mix_grid(int n_jobs, int64_t d, int64_t front, Runs* runs, dim3* grid) {
     const int64_t n4 = d >> 2, n_chunks = n4 > kThreads ? (n4 + kThreads - 1) / kThreads : 1;
-    return run_grid(n_jobs, n_chunks, stays_near(n_jobs, d, 3) ? 1 : n4 >= (1 << 20) ? 32 : 4, front, runs, grid);
+    return run_grid(n_jobs, n_chunks, hop_stays_near(n_jobs, d, 3) ? 1 : n4 >= (1 << 20) ? 32 : 4, front, runs, grid);
 }
 
 template <bool NEAR>
@@ -472,7 +462,7 @@ struct PairShape {
 inline bool pair_shape(PairShape* p, int n_jobs, int n_sources, int64_t d, bool may_near, bool margins = false, int64_t front = 0,
                        bool single = false) {
     p->vec = pair_vec(n_jobs, d, margins, single);
-    p->near = may_near && stays_near(n_jobs, d);
+    p->near = may_near && hop_stays_near(n_jobs, d);
     const int64_t n_chunks = pair_chunks(d, p->vec);
     int run = p->near ? 1 : pair_run(n_sources, n_chunks, p->vec);
     if (!p->near && p->vec != pair_vec(n_jobs, d, margins)) run *= 2;
@@ -1483,7 +1473,7 @@ int hopk_mix(const HopMixJob* jobs_dev, int n_jobs, int64_t d, void* stream) {
         Runs runs;
         dim3 grid;
         if (!mix_grid(n, d, 0, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-        const auto kernel = stays_near(n, d, 3) ? mix_kernel<true> : mix_kernel<false>;
+        const auto kernel = hop_stays_near(n, d, 3) ? mix_kernel<true> : mix_kernel<false>;
         hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, HOP_RUNS_OF(runs));
         return launch_status();
     });
@@ -1648,7 +1638,7 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    const auto kernel = stays_near(n, d, 3) ? mix_csr_margin_kernel<true> : mix_csr_margin_kernel<false>;
+    const auto kernel = hop_stays_near(n, d, 3) ? mix_csr_margin_kernel<true> : mix_csr_margin_kernel<false>;
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d,
                        runs.front, HOP_RUNS_OF(runs), (unsigned)margins, n, grad_dev, n_grad, B, (unsigned)csr_scatter_blocks(n_grad, B), loss);
     if (const int rc = launch_status()) return rc;

@@ -65,9 +65,9 @@ def test_generator_of_very_long_vectors(d):
         assert torch.equal(a, b)
 
 
-# Waves that write 32 MB (three times a velocity's share) and a little more, with 1, 2 and 3 columns over a multiple of four:
-# results stored for the L2s or past them, wave by wave, against the pass in one launch, bit for bit
-@pytest.mark.parametrize("d,momentum", [(2097152, 0.0), (2097153, 0.0), (699050, 0.9), (699051, 0.9), (4099, 0.0), (4098, 0.9)])
+# Waves whose jobs (two pairs; with velocities four records, three times their share) come to 32 MB and a little more, with 1, 2 and 3
+# columns over a multiple of four: results stored for the L2s or past them, wave by wave, against the pass in one launch, bit for bit
+@pytest.mark.parametrize("d,momentum", [(4194304, 0.0), (4194305, 0.0), (2097153, 0.0), (699050, 0.9), (699051, 0.9), (4099, 0.0), (4098, 0.9)])
 @pytest.mark.parametrize("gradient", [hop.HOP_GRAD_ZERO, hop.HOP_GRAD_SYNTH])
 def test_waves_that_stay_near(d, momentum, gradient):
     from paper_1902_01064_amd.session import Session
@@ -87,6 +87,7 @@ def test_waves_that_stay_near(d, momentum, gradient):
                 for at in [(0, n)] if whole else [(w, w + 1) for w in range(n)]:
                     sess.step(*at)
             sess.sync()
+            assert hop.hop_pass_path(sess.ctx, sess.sched) == hop.HOP_PASS_ONE_LAUNCH       # what the whole pass took
             got.append(sess.arena[:4 * sess.D * sess.stride].clone())
         finally:
             sess.close()

@@ -53,3 +53,12 @@ def test_one_xcd(launches, n, d, B, one, alone):
 def test_slices(launches, n, d, B, of_pass, of_wave):
     (_, got), = launches("rules", n, d, B)
     assert (got["slices"], got["wave_slices"]) == (str(of_pass), str(of_wave))
+
+
+# Waves that stay in the L2s: by their jobs, so that the two pairs of a lock-step ring of four stay up to 64 MB of results
+def test_waves_that_stay_near(launches):
+    assert launches("external", 4, 4096, 0, 0, 0.0) == [("pair", dict(jobs="2"))] * 2
+    assert launches("external", 4, 4096, 0, 0, 0.9) == [("mix", dict(jobs="4"))] * 2
+    for n, d, near, with_velocity in [(2, 4194304, 1, 0), (2, 4194305, 0, 0), (4, 699050, 1, 1), (4, 699051, 1, 0), (1, 8388608, 1, 0), (1, 8388609, 0, 0)]:
+        (_, got), = launches("rules", n, d, 1)
+        assert (got["near"], got["near_velocity"]) == (str(near), str(with_velocity))

@@ -33,36 +33,35 @@ def test_mix_of_many_jobs(n, momentum):
         assert bool(((vel.double() - v).abs() <= room / eta)[:, :d].all()) and torch.equal(vel[:, d:].double(), before[:, d:])
 
 
-# 65535 layers of 8 chunks of 2048 columns are not enough for the generator of a wave: the same bits as the pass in one launch
+# 65535 layers of 8 chunks of 2048 columns are not enough for the generator of a wave: parameters of zero become a step along the
+# gradients that a call by itself, on a grid of one row, gives
 @pytest.mark.parametrize("d", [65535 * 8 * 2048, 65535 * 8 * 2048 + 5])
 def test_generator_of_very_long_vectors(d):
     from paper_1902_01064_amd.session import Session
     nb = inputs.ring(2)
     c = dict(inputs.config(4, d=d, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=2, s=1, b=0, skip_on=False, mult=None,
              delay_kind=inputs.DELAY_NONE, grad_ahead=1)
-    some = torch.cat([torch.arange(0, 4096), torch.randint(0, d, (1 << 16,), generator=torch.Generator().manual_seed(d % 97)),
-                      torch.arange(d - 4096, d)]).cuda()
-    p0 = torch.zeros(d, device="cuda")
-    got = []
+    pieces = list(range(0, d, 1 << 26)) + [d]              # every column, a few at a time
     print("generator of", d, "columns", flush=True)
-    for whole in (True, False):
-        sess = Session(c)
-        try:
-            hop.hop_set_grad_source(sess.ctx, hop.HOP_GRAD_SYNTH, 1e-3)
-            sess.set_params(p0)
-            n = sess.simulate().n_waves
-            for at in [(0, n)] if whole else [(w, w + 1) for w in range(n)]:
-                hop.hop_profile(sess.ctx, int(not whole))            # a profiled pass goes wave by wave
-                sess.step(*at)
-            sess.sync()
-            got.append([p[some].clone() for p in sess.params()[0]])
-            assert all(bool((p != 0).any()) for p in got[-1])
-        finally:
-            sess.close()
-            del sess
-            torch.cuda.empty_cache()
-    for a, b in zip(*got):
-        assert torch.equal(a, b)
+    g = torch.empty((d + 3) // 4 * 4, device="cuda")
+    sess = Session(c)
+    try:
+        hop.hop_set_grad_source(sess.ctx, hop.HOP_GRAD_SYNTH, 1e-3)
+        sess.set_params(torch.zeros(d, device="cuda"))
+        sess.simulate()
+        hop.hop_profile(sess.ctx, 1)                       # a profiled pass goes wave by wave
+        sess.step()
+        sess.sync()
+        lr = torch.tensor(c["lr"], dtype=torch.float32, device="cuda")
+        for i, p in enumerate(sess.params()[0]):
+            hop.hop_synth_grad(c["seed"], i, 0, 1e-3, g.data_ptr(), d, sess.stream)
+            torch.cuda.synchronize()
+            assert bool((g[:d] != 0).any())
+            for lo, hi in zip(pieces, pieces[1:]):         # sums of zeros, then one product: exact
+                assert torch.equal(p[lo:hi], -(lr * g[lo:hi]))
+    finally:
+        sess.close()
+        torch.cuda.empty_cache()
 
 
 # Waves whose jobs (two pairs; with velocities four records, three times their share) come to 32 MB and a little more, with 1, 2 and 3

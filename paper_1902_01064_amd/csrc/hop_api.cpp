@@ -1366,7 +1366,7 @@ int hop_mix(const hop_mix_job* jobs, int32_t n_jobs, int64_t d, void* stream) {
     int rc = 0;
     if (e == hipSuccess)
         rc = any_vel ? hopk_mix((const HopMixJob*)dev, n_jobs, d, stream)
-                     : hopk_pair((const HopPairJob*)dev, (int)pairs.size(), n_sources, 0, d, stream);
+                     : hopk_pair_alone((const HopPairJob*)dev, (int)pairs.size(), n_jobs, n_sources, d, stream);
     hipError_t e2 = hipStreamSynchronize((hipStream_t)stream);
     (void)hipFree(dev);
     if (e != hipSuccess) return hip_fail(nullptr, e, "hipMemcpy");

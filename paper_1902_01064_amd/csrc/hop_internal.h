@@ -169,8 +169,10 @@ int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int6
 int hopk_copy(void* dst, const void* src, size_t bytes, void* stream);
 // weak, so that the host files still link for checks that stub the launchers above and never reach a device
 __attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
-// one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out), the Reduce of up to kPairArgs jobs: descriptors on the host
+// one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out); the Reduce of a call's records in any number of jobs, and in up to
+// kPairArgs jobs with descriptors on the host
 __attribute__((weak)) int hopk_one_grad(const HopGradJob& job, int mode, int B, int64_t d, float lambda, int loss, void* stream);
+__attribute__((weak)) int hopk_pair_alone(const HopPairJob* jobs_dev, int n_jobs, int n_results, int n_sources, int64_t d, void* stream);
 __attribute__((weak)) int hopk_pair_args(const HopPairArg* jobs, int n_jobs, int n_sources, int64_t d, void* stream);
 // rows_again: later waves read the same rows while a cache may still hold them (hop_rows_again)
 __attribute__((weak)) int hopk_dense_grad(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, float lambda, int loss, bool rows_again,
@@ -189,6 +191,12 @@ constexpr int64_t kNearBytes = 32ll << 20;
 // `vectors` that go with a job: with a velocity its own share is written and read between, which counts as three (16 x 300 000,
 // sparse, 419 / 402; 64 x 500 000 1357 / 1375).
 inline bool hop_stays_near(int n_jobs, int64_t d, int vectors = 1) { return vectors * n_jobs * d * (int64_t)sizeof(float) <= kNearBytes; }
+
+// A stand-alone average of uploaded jobs, past the L2s -> near, us a call: records of 13 sources, which run singly, 16 x 60 000 columns 47.7 ->
+// 47.2, 16 x 240 000 (15 MB) 57.5 -> 56.4, 64 x 60 000 (15 MB) 89.9 -> 87.1, 16 x 350 000 (21 MB) 64.6 -> 69.7, 16 x 480 000 74.0 -> 80.5, 64 x 120 000
+// 108.7 -> 111.8; 64 records in pairs, 60 000 columns (15 MB) 69.1 -> 70.8, 80 000 72.0 -> 73.5, 240 000 91.3 -> 90.5.  With velocities, which a
+// call brings back into the L2s to write them, the rule of the waves: 17 sizes of 4 to 32 MB 1.4 % faster, the most 1.4 % slower.
+inline bool hop_near_alone(int n_jobs, int n_results, int64_t d) { return n_jobs == n_results && hop_stays_near(n_jobs, d, 2); }
 
 constexpr int64_t kMemorySideCache = 256ll << 20;
 constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce

@@ -450,8 +450,8 @@ inline int pair_run(int n_sources, int64_t n_chunks, int vec) {
     return run < 1 ? 1 : run;
 }
 
-// A launch over pairs.  `may_near`: whether the next launches read the results (a stand-alone call waits for them to get out of
-// the L2s instead: 16 jobs x 400 000 columns 34.0 -> 34.9 us); margins: `front` workgroups of them in front; single: sparse margins
+// A launch over pairs.  `may_near`: whether the results may stay in the L2s (a few jobs as an argument are a call by itself, which waits
+// for them to get out: 16 x 400 000 columns 34.0 -> 34.9 us); margins: `front` workgroups of them in front; single: sparse margins
 // beside single records.
 struct PairShape {
     int vec;
@@ -1645,15 +1645,23 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
     return hopk_mix(mix_dev + n, n_mix - n, d, stream);
 }
 
-int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream) {
+static int launch_pairs(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, bool may_near, void* stream) {
     return in_parts(jobs_dev, n_jobs, [&](const HopPairJob* jobs, int n) {
         PairShape p;
-        if (!pair_shape(&p, n, n_sources, d, true)) return (int)hipErrorInvalidConfiguration;
+        if (!pair_shape(&p, n, n_sources, d, may_near)) return (int)hipErrorInvalidConfiguration;
         const auto kernel = p.vec == 4 ? p.near ? pair_mix_kernel<4, true> : pair_mix_kernel<4, false>
                                        : p.near ? pair_mix_kernel<kPairPlain, true> : pair_mix_kernel<kPairPlain, false>;
         hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, jobs, d, p.near ? 0 : reverse, HOP_RUNS_OF(p.runs));
         return launch_status();
     });
+}
+
+int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream) {
+    return launch_pairs(jobs_dev, n_jobs, n_sources, reverse, d, true, stream);
+}
+
+int hopk_pair_alone(const HopPairJob* jobs_dev, int n_jobs, int n_results, int n_sources, int64_t d, void* stream) {
+    return launch_pairs(jobs_dev, n_jobs, n_sources, 0, d, hop_near_alone(n_jobs, n_results, d), stream);
 }
 
 int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,

@@ -1,6 +1,7 @@
 // What a pass launches, on the CPU: hop_api.cpp with a HIP runtime of plain memory and launchers that print their arguments.
 //   launch_driver dense|csr|external WORKERS COLUMNS BATCH ROWS MOMENTUM
 //   launch_driver rules RECORDS COLUMNS BATCH
+//   launch_driver average RECORDS COLUMNS SOURCES MOMENTUM
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -51,6 +52,11 @@ int hopk_mix_csr_margin(const HopMixJob*, int n, int64_t, const HopGradJob*, int
     return 0;
 }
 int hopk_pair(const HopPairJob*, int n, int, int, int64_t, void*) { std::printf("pair jobs=%d\n", n); return 0; }
+int hopk_pair_alone(const HopPairJob*, int n, int results, int, int64_t d, void*) {
+    std::printf("pair_alone jobs=%d results=%d near=%d\n", n, results, hop_near_alone(n, results, d));
+    return 0;
+}
+int hopk_pair_args(const HopPairArg*, int n, int, int64_t, void*) { std::printf("pair_args jobs=%d\n", n); return 0; }
 int hopk_pair_csr_margin(const HopPairJob*, int n, int, int, int64_t, const HopGradJob*, int g, int, int, void*) {
     std::printf("pair_csr_margin jobs=%d gradients=%d\n", n, g);
     return 0;
@@ -77,6 +83,18 @@ int main(int argc, char** argv) {
         std::printf("rules one_xcd=%d one_xcd_alone=%d slices=%d wave_slices=%d near=%d near_velocity=%d\n", hop_one_xcd(n, B, d),
                     hop_one_xcd_alone(B, d), hop_dense_slices(B, d), hop_wave_slices(n, B, d), hop_stays_near(n, d), hop_stays_near(n, d, 3));
         return 0;
+    }
+    if (argc == 6) {                          // every record reads the same vectors
+        const int n = std::atoi(argv[2]), A = std::atoi(argv[4]);
+        std::vector<hop_mix_job> jobs((size_t)n);
+        std::memset(jobs.data(), 0, jobs.size() * sizeof(hop_mix_job));
+        for (hop_mix_job& j : jobs) {
+            j.out = (float*)4096;             // never read here
+            j.vel = std::atof(argv[5]) > 0 ? (float*)8192 : nullptr;
+            j.A = A;
+            for (int a = 0; a < A; ++a) j.src[a] = (const float*)(uintptr_t)(16384 + 4096 * a);
+        }
+        return hop_mix(jobs.data(), n, std::atoll(argv[3]), nullptr);
     }
     if (argc != 7) return 2;
     const std::string model = argv[1];

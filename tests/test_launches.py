@@ -62,3 +62,12 @@ def test_waves_that_stay_near(launches):
     for n, d, near, with_velocity in [(2, 4194304, 1, 0), (2, 4194305, 0, 0), (4, 699050, 1, 1), (4, 699051, 1, 0), (1, 8388608, 1, 0), (1, 8388609, 0, 0)]:
         (_, got), = launches("rules", n, d, 1)
         assert (got["near"], got["near_velocity"]) == (str(near), str(with_velocity))
+
+
+# Averages by themselves: a few jobs as an argument, more in memory; these stay in the L2s up to 16 MB and where no two records share a job
+@pytest.mark.parametrize("n,d,sources,momentum,want", [
+    (32, 1000, 5, 0.0, ("pair_args", dict(jobs="16"))), (34, 1000, 5, 0.0, ("pair_alone", dict(jobs="17", results="34", near="0"))),
+    (16, 262144, 13, 0.0, ("pair_alone", dict(jobs="16", results="16", near="1"))),
+    (16, 262145, 13, 0.0, ("pair_alone", dict(jobs="16", results="16", near="0"))), (34, 1000, 5, 0.9, ("mix", dict(jobs="34")))])
+def test_stand_alone_averages(launches, n, d, sources, momentum, want):
+    assert launches("average", n, d, sources, momentum) == [want]

@@ -198,6 +198,14 @@ inline bool hop_stays_near(int n_jobs, int64_t d, int vectors = 1) { return vect
 // call brings back into the L2s to write them, the rule of the waves: 17 sizes of 4 to 32 MB 1.4 % faster, the most 1.4 % slower.
 inline bool hop_near_alone(int n_jobs, int n_results, int64_t d) { return n_jobs == n_results && hop_stays_near(n_jobs, d, 2); }
 
+// Results that the gradient kernel of the same wave finishes in place stay near further: it reads them next.  Near against past the L2s by
+// what the records with a gradient write, geometric means of 2 to 16 runs of 24 to 144 workers each: without velocities 30 to 50 MB 0.95, 70 to 90
+// 0.96, 90 to 110 0.99, 127 to 160 1.03, 160 to 300 1.02 (64 workers x 200 000 columns 616 -> 615 us per pass, 64 x 330 000 1102 -> 1029, 144 x 524 288
+// 4583 -> 4674); with velocities 30 to 50 MB 0.95, 70 to 110 1.00, 110 to 127 1.02, 127 to 160 1.04, 160 to 300 1.01 (32 x 330 000 684 -> 626, 100 x
+// 400 000 2949 -> 3034).
+constexpr int64_t kInPlaceNear = 96ll << 20;
+inline bool hop_in_place_near(int n_records, int64_t d) { return n_records * d * (int64_t)sizeof(float) <= kInPlaceNear; }
+
 constexpr int64_t kMemorySideCache = 256ll << 20;
 constexpr int64_t kDenseInPlaceBytes = 2 << 20; // rows of a minibatch up to which its margins run beside the Reduce
 // Whether the columns of a pass's dense minibatches may be dealt out to the 8 XCDs in slices.  The partial products, 8 a row, are in

@@ -1021,20 +1021,20 @@ __global__ __launch_bounds__(kThreads) void dense_margin_one(const HopGradJob jo
 // The partial margins of a wave's STEP records and the wave's Reduce in one launch: both only read x_k
 // (the parallel approach of Section 3.2 runs Compute beside Reduce).  The Reduce leaves sum_a w'_a x_a
 // in the result slot; dense_grad_kernel then applies -eta g to it.
-// (NEAR: each record on one XCD, n their number; else n the segments of a row)
-template <bool NEAR>
+// (ONE: each record on one XCD, n their number; else n the segments of a row.  NEAR: hop_in_place_near)
+template <bool ONE, bool NEAR>
 __global__ __launch_bounds__(kThreads) void mix_dense_margin_kernel(const HopMixJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                     HOP_RUNS_IN, unsigned margins, int n_mix,
                                                                     const HopGradJob* __restrict__ grad_jobs, int B,
                                                                     int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
-        mix_block<true>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
+        mix_block<NEAR>(mix_jobs, d, HOP_RUNS, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
     if (b >= margins) return;
-    if (NEAR) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
+    if (ONE) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
     else dense_margin_block(grad_jobs, B, d, n, b, red);
 }
 
@@ -1313,19 +1313,19 @@ __global__ __launch_bounds__(kThreads) void pair_csr_margin_kernel(const HopPair
     if (b < margins) csr_margin_block(grad_jobs, (unsigned)n_grad, B, per, loss, b);
 }
 
-template <int VEC, bool NEAR>
+template <int VEC, bool ONE, bool NEAR>
 __global__ __launch_bounds__(kThreads) void pair_dense_margin_kernel(const HopPairJob* __restrict__ mix_jobs, int64_t d, int front,
                                                                      HOP_RUNS_IN, int reverse, unsigned margins, int n_mix,
                                                                      const HopGradJob* __restrict__ grad_jobs, int B,
                                                                     int n) {
     __shared__ float red[1][kThreads / 64];
     if ((int)blockIdx.z >= front) {
-        pair_block<VEC, true>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
+        pair_block<VEC, NEAR>(mix_jobs, d, HOP_RUNS, reverse, (int)blockIdx.z - front);
         return;
     }
     const unsigned b = grid_index(HOP_RUNS, n_mix);
     if (b >= margins) return;
-    if (NEAR) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
+    if (ONE) dense_margin_near(grad_jobs, (unsigned)n, B, d, b, red);
     else dense_margin_block(grad_jobs, B, d, n, b, red);
 }
 
@@ -1622,7 +1622,9 @@ int hopk_mix_dense_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const 
     Runs runs;
     dim3 grid;
     if (!mix_grid(n, d, margins, &runs, &grid)) return (int)hipErrorInvalidConfiguration;
-    const auto kernel = one ? mix_dense_margin_kernel<true> : mix_dense_margin_kernel<false>;
+    const auto kernel = one                            ? mix_dense_margin_kernel<true, true>
+                        : hop_in_place_near(n_grad, d) ? mix_dense_margin_kernel<false, true>
+                                                       : mix_dense_margin_kernel<false, false>;
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, runs.front, HOP_RUNS_OF(runs),
                        (unsigned)margins, n, grad_dev, B, one ? n_grad : nseg);
     if (const int rc = launch_status()) return rc;
@@ -1708,9 +1710,10 @@ int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, 
     const int64_t margins = one ? near_margins(n_grad, B) : (int64_t)n_grad * B * nseg;
     PairShape p;
     if (!pair_shape(&p, n, n_sources, d, true, true, margins)) return (int)hipErrorInvalidConfiguration;
-    const auto kernel = p.vec == 4 ? pair_dense_margin_kernel<4, false>
-                        : one      ? pair_dense_margin_kernel<kPairMargin, true>
-                                   : pair_dense_margin_kernel<kPairMargin, false>;
+    const auto kernel = p.vec == 4                     ? pair_dense_margin_kernel<4, false, false>       // 128 MB of jobs and more
+                        : one                          ? pair_dense_margin_kernel<kPairMargin, true, true>
+                        : hop_in_place_near(n_grad, d) ? pair_dense_margin_kernel<kPairMargin, false, true>
+                                                       : pair_dense_margin_kernel<kPairMargin, false, false>;
     hipLaunchKernelGGL(kernel, p.grid, dim3(kThreads), 0, (hipStream_t)stream, mix_dev, d, p.runs.front, HOP_RUNS_OF(p.runs),
                        p.near ? 0 : reverse, (unsigned)margins, n, grad_dev, B, one ? n_grad : nseg);
     if (const int rc = launch_status()) return rc;

@@ -80,8 +80,9 @@ int main(int argc, char** argv) {
     if (argc == 5) {
         const int n = std::atoi(argv[2]), B = std::atoi(argv[4]);
         const int64_t d = std::atoll(argv[3]);
-        std::printf("rules one_xcd=%d one_xcd_alone=%d slices=%d wave_slices=%d near=%d near_velocity=%d\n", hop_one_xcd(n, B, d),
-                    hop_one_xcd_alone(B, d), hop_dense_slices(B, d), hop_wave_slices(n, B, d), hop_stays_near(n, d), hop_stays_near(n, d, 3));
+        std::printf("rules one_xcd=%d one_xcd_alone=%d slices=%d wave_slices=%d near=%d near_velocity=%d in_place=%d\n", hop_one_xcd(n, B, d),
+                    hop_one_xcd_alone(B, d), hop_dense_slices(B, d), hop_wave_slices(n, B, d), hop_stays_near(n, d), hop_stays_near(n, d, 3),
+                    hop_in_place_near(n, d));
         return 0;
     }
     if (argc == 6) {                          // every record reads the same vectors

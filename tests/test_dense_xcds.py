@@ -45,6 +45,13 @@ def test_wave_of_many_rows_in_slices(N, d, B, momentum):
     _check_wave(N, d, B, momentum, 70)
 
 
+# Results finished in place: 96 MB of them and more, and with workgroups of 4096 columns; jobs end with 0, 2 and 1 columns over four
+@pytest.mark.parametrize("N,d,B", [(64, 393216, 1), (64, 393218, 1), (140, 500001, 1), (3, 150001, 3)])
+@pytest.mark.parametrize("momentum", [0.0, 0.9])
+def test_wave_in_place(N, d, B, momentum):
+    _check_wave(N, d, B, momentum, 5)
+
+
 def _check_wave(N, d, B, momentum, rows):
     nb = [[]] if N == 1 else inputs.ring(N)
     c = dict(inputs.config(1, d=d, rows=rows, K=1), in_nbrs=nb, W=inputs.uniform_weights(nb), N=N, s=0, b=0, batch=B, loss=1, lam=0.25,

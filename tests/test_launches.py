@@ -71,3 +71,10 @@ def test_waves_that_stay_near(launches):
     (16, 262145, 13, 0.0, ("pair_alone", dict(jobs="16", results="16", near="0"))), (34, 1000, 5, 0.9, ("mix", dict(jobs="34")))])
 def test_stand_alone_averages(launches, n, d, sources, momentum, want):
     assert launches("average", n, d, sources, momentum) == [want]
+
+
+# Results that the same wave's gradient reads next
+@pytest.mark.parametrize("n,d,near", [(4, 1024, 1), (64, 393216, 1), (64, 393217, 0), (48, 524288, 1), (49, 524288, 0)])
+def test_results_in_place(launches, n, d, near):
+    (_, got), = launches("rules", n, d, 1)
+    assert got["in_place"] == str(near)

@@ -1153,7 +1153,7 @@ static int launch_waves(hop_ctx* c, hop_schedule* s, int wb, int we, void* strea
         const bool csr = ng > 0 && mode == HOP_GRAD_SVM_CSR;
         if (timed && (rc = prof_begin(c, HOP_KERNEL_MIX, s->wave_mix_bytes[w]))) return rc;
         if (csr && pj)   // margins and Reduce + Apply both only read x_k: one launch
-            HOP_LAUNCH(c, hopk_pair_csr_margin(pj, np, s->wave_sources[w], w & 1, c->d, gj, ng, B, c->opts.loss, stream));
+            HOP_LAUNCH(c, hopk_pair_csr_margin(pj, np, nj, s->wave_sources[w], w & 1, c->d, gj, ng, B, c->opts.loss, stream));
         else if (csr)
             HOP_LAUNCH(c, hopk_mix_csr_margin(s->mix_dev + jb, nj, c->d, gj, ng, B, c->opts.loss, stream));
         else if (pj)

@@ -158,8 +158,6 @@ int hopk_mix_csr_margin(const HopMixJob* mix_dev, int n_mix, int64_t d, const Ho
                         int loss, void* stream);
 // n_sources: distinct vectors the jobs read (sizes the XCD runs); reverse: walk the vectors from their end
 int hopk_pair(const HopPairJob* jobs_dev, int n_jobs, int n_sources, int reverse, int64_t d, void* stream);
-int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
-                         const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream);
 int hopk_pair_dense_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
                            const HopGradJob* grad_dev, int n_grad, int B, void* stream);
 // out += factor c_m x_m over the active rows; into_velocity: vel -= c_m x_m too
@@ -168,6 +166,8 @@ int hopk_csr_check(const int64_t* rowptr, const int32_t* col, int64_t rows, int6
                    int* flag_dev, void* stream);
 int hopk_copy(void* dst, const void* src, size_t bytes, void* stream);
 // weak, so that the host files still link for checks that stub the launchers above and never reach a device
+__attribute__((weak)) int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_results, int n_sources, int reverse, int64_t d,
+                                               const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream);
 __attribute__((weak)) int hopk_sweep(const HopSweepArgs& args, void* stream);
 // one gradient written to job.g (HOP_GRAD_SVM_CSR: to job.out); the Reduce of a call's records in any number of jobs, and in up to
 // kPairArgs jobs with descriptors on the host

@@ -1666,15 +1666,14 @@ int hopk_pair_alone(const HopPairJob* jobs_dev, int n_jobs, int n_results, int n
     return launch_pairs(jobs_dev, n_jobs, n_sources, 0, d, hop_near_alone(n_jobs, n_results, d), stream);
 }
 
-int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_sources, int reverse, int64_t d,
+int hopk_pair_csr_margin(const HopPairJob* mix_dev, int n_mix, int n_results, int n_sources, int reverse, int64_t d,
                          const HopGradJob* grad_dev, int n_grad, int B, int loss, void* stream) {
     if (n_grad <= 0 || B <= 0) return hopk_pair(mix_dev, n_mix, n_sources, reverse, d, stream);
     if (n_mix <= 0) return hopk_csr_margin(grad_dev, n_grad, B, loss, stream);
     const int n = (int)std::min<int64_t>(n_mix, kMaxGridYZ);
     const int64_t margins = csr_margin_blocks(n_grad, B);
     PairShape p;
-    // fewer jobs than gradients: some hold two records
-    if (!pair_shape(&p, n, n_sources, d, true, true, margins, n_mix >= n_grad)) return (int)hipErrorInvalidConfiguration;
+    if (!pair_shape(&p, n, n_sources, d, true, true, margins, n_mix == n_results)) return (int)hipErrorInvalidConfiguration;
     const auto kernel = p.vec == 4 ? pair_csr_margin_kernel<4, false>
                         : p.near   ? pair_csr_margin_kernel<kPairMargin, true>
                                    : pair_csr_margin_kernel<kPairMargin, false>;

@@ -1,5 +1,5 @@
 // What a pass launches, on the CPU: hop_api.cpp with a HIP runtime of plain memory and launchers that print their arguments.
-//   launch_driver dense|csr|external WORKERS COLUMNS BATCH ROWS MOMENTUM
+//   launch_driver dense|csr|skipping|external WORKERS COLUMNS BATCH ROWS MOMENTUM
 //   launch_driver rules RECORDS COLUMNS BATCH
 //   launch_driver average RECORDS COLUMNS SOURCES MOMENTUM
 #include <cstdio>
@@ -57,8 +57,8 @@ int hopk_pair_alone(const HopPairJob*, int n, int results, int, int64_t d, void*
     return 0;
 }
 int hopk_pair_args(const HopPairArg*, int n, int, int64_t, void*) { std::printf("pair_args jobs=%d\n", n); return 0; }
-int hopk_pair_csr_margin(const HopPairJob*, int n, int, int, int64_t, const HopGradJob*, int g, int, int, void*) {
-    std::printf("pair_csr_margin jobs=%d gradients=%d\n", n, g);
+int hopk_pair_csr_margin(const HopPairJob*, int n, int results, int, int, int64_t, const HopGradJob*, int g, int, int, void*) {
+    std::printf("pair_csr_margin jobs=%d results=%d gradients=%d\n", n, results, g);
     return 0;
 }
 int hopk_pair_dense_margin(const HopPairJob*, int n, int, int, int64_t, const HopGradJob*, int g, int, void*) {
@@ -115,27 +115,35 @@ int main(int argc, char** argv) {
     hop_opts_default(&o);
     o.batch = B;
     o.momentum = (float)std::atof(argv[6]);
+    o.skip_on = model == "skipping";          // csr, Exp(1) delays, every second worker four times as slow
+    const int bound = o.skip_on ? 2 : 1;
     const hop_graph g{N, row_ptr.data(), col.data()};
     hop_device dev;
     std::vector<char> arena, workspace;
-    dev.arena_bytes = hop_arena_bytes(N, d, 1, 0, &o);
+    dev.arena_bytes = hop_arena_bytes(N, d, bound, 0, &o);
     dev.arena = aligned(arena, dev.arena_bytes);
     dev.hip_stream = nullptr;
     hop_ctx* c = nullptr;
-    if (hop_init(&c, &g, W.data(), N, d, 1, 0, &o, &dev)) return 3;
+    if (hop_init(&c, &g, W.data(), N, d, bound, 0, &o, &dev)) return 3;
     // never read here: the launchers only print
     std::vector<int64_t> rowptr((size_t)rows + 1, 0);
     float* some = (float*)dev.arena;
     for (int i = 0; i < N; ++i) {
         const int rc = model == "dense" ? hop_set_data_dense(c, i, some, some, rows)
-                       : model == "csr" ? hop_set_data_csr(c, i, rowptr.data(), (const int32_t*)some, some, some, rows)
+                       : model == "csr" || model == "skipping" ? hop_set_data_csr(c, i, rowptr.data(), (const int32_t*)some, some, some, rows)
                                         : HOP_OK;
         if (rc) return 4;
     }
-    if (hop_set_grad_source(c, model == "dense" ? HOP_GRAD_SVM_DENSE : model == "csr" ? HOP_GRAD_SVM_CSR : HOP_GRAD_EXTERNAL, 0.f, some)) return 5;
+    if (hop_set_grad_source(c, model == "dense" ? HOP_GRAD_SVM_DENSE : model == "csr" || model == "skipping" ? HOP_GRAD_SVM_CSR : HOP_GRAD_EXTERNAL, 0.f, some)) return 5;
     if (hop_set_params(c, some, 0, 1)) return 6;
     hop_schedule* s = nullptr;
-    if (hop_simulate(c, nullptr, 2, &s)) return 7;
+    std::vector<double> slow((size_t)N, 1.0);
+    for (int i = 1; i < N; i += 2) slow[(size_t)i] = 4.0;
+    hop_delay_model delays;
+    std::memset(&delays, 0, sizeof delays);
+    delays.kind = HOP_DELAY_EXP1;
+    delays.mult = slow.data();
+    if (hop_simulate(c, o.skip_on ? &delays : nullptr, o.skip_on ? 30 : 2, &s)) return 7;
     const size_t need = hop_schedule_bytes(s);
     if (hop_schedule_bind(c, s, aligned(workspace, need), need)) return 8;
     hop_schedule_arrays v;

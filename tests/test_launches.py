@@ -78,3 +78,10 @@ def test_stand_alone_averages(launches, n, d, sources, momentum, want):
 def test_results_in_place(launches, n, d, near):
     (_, got), = launches("rules", n, d, 1)
     assert got["in_place"] == str(near)
+
+
+# Sparse margins beside records that run singly: known by the results of the jobs, not by fewer jobs than gradients, as jumps pair up too
+def test_single_records(launches):
+    got = [tuple(int(a[k]) for k in ("jobs", "results", "gradients")) for name, a in launches("skipping", 4, 256, 4, 50, 0.0) if name == "pair_csr_margin"]
+    assert all(jobs <= results <= 2 * jobs and gradients <= results for jobs, results, gradients in got)
+    assert any(jobs == results for jobs, results, _ in got) and any(gradients <= jobs < results for jobs, results, gradients in got)

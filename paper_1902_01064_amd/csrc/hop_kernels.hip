@@ -995,6 +995,7 @@ constexpr int kMarginRows = 4;
 constexpr int kSliceRows = 2;
 constexpr int64_t kMarginFew = 384;
 constexpr int64_t kMarginNear = 128ll << 20;           // bytes of rows in a launch up to which they are left in the caches
+static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "a launch of few workgroups by segments always is");
 
 template <int ROWS, bool STREAM, Cut CUT>
 __global__ __launch_bounds__(kThreads) void dense_margin_kernel(const HopGradJob* __restrict__ jobs, int B, int64_t d,
@@ -1542,10 +1543,8 @@ int hopk_dense_margin(const HopGradJob* jobs_dev, int n_jobs, int B, int64_t d, 
         const dim3 rows((unsigned)nseg, (unsigned)B, (unsigned)n), fours((unsigned)nseg, (unsigned)groups, (unsigned)n);
 #define HOP_MARGINS(GRID, ROWS, STREAM, ONE)                                                                                \
     hipLaunchKernelGGL((dense_margin_kernel<ROWS, STREAM, ONE>), GRID, dim3(kThreads), 0, (hipStream_t)stream, jobs, B, d, nseg)
-        static_assert(kMarginFew * kMarginRows * kSegCols * 4 <= kMarginNear, "few workgroups of one segment: near");
         if (blocks < kMarginFew && nseg == 1) HOP_MARGINS(rows, 1, false, Cut::one);
-        else if (blocks < kMarginFew && near) HOP_MARGINS(rows, 1, false, Cut::segments);
-        else if (blocks < kMarginFew) HOP_MARGINS(rows, 1, true, Cut::segments);
+        else if (blocks < kMarginFew) HOP_MARGINS(rows, 1, false, Cut::segments);
         else if (nseg == 1) HOP_MARGINS(fours, kMarginRows, true, Cut::one);
         else HOP_MARGINS(fours, kMarginRows, true, Cut::segments);
 #undef HOP_MARGINS
@@ -1749,13 +1748,10 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
             hipLaunchKernelGGL(dense_grad_near_one, dim3(kXcd, (unsigned)((d + 255) / 256)), dim3(512), 0, st, job, B, d, lambda, loss);
             return launch_status();
         }
-        const bool near = (int64_t)B * d * 4 <= kMarginNear;
-        if (nseg == 1 && grid < kMarginFew)                          // a row of one segment is at most 64 KB: always near
+        if (nseg == 1 && grid < kMarginFew)
             hipLaunchKernelGGL((dense_margin_one<1, false, true>), rows, threads, 0, st, job, B, d, nseg);
-        else if (grid < kMarginFew && near)
-            hipLaunchKernelGGL((dense_margin_one<1, false, false>), rows, threads, 0, st, job, B, d, nseg);
         else if (grid < kMarginFew)
-            hipLaunchKernelGGL((dense_margin_one<1, true, false>), rows, threads, 0, st, job, B, d, nseg);
+            hipLaunchKernelGGL((dense_margin_one<1, false, false>), rows, threads, 0, st, job, B, d, nseg);
         else
             hipLaunchKernelGGL((dense_margin_one<kMarginRows, true, false>), groups, threads, 0, st, job, B, d, nseg);
         if (const int rc = launch_status()) return rc;

@@ -104,8 +104,8 @@ def cpu_baseline(c, recs, p0):
 def wave_compulsory_bytes(sched, d, mode, momentum):
     """HBM bytes one Reduce + Apply launch cannot avoid, per wave, from the schedule itself: every distinct
     (worker, slot) vector the wave reads once, one result per record, one gradient per STEP record where the
-    kernel reads a dense one (synthetic, external), the velocity read and written.  With large dense minibatches
-    ("dense_fused") the gradient kernel reduces its own records and the mix launch holds the jumps only."""
+    kernel reads a dense one (synthetic, external), the velocity read and written.  With dense minibatches ("dense_fused")
+    a mix launch holds the jumps only: the gradient kernels finish the other records."""
     import numpy as np
     out = np.zeros(int(sched.n_waves))
     for w in range(int(sched.n_waves)):
@@ -122,6 +122,16 @@ def wave_compulsory_bytes(sched, d, mode, momentum):
                 vectors += 1 + (2 if momentum else 0)
         out[w] = 4.0 * d * (len(srcs) + vectors)
     return out
+
+
+def dense_mix_bytes(sched, per_wave, launches):
+    """Of wave_compulsory_bytes(.., "dense_fused", ..) what the `launches` mix launches of a pass move.  Where the library
+    has margins and Reduce in one launch, the jumps of a wave with gradients ride there, and fewer waves than hold jumps
+    have a mix launch: those without a gradient."""
+    import numpy as np
+    grads = np.array([np.isin(sched.kind[sched.wave_order[a:b]], (0, 2)).any()
+                      for a, b in zip(sched.wave_begin[:-1], sched.wave_begin[1:])], dtype=bool)
+    return float(per_wave.sum() if launches == np.count_nonzero(per_wave) else per_wave[~grads].sum())
 
 
 def pass_compulsory_bytes(sched, d, momentum):
@@ -161,7 +171,7 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
             hop.hop_set_grad_source(sess.ctx, hop.HOP_GRAD_SYNTH, c["grad_var"])
         sess.set_params(p0)
         sched = sess.simulate()
-        mix_mode = "synth" if c["model"] == "synth" else ("dense_fused" if c["model"] == "dense" and c["batch"] * c["d"] * 4 > (2 << 20) else "none")
+        mix_mode = {"synth": "synth", "dense": "dense_fused"}.get(c["model"], "none")
         compulsory = wave_compulsory_bytes(sched, c["d"], mix_mode, c.get("momentum", 0.0) > 0)
         n_step = int((sched.kind == hop.HOP_STEP).sum())
         n_jump = int((sched.kind == hop.HOP_JUMP).sum())
@@ -191,6 +201,8 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
         way = {hop.HOP_PASS_ONE_LAUNCH: "one launch per pass (sweep_kernel)", hop.HOP_PASS_GRAPH: "hip graph replay",
                hop.HOP_PASS_WAVES: "kernel by kernel"}[hop.hop_pass_path(sess.ctx, sched)]
 
+        mix_compulsory = float(compulsory.sum()) if c["model"] != "dense" else dense_mix_bytes(sched, compulsory, mix_n / profiled)
+
         def rate(b, ms):
             return b / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
         res = {
@@ -207,7 +219,7 @@ def run_config(cfgn, steps, warmup, graph, over=None, external=False):
                 "launch": way,
             },
             "mix": {"ms": mix_ms, "launches": int(mix_n), "bytes": mix_bytes, "GBps": rate(mix_bytes, mix_ms),
-                    "compulsory_bytes_per_pass": float(compulsory.sum()),
+                    "compulsory_bytes_per_pass": mix_compulsory,
                     "passes_timed": profiled},
             "grad": {"ms": grad_ms, "launches": int(grad_n), "GBps": rate(grad_bytes, grad_ms)},
             "synth": {"ms": syn_ms, "launches": int(syn_n), "GBps": rate(syn_bytes, syn_ms)},
@@ -335,8 +347,7 @@ def main():
         us = grad["ms"] * 1e3 / n_g
         out["roofline"] = r = {
             "bound": "hbm",
-            "kernel": ("dense_margin_kernel + dense_grad_kernel (one group per wave)" if c["batch"] * c["d"] * 4 > (2 << 20) or c["d"] > 11264
-                       else "pair_dense_margin_kernel + dense_grad_kernel (one group per wave; bound by launches)"),
+            "kernel": "dense margins, then dense gradients (one group per wave; the forms go by the wave's sizes)",
             "achieved": grad["GBps"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": grad["GBps"] / HBM_PEAK_GBS,
             "traffic": None, "launches": grad["launches"], "avg_launch_us": us,
             "algorithmic_bytes_per_launch": grad["GBps"] * 1e9 * us * 1e-6,

@@ -41,6 +41,32 @@ def test_compulsory_bytes_of_a_lock_step_ring():
         hop.hop_destroy(ctx)
 
 
+def test_bytes_of_the_mix_launches_of_a_dense_pass():
+    """The jumps of a wave with gradients count where they have a launch of their own, not where margins and Reduce are
+    one launch; which of the two a pass has is told by its number of mix launches, at any number of columns."""
+    c = inputs.config(2, K=60)
+    ctx = host_ctx(c)
+    try:
+        s = hop.hop_simulate(ctx, c["K"], c["delay_kind"], c["mult"])
+        per = bench.wave_compulsory_bytes(s, 1000, "dense_fused", False)
+        alone, beside = 0.0, 0.0
+        n_alone = n_beside = 0
+        for w in range(s.n_waves):
+            kinds = [int(s.kind[e]) for e in s.wave_order[s.wave_begin[w]:s.wave_begin[w + 1]]]
+            if hop.HOP_JUMP not in kinds:
+                assert per[w] == 0
+            elif all(k == hop.HOP_JUMP for k in kinds):
+                alone, n_alone = alone + per[w], n_alone + 1
+            else:
+                beside, n_beside = beside + per[w], n_beside + 1
+        assert n_beside > 0 and beside > 0
+        assert bench.dense_mix_bytes(s, per, n_alone + n_beside) == alone + beside
+        assert bench.dense_mix_bytes(s, per, n_alone) == alone
+        s.free()
+    finally:
+        hop.hop_destroy(ctx)
+
+
 def test_counter_summaries_parse_and_match_their_own_text():
     for name, low, high in (("hop_mix_cfg4_traffic.txt", 7.9e9, 8.3e9), ("hop_mix_cfg5_traffic.txt", 2.1e9, 2.3e9)):
         v = bench.read_traffic(name)

@@ -339,13 +339,14 @@ float* slot_ptr(const hop_ctx* c, int worker, int slot) {
     return c->ring + ((int64_t)worker * c->slots + slot) * c->stride;
 }
 
-// A pass in microseconds as one sweep and wave by wave, to choose between the two.  The waves' side is fitted to 5082 passes
-// on MI355X (rings, tori, rings with chords and complete graphs of 4 to 100 workers, 64 to 4 M columns, each gradient, with
-// and without a velocity, in lock-step, with Exp(1) delays and with a straggler), the sweep's to 1344 like them: half of
-// them within 10 %, nine in ten within 30 %.  Of those 1344, 13 go the way that is slower by more than 4 %, at most by 30 %
-// (32 workers of 7 sources x 64 columns, synthetic gradients and a velocity, lock-step: 80 us in waves, 62 in the sweep); three
-// of them go into the sweep, at most 9 % slower there (64 workers x 20 000 columns, external gradients and a velocity, lock-step:
-// 130 us in waves, 142).
+// A pass in microseconds as one sweep and wave by wave, to choose between the two.  Fitted to 2120 passes on MI355X, both ways each
+// (rings, tori, rings with chords and complete graphs of 2 to 100 workers, 64 to 3 M columns, each gradient, with and without a
+// velocity, in lock-step and with Exp(1) delays, 15 and 31 iterations): half of them within 6 %, nine in ten within 20 %.  25 go
+// the way that is slower by more than 4 %, at most by 42 % (36 workers x 9000 columns in a torus, external gradients and a velocity,
+// lock-step: 90 us in waves, 127 in the sweep).  With the constants from before waves kept to the L2s and a velocity's Reduce took one
+// float4 a thread it was 61, at most 85 % (32 workers x 4096, complete, external gradients and a velocity, lock-step: 96 and 178); of
+// the 62 passes that changed ways 43 got more than 4 % faster and 7 slower, by 6 to 19 %.  Fitted to the 1280 of 15 iterations
+// alone, 19 of the other 840 went the slower way.
 struct SweepCost {
     int64_t d = 0;
     int waves = 0, records = 0, gradients = 0, mode = 0, workers = 0;
@@ -363,41 +364,40 @@ struct SweepCost {
     // half, and the wavefronts there are registers for fill the rest.  A pass is the larger of the two, or what it reads and
     // writes.  Synthetic gradients are worked out beside every part, whether it takes one or not.  External gradients are read
     // while the record before is at work, which is too short where wavefronts take turns.
-    // The parts of wide records count like any record.  (Counted 1.7 times, 112 of the 1344 passes went the slower way, up to
-    // 2.2 times slower: 24 workers x 65 540 columns, complete and in lock-step, 285 us in waves, 177 in the sweep.)
+    // The parts of wide records count like any record.
     double sweep_us(int n_local) const {
         const double per_simd = std::max(1.0, (double)((d + 255) / 256) / 256.0);
         const int at_a_time = n_local <= 48 ? 8 : n_local <= 80 ? 5 : n_local <= 112 ? 4 : 2;
         const double turns = std::ceil(per_simd / at_a_time);
         const bool synth = mode == HOP_GRAD_SYNTH, external = mode == HOP_GRAD_EXTERNAL;
-        double one = 0.069 * parts + 0.0043 * sources + 0.94 * ((n_local + 7) / 8);
-        one += synth ? 0.047 * parts : external ? (turns > 1 ? 0.17 : 0.011) * gradients : 0.0;
-        double issue = 0.017 * parts + 0.002 * sources;
-        issue += (synth ? 0.021 * parts : 0.0) + (vel ? 0.0094 * gradients : 0.0);
+        double one = 0.069 * parts + 0.0028 * sources + 0.58 * ((n_local + 7) / 8);
+        one += synth ? 0.03 * parts : external ? (turns > 1 ? 0.18 : 0.016) * gradients : 0.0;
+        double issue = 0.013 * parts + 0.002 * sources;
+        issue += (synth ? 0.021 * parts : 0.0) + (vel ? 0.0073 * gradients : 0.0);
         double vectors = 4.0 * workers;                          // read at the start and stored, about
         if (vel && gradients) vectors += 2.0 * workers;
         if (external) vectors += gradients;
-        return 3.8 + std::max(one * turns, std::max(issue * per_simd, 4.0 * (double)d * vectors / 7.2e6) + 0.69 * one);
+        return 2.0 + std::max(one * turns, std::max(issue * per_simd, 4.0 * (double)d * vectors / 8.5e6) + 0.63 * one);
     }
 
     // Launches (one per wave, two with synthetic gradients) that partly hide behind what they move: every source to the
-    // CUs, every distinct vector from where the rings are.  A wide record reads one source after the other, 0.13 us for
-    // each 1024 of up to 4096 columns.
+    // CUs, every distinct vector from where the rings are.  A wide record reads one source after the other, 0.15 us for
+    // each 1024 of up to 4096 columns, or with a velocity 0.16 us, as a thread has one float4 of each.
     double waves_us() const {
-        const bool mostly_wide = 2 * wide > records, cached = ring_bytes < 30e6 && !mostly_wide, moved = vel && gradients > 0;
+        const bool mostly_wide = 2 * wide > records && !vel, cached = ring_bytes < 30e6 && !mostly_wide, moved = vel && gradients > 0;
         const double mean = std::min(sources / records, 8.0);
-        double launch = waves * (vel ? 2.9 : 2.1 + (wide ? 0.2 : 0.31) * mean);      // sources of wide records: in the chain
-        if (d >= 4096) launch += records * (moved ? 0.062 : 0.012);
-        if (d >= 16384 && !vel) launch += 1.3 * waves;
-        const double chain = 0.13 * (double)std::min<int64_t>(4, (d + 1023) / 1024) * wide_chain;
-        double rate = moved ? 9.3e6 : vel ? 13e6 : 12e6 + 0.54e6 * mean;
-        if (cached) rate *= 2;
-        if (mostly_wide && ring_bytes > 450e6) rate *= 0.73;
-        const double from = cached ? 20e6 : mostly_wide && ring_bytes > 95e6 ? 1.8e6 : 7e6;
+        double launch = waves * (vel ? 2.6 : 1.9 + (wide ? 0.11 : 0.27) * mean);     // sources of wide records: in the chain
+        if (d >= 4096) launch += records * (moved ? 0.027 : 0.013);
+        if (d >= 16384 && !vel) launch += 0.45 * waves;
+        const double chain = (vel ? 0.16 : 0.15 * (double)std::min<int64_t>(4, (d + 1023) / 1024)) * wide_chain;
+        double rate = moved ? 14e6 : vel ? 15.5e6 : 10.9e6 + 0.54e6 * mean;
+        if (cached) rate *= 1.2;
+        if (mostly_wide && ring_bytes > 450e6) rate *= 0.6;
+        const double from = cached ? 20e6 : mostly_wide && ring_bytes > 95e6 ? 2.9e6 : 6.1e6;
         const double own = bytes - 4.0 * d * sources;
         const double move = std::max(chain, std::max(bytes / rate, (4.0 * d * distinct + own) / from));
-        const double us = std::max(launch + 0.72 * move, move + 0.72 * launch);
-        return mode == HOP_GRAD_SYNTH ? us + 2.4 * waves + 4.0 * d * gradients / 8e6 : us;
+        const double us = std::max(launch + 0.43 * move, move + 0.43 * launch);
+        return mode == HOP_GRAD_SYNTH ? us + 2.5 * waves + 4.0 * d * gradients / 5.3e6 : us;
     }
 };
 

@@ -1,5 +1,5 @@
 // What a pass launches, on the CPU: hop_api.cpp with a HIP runtime of plain memory and launchers that print their arguments.
-//   launch_driver dense|csr|skipping|external WORKERS COLUMNS BATCH ROWS MOMENTUM
+//   launch_driver dense|csr|skipping|external|complete WORKERS COLUMNS BATCH ROWS MOMENTUM
 //   launch_driver rules RECORDS COLUMNS BATCH
 //   launch_driver average RECORDS COLUMNS SOURCES MOMENTUM
 #include <cstdio>
@@ -104,7 +104,9 @@ int main(int argc, char** argv) {
     std::vector<int32_t> row_ptr{0}, col;
     std::vector<float> W((size_t)N * N, 0.f);
     for (int i = 0; i < N; ++i) {
-        for (int j : {(i + N - 1) % N < (i + 1) % N ? (i + N - 1) % N : (i + 1) % N, (i + N - 1) % N < (i + 1) % N ? (i + 1) % N : (i + N - 1) % N})
+        for (int j = 0; j < N && model == "complete"; ++j)       // external gradients, a whole pass of 15 iterations
+            if (j != i) col.push_back(j);
+        if (model != "complete") for (int j : {(i + N - 1) % N < (i + 1) % N ? (i + N - 1) % N : (i + 1) % N, (i + N - 1) % N < (i + 1) % N ? (i + 1) % N : (i + N - 1) % N})
             if (j != i && (col.size() == (size_t)row_ptr.back() || col.back() != j)) col.push_back(j);
         const int deg = (int)col.size() - row_ptr.back();
         for (size_t p = (size_t)row_ptr.back(); p < col.size(); ++p) W[(size_t)col[p] * N + i] = 1.0f / (float)(deg + 1);
@@ -143,12 +145,13 @@ int main(int argc, char** argv) {
     std::memset(&delays, 0, sizeof delays);
     delays.kind = HOP_DELAY_EXP1;
     delays.mult = slow.data();
-    if (hop_simulate(c, o.skip_on ? &delays : nullptr, o.skip_on ? 30 : 2, &s)) return 7;
+    if (hop_simulate(c, o.skip_on ? &delays : nullptr, o.skip_on ? 30 : model == "complete" ? 15 : 2, &s)) return 7;
     const size_t need = hop_schedule_bytes(s);
     if (hop_schedule_bind(c, s, aligned(workspace, need), need)) return 8;
     hop_schedule_arrays v;
     hop_schedule_view(s, &v);
-    for (int w = 0; w < v.n_waves; ++w)
+    if (model == "complete" && hop_step(c, s, 0, -1)) return 9;
+    for (int w = 0; w < v.n_waves && model != "complete"; ++w)
         if (hop_step(c, s, w, w + 1)) return 9;
     hop_schedule_free(s);
     return hop_destroy(c);

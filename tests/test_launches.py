@@ -85,3 +85,11 @@ def test_single_records(launches):
     got = [tuple(int(a[k]) for k in ("jobs", "results", "gradients")) for name, a in launches("skipping", 4, 256, 4, 50, 0.0) if name == "pair_csr_margin"]
     assert all(jobs <= results <= 2 * jobs and gradients <= results for jobs, results, gradients in got)
     assert any(jobs == results for jobs, results, _ in got) and any(gradients <= jobs < results for jobs, results, gradients in got)
+
+
+# Which way whole passes go: us in waves / in one launch on MI355X 96 / 178, 119 / 184, 282 / 198, 79 / 134, 227 / 131, 72 / 128, 40 / 8
+@pytest.mark.parametrize("n,d,momentum,one", [(32, 4096, 0.9, 0), (32, 20000, 0.9, 0), (32, 65540, 0.9, 1), (24, 4096, 0.9, 0), (24, 4096, 0.0, 1),
+                                              (24, 336, 0.0, 0), (4, 64, 0.0, 1)])
+def test_way_of_whole_passes(launches, n, d, momentum, one):
+    got = [name for name, _ in launches("complete", n, d, 0, 0, momentum)]
+    assert got == (["sweep"] if one else ["mix" if momentum else "pair"] * 15)

@@ -264,10 +264,11 @@ int hop_schedule_bind(hop_ctx* ctx, hop_schedule* s, void* workspace, size_t byt
 
 /* Enqueues waves [wave_begin, wave_end) of the schedule: per wave the gradient kernels of its STEP
  * records (Compute on x_k, Section 3.2), then one fused Reduce + Apply launch over all its records.
- * Variations by gradient source: with CSR data, and with dense minibatches of up to 2 MB and 11264
- * columns, the margins ride in the Reduce launch and the gradient is applied to the results right after it (scattered,
- * or in place); with larger dense minibatches the gradient kernel itself reduces and applies its record,
- * and the Reduce of the records without a gradient is a launch of its own or rides with the margins; synthetic gradients of up to
+ * Variations by gradient source: with CSR data, and with dense minibatches of up to 2 MB that have up to
+ * 11264 or over 131072 columns (between, the XCDs take slices of the columns), the margins ride in the
+ * Reduce launch and the gradient is applied to the results right after it (scattered, or in place); with
+ * all other dense minibatches the gradient kernel itself reduces and applies its record, and the Reduce of
+ * the records without a gradient is a launch of its own or rides with the margins; synthetic gradients of up to
  * hop_opts.grad_ahead consecutive waves are generated in front of the first of them.  A call that covers the
  * whole schedule (wave_begin 0, wave_end -1 or n_waves) and is not being profiled runs as ONE launch when
  * gradients are absent, synthetic or external and an estimate of both ways has it ahead (it is not with very

@@ -1241,7 +1241,7 @@ __global__ __launch_bounds__(64 * SPLIT * WIDE) void dense_grad_one(const HopGra
 constexpr int64_t kCsrTurns = 256;      // workgroups of the scatter
 __device__ __forceinline__ unsigned csr_margin_group(unsigned b) { return b / (4 * kXcd) * kXcd + b % kXcd; }
 
-// its rows: of the scatter's workgroup `group` of this record
+// its rows: of the scatter's workgroup `group` of this record; b / 8 mod 4 says which of its four blocks
 __device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ job, int B, int loss, int group, unsigned b) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int m = (group * 4 + (int)(b / kXcd % 4)) * (kThreads / 64) + wv;
@@ -1256,11 +1256,14 @@ __device__ __forceinline__ void csr_margin_rows(const HopGradJob* __restrict__ j
 }
 
 // Margins and the dense part lambda w of a gradient that is wanted as a dense vector, side by side (the sparse part is
-// scattered into g afterwards).
+// scattered into g afterwards).  The margins' workgroups in the order of their rows and no more than there are: in turns of the XCDs
+// a call of few rows waits for idle ones and larger ones gain nothing (us, in turns -> in order, medians of 6 processes each: 600 columns, B = 1
+// 15.97 -> 15.18, 256 17.91 -> 17.73; 200 000, B = 1 16.09 -> 15.82, 40 17.16 -> 16.91, 512 17.69 -> 17.67; 2^20, B = 2 16.51 -> 16.31, 256 17.69 ->
+// 17.81; 3 M, B = 40 19.50 -> 19.92, 512 20.93 -> 21.01).
 __global__ __launch_bounds__(kThreads) void csr_margin_dense_one(const HopGradJob job, int B, int64_t d, float lambda,
                                                                  int loss, int margin_blocks) {
     if ((int)blockIdx.x < margin_blocks) {
-        csr_margin_rows(&job, B, loss, (int)csr_margin_group(blockIdx.x), blockIdx.x);
+        csr_margin_rows(&job, B, loss, (int)(blockIdx.x / 4), blockIdx.x % 4 * kXcd);
         return;
     }
     const int64_t c = ((int64_t)(blockIdx.x - margin_blocks) * kThreads + threadIdx.x) * 4;
@@ -1767,7 +1770,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
         else
             hipLaunchKernelGGL((dense_grad_one<1, 4, false>), dim3((chunks + 3) / 4), dim3(256), 0, st, job, B, d, nseg, lambda, loss);
     } else if (mode == HOP_GRAD_SVM_CSR) {
-        const int margin_blocks = (int)csr_margin_blocks(1, B);
+        const int margin_blocks = (B + kThreads / 64 - 1) / (kThreads / 64);
         const int64_t dense_blocks = (d + 4 * kThreads - 1) / (4 * kThreads), grid = margin_blocks + dense_blocks;
         if (grid > 0x7FFFFFFFll) return (int)hipErrorInvalidConfiguration;
         const uintptr_t w0 = (uintptr_t)job.w, g0 = (uintptr_t)job.out, bytes = (uintptr_t)d * sizeof(float);
@@ -1781,7 +1784,7 @@ int hopk_one_grad(const HopGradJob& given, int mode, int B, int64_t d, float lam
                                margin_blocks);
         }
         if (const int rc = launch_status()) return rc;
-        hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)csr_scatter_blocks(1, B)), dim3(kScatterThreads), 0,
+        hipLaunchKernelGGL(csr_scatter_one, dim3((unsigned)((B + kScatterRows - 1) / kScatterRows)), dim3(kScatterThreads), 0,
                            st, job, B, -1.0f);
     } else {
         const int64_t n = ((d >> 2) + kSynthChunk4 - 1) / kSynthChunk4, n_chunks = n < 1 ? 1 : n;

@@ -118,3 +118,31 @@ def test_margins_of_small_minibatches(N, B, momentum):
             assert bool(((got - acc).abs() <= 2.0 ** -24 * (0.5 * (B + 4) * mag + 8 * size)).all())
     finally:
         sess.close()
+
+
+# A call by itself: edges of the margins' blocks (4 rows) and of the scatter's (16), and of the columns that it adds up first (1024)
+@pytest.mark.parametrize("d", [600, 1024, 1025, 70001])
+@pytest.mark.parametrize("B", [1, 4, 5, 16, 17, 33, 129, 1024])
+def test_gradient_by_itself(d, B):
+    """Every row's coefficient and every column against 64 bits.  A margin is off by at most (n + 5) 2^-24 sum |x w| with n = 130 terms, a
+    coefficient by a quarter of that and 8 roundings, a column by the rounding of its terms and by its rows' coefficients."""
+    rows, lam, eps = 300, 1e-3, 2.0 ** -24
+    rowptr, col, val, y = _data(d + B, rows, d)
+    gen = torch.Generator().manual_seed(B)
+    w = (0.1 * torch.randn(d, generator=gen)).cuda()
+    ids = torch.randint(0, rows, (B,), generator=gen).int().cuda()
+    g, coef = torch.full((d,), 7.0, device="cuda"), torch.full((B,), 7.0, device="cuda")
+    hop.hop_svm_grad_csr(rowptr.data_ptr(), col.data_ptr(), val.data_ptr(), y.data_ptr(), w.data_ptr(), ids.data_ptr(), B, d, lam, g.data_ptr(),
+                         coef.data_ptr(), torch.cuda.current_stream().cuda_stream, hop.HOP_LOSS_LOG)
+    torch.cuda.synchronize()
+    x = torch.zeros(rows, d, dtype=torch.float64, device="cuda")
+    of_row = torch.repeat_interleave(torch.arange(rows, device="cuda"), rowptr[1:] - rowptr[:-1])
+    x[of_row, col.long()] = val.double()
+    x, yd, wd = x[ids.long()], y[ids.long()].double(), w.double()
+    want = yd / (B * (1 + torch.exp(yd * (x @ wd))))
+    off = ((130 + 5) * eps * (x.abs() @ wd.abs()) / 4 + 8 * eps) / B
+    assert bool(((coef.double() - want).abs() <= off).all())
+    lam = float(np.float32(lam))
+    terms = (x != 0).sum(0) + 1
+    mag = lam * wd.abs() + want.abs() @ x.abs()
+    assert bool(((g.double() - (lam * wd - want @ x)).abs() <= (terms + 3) * eps * mag + off @ x.abs()).all())

@@ -1168,8 +1168,20 @@ __device__ __forceinline__ void dense_grad_chunk(const HopGradJob* __restrict__ 
             }
         }
     };
-    if (n == 4) add_rows([&](const float* x) { return LAST ? ldu4_stream(x, c) : ldu4(x, c); });
-    else if (n > 0) add_rows([&](const float* x) { return ldu4(x, c, n); });     // the end of a vector, d mod 4 columns left
+    // The thread at the end of a vector, with d mod 4 columns left, reads the last four like any other and keeps its own: a pass over
+    // the rows for itself made its wavefront's chain twice as long.  us per pass, log loss, 12 iterations: 16 workers x 14 columns, B = 120
+    // 160 -> 121, 566 460 -> 276; 8 x 255, B = 566 376 -> 211; 32 x 1023, B = 120 198 -> 174.
+    const auto at = [&](int64_t i) { return [=](const float* x) { return LAST ? ldu4_stream(x, i) : ldu4(x, i); }; };
+    if (d % 4 == 0) {
+        if (n == 4) add_rows(at(c));
+    } else if (d > 4) {
+        if (n > 0) add_rows(at(min(c, d - 4)));
+        if (n == 3) acc = make_float4(acc.y, acc.z, acc.w, 0.f);
+        else if (n == 2) acc = make_float4(acc.z, acc.w, 0.f, 0.f);
+        else if (n == 1) acc = make_float4(acc.w, 0.f, 0.f, 0.f);
+    } else if (n > 0) {
+        add_rows([&](const float* x) { return ldu4(x, c, n); });
+    }
     if constexpr (SPLIT > 1) {                     // join the shares: ((part 0 + part 1) + part 2) + ...
         if (part > 0) joinS[(part - 1) * kCols + col] = acc;
         __syncthreads();

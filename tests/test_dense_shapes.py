@@ -99,3 +99,10 @@ def test_samples_that_are_not_finite(d, B, loss):
 @pytest.mark.parametrize("d,B", [(511, 1024), (513, 1024), (61, 769), (1024, 512), (1024, 513)])
 def test_dense_gradient_of_many_rows(d, B, loss):
     test_dense_gradient_at_the_edges(d, B, 0, loss)
+
+
+# the end of a vector: no column or one, two, three are left for the last thread, alone or beside others
+@pytest.mark.parametrize("loss", ["hinge", "log"])
+@pytest.mark.parametrize("d,B", [(4, 70), (5, 70), (6, 300), (7, 9), (1022, 300), (1023, 64), (16386, 100), (65538, 20), (65539, 128), (262147, 33)])
+def test_dense_gradient_at_the_end_of_a_vector(d, B, loss):
+    test_dense_gradient_at_the_edges(d, B, 0, loss)
